@@ -70,7 +70,8 @@ typedef enum kvzap_call {
   KVZAP_CALL_TOPK_THRESHOLD = 6, /* pass M = per_layer (0 or 1) */
   KVZAP_CALL_TEACHER_SCORES = 7, /* pass B = 1, T = prompt length, Dh = HQ, M = Tq */
   KVZAP_CALL_COMPRESS = 8,       /* as KVZAP_CALL_SCORE: the larger of the score and mask needs */
-  KVZAP_CALL_MASK_COMPACT = 9    /* as KVZAP_CALL_MASK */
+  KVZAP_CALL_MASK_COMPACT = 9,   /* as KVZAP_CALL_MASK */
+  KVZAP_CALL_SCORE_PREPARED = 10 /* kvzap_score_prepared_ws and kvzap_score_rmsnorm_ws; may be 0 */
 } kvzap_call;
 
 /* Text for a status code (host pointer to a static string, never NULL). */
@@ -83,10 +84,10 @@ const char* kvzap_version(void);
  * Minimum workspace size in bytes for one call.  For KVZAP_CALL_DECODE_EVICT
  * pass T = 1 (one new token per sequence).  Returns 0 for calls that need no
  * workspace and for invalid arguments.  Pure host function.
- * KVZAP_CALL_SCORE with M > 0 needs M*Dh*2 bytes: every call copies W1 there in
- * the order the matrix-core loads want it (a few microseconds); for inputs too short
- * to fill the chip (B*T up to about 16k tokens) it needs more, for the fp32 partial sums
- * of a first projection that is split over K -- so query with the B and T of the call.
+ * KVZAP_CALL_SCORE with M > 0 needs M*Dh*2 bytes, where a long input gets its copy of W1 in
+ * the order the matrix-core loads want it (a few microseconds per call), and up to
+ * B*T*M*4 bytes more where the input, or what whole rounds of token blocks leave over, is
+ * scored in tiles over the hidden units -- so query with the B and T of the call.
  */
 size_t kvzap_workspace_bytes(int which_call, int B, int T, int Dh, int M, int H);
 
@@ -115,11 +116,11 @@ size_t kvzap_workspace_bytes(int which_call, int B, int T, int Dh, int M, int H)
  * within 2.6e-5 (absolute) of z * Phi(z) for every z, evaluated in fp32; its result is rounded
  * to fp16 (relative 2^-11; values beyond 65504 become infinite) and W2 is converted to fp16
  * (exact for bf16 magnitudes in [2^-14, 65504], subnormal or infinite beyond) for the second
- * projection on the matrix cores, accumulated in fp32.  Short inputs (see the workspace
- * query) take a split first projection whose GELU (erf to 1.5e-7) and second projection are
- * plain fp32.  Both are far inside the 1e-2 score tolerance.  The sum order is fixed for a
- * given shape, so results are run-to-run deterministic; the same token scored in calls of
- * different B*T may differ in the last bits.  B*T == 0 is a no-op.
+ * projection on the matrix cores, accumulated in fp32.  Short inputs, and the last tokens of
+ * inputs that are no whole number of rounds of token blocks, take a tiled form whose GELU (erf
+ * to 1.5e-7) and second projection are fp32.  Both are far inside the 1e-2 score tolerance.
+ * The sum order is fixed for a given shape, so results are run-to-run deterministic; the same
+ * token scored in calls of different B*T may differ in the fourth digit.  B*T == 0 is a no-op.
  */
 int kvzap_score(const void* hidden, const void* W1, const void* b1,
                 const void* W2, const void* b2, float* scores,
@@ -156,8 +157,10 @@ int kvzap_score(const void* hidden, const void* W1, const void* b1,
  *                a second time: x is read twice and `normed` written once, which is the traffic
  *                of the separate norm and scorer, but inside one launch.  Must not overlap x.
  *
- * MLP surrogates only (M > 0; M == 0 returns KVZAP_ERR_UNSUPPORTED), Dh >= 256; always the
- * single-kernel path (no workspace).  Arithmetic as kvzap_score's single-kernel path; the sum
+ * MLP surrogates only (M > 0; M == 0 returns KVZAP_ERR_UNSUPPORTED), Dh >= 256.
+ * kvzap_score_rmsnorm always runs the single kernel; kvzap_score_rmsnorm_ws takes a workspace
+ * (KVZAP_CALL_SCORE_PREPARED) and is several times faster on inputs that do not fill the chip
+ * (1k tokens: 24 us against 179 us with the states written).  Arithmetic as kvzap_score's single-kernel path; the sum
  * of squares is accumulated in fp32 from bf16 pairs.  Scores equal those of kvzap_score on a
  * separately normalised input up to the bf16 rounding that pipeline applies to `hidden` and
  * this one to W1 * gain: both are within the score tolerance of the un-rounded definition.
@@ -168,6 +171,11 @@ int kvzap_score_rmsnorm(const void* x, const void* W1_prepared, const void* gain
                         const void* b1, const void* W2, const void* b2,
                         float* scores, float* rstd, void* normed,
                         int B, int T, int Dh, int M, int H, void* stream);
+int kvzap_score_rmsnorm_ws(const void* x, const void* W1_prepared, const void* gain, float eps,
+                           const void* b1, const void* W2, const void* b2,
+                           float* scores, float* rstd, void* normed,
+                           int B, int T, int Dh, int M, int H,
+                           void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * kvzap_mask -- threshold plus sliding window (Sec. 3.3; Algorithm 1).
@@ -223,10 +231,11 @@ int kvzap_mask_static(const float* scores, float tau, int window,
  * matrix cores' operand order in its workspace on every call; kvzap_prepare_scorer does that
  * once, into a buffer the caller keeps (W1_prepared: device, 256-byte aligned, at least
  * M * Dh * 2 bytes rounded up to 256, not overlapping W1), and
- * kvzap_score_prepared takes that buffer in place of W1 and needs no workspace.  Scores are
- * bit-identical to kvzap_score's when that runs the same single kernel (from about 16k
- * tokens); for shorter inputs kvzap_score splits the first projection over K (it has the
- * workspace for the partial sums) and the two agree within fp32 rounding.  M > 0 only (the linear surrogate has nothing to prepare);
+ * kvzap_score_prepared takes that buffer in place of W1 and needs no workspace: it runs the
+ * single kernel over token blocks, whatever the length.  kvzap_score_prepared_ws takes a
+ * workspace as well (KVZAP_CALL_SCORE_PREPARED; may be NULL where that is 0) and runs what
+ * kvzap_score runs for the same B and T, bit for bit: short inputs and remainders in tiles
+ * (1k tokens: 17 us against 83 us).  M > 0 only (the linear surrogate has nothing to prepare);
  * other arguments, layouts and errors as kvzap_score.  The prepared layout is private to
  * the library version that wrote it.
  */
@@ -235,6 +244,9 @@ int kvzap_prepare_scorer(const void* W1, int Dh, int M, void* W1_prepared, size_
 int kvzap_score_prepared(const void* hidden, const void* W1_prepared, const void* b1,
                          const void* W2, const void* b2, float* scores, int B, int T, int Dh,
                          int M, int H, void* stream);
+int kvzap_score_prepared_ws(const void* hidden, const void* W1_prepared, const void* b1,
+                            const void* W2, const void* b2, float* scores, int B, int T, int Dh,
+                            int M, int H, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * kvzap_topk_threshold -- thresholds for the fixed-budget variants (Sec. 3.3: keeping a

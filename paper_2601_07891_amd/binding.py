@@ -19,7 +19,7 @@ LIB_PATH = os.path.join(_HERE, "libkvzap.so")
 
 CALL_SCORE, CALL_MASK, CALL_COMPACT, CALL_DECODE_EVICT, CALL_ATTEND_DECODE = 0, 1, 2, 3, 4
 CALL_ASSIGN_PAGES, CALL_TOPK_THRESHOLD, CALL_TEACHER_SCORES, CALL_COMPRESS = 5, 6, 7, 8
-CALL_MASK_COMPACT = 9
+CALL_MASK_COMPACT, CALL_SCORE_PREPARED = 9, 10
 
 _c_void_p, _c_int, _c_float, _c_size_t, _c_int64 = (
     ctypes.c_void_p, ctypes.c_int, ctypes.c_float, ctypes.c_size_t, ctypes.c_int64)
@@ -36,10 +36,13 @@ SIGNATURES = {
                                    _c_void_p, _c_void_p, _c_void_p, _c_void_p]),
     "kvzap_prepare_scorer": (_c_int, [_c_void_p, _c_int, _c_int, _c_void_p, _c_size_t, _c_void_p]),
     "kvzap_score_prepared": (_c_int, [_c_void_p] * 6 + [_c_int] * 5 + [_c_void_p]),
+    "kvzap_score_prepared_ws": (_c_int, [_c_void_p] * 6 + [_c_int] * 5 + [_c_void_p, _c_size_t, _c_void_p]),
     "kvzap_prepare_scorer_rmsnorm": (_c_int, [_c_void_p, _c_void_p, _c_int, _c_int, _c_void_p, _c_size_t,
                                               _c_void_p]),
     "kvzap_score_rmsnorm": (_c_int, [_c_void_p] * 3 + [_c_float] + [_c_void_p] * 6 + [_c_int] * 5 +
                             [_c_void_p]),
+    "kvzap_score_rmsnorm_ws": (_c_int, [_c_void_p] * 3 + [_c_float] + [_c_void_p] * 6 + [_c_int] * 5 +
+                               [_c_void_p, _c_size_t, _c_void_p]),
     "kvzap_compress": (_c_int, [_c_void_p] * 7 + [_c_float, _c_int] + [_c_void_p] * 7 + [_c_int64] +
                        [_c_int] * 6 + [_c_void_p, _c_size_t, _c_void_p]),
     "kvzap_mask_compact": (_c_int, [_c_void_p, _c_float, _c_int] + [_c_void_p] * 8 + [_c_int64] +
@@ -762,17 +765,18 @@ def kvzap_score_rmsnorm(x: torch.Tensor, W1_prepared: torch.Tensor, gain: torch.
     _check(normed, bf, "normed", True)
     if scores.shape != (B, H, T) or rstd.shape != (B, T) or (normed is not None and normed.shape != x.shape):
         raise ValueError("scores must be [B,H,T], rstd [B,T], normed like x")
-    rc = lib().kvzap_score_rmsnorm(_ptr(x), _ptr(W1_prepared), _ptr(gain), float(eps), _ptr(b1),
-                                   _ptr(W2), _ptr(b2), _ptr(scores), _ptr(rstd), _ptr(normed),
-                                   B, T, Dh, M, H, _stream(stream))
+    ws, ws_bytes = _workspace(kvzap_workspace_bytes(CALL_SCORE_PREPARED, B, T, Dh, M, H), x.device, None, stream)
+    rc = lib().kvzap_score_rmsnorm_ws(_ptr(x), _ptr(W1_prepared), _ptr(gain), float(eps), _ptr(b1),
+                                      _ptr(W2), _ptr(b2), _ptr(scores), _ptr(rstd), _ptr(normed),
+                                      B, T, Dh, M, H, _ptr(ws), ws_bytes, _stream(stream))
     if rc != 0:
-        raise KvzapError(rc, "kvzap_score_rmsnorm")
+        raise KvzapError(rc, "kvzap_score_rmsnorm_ws")
     return scores, rstd, normed
 
 
 def kvzap_score_prepared(hidden: torch.Tensor, W1_prepared: torch.Tensor, b1, W2: torch.Tensor, b2,
                          scores: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
-    """kvzap_score with W1 replaced by kvzap_prepare_scorer's output; no workspace."""
+    """kvzap_score with W1 replaced by kvzap_prepare_scorer's output (same scores, bit for bit)."""
     bf = torch.bfloat16
     _check(hidden, bf, "hidden"); _check(W1_prepared, torch.uint8, "W1_prepared")
     _check(b1, bf, "b1", True); _check(W2, bf, "W2"); _check(b2, bf, "b2", True)
@@ -785,8 +789,10 @@ def kvzap_score_prepared(hidden: torch.Tensor, W1_prepared: torch.Tensor, b1, W2
     _check(scores, torch.float32, "scores")
     if scores.shape != (B, H, T):
         raise ValueError("scores must be [B,H,T]")
-    rc = lib().kvzap_score_prepared(_ptr(hidden), _ptr(W1_prepared), _ptr(b1), _ptr(W2), _ptr(b2),
-                                    _ptr(scores), B, T, Dh, M, H, _stream(stream))
+    ws, ws_bytes = _workspace(kvzap_workspace_bytes(CALL_SCORE_PREPARED, B, T, Dh, M, H), hidden.device,
+                              None, stream)
+    rc = lib().kvzap_score_prepared_ws(_ptr(hidden), _ptr(W1_prepared), _ptr(b1), _ptr(W2), _ptr(b2),
+                                       _ptr(scores), B, T, Dh, M, H, _ptr(ws), ws_bytes, _stream(stream))
     if rc != 0:
-        raise KvzapError(rc, "kvzap_score_prepared")
+        raise KvzapError(rc, "kvzap_score_prepared_ws")
     return scores

@@ -78,11 +78,14 @@ size_t kvzap_workspace_bytes(int which_call, int B, int T, int Dh, int M, int H)
       return kvzap::decode_workspace_bytes(B, Dh, M, H);
     case KVZAP_CALL_SCORE:
       if (check_scorer_shape(Dh, M, H) != KVZAP_OK) return 0;
-      // W1 in fragment order, or the first projection's partial sums of a short prompt
-      return M > 0 ? kvzap::score_mlp_workspace_bytes((long long)(B > 0 ? B : 0) * (T > 0 ? T : 0), Dh, M) : 0;
+      // W1 in fragment order and the unit tiles' shares of the scores
+      return M > 0 ? kvzap::score_mlp_workspace_bytes((long long)B * T, Dh, M, false) : 0;
+    case KVZAP_CALL_SCORE_PREPARED:
+      if (check_scorer_shape(Dh, M, H) != KVZAP_OK || M == 0) return 0;
+      return kvzap::score_mlp_workspace_bytes((long long)B * T, Dh, M, true);
     case KVZAP_CALL_COMPRESS: {
       if (check_scorer_shape(Dh, M, H) != KVZAP_OK || (long long)B * H > 65535) return 0;
-      const size_t a = M > 0 ? kvzap::score_mlp_workspace_bytes((long long)(B > 0 ? B : 0) * (T > 0 ? T : 0), Dh, M) : 0;
+      const size_t a = M > 0 ? kvzap::score_mlp_workspace_bytes((long long)B * T, Dh, M, false) : 0;
       const size_t b = mask_workspace(B, H, T);
       return a > b ? a : b;
     }
@@ -124,7 +127,7 @@ int check_score(const void* hidden, const void* W1, const void* b1, const void* 
       !aligned16(b1) || !aligned16(b2))
     return KVZAP_ERR_ALIGN;
   if (M > 0) {
-    const size_t need = kvzap::score_mlp_workspace_bytes((long long)B * T, Dh, M);
+    const size_t need = kvzap::score_mlp_workspace_bytes((long long)B * T, Dh, M, false);
     if (!workspace || !aligned256(workspace) || workspace_bytes < need) return KVZAP_ERR_WORKSPACE;
   }
   return KVZAP_OK;
@@ -171,7 +174,7 @@ int run_score(const void* hidden, const void* W1, const void* b1, const void* W2
               float* scores, int B, int T, int Dh, int M, int H, void* workspace, hipStream_t s) {
   if ((long long)B * T == 0) return KVZAP_OK;
   if (M > 0)
-    return kvzap::launch_score_mlp(hidden, W1, b1, W2, b2, scores, B, T, Dh, M, H, workspace, s);
+    return kvzap::launch_score_mlp(hidden, W1, b1, W2, b2, scores, B, T, Dh, M, H, false, workspace, s);
   return kvzap::launch_score_linear(hidden, W1, b1, scores, B, T, Dh, H, s);
 }
 }  // namespace
@@ -215,10 +218,19 @@ int kvzap_prepare_scorer_rmsnorm(const void* W1, const void* gain, int Dh, int M
   return kvzap::launch_prepare_w1(W1, gain, Dh, M, W1_prepared, static_cast<hipStream_t>(stream));
 }
 
-int kvzap_score_rmsnorm(const void* x, const void* W1_prepared, const void* gain, float eps,
-                        const void* b1, const void* W2, const void* b2, float* scores,
-                        float* rstd, void* normed, int B, int T, int Dh, int M, int H,
-                        void* stream) {
+namespace {
+// the optional workspace of the entry points that take a prepared W1
+int check_prepared_workspace(int B, int T, int Dh, int M, const void* workspace, size_t workspace_bytes) {
+  const size_t need = kvzap::score_mlp_workspace_bytes((long long)B * T, Dh, M, true);
+  if (need > 0 && (!workspace || !aligned256(workspace) || workspace_bytes < need)) return KVZAP_ERR_WORKSPACE;
+  return KVZAP_OK;
+}
+
+// with_workspace: the caller passed one (its size is checked), so short inputs may be tiled
+int score_rmsnorm(const void* x, const void* W1_prepared, const void* gain, float eps, const void* b1,
+                  const void* W2, const void* b2, float* scores, float* rstd, void* normed, int B,
+                  int T, int Dh, int M, int H, bool with_workspace, void* workspace,
+                  size_t workspace_bytes, void* stream) {
   if (M <= 0) return M == 0 ? KVZAP_ERR_UNSUPPORTED : KVZAP_ERR_SHAPE;   // MLP surrogate only
   if (!(eps >= 0.0f)) return KVZAP_ERR_SHAPE;                          // also NaN
   int rc = check_score(x, W1_prepared, b1, W2, b2, scores, B, T, Dh, M, H, W1_prepared, ~(size_t)0);
@@ -232,21 +244,56 @@ int kvzap_score_rmsnorm(const void* x, const void* W1_prepared, const void* gain
     const uintptr_t a = reinterpret_cast<uintptr_t>(x), b = reinterpret_cast<uintptr_t>(normed);
     if (a < b + n && b < a + n) return KVZAP_ERR_SHAPE;
   }
+  if (with_workspace) rc = check_prepared_workspace(B, T, Dh, M, workspace, workspace_bytes);
+  if (rc != KVZAP_OK) return rc;
   return kvzap::launch_score_mlp_rmsnorm(x, W1_prepared, gain, eps, b1, W2, b2, scores, rstd, normed,
-                                         B, T, Dh, M, H, static_cast<hipStream_t>(stream));
+                                         B, T, Dh, M, H, with_workspace ? workspace : nullptr,
+                                         static_cast<hipStream_t>(stream));
 }
 
-int kvzap_score_prepared(const void* hidden, const void* W1_prepared, const void* b1,
-                         const void* W2, const void* b2, float* scores, int B, int T, int Dh,
-                         int M, int H, void* stream) {
+int score_prepared(const void* hidden, const void* W1_prepared, const void* b1, const void* W2,
+                   const void* b2, float* scores, int B, int T, int Dh, int M, int H,
+                   bool with_workspace, void* workspace, size_t workspace_bytes, void* stream) {
   if (M <= 0) return KVZAP_ERR_SHAPE;
   // as kvzap_score, with the workspace requirement replaced by the prepared copy's alignment
   int rc = check_score(hidden, W1_prepared, b1, W2, b2, scores, B, T, Dh, M, H,
                        W1_prepared, ~(size_t)0);
   if (rc != KVZAP_OK) return rc == KVZAP_ERR_WORKSPACE ? KVZAP_ERR_ALIGN : rc;
   if ((long long)B * T == 0) return KVZAP_OK;
-  return kvzap::launch_score_mlp(hidden, W1_prepared, b1, W2, b2, scores, B, T, Dh, M, H, nullptr,
-                                 static_cast<hipStream_t>(stream));
+  if (with_workspace) rc = check_prepared_workspace(B, T, Dh, M, workspace, workspace_bytes);
+  if (rc != KVZAP_OK) return rc;
+  return kvzap::launch_score_mlp(hidden, W1_prepared, b1, W2, b2, scores, B, T, Dh, M, H, true,
+                                 with_workspace ? workspace : nullptr, static_cast<hipStream_t>(stream));
+}
+}  // namespace
+
+int kvzap_score_rmsnorm(const void* x, const void* W1_prepared, const void* gain, float eps,
+                        const void* b1, const void* W2, const void* b2, float* scores,
+                        float* rstd, void* normed, int B, int T, int Dh, int M, int H,
+                        void* stream) {
+  return score_rmsnorm(x, W1_prepared, gain, eps, b1, W2, b2, scores, rstd, normed, B, T, Dh, M, H,
+                       false, nullptr, 0, stream);
+}
+
+int kvzap_score_rmsnorm_ws(const void* x, const void* W1_prepared, const void* gain, float eps,
+                           const void* b1, const void* W2, const void* b2, float* scores,
+                           float* rstd, void* normed, int B, int T, int Dh, int M, int H,
+                           void* workspace, size_t workspace_bytes, void* stream) {
+  return score_rmsnorm(x, W1_prepared, gain, eps, b1, W2, b2, scores, rstd, normed, B, T, Dh, M, H,
+                       true, workspace, workspace_bytes, stream);
+}
+
+int kvzap_score_prepared(const void* hidden, const void* W1_prepared, const void* b1,
+                         const void* W2, const void* b2, float* scores, int B, int T, int Dh,
+                         int M, int H, void* stream) {
+  return score_prepared(hidden, W1_prepared, b1, W2, b2, scores, B, T, Dh, M, H, false, nullptr, 0, stream);
+}
+
+int kvzap_score_prepared_ws(const void* hidden, const void* W1_prepared, const void* b1,
+                            const void* W2, const void* b2, float* scores, int B, int T, int Dh,
+                            int M, int H, void* workspace, size_t workspace_bytes, void* stream) {
+  return score_prepared(hidden, W1_prepared, b1, W2, b2, scores, B, T, Dh, M, H, true, workspace,
+                        workspace_bytes, stream);
 }
 
 int kvzap_mask(const float* scores, float tau, int window, const int32_t* seq_lens, int B,

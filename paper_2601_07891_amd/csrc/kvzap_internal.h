@@ -97,6 +97,36 @@ __device__ __forceinline__ void load_to_lds_b32(const void* gptr, unsigned lds_b
                : "memory");
 }
 
+// GELU(z) = z * Phi(z) with Phi from the rational erfc approximation of Abramowitz & Stegun
+// 7.1.26 (|error| <= 1.5e-7 on erf, i.e. at fp32 rounding level): one rcp, one exp2 and
+// ten FMA-class operations per element instead of the ~40 of a library erff, which matters
+// where the vector ALU work is not overlapped with matrix-core work.
+__device__ __forceinline__ float gelu_exact(float z) {
+  const float x = fabsf(z);
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, x, 1.0f));
+  // 0.5 * (a1 t + ... + a5 t^5): the 0.5 of Phi is folded into the coefficients
+  float p = fmaf(t, 0.5f * 1.061405429f, 0.5f * -1.453152027f);
+  p = fmaf(t, p, 0.5f * 1.421413741f);
+  p = fmaf(t, p, 0.5f * -0.284496736f);
+  p = fmaf(t, p, 0.5f * 0.254829592f);
+  // exp(-z^2 / 2) = 2^(-z^2 * log2(e) / 2)
+  const float e = __builtin_amdgcn_exp2f(z * z * (-0.5f * 1.4426950408889634f));
+  const float half_erfc = (t * p) * e;                 // 0.5 * erfc(|z| / sqrt 2) = Phi(-|z|)
+  // Phi(z) = 0.5 + copysign(0.5 - Phi(-|z|), z)
+  const float phi = 0.5f + copysignf(0.5f - half_erfc, z);
+  return z * phi;
+}
+
+// LDS tile of 128-byte rows (eight 16-byte pieces): byte offset of logical piece `piece` of
+// `row`.  The piece index is XOR-ed with bits 1..3 of the row: a ds_read_b128 serves 16 lanes
+// (16 consecutive rows, one piece each) at a time, and with two rows per 256 bytes of banks
+// the 16 accesses then fall on 16 different 16-byte bank groups (with row & 7 rows r and r+8
+// met in the same group).
+__device__ __forceinline__ int lds_swizzle(int row) { return (row >> 1) & 7; }
+__device__ __forceinline__ int lds_off(int row, int piece) {   // bytes
+  return row * 128 + ((piece ^ lds_swizzle(row)) << 4);
+}
+
 // launchers (each returns a kvzap_status); arguments are already validated
 int launch_mask(const float* scores, float tau, const float* tau_head, int window,
                 const int32_t* seq_lens, int B, int H, int T, int32_t* keep_idx,
@@ -125,23 +155,44 @@ int launch_compact(const void* K, const void* V, const int32_t* keep_idx,
 int launch_score_linear(const void* hidden, const void* W, const void* b, float* scores,
                         int B, int T, int Dh, int H, hipStream_t stream);
 
-int skinny_ksplit(long long rows, int Dh, int M, int target_blocks);
-int launch_skinny_gemm(const void* hidden, const void* W1, float* partial, long long rows, int Dh,
-                       int M, int ks, hipStream_t stream);
-// bytes kvzap_score's workspace needs for an MLP surrogate on `rows` tokens
-size_t score_mlp_workspace_bytes(long long rows, int Dh, int M);
+// What a scorer kernel does besides scoring when its input is the un-normalised residual stream:
+// every token's 1 / sqrt(mean x^2 + eps) is accumulated next to the first projection, applied to
+// the accumulators before b1 and GELU -- the gain is already in the prepared W1 -- written to
+// `rstd`, and, if `normed` is given, the block finally re-reads its own rows and writes
+// x * rstd * gain as bf16.
+struct NormArgs {
+  const unsigned short* gain;    // bf16 [Dh]
+  float eps;
+  float* rstd;                   // fp32 [rows]
+  unsigned short* normed;        // bf16 [rows, Dh] or nullptr
+};
+
+// score_tile.hip: tiles over tokens and units; index 0 is the largest, tiles get smaller from there
+constexpr int kScoreTiles = 5;
+long long score_tile_blocks(int tile, long long rows, int M);
+// rows [row_first, row_first + rows) of the input; frag: W1 in fragment order; part: fp32
+// [M / units of the tile][H][rows], used between the two launches; norm: nullptr or the
+// normalising form (frag only)
+int launch_score_tile(int tile, bool frag, const void* hidden, const void* W1, const void* b1,
+                      const void* W2, const void* b2, float* scores, float* part, long long rows,
+                      long long row_first, int T, int Dh, int M, int H, const NormArgs* norm,
+                      hipStream_t stream);
+
+// bytes the workspace of kvzap_score (prepared: of the entry points that take a prepared W1)
+// needs for an MLP surrogate on `rows` tokens
+size_t score_mlp_workspace_bytes(long long rows, int Dh, int M, bool prepared);
 // gain (optional): the prepared copy holds W1 * diag(gain), for launch_score_mlp_rmsnorm
 int launch_prepare_w1(const void* W1, const void* gain, int Dh, int M, void* out, hipStream_t stream);
-// the MLP surrogate on the un-normalised residual stream (single-kernel path only)
+// the MLP surrogate on the un-normalised residual stream; workspace as launch_score_mlp's prepared form
 bool score_rmsnorm_supports(int Dh);
 int launch_score_mlp_rmsnorm(const void* x, const void* W1_prepared, const void* gain, float eps,
                              const void* b1, const void* W2, const void* b2, float* scores,
                              float* rstd, void* normed, int B, int T, int Dh, int M, int H,
-                             hipStream_t stream);
-// workspace == nullptr: W1 is the copy made by launch_prepare_w1
+                             void* workspace, hipStream_t stream);
+// prepared: W1 is the copy made by launch_prepare_w1 and the workspace is optional
 int launch_score_mlp(const void* hidden, const void* W1, const void* b1, const void* W2,
                      const void* b2, float* scores, int B, int T, int Dh, int M, int H,
-                     void* workspace, hipStream_t stream);
+                     bool prepared, void* workspace, hipStream_t stream);
 
 struct DecodeArgs {
   const void* hidden_new; const void* W1; const void* b1; const void* W2; const void* b2;

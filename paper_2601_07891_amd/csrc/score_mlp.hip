@@ -9,10 +9,10 @@
 // are then fused into the epilogue without moving data between lanes, and the
 // [tokens x M] activation never exists in memory.
 //
-// Which kernel runs (launch_score_mlp): D_h >= 256 takes score_mlp_frag_kernel (below, the
-// one the throughput figures are about) -- cut over K as well while its token blocks do not
-// fill the chip, and replaced by the decode path's skinny GEMM for a few hundred tokens
-// (both finish in score_finish_kernel); D_h < 256 takes score_mlp_kernel, described here:
+// Which kernel runs (plan_score below): score_mlp_frag_kernel (below, the one the throughput
+// figures are about) where its token blocks fill the chip, the tiled kernel of score_tile.hip
+// for short inputs and for what whole rounds of token blocks leave over; score_mlp_kernel,
+// described here, for D_h < 256 beyond the tiled kernel's range:
 //
 // Block = 512 threads (8 wavefronts) = all M units x 128 tokens, so `hidden` is
 // read from HBM exactly once and W1 (<= 6.6 MB, L2 resident) once per block.
@@ -35,26 +35,6 @@ constexpr int kThreads = 512;
 constexpr int kTok = 128;     // tokens per block
 constexpr int kBK = 64;       // K per LDS tile
 
-// GELU(z) = z * Phi(z) with Phi from the rational erfc approximation of Abramowitz & Stegun
-// 7.1.26 (|error| <= 1.5e-7 on erf, i.e. at fp32 rounding level): one rcp, one exp2 and
-// ten FMA-class operations per element instead of the ~40 of a library erff, which matters
-// because the epilogue's vector ALU work is not overlapped with matrix-core work.
-__device__ __forceinline__ float gelu_exact(float z) {
-  const float x = fabsf(z);
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, x, 1.0f));
-  // 0.5 * (a1 t + ... + a5 t^5): the 0.5 of Phi is folded into the coefficients
-  float p = fmaf(t, 0.5f * 1.061405429f, 0.5f * -1.453152027f);
-  p = fmaf(t, p, 0.5f * 1.421413741f);
-  p = fmaf(t, p, 0.5f * -0.284496736f);
-  p = fmaf(t, p, 0.5f * 0.254829592f);
-  // exp(-z^2 / 2) = 2^(-z^2 * log2(e) / 2)
-  const float e = __builtin_amdgcn_exp2f(z * z * (-0.5f * 1.4426950408889634f));
-  const float half_erfc = (t * p) * e;                 // 0.5 * erfc(|z| / sqrt 2) = Phi(-|z|)
-  // Phi(z) = 0.5 + copysign(0.5 - Phi(-|z|), z)
-  const float phi = 0.5f + copysignf(0.5f - half_erfc, z);
-  return z * phi;
-}
-
 // The fused epilogue's GELU: z * sigmoid(z * (c0 + c1 z^2 + c2 z^4)), the coefficients fitted
 // to z * Phi(z) (the erf form) in the minimax sense: |error| <= 2.6e-5 absolute for every z
 // (z^2 is clamped at 64, beyond which the sigmoid is 0 or 1 to 1e-12).  Its result is rounded
@@ -69,16 +49,6 @@ __device__ __forceinline__ float gelu_fused(float z) {
   q = fmaf(z2, q, -2.301121234893799f);
   const float e = __builtin_amdgcn_exp2f(z * q);
   return z * __builtin_amdgcn_rcpf(1.0f + e);
-}
-
-// LDS tile of 128-byte rows (eight 16-byte pieces): byte offset of logical piece `piece` of
-// `row`.  The piece index is XOR-ed with bits 1..3 of the row: a ds_read_b128 serves 16 lanes
-// (16 consecutive rows, one piece each) at a time, and with two rows per 256 bytes of banks
-// the 16 accesses then fall on 16 different 16-byte bank groups (with row & 7 rows r and r+8
-// met in the same group).
-__device__ __forceinline__ int lds_swizzle(int row) { return (row >> 1) & 7; }
-__device__ __forceinline__ int lds_off(int row, int piece) {   // bytes
-  return row * 128 + ((piece ^ lds_swizzle(row)) << 4);
 }
 
 template <int UB>
@@ -264,6 +234,7 @@ __global__ __launch_bounds__(kThreads) void score_mlp_kernel(
 //     (isa_lint.py), and no branch may sit between such a load and its wait.
 // ---------------------------------------------------------------------------
 constexpr int kChipCUs = 256;                // compute units of the part (8 XCDs x 32)
+constexpr long long kTileMaxRows = 28672;    // beyond, the tiles never won (and their workspace grows with the rows)
 constexpr int kPD = 3;                       // hidden tiles in flight
 constexpr int kNS = kPD + 1;                 // LDS stages
 
@@ -294,18 +265,6 @@ __global__ __launch_bounds__(256) void arrange_w1_kernel(const u32x4* __restrict
     W1f[i] = w;
   }
 }
-
-// What the kernel does besides scoring when its input is the un-normalised residual stream
-// (kNorm): every token's 1 / sqrt(mean x^2 + eps) is accumulated next to the first projection
-// (the B fragments are in registers anyway), applied to the accumulators before b1 and GELU
-// -- the gain is already in the prepared W1 -- written to `rstd`, and, if `normed` is given,
-// the block finally re-reads its own rows and writes x * rstd * gain as bf16.
-struct NormArgs {
-  const unsigned short* gain;    // bf16 [Dh]
-  float eps;
-  float* rstd;                   // fp32 [rows]
-  unsigned short* normed;        // bf16 [rows, Dh] or nullptr
-};
 
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>), in order: loops whose index
 // has to be a constant expression (an instruction's immediate offset, a wait count)
@@ -376,15 +335,14 @@ __device__ __forceinline__ void wait_lds_fragment(bf16x8& frag) {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// UB 32-unit blocks per wavefront, TB 32-token blocks per block; kSplit: the block covers one
-// K-slice (blockIdx.y) and writes its part of the first projection to `partial`
-template <int UB, int TB, bool kSplit, bool kNorm = false>
+// UB 32-unit blocks per wavefront, TB 32-token blocks per block
+template <int UB, int TB, bool kNorm>
 __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
     const unsigned short* hidden, const unsigned char* W1f,   // not __restrict__: their loads must stay ordered w.r.t. the waits
     const unsigned short* __restrict__ b1, const unsigned short* __restrict__ W2,
     const unsigned short* __restrict__ b2, float* __restrict__ scores,
-    long long rows, int T, int Dh, int H, int nk, float* __restrict__ partial, NormArgs norm) {
-  static_assert(!(kSplit && kNorm), "the normalising form is the single-kernel path");
+    long long rows, int T, int Dh, int H, NormArgs norm) {
+  const int nk = Dh / kBK;
   constexpr int U = 128 * UB;
   constexpr int TOK = 32 * TB;               // tokens per block
   constexpr int STAGE = TOK * 128;           // bytes per LDS stage (TOK rows of one K tile)
@@ -412,13 +370,11 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
   }
   // accumulator register 4q+e of block (ub, .) is unit wid*32*UB + 32*ub + 8*q + 4*kg + e
   u32x2 b1_stage[UB][4];
-  if constexpr (!kSplit) {
 #pragma unroll
-    for (int ub = 0; ub < UB; ++ub)
+  for (int ub = 0; ub < UB; ++ub)
 #pragma unroll
-      for (int q = 0; q < 4; ++q)   // without b1: the same offsets into W2 (H*U >= U elements), zeroed later
-        load_async(b1_stage[ub][q], (b1 ? b1 : W2) + wid * (32 * UB) + 32 * ub + 8 * q + 4 * kg);
-  }
+    for (int q = 0; q < 4; ++q)   // without b1: the same offsets into W2 (H*U >= U elements), zeroed later
+      load_async(b1_stage[ub][q], (b1 ? b1 : W2) + wid * (32 * UB) + 32 * ub + 8 * q + 4 * kg);
 
   // b2 is loaded here and waits in LDS for the very end: a global load in the tail would
   // expose a memory round trip with nothing left to overlap it
@@ -428,9 +384,7 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
 
   // hidden load-to-LDS: instruction j (0..3) of wavefront w fills LDS chunk j*4+w of a
   // stage = rows (j*4+w)*8 + lane/8, physical piece lane%8 <- logical piece (lane%8) ^ lds_swizzle(row)
-  // blockIdx.y: the K-slice of nk tiles this block covers (one slice unless `partial` is set)
-  const int kt0 = kSplit ? blockIdx.y * nk : 0;
-  const unsigned char* hb = reinterpret_cast<const unsigned char*>(hidden + (size_t)row0 * Dh) + (size_t)kt0 * (kBK * 2);
+  const unsigned char* hb = reinterpret_cast<const unsigned char*>(hidden + (size_t)row0 * Dh);
   unsigned h_off[NDJ];
 #pragma unroll
   for (int j = 0; j < NDJ; ++j) {
@@ -451,7 +405,7 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
   // kLead tiles ahead into kLead register sets.
   constexpr int kLead = (UB <= 4 && !kNorm) ? 2 : 1;
   constexpr size_t kATile = (size_t)(U / 32) * 4 * 1024;
-  const unsigned char* abase = W1f + ((size_t)kt0 * (U / 32) * 4 + (size_t)wid * UB * 4) * 1024;
+  const unsigned char* abase = W1f + (size_t)wid * UB * 4 * 1024;
   unsigned a_voff[UB];
 #pragma unroll
   for (int ub = 0; ub < UB; ++ub) a_voff[ub] = (unsigned)lane * 16u + (unsigned)ub * 4096u;
@@ -513,15 +467,13 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
     arrived(w2_stage[i]);
     if (i * 256 + tid >= H * (U / 8)) w2_stage[i] = u32x4{0u, 0u, 0u, 0u};
   }
-  if constexpr (!kSplit) {
 #pragma unroll
-    for (int ub = 0; ub < UB; ++ub)
+  for (int ub = 0; ub < UB; ++ub)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        arrived(b1_stage[ub][q]);
-        if (!b1) b1_stage[ub][q] = u32x2{0u, 0u};
-      }
-  }
+    for (int q = 0; q < 4; ++q) {
+      arrived(b1_stage[ub][q]);
+      if (!b1) b1_stage[ub][q] = u32x2{0u, 0u};
+    }
   arrived(b2_stage);
   if (!b2 || tid >= H) b2_stage = 0u;
 #pragma unroll
@@ -550,13 +502,13 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
         }
     }
   }
-  // the first projection accumulates on top of b1 (a K-slice of a split launch: on zero)
+  // the first projection accumulates on top of b1 (the normalising form: on zero)
 #pragma unroll
   for (int ub = 0; ub < UB; ++ub)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       float v[4] = {0.f, 0.f, 0.f, 0.f};
-      if constexpr (!kSplit && !kNorm) {
+      if constexpr (!kNorm) {
         v[0] = __uint_as_float(b1_stage[ub][q].x << 16); v[1] = __uint_as_float(b1_stage[ub][q].x & 0xffff0000u);
         v[2] = __uint_as_float(b1_stage[ub][q].y << 16); v[3] = __uint_as_float(b1_stage[ub][q].y & 0xffff0000u);
       }
@@ -723,27 +675,6 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
     tile_body(nk - 2, integral_constant<int, 2>{}, s0);
     tile_body(nk - 1, integral_constant<int, 1>{}, s1);
   }
-  if constexpr (kSplit) {
-    // split-K launch: the slice's part of the first projection goes to partial[slice][row][unit]
-    // as it is; bias, GELU and the second projection follow in score_finish_kernel
-    float* out = partial + ((size_t)blockIdx.y * rows + row0) * U + wid * (32 * UB) + 4 * kg;
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-      const int r = 32 * tb + l32;
-      if (r < rows_here) {
-#pragma unroll
-        for (int ub = 0; ub < UB; ++ub)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            floatx4 v4;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v4[e] = acc[ub][tb][4 * q + e];
-            *reinterpret_cast<floatx4*>(out + (size_t)r * U + 32 * ub + 8 * q) = v4;
-          }
-      }
-    }
-    return;
-  }
   if constexpr (kNorm) {
     // each token's sum of squares (both lane halves) goes through LDS to the lanes that hold
     // its accumulators; the barrier below publishes it
@@ -753,22 +684,20 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
   }
   __syncthreads();      // LDS is reused for the reduction below
 
-  if constexpr (!kSplit) {
-    // Warm the L2 for the block that starts on this CU when this one ends: workgroups go to
-    // the 8 XCDs round-robin and to a CU as it frees up, so with one block per CU that block is
-    // blockIdx.x + (number of CUs), on the same XCD and therefore behind the same L2.  One lane
-    // per 128-byte line of its first kPD hidden tiles.  The loaded dwords are never used, only
-    // where they leave the lines matters: they go to the ring's last stage, which nothing reads
-    // any more (the reduction below uses the first two), as load-to-LDS because an ordinary load
-    // would need a register that stays reserved until it returns.
-    const long long nrow0 = row0 + (long long)kChipCUs * TOK;
+  // Warm the L2 for the block that starts on this CU when this one ends: workgroups go to
+  // the 8 XCDs round-robin and to a CU as it frees up, so with one block per CU that block is
+  // blockIdx.x + (number of CUs), on the same XCD and therefore behind the same L2.  One lane
+  // per 128-byte line of its first kPD hidden tiles.  The loaded dwords are never used, only
+  // where they leave the lines matters: they go to the ring's last stage, which nothing reads
+  // any more (the reduction below uses the first two), as load-to-LDS because an ordinary load
+  // would need a register that stays reserved until it returns.
+  const long long nrow0 = row0 + (long long)kChipCUs * TOK;
 #pragma unroll
-    for (int i0 = 0; i0 < kPD * TOK; i0 += 256) {
-      const int i = i0 + tid, d = i / TOK, r = i - d * TOK;
-      if (i < kPD * TOK && nrow0 + r < rows)
-        load_to_lds_b32(hidden + (size_t)(nrow0 + r) * Dh + (size_t)(kt0 + d) * kBK,
-                        lds0 + (unsigned)((kNS - 1) * STAGE + wid * 256));
-    }
+  for (int i0 = 0; i0 < kPD * TOK; i0 += 256) {
+    const int i = i0 + tid, d = i / TOK, r = i - d * TOK;
+    if (i < kPD * TOK && nrow0 + r < rows)
+      load_to_lds_b32(hidden + (size_t)(nrow0 + r) * Dh + (size_t)d * kBK,
+                      lds0 + (unsigned)((kNS - 1) * STAGE + wid * 256));
   }
 
   // ---- epilogue: GELU, then the M -> H projection as a second MFMA (fp16 operands) ----
@@ -914,81 +843,10 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
   }
 }
 
-// ---- short prompts ----
-// One block of the kernels above walks all of K for its tokens, which takes 50-85 us however
-// few blocks there are.  Two remedies, both with the first projection's partial sums in the
-// workspace and this kernel to finish (K-slices in a fixed order, bias, GELU, second
-// projection in fp32; one wavefront per token, 8 hidden units per lane and round):
-//  * while the token blocks do not fill the chip, the main kernel is cut over K as well
-//    (frag_ksplit): 37-50 us from 640 to 4096 tokens, 68 us at 8192, against 85-88 us;
-//  * up to kTwoStageRows tokens the decode path's skinny GEMM over (unit block x K-slice x
-//    64 tokens) blocks is faster still (128 tokens 20 us, 256: 26 us); it reads its operands
-//    from global memory in 32-byte pieces and re-reads W1 per 64 tokens, so it loses beyond
-//    a few hundred tokens (512: 38 us, 1024: 49 us, 4096: 120 us).
-constexpr long long kTwoStageRows = 384;
-constexpr int kTwoStageBlocks = 2048;
-
-__global__ __launch_bounds__(256) void score_finish_kernel(
-    const float* __restrict__ partial, const unsigned short* __restrict__ b1,
-    const unsigned short* __restrict__ W2, const unsigned short* __restrict__ b2,
-    float* __restrict__ scores, long long rows, int T, int M, int H, int ks) {
-  const int lane = threadIdx.x & 63;
-  const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;                                  // uniform per wavefront; no barrier below
-  float acc[16];
-#pragma unroll
-  for (int h = 0; h < 16; ++h) acc[h] = 0.f;
-  for (int u0 = lane * 8; u0 < M; u0 += 512) {
-    floatx4 z0 = {0.f, 0.f, 0.f, 0.f}, z1 = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < ks; ++s) {
-      const float* p = partial + ((size_t)s * rows + row) * M + u0;
-      z0 += *reinterpret_cast<const floatx4*>(p);
-      z1 += *reinterpret_cast<const floatx4*>(p + 4);
-    }
-    u32x4 bb = {0u, 0u, 0u, 0u};
-    if (b1) bb = *reinterpret_cast<const u32x4*>(b1 + u0);
-    float g[8];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      g[2 * e] = gelu_exact((e < 2 ? z0[2 * e] : z1[2 * e - 4]) + __uint_as_float(bb[e] << 16));
-      g[2 * e + 1] = gelu_exact((e < 2 ? z0[2 * e + 1] : z1[2 * e - 3]) + __uint_as_float(bb[e] & 0xffff0000u));
-    }
-#pragma unroll
-    for (int h = 0; h < 16; ++h) {
-      if (h < H) {
-        const u32x4 w = *reinterpret_cast<const u32x4*>(W2 + (size_t)h * M + u0);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          acc[h] += g[2 * e] * __uint_as_float(w[e] << 16) + g[2 * e + 1] * __uint_as_float(w[e] & 0xffff0000u);
-      }
-    }
-  }
-  const long long bidx = row / T;
-  const int t = (int)(row - bidx * T);
-#pragma unroll
-  for (int h = 0; h < 16; ++h) {
-    if (h < H) {
-      float v = acc[h];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-      if (lane == 0) scores[((size_t)bidx * H + h) * T + t] = v + (b2 ? bf16_bits_to_float(b2[h]) : 0.f);
-    }
-  }
-}
-
-// K-slices for a launch of `blocks` token blocks over nk_total K tiles: enough blocks for the
-// chip's 256 CUs, slices of at least kPD + 1 tiles that divide K evenly, at most 8.
-inline int frag_ksplit(long long blocks, int nk_total) {
-  int ks = 1;
-  for (int d = 2; d <= 8; ++d)
-    if (nk_total % d == 0 && nk_total / d >= kPD + 1 && blocks * d <= 256 && blocks <= 112) ks = d;
-  return ks;
-}
-
-template <int UB, int TB>
-int launch_frag(const void* hidden, const void* W1, const void* b1, const void* W2,
-                const void* b2, float* scores, long long rows, int T, int Dh, int H,
-                void* workspace, hipStream_t stream, const NormArgs* norm) {
+template <int UB, int TB, bool kNorm>
+int launch_frag(const void* hidden, const void* W1f, const void* b1, const void* W2, const void* b2,
+                float* scores, long long rows, int T, int Dh, int H, const NormArgs& norm,
+                hipStream_t stream) {
   constexpr int TOK = 32 * TB;
   constexpr size_t ring = (size_t)kNS * TOK * 128;
   static_assert(ring >= (size_t)4 * 16 * TOK * sizeof(float), "reduction buffer fits");
@@ -997,53 +855,29 @@ int launch_frag(const void* hidden, const void* W1, const void* b1, const void* 
                          (128 * UB) * sizeof(float) + TOK * sizeof(float) + 16 * sizeof(float);   // + b2
   // once per process, which drives one GPU (thread-safe: a function-local static)
   static const hipError_t attr_rc =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(score_mlp_frag_kernel<UB, TB, false>),
+      hipFuncSetAttribute(reinterpret_cast<const void*>(score_mlp_frag_kernel<UB, TB, kNorm>),
       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  static const hipError_t attr_rc_split =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(score_mlp_frag_kernel<UB, TB, true>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  static const hipError_t attr_rc_norm =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(score_mlp_frag_kernel<UB, TB, false, true>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (attr_rc != hipSuccess || attr_rc_split != hipSuccess || attr_rc_norm != hipSuccess)
-    return KVZAP_ERR_RUNTIME;
-  const int M = 128 * UB;
-  if (norm) {     // residual stream in, W1 already prepared with the gain folded in
-    score_mlp_frag_kernel<UB, TB, false, true><<<dim3((unsigned)((rows + TOK - 1) / TOK)), 256, lds, stream>>>(
-        static_cast<const unsigned short*>(hidden), static_cast<const unsigned char*>(W1),
-        static_cast<const unsigned short*>(b1), static_cast<const unsigned short*>(W2),
-        static_cast<const unsigned short*>(b2), scores, rows, T, Dh, H, Dh / kBK, nullptr, *norm);
-    return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
-  }
-  // workspace == nullptr: W1 already is the fragment-ordered copy (launch_prepare_w1)
-  if (workspace)
-    arrange_w1_kernel<<<512, 256, 0, stream>>>(static_cast<const u32x4*>(W1),
-                                               static_cast<u32x4*>(workspace), M, Dh, nullptr);
-  const void* w1f = workspace ? workspace : W1;
-  const long long blocks = (rows + TOK - 1) / TOK;
-  // Few blocks (mid-length prompts): a block needs 50-85 us for all of K whatever the grid,
-  // so K is cut over blockIdx.y and the epilogue moves to score_finish_kernel; the partial
-  // sums live behind the fragment copy in the workspace (only with a workspace).
-  const int ks = workspace ? frag_ksplit(blocks, Dh / kBK) : 1;
-  float* partial = ks > 1 ? reinterpret_cast<float*>(static_cast<char*>(workspace) +
-                                                     align_up((size_t)M * Dh * 2, 256))
-                          : nullptr;
-  if (ks > 1)
-    score_mlp_frag_kernel<UB, TB, true><<<dim3((unsigned)blocks, ks), 256, lds, stream>>>(
-        static_cast<const unsigned short*>(hidden), static_cast<const unsigned char*>(w1f),
-        static_cast<const unsigned short*>(b1), static_cast<const unsigned short*>(W2),
-        static_cast<const unsigned short*>(b2), scores, rows, T, Dh, H, Dh / kBK / ks, partial, NormArgs{});
-  else
-    score_mlp_frag_kernel<UB, TB, false><<<dim3((unsigned)blocks), 256, lds, stream>>>(
-        static_cast<const unsigned short*>(hidden), static_cast<const unsigned char*>(w1f),
-        static_cast<const unsigned short*>(b1), static_cast<const unsigned short*>(W2),
-        static_cast<const unsigned short*>(b2), scores, rows, T, Dh, H, Dh / kBK, nullptr, NormArgs{});
-  if (hipGetLastError() != hipSuccess) return KVZAP_ERR_RUNTIME;
-  if (ks > 1)
-    score_finish_kernel<<<dim3((unsigned)((rows + 3) / 4)), 256, 0, stream>>>(
-        partial, static_cast<const unsigned short*>(b1), static_cast<const unsigned short*>(W2),
-        static_cast<const unsigned short*>(b2), scores, rows, T, M, H, ks);
+  if (attr_rc != hipSuccess) return KVZAP_ERR_RUNTIME;
+  score_mlp_frag_kernel<UB, TB, kNorm><<<dim3((unsigned)((rows + TOK - 1) / TOK)), 256, lds, stream>>>(
+      static_cast<const unsigned short*>(hidden), static_cast<const unsigned char*>(W1f),
+      static_cast<const unsigned short*>(b1), static_cast<const unsigned short*>(W2),
+      static_cast<const unsigned short*>(b2), scores, rows, T, Dh, H, norm);
   return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
+}
+
+template <bool kNorm>
+int launch_blocks(const void* hidden, const void* W1f, const void* b1, const void* W2, const void* b2,
+                  float* scores, long long rows, int T, int Dh, int M, int H, const NormArgs& norm,
+                  hipStream_t stream) {
+  switch (M / 128) {
+    case 1: return launch_frag<1, 4, kNorm>(hidden, W1f, b1, W2, b2, scores, rows, T, Dh, H, norm, stream);
+    case 2: return launch_frag<2, 4, kNorm>(hidden, W1f, b1, W2, b2, scores, rows, T, Dh, H, norm, stream);
+    case 3: return launch_frag<3, 4, kNorm>(hidden, W1f, b1, W2, b2, scores, rows, T, Dh, H, norm, stream);
+    case 4: return launch_frag<4, 4, kNorm>(hidden, W1f, b1, W2, b2, scores, rows, T, Dh, H, norm, stream);
+    // M = 640: 96-token blocks so that the 5 x 3 accumulator blocks fit (240 registers)
+    case 5: return launch_frag<5, 3, kNorm>(hidden, W1f, b1, W2, b2, scores, rows, T, Dh, H, norm, stream);
+    default: return KVZAP_ERR_UNSUPPORTED;
+  }
 }
 
 template <int UB>
@@ -1070,10 +904,99 @@ __global__ __launch_bounds__(256) void copy_w1_kernel(const u32x4* __restrict__ 
     out[i] = W1[i];
 }
 
+// ---- which kernels score an input ----
+// Measured (D_h = 4096, M = 512, us per call, event pairs over rotating inputs; "blocks" =
+// score_mlp_frag_kernel alone, which is also what a call without a workspace runs):
+//   tokens            128   512  1024  2048  4096  8192 10000 12288 16384 24576 32768
+//   blocks             83    83    83    83    83    84    85    87    89    98   115
+//   best tile          15    16    17    21    27    39    75    85    89   131   175
+// A block of score_mlp_frag_kernel walks all of K for all M units, which takes 75-85 us until
+// 256 of them fill the chip; a tile's time hardly moves until its own grid passes 256 blocks.
+// So: the cost of a round of each kernel as a fixed part plus a part per 64 inputs (fitted to
+// the table above and its like at M = 128 .. 640, within about 10 %), and the cheapest of
+//   tiles alone | whole token blocks alone | full rounds of token blocks, the rest as tiles |
+//   full rounds of the largest tile, the rest as a smaller one.
+// (40000 tokens: 32768 as one full round of blocks and 7232 as tiles instead of two rounds of
+// blocks with the second one mostly empty.)
+struct Segment { int tile; long long rows; };      // tile < 0: score_mlp_frag_kernel
+struct Plan {
+  int n;
+  Segment seg[3];
+  float us;
+  void add(int tile, long long rows, float cost) { seg[n++] = Segment{tile, rows}; us += cost; }
+};
+
+constexpr float kBlockFixed = 7.0f;                                        // us per launch of token blocks
+constexpr float kBlockThin[5] = {0.55f, 0.77f, 0.97f, 1.15f, 1.29f};       // us per 64 inputs, few blocks
+constexpr float kBlockFull[5] = {0.70f, 1.07f, 1.33f, 1.68f, 1.58f};       // ... 256 blocks
+constexpr float kTileFixed[kScoreTiles] = {10.5f, 10.0f, 10.0f, 9.5f, 9.5f};
+constexpr float kTileStep[kScoreTiles] = {0.44f, 0.25f, 0.16f, 0.10f, 0.085f};   // us per 64 inputs and round
+
+inline float cost_blocks(long long rows, int Dh, int M) {
+  const int tok = M / 128 <= 4 ? 128 : 96, i = M / 128 - 1;
+  const long long blocks = (rows + tok - 1) / tok, full = blocks / kChipCUs, rest = blocks % kChipCUs;
+  const float planes = (float)(Dh / kBK);
+  float us = kBlockFixed + (float)full * planes * kBlockFull[i];
+  if (rest) us += planes * (kBlockThin[i] + (kBlockFull[i] - kBlockThin[i]) * (float)rest / kChipCUs);
+  return us;
+}
+
+inline float cost_tile(int tile, long long rows, int Dh, int M) {
+  const long long blocks = score_tile_blocks(tile, rows, M);
+  const long long rounds = (blocks + kChipCUs - 1) / kChipCUs;
+  const float fill = rounds > 1 ? 1.0f : 0.75f + 0.25f * (float)blocks / kChipCUs;
+  return kTileFixed[tile] + (float)(rounds - 1) * 3.0f + (float)rounds * fill * (float)(Dh / kBK) * kTileStep[tile];
+}
+
+inline Plan plan_tile(long long rows, int Dh, int M) {                     // one tile for all rows
+  int best = 0;
+  for (int t = 1; t < kScoreTiles; ++t)
+    if (cost_tile(t, rows, Dh, M) < cost_tile(best, rows, Dh, M)) best = t;
+  Plan p{};
+  p.add(best, rows, cost_tile(best, rows, Dh, M));
+  return p;
+}
+
+Plan plan_score(long long rows, int Dh, int M) {
+  const long long tile_round = (long long)kChipCUs / (M / 128) * 128;      // tokens in a round of the largest tile
+  Plan best{};
+  if (Dh / kBK < kPD + 1) {                 // too few K tiles for token blocks: tiles, or score_mlp_kernel
+    best.add(rows <= kTileMaxRows ? plan_tile(rows, Dh, M).seg[0].tile : -1, rows, 0.0f);
+    return best;
+  }
+  best.add(-1, rows, cost_blocks(rows, Dh, M));
+  auto consider = [&](int head_tile, long long head, float head_cost) {    // head rows, the rest as one tile
+    Plan p{};
+    if (head > 0) p.add(head_tile, head, head_cost);
+    const Plan rest = plan_tile(rows - head, Dh, M);
+    p.add(rest.seg[0].tile, rest.seg[0].rows, rest.us);
+    if (p.us < best.us) best = p;
+  };
+  const long long block_round = (long long)kChipCUs * (M / 128 <= 4 ? 128 : 96);
+  if (rows <= kTileMaxRows) consider(0, 0, 0.0f);
+  if (rows <= kTileMaxRows)
+    for (long long head = tile_round; head < rows; head += tile_round)
+      consider(0, head, cost_tile(0, head, Dh, M));
+  const long long head = rows / block_round * block_round;
+  if (head > 0 && head < rows && rows - head <= kTileMaxRows) consider(-1, head, cost_blocks(head, Dh, M));
+  return best;
+}
+
+long long tile_rows(const Plan& p) {
+  long long n = 0;
+  for (int i = 0; i < p.n; ++i)
+    if (p.seg[i].tile >= 0) n += p.seg[i].rows;
+  return n;
+}
+// the tiles' shares of the scores: at most 16 heads x M/32 unit tiles x rows fp32
+size_t tile_workspace_bytes(long long rows, int M) {
+  return rows > 0 ? align_up((size_t)rows * M * sizeof(float), 256) : 0;
+}
+
 }  // namespace
 
-// The form of W1 that launch_score_mlp takes with workspace == nullptr: fragment order for
-// the main kernel, a plain copy for the small-D_h kernel.
+// The form of W1 that launch_score_mlp takes with prepared == true: fragment order for the main
+// kernel, a plain copy for D_h < 256.
 int launch_prepare_w1(const void* W1, const void* gain, int Dh, int M, void* out, hipStream_t stream) {
   const bool frag = (Dh / kBK) >= kPD + 1;
   if (gain && !frag) return KVZAP_ERR_UNSUPPORTED;
@@ -1087,18 +1010,10 @@ int launch_prepare_w1(const void* W1, const void* gain, int Dh, int M, void* out
   return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
 }
 
-size_t score_mlp_workspace_bytes(long long rows, int Dh, int M) {
-  size_t need = align_up((size_t)M * Dh * 2, 256);                 // W1 in fragment order
-  if (rows > 0 && rows <= kTwoStageRows) {
-    const size_t part = align_up((size_t)skinny_ksplit(rows, Dh, M, kTwoStageBlocks) * rows * M * sizeof(float), 256);
-    need = need > part ? need : part;
-  } else if (rows > 0 && (Dh / kBK) >= kPD + 1) {
-    // mid-length prompts: the main kernel split over K, partial sums behind the fragment copy
-    const int tok = 32 * (M / 128 <= 4 ? 4 : 3);
-    const int ks = frag_ksplit((rows + tok - 1) / tok, Dh / kBK);
-    if (ks > 1) need += align_up((size_t)ks * rows * M * sizeof(float), 256);
-  }
-  return need;
+size_t score_mlp_workspace_bytes(long long rows, int Dh, int M, bool prepared) {
+  const size_t copy = prepared ? 0 : align_up((size_t)M * Dh * 2, 256);      // W1 in fragment order
+  if (rows <= 0) return copy;
+  return copy + tile_workspace_bytes(tile_rows(plan_score(rows, Dh, M)), M);
 }
 
 bool score_rmsnorm_supports(int Dh) { return (Dh / kBK) >= kPD + 1; }
@@ -1106,49 +1021,70 @@ bool score_rmsnorm_supports(int Dh) { return (Dh / kBK) >= kPD + 1; }
 int launch_score_mlp_rmsnorm(const void* x, const void* W1_prepared, const void* gain, float eps,
                              const void* b1, const void* W2, const void* b2, float* scores,
                              float* rstd, void* normed, int B, int T, int Dh, int M, int H,
-                             hipStream_t stream) {
+                             void* workspace, hipStream_t stream) {
   const long long rows = (long long)B * T;
   const NormArgs norm{static_cast<const unsigned short*>(gain), eps, rstd,
                       static_cast<unsigned short*>(normed)};
-  switch (M / 128) {
-    case 1: return launch_frag<1, 4>(x, W1_prepared, b1, W2, b2, scores, rows, T, Dh, H, nullptr, stream, &norm);
-    case 2: return launch_frag<2, 4>(x, W1_prepared, b1, W2, b2, scores, rows, T, Dh, H, nullptr, stream, &norm);
-    case 3: return launch_frag<3, 4>(x, W1_prepared, b1, W2, b2, scores, rows, T, Dh, H, nullptr, stream, &norm);
-    case 4: return launch_frag<4, 4>(x, W1_prepared, b1, W2, b2, scores, rows, T, Dh, H, nullptr, stream, &norm);
-    case 5: return launch_frag<5, 3>(x, W1_prepared, b1, W2, b2, scores, rows, T, Dh, H, nullptr, stream, &norm);
-    default: return KVZAP_ERR_UNSUPPORTED;
+  Plan plan{};
+  if (workspace) plan = plan_score(rows, Dh, M);
+  else plan.add(-1, rows, 0.0f);
+  long long first = 0;
+  for (int i = 0; i < plan.n; ++i) {
+    const Segment& s = plan.seg[i];
+    const int rc = s.tile < 0
+        ? launch_blocks<true>(x, W1_prepared, b1, W2, b2, scores, s.rows, T, Dh, M, H, norm, stream)
+        : launch_score_tile(s.tile, true, x, W1_prepared, b1, W2, b2, scores,
+                            static_cast<float*>(workspace), s.rows, first, T, Dh, M, H, &norm, stream);
+    if (rc != KVZAP_OK) return rc;
+    first += s.rows;
   }
+  return KVZAP_OK;
 }
 
+// prepared: W1 is the copy made by launch_prepare_w1 (a workspace is then optional: without one
+// the token-block kernels score everything); otherwise the workspace receives that copy if needed
 int launch_score_mlp(const void* hidden, const void* W1, const void* b1, const void* W2,
                      const void* b2, float* scores, int B, int T, int Dh, int M, int H,
-                     void* workspace, hipStream_t stream) {
+                     bool prepared, void* workspace, hipStream_t stream) {
   const long long rows = (long long)B * T;
-  if (workspace && rows <= kTwoStageRows) {        // short prompt and the original W1 at hand
-    const int ks = skinny_ksplit(rows, Dh, M, kTwoStageBlocks);
-    const int rc = launch_skinny_gemm(hidden, W1, static_cast<float*>(workspace), rows, Dh, M, ks, stream);
+  const bool frag = (Dh / kBK) >= kPD + 1;
+  Plan plan{};
+  if (workspace) plan = plan_score(rows, Dh, M);
+  else plan.add(-1, rows, 0.0f);
+  const void* blocks_w1 = W1;
+  bool tiles_frag = prepared && frag;
+  float* part = static_cast<float*>(workspace);
+  if (!prepared) {
+    part = reinterpret_cast<float*>(static_cast<char*>(workspace) + align_up((size_t)M * Dh * 2, 256));
+    if (frag && plan.seg[0].tile < 0) {
+      const int rc = launch_prepare_w1(W1, nullptr, Dh, M, workspace, stream);
+      if (rc != KVZAP_OK) return rc;
+      blocks_w1 = workspace;
+    }
+  }
+  long long first = 0;
+  for (int i = 0; i < plan.n; ++i) {
+    const Segment& s = plan.seg[i];
+    int rc;
+    if (s.tile >= 0) {
+      rc = launch_score_tile(s.tile, tiles_frag, hidden, W1, b1, W2, b2, scores, part, s.rows, first,
+                             T, Dh, M, H, nullptr, stream);
+    } else if (frag) {
+      rc = launch_blocks<false>(hidden, blocks_w1, b1, W2, b2, scores, s.rows, T, Dh, M, H, NormArgs{}, stream);
+    } else {
+      switch (M / 128) {
+        case 1: rc = launch_one<1>(hidden, W1, b1, W2, b2, scores, s.rows, T, Dh, H, stream); break;
+        case 2: rc = launch_one<2>(hidden, W1, b1, W2, b2, scores, s.rows, T, Dh, H, stream); break;
+        case 3: rc = launch_one<3>(hidden, W1, b1, W2, b2, scores, s.rows, T, Dh, H, stream); break;
+        case 4: rc = launch_one<4>(hidden, W1, b1, W2, b2, scores, s.rows, T, Dh, H, stream); break;
+        case 5: rc = launch_one<5>(hidden, W1, b1, W2, b2, scores, s.rows, T, Dh, H, stream); break;
+        default: rc = KVZAP_ERR_UNSUPPORTED;
+      }
+    }
     if (rc != KVZAP_OK) return rc;
-    score_finish_kernel<<<dim3((unsigned)((rows + 3) / 4)), 256, 0, stream>>>(
-        static_cast<const float*>(workspace), static_cast<const unsigned short*>(b1),
-        static_cast<const unsigned short*>(W2), static_cast<const unsigned short*>(b2), scores,
-        rows, T, M, H, ks);
-    return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
+    first += s.rows;
   }
-  const bool frag = (Dh / kBK) >= kPD + 1;     // the main variant needs at least kPD+1 K tiles
-#define KVZAP_MLP_CASE(UBV)                                                                     \
-  case UBV:                                                                                     \
-    return frag ? launch_frag<UBV, (UBV <= 4 ? 4 : 3)>(hidden, W1, b1, W2, b2, scores, rows, T, \
-                                                       Dh, H, workspace, stream, nullptr)       \
-                : launch_one<UBV>(hidden, W1, b1, W2, b2, scores, rows, T, Dh, H, stream);
-  switch (M / 128) {
-    KVZAP_MLP_CASE(1)
-    KVZAP_MLP_CASE(2)
-    KVZAP_MLP_CASE(3)
-    KVZAP_MLP_CASE(4)
-    KVZAP_MLP_CASE(5)   // M = 640: 96-token blocks so that the 5 x 3 accumulator blocks fit (240 registers)
-    default: return KVZAP_ERR_UNSUPPORTED;
-  }
-#undef KVZAP_MLP_CASE
+  return KVZAP_OK;
 }
 
 }  // namespace kvzap

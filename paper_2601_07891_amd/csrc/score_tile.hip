@@ -1,0 +1,519 @@
+// KVzap-MLP forward for the inputs that do not fill the chip with whole token blocks (Sec. 3.3,
+// Sec. 4.1; App. B Eq. 5): up to some thousand tokens, and what a long input leaves over.
+//
+// score_mlp_frag_kernel gives one block all M hidden units of 128 tokens, so that `hidden` is
+// read once; a block then walks K for 75-85 us however few blocks there are.  Here the first
+// projection is tiled over units as well: a block owns BU*32 units x BT*32 tokens and all of
+// K, the tile is chosen so that the grid covers the 256 CUs once, and no partial
+// sum of the first projection ever leaves the CU.  The epilogue applies b1 and GELU in fp32 and
+// reduces the block's units against W2; the M/(BU*32) unit tiles of a token meet in a second,
+// small launch (score_tile_sum_kernel) in a fixed order.
+//
+// What bounds it: operand bytes from L2 into the CU.  A block reads (BU + BT)*32*D_h*2 bytes
+// (2 MB at 128 x 128 and D_h = 4096) at 64 bytes per clock at best, against
+// BU*BT*D_h/16*32/4 cycles of matrix pipe; the larger tile is the better one as soon as its
+// grid fills the chip.  Both operands pass through LDS (ring of S stages filled by
+// load-to-LDS), because a wavefront's own loads would fetch every byte two to four times.
+//
+// The eight wavefronts of a block split the K of every stage into KG groups and the tile into
+// WU*32 x WT*32 pieces: a wavefront then always multiplies 2 x 2 (or 2 x 1, 1 x 1) fragments,
+// i.e. one KB of LDS reads per MFMA, two wavefronts share each SIMD and hide each other's
+// waits, and small tiles still occupy all four SIMDs.  The KG partial accumulators are added
+// in a fixed order through LDS.
+//
+// Measured (D_h = 4096, M = 512, both launches, us per call; before: a first projection cut over K
+// with fp32 partial sums in memory and a finishing kernel, and without a workspace
+// score_mlp_frag_kernel alone): 128 tokens 15 (21 / 83), 1024: 17 (37 / 83), 2048: 21 (39 / 83),
+// 4096: 27 (49 / 83), 8192: 38 (64 / 84).  Of the 38 us about 5 are launch and prologue, 4 the
+// epilogue, 4 the second launch; a stage of the 128 x 128 tile takes 0.40 us with the chip full
+// (0.29 with few blocks, 0.23 at the matrix cores' rate), i.e. what is left is power and L2.
+#include <type_traits>
+
+#include "kvzap_internal.h"
+
+namespace kvzap {
+namespace {
+
+constexpr int kWaves = 8;
+constexpr int kThreads = kWaves * 64;
+constexpr int kXcds = 8;
+
+__device__ __forceinline__ void load_to_lds(const void* base, unsigned lane_offset, unsigned lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               ::"s"(lds_base), "v"(lane_offset), "s"(base)
+               : "memory");
+}
+
+// BU x BT: tile in blocks of 32 units / tokens; WU x WT: piece of a wavefront; KG groups of
+// wavefronts over K, P MFMA steps of 16 inputs per wavefront and stage; S stages.
+template <int BU_, int BT_, int WU_, int WT_, int KG_, int P_, int S_>
+struct Tile {
+  static constexpr int BU = BU_, BT = BT_, WU = WU_, WT = WT_, KG = KG_, P = P_, S = S_;
+  static_assert((BU / WU) * (BT / WT) * KG == kWaves, "eight wavefronts");
+  static constexpr int NU = BU * 32, NT = BT * 32;
+  static constexpr int SUB = KG * P * 16 / 64;               // 64-input planes per stage
+  static constexpr int PLANE = (BU + BT) * 4096;             // bytes: unit rows, then token rows
+  static constexpr int STAGE = SUB * PLANE;
+  static constexpr int NL = SUB * (BU + BT) * 4 / kWaves;    // load-to-LDS per wavefront and stage
+  static_assert(SUB * (BU + BT) * 4 % kWaves == 0, "chunks split evenly");
+  // epilogue: a wavefront finishes OWN of the 8-register groups (16 units x 32 tokens) of its
+  // piece; where there are fewer groups than K groups, the wavefronts g >= GROUPS finish none
+  static constexpr int GROUPS = WU * WT * 2;
+  static constexpr int OWN = GROUPS >= KG ? GROUPS / KG : 1;
+  static constexpr int SHARES = (GROUPS / WT / OWN) * (BU / WU);   // wavefronts that finish units of one token
+  static constexpr int RED = kWaves * WU * WT * 4096;
+  static constexpr int DOT = SHARES * 16 * NT * 4;
+  // the ring, and in the same bytes after the main loop what the epilogue needs
+  static constexpr int EPI = RED + DOT + NU * 16 * 2 + NU * 4 + (2 * KG + 1) * NT * 4;
+  static constexpr int LDS = S * STAGE > EPI ? S * STAGE : EPI;
+  static_assert(LDS <= 160 * 1024, "fits the CU");
+};
+
+template <class C, bool kFrag, bool kNorm>
+__global__ __launch_bounds__(kThreads) void score_tile_kernel(
+    const unsigned char* hidden, const unsigned char* W1,
+    const unsigned short* __restrict__ b1, const unsigned short* __restrict__ W2,
+    const unsigned short* __restrict__ b2, float* __restrict__ scores, float* __restrict__ part,
+    long long rows, long long row_first, int T, int Dh, int M, int H, int token_tiles, NormArgs norm) {
+  constexpr int BU = C::BU, BT = C::BT, WU = C::WU, WT = C::WT, KG = C::KG, P = C::P, S = C::S;
+  constexpr int NU = C::NU, NT = C::NT, SUB = C::SUB, NL = C::NL, STAGE = C::STAGE;
+  extern __shared__ __align__(16) unsigned char smem[];
+  float* const sDot = reinterpret_cast<float*>(smem + C::RED);       // [SHARES][16][NT]
+  unsigned char* const sW2 = smem + C::RED + C::DOT;                 // [16][NU] bf16, zero beyond H
+  float* const sB1 = reinterpret_cast<float*>(sW2 + NU * 32);        // [NU]
+  float* const sSsq = sB1 + NU;                                      // [2*KG][NT]
+  float* const sRs = sSsq + 2 * KG * NT;                             // [NT]
+
+  // Workgroups go to the XCDs round-robin: the unit tiles of one token tile sit on one XCD,
+  // one after the other, so that its `hidden` rows are fetched into that L2 once.
+  const int nut = M / NU;
+  const int slot = blockIdx.x / kXcds;
+  const int tt = (slot / nut) * kXcds + (int)(blockIdx.x % kXcds);
+  const int ut = slot % nut;
+  if (tt >= token_tiles) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, kg = lane >> 5;
+  const long long row0 = (long long)tt * NT;                         // relative to row_first
+  const int rows_here = rows - row0 < NT ? (int)(rows - row0) : NT;
+
+  // W2's columns and b1 of this block: held in registers through the main loop
+  unsigned w2_pair[NU / 64 > 0 ? NU / 64 : 1];
+#pragma unroll
+  for (int i = 0; i < (NU / 64 > 0 ? NU / 64 : 1); ++i) {
+    const int x = i * kThreads + tid, h = x / (NU / 2), up = x % (NU / 2);
+    const unsigned v = *reinterpret_cast<const unsigned*>(W2 + (size_t)(h < H ? h : H - 1) * M + ut * NU + 2 * up);
+    w2_pair[i] = h < H ? v : 0u;
+  }
+  const unsigned b1_pair = *reinterpret_cast<const unsigned*>((b1 ? b1 : W2) + ut * NU + 2 * (tid % (NU / 2)));
+
+  // ---- load-to-LDS: chunk c = wid + 8*j of a stage is LDS bytes [c*1024, +1024) ----
+  const int nk = Dh / 64;                                            // 64-input planes in all
+  const int stages = (nk + SUB - 1) / SUB;
+  const unsigned lds0 = lds_address(smem);
+  const unsigned char* const hbase = hidden + (size_t)(row_first + row0) * Dh * 2;
+  const unsigned char* const wbase = kFrag ? W1 + (size_t)ut * BU * 4096 : W1 + (size_t)ut * NU * Dh * 2;
+  const size_t wstep = kFrag ? (size_t)(M / 32) * 4096 : 128;        // bytes from plane to plane
+  unsigned off[NL];
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    const int r = (wid + kWaves * j) % ((BU + BT) * 4);              // chunk within its plane
+    if (r < BU * 4) {
+      const int row = r * 8 + (lane >> 3), p = (lane & 7) ^ lds_swizzle(row);
+      off[j] = kFrag ? (unsigned)r * 1024u + (unsigned)lane * 16u
+                     : (unsigned)row * (unsigned)Dh * 2u + (unsigned)p * 16u;
+    } else {
+      int row = (r - BU * 4) * 8 + (lane >> 3);
+      const int p = (lane & 7) ^ lds_swizzle(row);
+      if (row > rows_here - 1) row = rows_here - 1;                  // clamp: in bounds, result discarded
+      off[j] = (unsigned)row * (unsigned)Dh * 2u + (unsigned)p * 16u;
+    }
+  }
+  // uniform source address of chunk j, moved on by one stage after every issue
+  const unsigned char* src[NL];
+  size_t src_step[NL];
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    const int c = wid + kWaves * j, sub = c / ((BU + BT) * 4), r = c % ((BU + BT) * 4);
+    const size_t plane = r < BU * 4 ? wstep : 128;
+    src[j] = (r < BU * 4 ? wbase : hbase) + sub * plane;
+    src_step[j] = SUB * plane;
+  }
+  // stage `t` of the input into ring stage `stage`.  kEnd: t may be the last stage of an odd
+  // number of planes, whose second plane does not exist: its chunks re-read the first one
+  // (in bounds, not used).
+  auto dma = [&](int j, int t, unsigned stage, auto end_tag) {
+    constexpr bool kEnd = decltype(end_tag)::value;
+    const int c = wid + kWaves * j;
+    const unsigned char* from = src[j];
+    if (kEnd && SUB > 1 && c >= (BU + BT) * 4 && (t + 1) * SUB > nk) from -= src_step[j] / SUB;
+    load_to_lds(from, off[j], lds0 + stage + (unsigned)c * 1024u);
+    src[j] += src_step[j];
+  };
+  typedef std::integral_constant<bool, true> Yes;
+  typedef std::integral_constant<bool, false> No;
+#pragma unroll
+  for (int t = 0; t < S; ++t)
+    if (t < stages) {
+#pragma unroll
+      for (int j = 0; j < NL; ++j) dma(j, t, t * STAGE, Yes{});
+    }
+
+  // ---- this wavefront's piece and K group ----
+  constexpr int NWU = BU / WU;
+  const int wu = wid % NWU, wt = (wid / NWU) % (BT / WT), g = wid / (kWaves / KG);
+  // byte offsets of its fragments in a stage, step p; block i of 32 is 4096 bytes on
+  unsigned a_off[P], b_off[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const int s = g * P + p, sub = s / 4, kk = s % 4;
+    const unsigned piece = ((unsigned)(kk * 2 + kg) ^ (unsigned)lds_swizzle(l32)) * 16u + (unsigned)l32 * 128u;
+    a_off[p] = (unsigned)(sub * C::PLANE + wu * WU * 4096) + (kFrag ? (unsigned)kk * 1024u + (unsigned)lane * 16u : piece);
+    b_off[p] = (unsigned)(sub * C::PLANE + BU * 4096 + wt * WT * 4096) + piece;
+  }
+  floatx16 acc[WU][WT];
+#pragma unroll
+  for (int u = 0; u < WU; ++u)
+#pragma unroll
+    for (int w = 0; w < WT; ++w)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[u][w][e] = 0.0f;
+  float ssq[WT];
+#pragma unroll
+  for (int w = 0; w < WT; ++w) ssq[w] = 0.0f;
+
+  bf16x8 fa[2][P][WU], fb[2][P][WT];
+  constexpr int kReads = P * (WU + WT), kMfmas = P * WU * WT;
+  auto read_one = [&](int buf, int i, unsigned stage) {              // fragment i of a stage
+    const int p = i / (WU + WT), x = i % (WU + WT);
+    if (x < WU) fa[buf][p][x] = *reinterpret_cast<const bf16x8*>(smem + stage + a_off[p] + x * 4096);
+    else fb[buf][p][x - WU] = *reinterpret_cast<const bf16x8*>(smem + stage + b_off[p] + (x - WU) * 4096);
+  };
+  auto mfma = [&](int buf, int m) {
+    const int p = m / (WU * WT), u = m / WT % WU, w = m % WT;
+    acc[u][w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][p][u], fb[buf][p][w], acc[u][w], 0, 0, 0);
+  };
+  auto squares = [&](int buf) {                                      // sum of x^2 of this wavefront's tokens
+    if (wu == 0) {
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int w = 0; w < WT; ++w)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+            const bf16x2 pr = {fb[buf][p][w][2 * e], fb[buf][p][w][2 * e + 1]};
+            ssq[w] = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, ssq[w], false);
+          }
+    }
+  };
+  // at most `left` younger stages may stay outstanding
+  auto wait_stage = [&](int left) {
+    if (left >= S - 2) wait_vmcnt<(S - 2) * NL>();
+    else if (S > 3 && left == S - 3) wait_vmcnt<(S > 3 ? S - 3 : 0) * NL>();
+    else if (S > 4 && left == S - 4) wait_vmcnt<(S > 4 ? S - 4 : 0) * NL>();
+    else if (S > 5 && left == S - 5) wait_vmcnt<(S > 5 ? S - 5 : 0) * NL>();
+    else if (S > 6 && left == S - 6) wait_vmcnt<(S > 6 ? S - 6 : 0) * NL>();
+    else wait_vmcnt<0>();
+  };
+  if (stages >= S) wait_vmcnt<(S - 1) * NL>();
+  else wait_stage(stages - 1);
+  block_barrier_no_drain();
+#pragma unroll
+  for (int i = 0; i < kReads; ++i) read_one(0, i, 0);
+
+  // Iteration t multiplies the fragments that iteration t-1 read.  Once every wavefront has
+  // them (lgkmcnt(0) ahead of the barrier) the stage they came from is free, and behind the
+  // same barrier stage t+1 has landed for everybody: its fragments are read, and the load of
+  // stage t+S is issued into the free one, between the MFMAs.
+  unsigned st_next = STAGE, st_free = 0;                             // ring stages of t+1 and of t
+  auto advance = [&]() {
+    st_next += STAGE; if (st_next == S * STAGE) st_next = 0;
+    st_free += STAGE; if (st_free == S * STAGE) st_free = 0;
+  };
+  constexpr int kLgkm0 = 0xc07f;                                     // s_waitcnt lgkmcnt(0)
+  auto full_step = [&](int t, auto buf_tag) {
+    constexpr int buf = decltype(buf_tag)::value;
+    __builtin_amdgcn_s_waitcnt(kLgkm0);
+    __builtin_amdgcn_sched_barrier(0);
+    mfma(buf, 0);                                                    // runs while the others arrive
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vmcnt<(S - 2) * NL>();
+    block_barrier_no_drain();
+    constexpr int kReadSlots = (kMfmas + 1) / 2, kDmaSlots = kMfmas - kReadSlots > 0 ? kMfmas - kReadSlots : 1;
+#pragma unroll
+    for (int m = 0; m < kMfmas; ++m) {
+      if (m > 0) mfma(buf, m);
+#pragma unroll
+      for (int i = 0; i < kReads; ++i)
+        if (i * kReadSlots / kReads == m) read_one(buf ^ 1, i, st_next);
+#pragma unroll
+      for (int j = 0; j < NL; ++j)
+        if ((kMfmas == 1 ? 0 : kReadSlots + j * kDmaSlots / NL) == m) dma(j, t + S, st_free, No{});
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (kNorm) squares(buf);
+    advance();
+  };
+  auto end_step = [&](int t, auto buf_tag) {
+    constexpr int buf = decltype(buf_tag)::value;
+    __builtin_amdgcn_s_waitcnt(kLgkm0);
+    if (t + 1 < stages) {
+      wait_stage(stages - 2 - t);
+      block_barrier_no_drain();
+#pragma unroll
+      for (int i = 0; i < kReads; ++i) read_one(buf ^ 1, i, st_next);
+      if (t + S < stages) {
+#pragma unroll
+        for (int j = 0; j < NL; ++j) dma(j, t + S, st_free, Yes{});
+      }
+    }
+    if (SUB == 1 || t * SUB + (g * P) / 4 < nk) {                    // odd end: no inputs left for this group
+#pragma unroll
+      for (int m = 0; m < kMfmas; ++m) mfma(buf, m);
+      if constexpr (kNorm) squares(buf);
+    }
+    advance();
+  };
+  typedef std::integral_constant<int, 0> Buf0;
+  typedef std::integral_constant<int, 1> Buf1;
+  int t = 0;
+  for (; t + S + 2 < stages; t += 2) {      // (the very last stage, which may be odd, is fetched below)
+    full_step(t, Buf0{});
+    full_step(t + 1, Buf1{});
+  }
+  for (; t < stages; t += 2) {
+    end_step(t, Buf0{});
+    if (t + 1 < stages) end_step(t + 1, Buf1{});
+  }
+  block_barrier_no_drain();                 // all reads of the ring are done: its LDS is reused
+
+  // ---- the KG partial tiles meet in LDS: red[wavefront][register / 4][lane] x 16 B ----
+  float* const red = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int u = 0; u < WU; ++u)
+#pragma unroll
+    for (int w = 0; w < WT; ++w)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        floatx4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[u][w][4 * q + e];
+        *reinterpret_cast<floatx4*>(red + (size_t)wid * (WU * WT * 1024) + (((w * WU + u) * 4 + q) * 64 + lane) * 4) = v;
+      }
+  if constexpr (kNorm) {
+    if (wu == 0) {
+#pragma unroll
+      for (int w = 0; w < WT; ++w) sSsq[(2 * g + kg) * NT + (wt * WT + w) * 32 + l32] = ssq[w];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < (NU / 64 > 0 ? NU / 64 : 1); ++i)
+    if (i * kThreads + tid < NU * 8) reinterpret_cast<unsigned*>(sW2)[i * kThreads + tid] = w2_pair[i];
+  if (tid < NU / 2) {
+    sB1[2 * tid] = b1 ? __uint_as_float(b1_pair << 16) : 0.0f;
+    sB1[2 * tid + 1] = b1 ? __uint_as_float(b1_pair & 0xffff0000u) : 0.0f;
+  }
+  __syncthreads();
+
+  // ---- b1, GELU and the block's share of the second projection ----
+  // Group s of 8 registers (index ((w*WU + u)*2 + s')) holds, for token l32 of block w, the
+  // units 32u + 16s' + 4kg + {0..3, 8..11}: the B operand of one MFMA against the same columns
+  // of W2.  The activation stays fp32: it enters as three bf16 terms (24 bits), W2 is bf16.
+  constexpr int kStride = kWaves / KG * WU * WT * 1024;              // floats from K group to K group
+  const int piece = wid % (kWaves / KG);                             // (wu, wt) of this wavefront
+  if (C::GROUPS >= KG || g < C::GROUPS) {
+    const int first = g * C::OWN;                                    // its groups: first .. first + OWN - 1
+    const int w = first / (2 * WU), tok = (wt * WT + w) * 32 + l32;
+    float rs = 1.0f;
+    if constexpr (kNorm) {
+      float s2 = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 2 * KG; ++i) s2 += sSsq[i * NT + tok];
+      rs = 1.0f / sqrtf(s2 / (float)Dh + norm.eps);
+    }
+    floatx16 dot;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) dot[e] = 0.0f;
+#pragma unroll
+    for (int o = 0; o < C::OWN; ++o) {
+      const int grp = first + o, u = grp / 2 % WU, s16 = grp % 2;
+      const int u0 = (wu * WU + u) * 32 + s16 * 16 + 4 * kg;         // units u0..u0+3 and u0+8..u0+11
+      const float* from = red + (size_t)piece * (WU * WT * 1024) + (grp * 128 + lane) * 4;
+      floatx4 z0 = *reinterpret_cast<const floatx4*>(from), z1 = *reinterpret_cast<const floatx4*>(from + 256);
+#pragma unroll
+      for (int i = 1; i < KG; ++i) {
+        z0 += *reinterpret_cast<const floatx4*>(from + i * kStride);
+        z1 += *reinterpret_cast<const floatx4*>(from + i * kStride + 256);
+      }
+      const floatx4 c0 = *reinterpret_cast<const floatx4*>(sB1 + u0), c1 = *reinterpret_cast<const floatx4*>(sB1 + u0 + 8);
+      u32x4 w2 = {0u, 0u, 0u, 0u};
+      if (l32 < 16) {
+        const uint2 p0 = *reinterpret_cast<const uint2*>(sW2 + ((size_t)l32 * NU + u0) * 2);
+        const uint2 p1 = *reinterpret_cast<const uint2*>(sW2 + ((size_t)l32 * NU + u0 + 8) * 2);
+        w2.x = p0.x; w2.y = p0.y; w2.z = p1.x; w2.w = p1.y;
+      }
+      bf16x8 hi, mid, lo;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float z = e < 4 ? z0[e] : z1[e - 4], c = e < 4 ? c0[e] : c1[e - 4];
+        const float a = gelu_exact(kNorm ? fmaf(z, rs, c) : z + c);
+        hi[e] = (__bf16)a;
+        const float r1 = a - (float)hi[e];
+        mid[e] = (__bf16)r1;
+        lo[e] = (__bf16)(r1 - (float)mid[e]);
+      }
+      const bf16x8 wa = __builtin_bit_cast(bf16x8, w2);
+      dot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, lo, dot, 0, 0, 0);
+      dot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, mid, dot, 0, 0, 0);
+      dot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, hi, dot, 0, 0, 0);
+    }
+    // dot[e], e < 8: head 8*(e/4) + 4*kg + e%4 of token `tok`
+    const int share = wu * (C::SHARES / NWU) + first % (2 * WU) / C::OWN;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (8 * (e / 4) < H) sDot[(share * 16 + 8 * (e / 4) + 4 * kg + (e % 4)) * NT + tok] = dot[e];
+    if constexpr (kNorm) {
+      if (share == 0 && kg == 0) {
+        sRs[tok] = rs;
+        if (ut == 0 && tok < rows_here) norm.rstd[row_first + row0 + tok] = rs;
+      }
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < H * NT; i += kThreads) {
+    const int h = i / NT, tk = i % NT;
+    if (tk < rows_here) {
+      float s = sDot[h * NT + tk];
+#pragma unroll
+      for (int p = 1; p < C::SHARES; ++p) s += sDot[(p * 16 + h) * NT + tk];
+      if (nut == 1) {
+        const long long r = row_first + row0 + tk, bidx = r / T;
+        scores[((size_t)bidx * H + h) * T + (r - bidx * T)] = s + (b2 ? bf16_bits_to_float(b2[h]) : 0.0f);
+      } else {
+        part[((size_t)ut * H + h) * rows + row0 + tk] = s;
+      }
+    }
+  }
+  if constexpr (kNorm) {
+    if (norm.normed) {
+      // the unit tiles of a token tile share the columns of its normalised states
+      const int ppr = Dh / 8, share = (ppr + nut - 1) / nut;
+      const int c0 = ut * share, c1 = c0 + share < ppr ? c0 + share : ppr;
+      const int width = c1 - c0;
+      const u32x4* xin = reinterpret_cast<const u32x4*>(hbase);
+      u32x4* yout = reinterpret_cast<u32x4*>(norm.normed + (size_t)(row_first + row0) * Dh);
+      const u32x4* gain8 = reinterpret_cast<const u32x4*>(norm.gain);
+      const int total = rows_here * width;
+      constexpr int kFly = 4;
+      for (int p0 = tid; p0 < total; p0 += kThreads * kFly) {
+        u32x4 x[kFly];
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+          const int p = p0 + kThreads * u;
+          if (p < total) x[u] = xin[(size_t)(p / width) * ppr + c0 + p % width];
+        }
+#pragma unroll
+        for (int u = 0; u < kFly; ++u) {
+          const int p = p0 + kThreads * u;
+          if (p < total) {
+            const int r = p / width, c = c0 + p % width;
+            const u32x4 gn = gain8[c];
+            const float sc = sRs[r];
+            u32x4 y;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float lo = __uint_as_float(x[u][e] << 16) * sc * __uint_as_float(gn[e] << 16);
+              const float hi = __uint_as_float(x[u][e] & 0xffff0000u) * sc * __uint_as_float(gn[e] & 0xffff0000u);
+              typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+              const bf16x2 pr = {(__bf16)lo, (__bf16)hi};
+              y[e] = __builtin_bit_cast(unsigned int, pr);
+            }
+            __builtin_nontemporal_store(y, yout + (size_t)r * ppr + c);
+          }
+        }
+      }
+    }
+  }
+}
+
+// scores[b,h,t] = sum over unit tiles (in order) + b2
+__global__ __launch_bounds__(256) void score_tile_sum_kernel(
+    const float* __restrict__ part, const unsigned short* __restrict__ b2, float* __restrict__ scores,
+    long long rows, long long row_first, int T, int H, int nut) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  const int h = blockIdx.y;
+  if (i >= rows) return;
+  float s = 0.0f;
+  for (int u = 0; u < nut; ++u) s += part[((size_t)u * H + h) * rows + i];
+  if (b2) s += bf16_bits_to_float(b2[h]);
+  const long long r = row_first + i, bidx = r / T;
+  scores[((size_t)bidx * H + h) * T + (r - bidx * T)] = s;
+}
+
+typedef Tile<4, 4, 2, 2, 2, 2, 5> T128x128;
+typedef Tile<4, 2, 2, 2, 4, 1, 6> T128x64;
+typedef Tile<2, 2, 2, 2, 8, 1, 5> T64x64;
+typedef Tile<2, 1, 2, 1, 8, 1, 6> T64x32;
+typedef Tile<1, 1, 1, 1, 8, 1, 8> T32x32;
+
+template <class C, bool kFrag, bool kNorm>
+int launch_tile(const void* hidden, const void* W1, const void* b1, const void* W2, const void* b2,
+                float* scores, float* part, long long rows, long long row_first, int T, int Dh, int M,
+                int H, const NormArgs& norm, hipStream_t stream) {
+  static const hipError_t attr_rc =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(score_tile_kernel<C, kFrag, kNorm>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+  if (attr_rc != hipSuccess) return KVZAP_ERR_RUNTIME;
+  const int nut = M / C::NU;
+  const long long tt = (rows + C::NT - 1) / C::NT;
+  const long long grid = (tt + kXcds - 1) / kXcds * kXcds * nut;
+  score_tile_kernel<C, kFrag, kNorm><<<dim3((unsigned)grid), kThreads, C::LDS, stream>>>(
+      static_cast<const unsigned char*>(hidden), static_cast<const unsigned char*>(W1),
+      static_cast<const unsigned short*>(b1), static_cast<const unsigned short*>(W2),
+      static_cast<const unsigned short*>(b2), scores, part, rows, row_first, T, Dh, M, H, (int)tt, norm);
+  if (hipGetLastError() != hipSuccess) return KVZAP_ERR_RUNTIME;
+  if (nut > 1)
+    score_tile_sum_kernel<<<dim3((unsigned)((rows + 255) / 256), H), 256, 0, stream>>>(
+        part, static_cast<const unsigned short*>(b2), scores, rows, row_first, T, H, nut);
+  return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
+}
+
+template <class C>
+int launch_form(bool frag, const void* hidden, const void* W1, const void* b1, const void* W2,
+                const void* b2, float* scores, float* part, long long rows, long long row_first,
+                int T, int Dh, int M, int H, const NormArgs* norm, hipStream_t stream) {
+  if (norm)
+    return launch_tile<C, true, true>(hidden, W1, b1, W2, b2, scores, part, rows, row_first, T, Dh, M, H, *norm, stream);
+  if (frag)
+    return launch_tile<C, true, false>(hidden, W1, b1, W2, b2, scores, part, rows, row_first, T, Dh, M, H, NormArgs{}, stream);
+  return launch_tile<C, false, false>(hidden, W1, b1, W2, b2, scores, part, rows, row_first, T, Dh, M, H, NormArgs{}, stream);
+}
+
+}  // namespace
+
+long long score_tile_blocks(int tile, long long rows, int M) {
+  auto n = [&](int nu, int nt) { return (rows + nt - 1) / nt * (M / nu); };
+  switch (tile) {
+    case 0: return n(T128x128::NU, T128x128::NT);
+    case 1: return n(T128x64::NU, T128x64::NT);
+    case 2: return n(T64x64::NU, T64x64::NT);
+    case 3: return n(T64x32::NU, T64x32::NT);
+    default: return n(T32x32::NU, T32x32::NT);
+  }
+}
+
+int launch_score_tile(int tile, bool frag, const void* hidden, const void* W1, const void* b1,
+                      const void* W2, const void* b2, float* scores, float* part, long long rows,
+                      long long row_first, int T, int Dh, int M, int H, const NormArgs* norm,
+                      hipStream_t stream) {
+  switch (tile) {
+    case 0: return launch_form<T128x128>(frag, hidden, W1, b1, W2, b2, scores, part, rows, row_first, T, Dh, M, H, norm, stream);
+    case 1: return launch_form<T128x64>(frag, hidden, W1, b1, W2, b2, scores, part, rows, row_first, T, Dh, M, H, norm, stream);
+    case 2: return launch_form<T64x64>(frag, hidden, W1, b1, W2, b2, scores, part, rows, row_first, T, Dh, M, H, norm, stream);
+    case 3: return launch_form<T64x32>(frag, hidden, W1, b1, W2, b2, scores, part, rows, row_first, T, Dh, M, H, norm, stream);
+    default: return launch_form<T32x32>(frag, hidden, W1, b1, W2, b2, scores, part, rows, row_first, T, Dh, M, H, norm, stream);
+  }
+}
+
+}  // namespace kvzap

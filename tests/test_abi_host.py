@@ -261,3 +261,18 @@ def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(binding, "LIB_PATH", str(tmp_path / "nope.so"))
     with pytest.raises(FileNotFoundError):
         binding.lib()
+
+
+def test_prepared_scorers_with_a_workspace(lib):
+    P, Q = 0x10000, 0x20000
+    need = lib.kvzap_workspace_bytes(binding.CALL_SCORE_PREPARED, 1, 1024, 4096, 512, 8)
+    assert 0 < need <= lib.kvzap_workspace_bytes(binding.CALL_SCORE, 1, 1024, 4096, 512, 8)
+    assert lib.kvzap_workspace_bytes(binding.CALL_SCORE_PREPARED, 1, 131072, 4096, 512, 8) == 0   # token blocks only
+    f = lib.kvzap_score_prepared_ws
+    assert f(P, P, None, P, None, P, 1, 1024, 4096, 512, 8, None, 0, None) == ERR["workspace"]
+    assert f(P, P, None, P, None, P, 1, 1024, 4096, 512, 8, Q, need - 1, None) == ERR["workspace"]
+    assert f(P, P, None, P, None, P, 1, 1024, 4096, 512, 8, Q + 16, need, None) == ERR["workspace"]
+    assert f(P, P, None, P, None, P, 1, 0, 4096, 512, 8, None, 0, None) == 0
+    g = lib.kvzap_score_rmsnorm_ws
+    assert g(P, P, P, 1e-6, None, P, None, P, P, None, 1, 1024, 4096, 512, 8, None, 0, None) == ERR["workspace"]
+    assert g(P, P, P, 1e-6, None, P, None, P, P, None, 1, 1024, 4096, 512, 8, Q, need - 1, None) == ERR["workspace"]

@@ -1,0 +1,117 @@
+"""The tiled MLP scorer (short inputs, and what whole rounds of token blocks leave over) and the
+rule that chooses between it and the token-block kernel, against the float64 oracle."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import kvzap_oracle as O
+from paper_2601_07891_amd import binding, synth
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _case(B, T, Dh, M, H, seed):
+    g = torch.Generator().manual_seed(seed)
+    w = {"W1": (torch.randn((M, Dh), generator=g) * Dh ** -0.5).bfloat16(),
+         "b1": (torch.randn((M,), generator=g) * 0.1).bfloat16(),
+         "W2": (torch.randn((H, M), generator=g) * M ** -0.5).bfloat16(),
+         "b2": (torch.randn((H,), generator=g) * 0.1).bfloat16()}
+    return torch.randn((B, T, Dh), generator=g).bfloat16(), w
+
+
+def _oracle(hid_rows, w):
+    ow = synth.oracle_weights(w)
+    return O.score_mlp(O.bf16_bits_to_f64(synth.bits(hid_rows)), ow["W1"], ow["b1"], ow["W2"], ow["b2"])
+
+
+# one token; one less, one more than each tile's 32 / 64 / 128 tokens; several tiles of each kind
+# (the rule takes smaller tiles for fewer tokens); every M; odd numbers of 64-input planes (the
+# small tiles take two planes a stage); fewer planes than ring stages; 16 heads
+SHAPES = [(1, 1, 64, 128, 1), (1, 31, 4096, 512, 8), (1, 33, 192, 128, 3), (1, 513, 4096, 512, 8),
+          (1, 1025, 4096, 512, 8), (1, 2049, 2048, 512, 8), (1, 4097, 1024, 512, 8),
+          (3, 701, 4096, 512, 8), (1, 257, 5120, 640, 16), (2, 100, 320, 384, 8), (5, 77, 576, 640, 9),
+          (1, 3000, 448, 256, 4)]
+
+
+@pytest.mark.parametrize("B,T,Dh,M,H", SHAPES)
+def test_tiles_against_the_oracle(B, T, Dh, M, H):
+    # fp32 sums of D_h products, then of M: relative 2-norm error ~ sqrt(D_h) * 2^-24 at most,
+    # 4e-6 at D_h = 5120 (the single kernel's fp16 activations would show 2e-4)
+    hid, w = _case(B, T, Dh, M, H, seed=T + M)
+    d = {k: v.to(DEV) for k, v in w.items()}
+    want = np.stack([_oracle(hid[b], w) for b in range(B)])
+    ws = torch.full((binding.kvzap_workspace_bytes(binding.CALL_SCORE, B, T, Dh, M, H),), 0xff,
+                    dtype=torch.uint8, device=DEV)
+    raw = binding.kvzap_score(hid.to(DEV), d["W1"], d["b1"], d["W2"], d["b2"], workspace=ws)
+    prep = binding.kvzap_score_prepared(hid.to(DEV), binding.kvzap_prepare_scorer(d["W1"]), d["b1"],
+                                        d["W2"], d["b2"])
+    assert torch.equal(raw, prep)
+    err = parity.to_np(raw).astype(np.float64) - want
+    assert np.linalg.norm(err) <= 4e-6 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("T,Dh,M", [(8192 + 33, 512, 512), (8192 + 4096 + 5, 512, 512), (32768 + 1, 256, 512),
+                                    (24576 + 700, 256, 640), (2 * 32768 + 3000, 256, 512), (20000, 192, 128)])
+def test_rounds_and_remainders(T, Dh, M):
+    # whole rounds by one kernel, the rest by another: the rows on both sides of every place
+    # where one kernel can hand over to the next, and the last ones, all within the tolerance
+    # of the fp16 form (reading 7: 1e-2 on max(|s|, 1); 6e-3 relative to the row is ample here)
+    H = 8
+    hid, w = _case(1, T, Dh, M, H, seed=T)
+    d = {k: v.to(DEV) for k, v in w.items()}
+    got = parity.to_np(binding.kvzap_score_prepared(hid.to(DEV), binding.kvzap_prepare_scorer(d["W1"]),
+                                                    d["b1"], d["W2"], d["b2"]))[0]
+    raw = parity.to_np(binding.kvzap_score(hid.to(DEV), d["W1"], d["b1"], d["W2"], d["b2"]))[0]
+    assert np.array_equal(got, raw) and np.isfinite(got).all()
+    at = sorted({t for edge in (0, 8192, 12288, 16384, 24576, 32768, 65536, T)
+                 for t in range(edge - 130, edge + 130) if 0 <= t < T})
+    want = _oracle(hid[0, at], w)
+    assert np.abs(got[:, at] - want).max() <= 6e-3
+
+
+@pytest.mark.parametrize("normed", [False, True])
+@pytest.mark.parametrize("T,Dh,M", [(1, 256, 128), (130, 4096, 512), (1500, 576, 640), (2049, 1024, 512),
+                                    (32768 + 77, 256, 512)])
+def test_normalising_tiles(T, Dh, M, normed):
+    H, eps = 8, 1e-6
+    x, w = _case(1, T, Dh, M, H, seed=T + 1)
+    x = (x.float() * torch.exp(0.5 * torch.randn((1, T, 1), generator=torch.Generator().manual_seed(T)))).bfloat16()
+    gain = (1 + 0.1 * torch.randn(Dh, generator=torch.Generator().manual_seed(3))).bfloat16()
+    d = {k: v.to(DEV) for k, v in w.items()}
+    prep = binding.kvzap_prepare_scorer_rmsnorm(d["W1"], gain.to(DEV))
+    scores, rstd, states = binding.kvzap_score_rmsnorm(x.to(DEV), prep, gain.to(DEV), eps, d["b1"], d["W2"],
+                                                       d["b2"], want_normed=normed)
+    at = [t for t in range(T) if t < 130 or t > T - 130]
+    x64 = x[0, at].double()
+    r64 = torch.rsqrt(x64.square().mean(-1) + eps)
+    # the prepared weights are W1 * gain rounded to bf16: the oracle gets those
+    wg = dict(w, W1=(w["W1"].float() * gain.float()).bfloat16())
+    ow = synth.oracle_weights(wg)
+    want = O.score_mlp((x64 * r64[:, None]).numpy(), ow["W1"], ow["b1"], ow["W2"], ow["b2"])
+    assert np.abs(parity.to_np(scores)[0][:, at] - want).max() <= 6e-3
+    assert np.abs(parity.to_np(rstd)[0][at] / r64.numpy() - 1).max() <= 1e-5    # sqrt(D_h) * 2^-24
+    if normed:
+        ref = x64 * r64[:, None] * gain.double()
+        got = states[0, at].double().cpu()
+        assert ((got - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-30).all()       # one bf16 rounding
+        assert torch.isfinite(states.float()).all()
+
+
+def test_entry_points_without_a_workspace_keep_the_token_blocks():
+    B, T, Dh, M, H = 1, 700, 512, 512, 8
+    hid, w = _case(B, T, Dh, M, H, seed=5)
+    d = {k: v.to(DEV) for k, v in w.items()}
+    prep = binding.kvzap_prepare_scorer(d["W1"])
+    x, out = hid.to(DEV), torch.full((B, H, T), float("nan"), device=DEV)
+    rc = binding.lib().kvzap_score_prepared(x.data_ptr(), prep.data_ptr(), d["b1"].data_ptr(), d["W2"].data_ptr(),
+                                            d["b2"].data_ptr(), out.data_ptr(), B, T, Dh, M, H,
+                                            ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    want = _oracle(hid[0], w)
+    err = parity.to_np(out)[0] - want
+    assert np.abs(err).max() <= 6e-3
+    assert np.linalg.norm(err) > 1e-5 * np.linalg.norm(want)       # fp16 activations: not the tiles
