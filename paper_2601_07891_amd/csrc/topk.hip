@@ -15,7 +15,7 @@
 //     (complete) histograms -- a sum over the group's pass-0 slots, then one block scan per
 //     level with two barriers -- so no select kernel and no host step sits between passes;
 //   * the last kernel follows the whole chain and writes the thresholds.
-// No block waits for another.
+// No block waits for another.  Groups of up to 65536 scores take topk_one_kernel instead.
 #include "kvzap_internal.h"
 
 namespace kvzap {
@@ -316,6 +316,136 @@ __global__ __launch_bounds__(kThreads) void topk_final_kernel(
   }
 }
 
+// ---- one launch: a block per group, the group's keys in registers ----
+// The chain above is four launches, and on a few ten thousand scores each of them is mostly
+// launch, barriers and the walk through the other passes' histograms.  Up to kOneMax scores
+// a single block holds its group's keys in registers (kPer per thread, every load issued at
+// once) and does all three passes (digits of 11, 11 and 10 bits) on LDS histograms.  Scores
+// crowd into few exponents, so the wavefronts' atomics would collide on a few words: each bin
+// has four counters side by side, chosen by the lane, which spread over four banks.
+// Measured, us per call (one launch / the four above), 8 heads: 1024 scores 7.1 / 19.8,
+// 16384: 9.1 / 21.8, 32768: 13.1 / 22.0, 65536: 21.2 / 22.8; 24 heads of 20011: 13.1 / 23.4;
+// 64 heads of 65536: 21.4 / 45.7; a layer of 8 pooled heads of 8192: 20.6 / 21.0.
+// Past 65536 the keys no longer fit the registers and the many blocks of the chain win.
+constexpr int kOneThreads = 1024;
+constexpr int kOneWaves = kOneThreads / 64;
+constexpr int kOneBins = 2048;
+constexpr int kCopies = 4;
+constexpr long long kOneMax = 64 * kOneThreads;            // scores of a group
+constexpr unsigned kNoKey = 0xffffffffu;                  // the key of a NaN: no score has it
+
+// Bin of the rank-th entry (1-based, in bin order) of s_hist, the rank inside it and the
+// total: every thread gets the same answer.  Outside [1, total] the bin is meaningless.
+__device__ __forceinline__ void pick_one(const unsigned* s_hist, long long& rank, unsigned& bin,
+                                         unsigned& total, unsigned* s_wave, unsigned* s_pick) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  __syncthreads();                                         // the histogram is complete
+  const u32x4 c0 = reinterpret_cast<const u32x4*>(s_hist)[2 * tid], c1 = reinterpret_cast<const u32x4*>(s_hist)[2 * tid + 1];
+  const unsigned v0 = c0.x + c0.y + c0.z + c0.w, v1 = c1.x + c1.y + c1.z + c1.w, mine = v0 + v1;
+  unsigned inc = mine;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const unsigned up = __shfl_up(inc, off, 64);
+    if (lane >= off) inc += up;
+  }
+  if (lane == 63) s_wave[wv] = inc;
+  if (tid == 0) { s_pick[0] = 0u; s_pick[1] = 0u; }
+  __syncthreads();
+  unsigned before = 0;
+  total = 0;
+#pragma unroll
+  for (int x = 0; x < kOneWaves; ++x) {
+    const unsigned t = s_wave[x];
+    if (x < wv) before += t;
+    total += t;
+  }
+  const long long ex = (long long)before + inc - mine;     // entries in bins before this thread's two
+  if (ex < rank && rank <= ex + mine) {                    // exactly one thread when 1 <= rank <= total
+    const bool second = rank > ex + v0;
+    s_pick[0] = 2u * tid + (second ? 1u : 0u);
+    s_pick[1] = (unsigned)(rank - ex - (second ? v0 : 0u));
+  }
+  __syncthreads();
+  bin = s_pick[0];
+  rank = s_pick[1];
+}
+
+template <int kPer>
+__global__ __launch_bounds__(kOneThreads) void topk_one_kernel(
+    const float* __restrict__ scores, int window, const int32_t* __restrict__ seq_lens, int H,
+    int T, int per_layer, long long k, float* __restrict__ tau_out) {
+  __shared__ __align__(16) unsigned s_hist[kOneBins * kCopies];
+  __shared__ unsigned s_wave[kOneWaves], s_pick[2];
+  const int tid = threadIdx.x, copy = tid & (kCopies - 1);
+  const int g = blockIdx.x, b = per_layer ? g : g / H;
+  const int rows = per_layer ? H : 1;
+  const float* base = scores + (size_t)g * rows * T;
+  const int Tb = seq_lens ? (seq_lens[b] < T ? seq_lens[b] : T) : T;
+  const int n_pop = Tb > window ? Tb - window : 0;          // entries of a row in the population
+  // element i of this thread is entry tid + i*kOneThreads of the pooled rows; past the end it
+  // re-reads entry 0 of the group, which exists, and drops it
+  unsigned key[kPer];
+  {
+    const int n = n_pop * rows, div = n_pop > 0 ? n_pop : 1;
+    const int dr = kOneThreads / div, dt = kOneThreads - dr * div;
+    int r = tid / div, t = tid - r * div;
+    float s[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      s[i] = base[tid + i * kOneThreads < n ? r * T + t : 0];
+      r += dr;
+      t += dt;
+      if (t >= div) { t -= div; ++r; }
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      key[i] = tid + i * kOneThreads < n && s[i] == s[i] ? desc_key(s[i]) : kNoKey;
+  }
+  auto clear = [&]() {
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < kOneBins * kCopies / 4 / kOneThreads; ++i)
+      reinterpret_cast<u32x4*>(s_hist)[i * kOneThreads + tid] = zero;
+    __syncthreads();
+  };
+  long long rank = k;
+  unsigned prefix = 0, bin, total, population = 0;
+  clear();
+#pragma unroll
+  for (int i = 0; i < kPer; ++i)
+    if (key[i] != kNoKey) atomicAdd(&s_hist[(key[i] >> 21) * kCopies + copy], 1u);
+  pick_one(s_hist, rank, bin, population, s_wave, s_pick);
+  float tau;
+  if (k <= 0) {
+    tau = INFINITY;
+  } else if (k >= (long long)population) {                  // also k == population: keep all of it
+    tau = -INFINITY;
+  } else {
+    prefix = bin;
+    clear();                                                // (its reader is past pick_one's last barrier)
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      if (key[i] != kNoKey && (key[i] >> 21) == prefix) atomicAdd(&s_hist[(key[i] >> 10 & 2047u) * kCopies + copy], 1u);
+    pick_one(s_hist, rank, bin, total, s_wave, s_pick);
+    prefix = prefix << 11 | bin;
+    clear();
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      if (key[i] != kNoKey && (key[i] >> 10) == prefix) atomicAdd(&s_hist[(key[i] & 1023u) * kCopies + copy], 1u);
+    pick_one(s_hist, rank, bin, total, s_wave, s_pick);
+    tau = key_to_float(prefix << 10 | bin);
+  }
+  for (int h = tid; h < rows; h += kOneThreads) tau_out[(size_t)g * rows + h] = tau;
+}
+
+template <int kPer>
+int launch_one(const float* scores, int window, const int32_t* seq_lens, long long k, bool per_layer,
+               int B, int H, int T, float* tau_out, hipStream_t stream) {
+  topk_one_kernel<kPer><<<per_layer ? B : B * H, kOneThreads, 0, stream>>>(
+      scores, window, seq_lens, H, T, per_layer ? 1 : 0, k, tau_out);
+  return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
+}
+
 }  // namespace
 
 size_t topk_workspace_bytes(int B, int H, int T, bool per_layer) {
@@ -328,6 +458,13 @@ size_t topk_workspace_bytes(int B, int H, int T, bool per_layer) {
 int launch_topk_threshold(const float* scores, int window, const int32_t* seq_lens, long long k,
                           bool per_layer, int B, int H, int T, float* tau_out, void* workspace,
                           hipStream_t stream) {
+  const long long pool = (long long)T * (per_layer ? H : 1);
+  if (pool <= kOneMax) {
+    if (pool <= 8 * kOneThreads) return launch_one<8>(scores, window, seq_lens, k, per_layer, B, H, T, tau_out, stream);
+    if (pool <= 16 * kOneThreads) return launch_one<16>(scores, window, seq_lens, k, per_layer, B, H, T, tau_out, stream);
+    if (pool <= 32 * kOneThreads) return launch_one<32>(scores, window, seq_lens, k, per_layer, B, H, T, tau_out, stream);
+    return launch_one<64>(scores, window, seq_lens, k, per_layer, B, H, T, tau_out, stream);
+  }
   const int groups = per_layer ? B : B * H;
   const Layout l = topk_layout(H, T, per_layer);
   unsigned* ws = static_cast<unsigned*>(workspace);

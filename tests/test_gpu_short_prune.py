@@ -1,0 +1,81 @@
+"""The single-launch forms of the mask, the mask with gather, the fixed-budget threshold and the
+page assignment, at the edges of the sizes they take (and one beyond, where the general kernels
+run): bit-exact against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import kvzap_oracle as O
+from paper_2601_07891_amd import binding, synth
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("B,H,T,D,w", [
+    (1, 8, 127, 128, 16), (1, 8, 128, 64, 128), (1, 8, 129, 256, 0), (3, 5, 701, 128, 128),
+    (2, 4, 1023, 64, 5), (2, 4, 1025, 64, 5), (1, 8, 5120, 128, 128), (1, 8, 5121, 128, 128),   # 40 segments, 48
+    (8, 5, 64, 128, 8), (8, 5, 1, 64, 0), (4, 5, 3, 128, 1), (41, 1, 70, 128, 1),
+])
+def test_mask_and_gather(B, H, T, D, w):
+    scores = synth.make_scores(B, H, T, seed=T + B, ties=True)
+    scores[0, 0, T // 2] = float("nan")
+    rng = np.random.default_rng(T)
+    seq_lens = rng.integers(0, T + 1, B).astype(np.int32)
+    seq_lens[0], seq_lens[-1] = T, min(T, 1)
+    sl = torch.from_numpy(seq_lens).to(DEV)
+    bits = torch.randint(-32768, 32768, (2, B, H, T, D), dtype=torch.int16)
+    K, V = bits.view(torch.bfloat16)
+    S64 = scores.double().numpy()
+    idx, n, off, Ko, Vo = binding.kvzap_mask_compact(scores.to(DEV), 0.25, w, K.to(DEV), V.to(DEV), sl)
+    parity.assert_prune_matches(idx, n, off, Ko, Vo, K, V, S64, 0.25, w, seq_lens)
+    tau = torch.linspace(-1.0, 1.0, B * H).view(B, H)
+    idx, n, off = binding.kvzap_mask_per_head(scores.to(DEV), tau.to(DEV), w, sl)
+    ref = O.prune(S64, tau.double().numpy(), w, None, None, seq_lens)
+    np.testing.assert_array_equal(parity.to_np(off), ref.offsets)
+    np.testing.assert_array_equal(parity.to_np(n), ref.lengths)
+    want = np.concatenate([i for row in ref.idx for i in row])
+    np.testing.assert_array_equal(parity.to_np(idx)[:len(want)], want)
+
+
+def test_gather_stops_at_the_capacity():
+    s = torch.ones((1, 2, 300), device=DEV)
+    K = torch.randn((1, 2, 300, 128)).bfloat16().to(DEV)
+    out = [torch.zeros((400, 128), dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    binding.kvzap_mask_compact(s, 0.0, 4, K, K, K_out=out[0], V_out=out[1], cap_rows=350)
+    for o in out:
+        assert torch.equal(o[:350], K.view(600, 128)[:350]) and not o[350:].any()
+
+
+@pytest.mark.parametrize("pool", [1, 1023, 8192, 8193, 16384, 16385, 32769, 65536, 65537])
+@pytest.mark.parametrize("heads", [1, 3])
+def test_threshold(pool, heads):
+    # `heads` pooled heads (per layer) that hold `pool` scores or just fewer, and one head of them
+    T = max(1, pool // heads)
+    rng = np.random.default_rng(pool + heads)
+    S = rng.standard_normal((2, heads, T)).astype(np.float32)
+    S[0, 0, :T // 5] = 0.5                                 # many ties
+    S[1, 0, T // 2] = np.nan
+    seq_lens = np.array([T, T // 3], np.int32)
+    w = min(37, T // 2)
+    for per_layer in (False, True):
+        for k in (1, T // 7, T // 2, heads * (T - w) - 1, heads * T):
+            tau = binding.kvzap_topk_threshold(torch.from_numpy(S).to(DEV), w, k, per_layer,
+                                               torch.from_numpy(seq_lens).to(DEV))
+            want = O.topk_threshold(S.astype(np.float64), w, k, per_layer, seq_lens)
+            np.testing.assert_array_equal(parity.to_np(tau).astype(np.float64), want)
+
+
+@pytest.mark.parametrize("heads", [1, 255, 256, 257, 1024, 1025])
+def test_assign_pages(heads):
+    rng = np.random.default_rng(heads)
+    lengths = rng.integers(0, 300, (1, heads)).astype(np.int32)
+    free = rng.permutation(heads * 20).astype(np.int32)
+    dev = [torch.from_numpy(a).to(DEV) for a in (lengths, free)]
+    want, used, ok = O.assign_pages(lengths, 16, free, 300)
+    table, res = binding.kvzap_assign_pages(dev[0], 16, dev[1], 300)
+    assert ok and res[:2].tolist() == [used, 0]
+    np.testing.assert_array_equal(parity.to_np(table), want)
+    table, res = binding.kvzap_assign_pages(dev[0], 16, dev[1][:max(used - 1, 0)].clone(), 300)
+    assert used == 0 or (res[:2].tolist() == [0, 1] and (parity.to_np(table) == -1).all())
