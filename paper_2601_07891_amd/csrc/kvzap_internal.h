@@ -132,6 +132,12 @@ int launch_mask(const float* scores, float tau, const float* tau_head, int windo
                 const int32_t* seq_lens, int B, int H, int T, int32_t* keep_idx,
                 int32_t* lengths, int64_t* offsets, void* workspace, hipStream_t stream);
 
+// launch_mask with one threshold, then the gather of the rows it keeps
+int launch_mask_compact(const float* scores, float tau, int window, const int32_t* seq_lens, int B,
+                        int H, int T, int32_t* keep_idx, int32_t* lengths, int64_t* offsets,
+                        const void* K, const void* V, void* K_out, void* V_out, int64_t cap_rows,
+                        int D, void* workspace, hipStream_t stream);
+
 // kvzap_mask on the library's own scratch (no workspace, nothing allocated)
 int launch_mask_static(const float* scores, float tau, int window, const int32_t* seq_lens, int B,
                        int H, int T, int32_t* keep_idx, int32_t* lengths, int64_t* offsets,

@@ -11,6 +11,7 @@
 //              before it (a few KB from L2), and the first chunk of every head
 //              also writes lengths and offsets; beyond that a single-block scan
 //              kernel runs between the two.
+// Short inputs take one launch instead (mask_direct_kernel), the gather included.
 // No block waits for another, so there is nothing that can spin.
 #include <mutex>
 
@@ -225,12 +226,193 @@ __global__ __launch_bounds__(kThreads) void mask_emit_kernel(
   }
 }
 
+// ---- short inputs: threshold, window and (kLpr > 0) the gather in one launch ----
+// A chunk is kDirectChunk tokens of one (b,h) row.  Its block finds its own prefix by testing
+// every score ahead of it in (b,h) order -- a few ten thousand floats from L2, which the whole
+// block reads at once -- instead of waiting for a launch that counts them, and moves the rows
+// it keeps as soon as it has ranked them.  Bound by launch and memory latency.
+constexpr int kDirectThreads = 1024;
+constexpr int kDirectWaves = kDirectThreads / 64;
+constexpr int kDirectChunk = 128;
+constexpr int kSegment = 1024;
+
+struct GatherArgs {
+  const u32x4* K; const u32x4* V; u32x4* K_out; u32x4* V_out;
+  int64_t cap_rows;
+};
+
+template <int kLpr>          // 16-byte pieces of a K/V row; 0: no gather
+__global__ __launch_bounds__(kDirectThreads) void mask_direct_kernel(
+    const float* __restrict__ scores, float tau_all, const float* __restrict__ tau_head, int window,
+    const int32_t* __restrict__ seq_lens, int H, int T, int32_t* __restrict__ keep_idx,
+    int32_t* __restrict__ lengths, int64_t* __restrict__ offsets, GatherArgs rows) {
+  __shared__ int s_before[kDirectWaves], s_own[kDirectWaves], s_first;
+  __shared__ int s_keep[kDirectChunk];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int bh = blockIdx.y, t_begin = blockIdx.x * kDirectChunk;
+  auto tau_of = [&](int row) { return tau_head ? tau_head[row] : tau_all; };
+  // this chunk's flags: one lane of the first two wavefronts per token
+  bool own = false;
+  const int t_mine = t_begin + tid;
+  if (tid < kDirectChunk && t_mine < T) {
+    const int Tb = seq_len_of(seq_lens, bh / H, T);
+    own = t_mine < Tb && (t_mine >= Tb - window || scores[(size_t)bh * T + t_mine] >= tau_of(bh));
+  }
+  // What is kept ahead of it, in earlier rows and earlier in its own (a head's length is the
+  // latter plus its last chunk).  The window's share of a row is known without reading; of the
+  // rest a wavefront takes segments of 1024 positions, four 16-byte loads per lane at once, the
+  // next segment's ahead of the current one's count.  Two vector operations per score: with a
+  // row lookup and a window test per score this part took 20 us on 65536 scores.
+  int before = 0, in_row = 0;
+  {
+    const int cpr = (T + kSegment - 1) / kSegment;
+    const int nseg = bh * cpr + (t_begin + kSegment - 1) / kSegment;
+    struct Segment { int lo, hi; float tau; int row; };      // linear positions to test
+    auto segment = [&](int sg, floatx4 (&q)[4]) {
+      Segment s;
+      s.row = sg / cpr;
+      const int c = sg - s.row * cpr, base = s.row * T;
+      const int Tb = seq_len_of(seq_lens, s.row / H, T), end = s.row == bh ? t_begin : T;
+      const int limit = Tb < end ? Tb : end;                 // positions that count
+      int tested = Tb > window ? Tb - window : 0;            // of those, below the window
+      if (tested > limit) tested = limit;
+      if (c == 0 && lane == 0) {                             // (limit < tested: none)
+        if (s.row == bh) in_row += limit - tested;
+        else before += limit - tested;
+      }
+      s.lo = base + c * kSegment;
+      s.hi = base + (tested < (c + 1) * kSegment ? tested : (c + 1) * kSegment);
+      s.tau = tau_of(s.row);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = (s.lo & ~3) + (u * 64 + lane) * 4;
+        if (i + 3 < s.hi) q[u] = *reinterpret_cast<const floatx4*>(scores + i);
+        else
+          for (int e = 0; e < 4; ++e) q[u][e] = i + e < s.hi ? scores[i + e] : 0.0f;
+      }
+      return s;
+    };
+    auto count = [&](const Segment& s, const floatx4 (&q)[4]) {
+      int n = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = (s.lo & ~3) + (u * 64 + lane) * 4;
+        if (i >= s.lo && i + 3 < s.hi) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) n += q[u][e] >= s.tau;
+        } else {
+          for (int e = 0; e < 4; ++e) n += i + e >= s.lo && i + e < s.hi && q[u][e] >= s.tau;
+        }
+      }
+      // a row that starts off a 16-byte boundary: the segment's last one to three positions
+      const int i = (s.lo & ~3) + 1024 + lane;
+      if (i < s.lo + kSegment && i < s.hi) n += scores[i] >= s.tau;
+      if (s.row == bh) in_row += n;
+      else before += n;
+    };
+    floatx4 qa[4], qb[4];
+    Segment sa, sb;
+    int sg = wv;
+    if (sg < nseg) sa = segment(sg, qa);
+    for (; sg < nseg; sg += 2 * kDirectWaves) {
+      if (sg + kDirectWaves < nseg) sb = segment(sg + kDirectWaves, qb);
+      count(sa, qa);
+      if (sg + 2 * kDirectWaves < nseg) sa = segment(sg + 2 * kDirectWaves, qa);
+      if (sg + kDirectWaves < nseg) count(sb, qb);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    before += __shfl_down(before, off, 64);
+    in_row += __shfl_down(in_row, off, 64);
+  }
+  const unsigned long long kept = __ballot(own);
+  if (lane == 0) { s_before[wv] = before; s_own[wv] = in_row; }
+  if (tid == 0) s_first = __popcll(kept);
+  __syncthreads();
+  int start = 0, mine = 0;
+#pragma unroll
+  for (int w = 0; w < kDirectWaves; ++w) { start += s_before[w]; mine += s_own[w]; }
+  const int first = s_first, out0 = start + mine;          // of this head; of this chunk
+  if (own) {
+    const int rank = (wv ? first : 0) + __popcll(kept & ((1ull << lane) - 1));
+    s_keep[rank] = t_mine;
+    keep_idx[out0 + rank] = t_mine;
+  }
+  const int count = __syncthreads_count(own);
+  if (tid == 0) {
+    if (blockIdx.x == 0) offsets[bh] = start;
+    if (blockIdx.x == gridDim.x - 1) {
+      lengths[bh] = mine + count;
+      if (bh == (int)gridDim.y - 1) offsets[bh + 1] = out0 + count;
+    }
+  }
+  if constexpr (kLpr > 0) {
+    constexpr int kRows = kDirectThreads / kLpr;           // rows of one tensor per pass
+    const int piece = tid % kLpr;
+    const size_t base = (size_t)bh * T * kLpr + piece;
+#pragma unroll 4
+    for (int j = tid / kLpr; j < count; j += kRows) {
+      if (out0 + j >= rows.cap_rows) break;
+      const size_t from = base + (size_t)s_keep[j] * kLpr, to = (size_t)(out0 + j) * kLpr + piece;
+      const u32x4 k = __builtin_nontemporal_load(rows.K + from), v = __builtin_nontemporal_load(rows.V + from);
+      __builtin_nontemporal_store(k, rows.K_out + to);
+      __builtin_nontemporal_store(v, rows.V_out + to);
+    }
+  }
+}
+
+// Where one launch is the faster way.  Every block goes over all segments ahead of it, so its
+// time grows with their number while count + emit stays at two launches.  Measured, us per call
+// (direct / count + emit; with the gather of half the rows: direct / three launches):
+//   8 rows of 1024: 4.9 / 7.8 (5.5 / 12.2)   of 2048: 5.0 / 8.2 (6.6 / 12.6)   of 4096 (32
+//   segments): 5.9 / 8.2 (8.9 / 12.7)   of 8192 (64): 10.5 / 8.3 (15.6 / 14.8)
+//   24 rows of 701: 5.7 / 8.1 (7.0 / 12.3)   128 rows of 512: 21 / 8.3 (25.7 / 18)
+constexpr long long kDirectSegments = 40;
+
+bool direct_fits(int B, int H, int T) {
+  return (long long)B * H * ((T + kSegment - 1) / kSegment) <= kDirectSegments;
+}
+
+template <int kLpr>
+int launch_direct(const float* scores, float tau, const float* tau_head, int window,
+                  const int32_t* seq_lens, int B, int H, int T, int32_t* keep_idx, int32_t* lengths,
+                  int64_t* offsets, const GatherArgs& rows, hipStream_t stream) {
+  const dim3 grid((T + kDirectChunk - 1) / kDirectChunk, B * H);
+  mask_direct_kernel<kLpr><<<grid, kDirectThreads, 0, stream>>>(scores, tau, tau_head, window, seq_lens, H, T,
+                                                                keep_idx, lengths, offsets, rows);
+  return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
+}
+
 }  // namespace
+
+int launch_mask_compact(const float* scores, float tau, int window, const int32_t* seq_lens, int B,
+                        int H, int T, int32_t* keep_idx, int32_t* lengths, int64_t* offsets,
+                        const void* K, const void* V, void* K_out, void* V_out, int64_t cap_rows,
+                        int D, void* workspace, hipStream_t stream) {
+  if (direct_fits(B, H, T)) {
+    const GatherArgs rows{static_cast<const u32x4*>(K), static_cast<const u32x4*>(V),
+                          static_cast<u32x4*>(K_out), static_cast<u32x4*>(V_out), cap_rows};
+    switch (D / 8) {
+      case 8: return launch_direct<8>(scores, tau, nullptr, window, seq_lens, B, H, T, keep_idx, lengths, offsets, rows, stream);
+      case 16: return launch_direct<16>(scores, tau, nullptr, window, seq_lens, B, H, T, keep_idx, lengths, offsets, rows, stream);
+      case 32: return launch_direct<32>(scores, tau, nullptr, window, seq_lens, B, H, T, keep_idx, lengths, offsets, rows, stream);
+      default: break;
+    }
+  }
+  const int rc = launch_mask(scores, tau, nullptr, window, seq_lens, B, H, T, keep_idx, lengths,
+                             offsets, workspace, stream);
+  if (rc != KVZAP_OK) return rc;
+  return launch_compact(K, V, keep_idx, lengths, offsets, K_out, V_out, cap_rows, B * H, T, D, stream);
+}
 
 int launch_mask(const float* scores, float tau, const float* tau_head, int window,
                 const int32_t* seq_lens,
                 int B, int H, int T, int32_t* keep_idx, int32_t* lengths,
                 int64_t* offsets, void* workspace, hipStream_t stream) {
+  if (direct_fits(B, H, T))
+    return launch_direct<0>(scores, tau, tau_head, window, seq_lens, B, H, T, keep_idx, lengths, offsets,
+                            GatherArgs{}, stream);
   const int BH = B * H;
   const int nchunks = mask_chunks(T);
   int32_t* chunk_counts = static_cast<int32_t*>(workspace);
