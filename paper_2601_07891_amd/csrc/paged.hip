@@ -94,6 +94,48 @@ __global__ __launch_bounds__(256) void assign_fill_kernel(
     page_counts[bh] = h + c;
 }
 
+// kvzap_assign_pages in one launch, grid (tiles, B*H): with up to kAssignDirect heads every
+// block adds up the pages of all heads itself (the lengths are a few KB in L2) instead of
+// waiting for a launch that scans them (24 heads: 3.9 us against 6.6; 1024: 5.5 against 6.7).
+constexpr int kAssignDirect = 1024;
+
+__global__ __launch_bounds__(256) void assign_direct_kernel(
+    const int32_t* __restrict__ lengths, int log_page, int reserve, int n_free,
+    const int32_t* __restrict__ free_pages, int32_t* __restrict__ block_table, int max_pages,
+    int32_t* __restrict__ result) {
+  __shared__ long long s_before[4], s_total[4];
+  const int bh = blockIdx.y, BH = gridDim.y, tid = threadIdx.x;
+  long long before = 0, total = 0;
+  int c = 0;
+  bool over = false;
+#pragma unroll
+  for (int u = 0; u < kAssignDirect / 256; ++u) {
+    const int i = tid + u * 256;
+    const int n = i < BH ? pages_for(lengths[i], reserve, log_page) : 0;
+    total += n;
+    over |= n > max_pages;
+    if (i < bh) before += n;
+  }
+  c = pages_for(lengths[bh], reserve, log_page);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    before += __shfl_down(before, off, 64);
+    total += __shfl_down(total, off, 64);
+  }
+  if ((tid & 63) == 0) { s_before[tid >> 6] = before; s_total[tid >> 6] = total; }
+  const bool any_over = __syncthreads_or(over);
+  before = s_before[0] + s_before[1] + s_before[2] + s_before[3];
+  total = s_total[0] + s_total[1] + s_total[2] + s_total[3];
+  const int status = any_over ? 2 : (total > n_free ? 1 : 0);
+  if (status) c = 0;
+  for (int i = blockIdx.x * 256 + tid; i < max_pages; i += gridDim.x * 256)
+    block_table[(size_t)bh * max_pages + i] = i < c ? free_pages[before + i] : -1;
+  if (bh == 0 && blockIdx.x == 0 && tid == 0) {
+    result[0] = status ? 0 : (int32_t)total;
+    result[1] = status;
+  }
+}
+
 constexpr int kThreads = 256;
 
 // Same work split as the contiguous gather: grid (tiles, B*H, {K,V}), a thread moves one
@@ -143,14 +185,19 @@ int launch_assign_pages(const int32_t* lengths, int32_t* page_counts, int BH, in
                         hipStream_t stream) {
   int log_page = 0;
   while ((1 << log_page) < page_rows) ++log_page;
+  int tiles = (max_pages + 255) / 256;
+  tiles = tiles < 64 ? tiles : 64;
+  if (!page_counts && BH <= kAssignDirect) {
+    assign_direct_kernel<<<dim3(tiles, BH), 256, 0, stream>>>(lengths, log_page, reserve_rows, n_free,
+                                                              free_pages, block_table, max_pages, result);
+    return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
+  }
   int32_t* start = static_cast<int32_t*>(workspace);
   int32_t* have = start + BH + 1;
   assign_scan_kernel<<<1, kScanThreads, 0, stream>>>(lengths, page_counts, BH, log_page,
                                                      reserve_rows, n_free, max_pages, start, have,
                                                      result);
   if (hipGetLastError() != hipSuccess) return KVZAP_ERR_RUNTIME;
-  int tiles = (max_pages + 255) / 256;
-  tiles = tiles < 64 ? tiles : 64;
   if (page_counts)
     assign_fill_kernel<false><<<dim3(tiles, BH), 256, 0, stream>>>(start, have, free_pages,
                                                                    block_table, page_counts, max_pages);
