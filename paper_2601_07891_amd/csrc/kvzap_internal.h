@@ -90,10 +90,22 @@ __device__ __forceinline__ unsigned lds_address(const void* p) {
   return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
 
+__device__ __forceinline__ void load_to_lds_b128(const void* base, unsigned lane_offset, unsigned lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               ::"s"(lds_base), "v"(lane_offset), "s"(base)
+               : "memory");
+}
+
 // The 4-byte form: lane i's dword lands at LDS byte lds_base + 4*i.
 __device__ __forceinline__ void load_to_lds_b32(const void* gptr, unsigned lds_base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
                ::"s"(lds_base), "v"(gptr)
+               : "memory");
+}
+
+__device__ __forceinline__ void load_to_lds_b32(const void* base, unsigned lane_offset, unsigned lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+               ::"s"(lds_base), "v"(lane_offset), "s"(base)
                : "memory");
 }
 

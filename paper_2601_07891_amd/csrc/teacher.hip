@@ -15,10 +15,25 @@
 // Both passes are Q K^T on v_mfma_f32_32x32x16_bf16 with the *reduced* index on the MFMA
 // row side (C rows live in a lane's 16 registers) and the kept index on the column side
 // (one lane = one query in pass 1, one key in pass 2), so the reductions are per-lane.
-// The operand that stays (128 rows of Q, resp. K) sits in registers; the other one streams
-// straight from global memory in operand layout (16 bytes of one row per lane and k-step),
-// one tile ahead.
+// A wavefront keeps 64 rows of Q, resp. K, in registers (two B operands); the other matrix
+// streams through LDS in tiles of 32 rows that the block's four wavefronts share.
+//
+// What bounds them: the matrix pipe (16 MFMAs of 32 cycles per tile and wavefront) and, in the
+// row pass, the vector ALUs, which spend 4 + 8 + 4 cycles (fma, exp2, add) on 64 logits, 512 per
+// tile and wavefront, beside about 8 cycles of issue per MFMA.  A wavefront issues in order:
+// with the 16 products of the next tile in one piece and then the vector work on the current
+// one, even two wavefronts per SIMD took the sum of both (1050 cycles per tile in the row pass).
+// So the loop is written as 16 slots, each ONE product of tile i+1, a sixteenth of the vector
+// work on tile i, and part of the LDS reads of tile i+2, pinned with scheduling barriers.
+// Measured (8 KV heads x 4, prompt 8192, rocprofv3, us; before: products and reduction as two
+// pieces, 128 kept rows in the column pass): row pass 780 -> 714, column pass 427 -> 376; on
+// all-zero inputs 622 -> 517 and 388 -> 282.  The difference between the two is the clock, which
+// the power limit sets: at 1.15 and 1.46 PFLOP/s the passes are near what random operands
+// sustain (a bare MFMA loop: 1.56), the row pass with its exponentials beside them.
 #include "kvzap_internal.h"
+
+#include <type_traits>
+#include <utility>
 
 namespace kvzap {
 namespace {
@@ -26,17 +41,16 @@ namespace {
 constexpr int kD = 128;
 constexpr int kRowVec = kD * 2 / 16;       // 16-byte pieces per row
 constexpr int kSteps = kD / 16;            // MFMA k-steps per tile
-constexpr int kStay = 4;                   // 32-row tiles of the operand kept in registers (column pass)
-constexpr int kStayRow = 2;                // row pass: it is bound by the exponentials, not by operand reuse,
-                                           // and two tiles leave room for two wavefronts per SIMD
+constexpr int kStay = 2;                   // 32-row tiles of the operand kept in registers
+constexpr int kBlockRows = 4 * kStay * 32; // rows of that operand per block
+constexpr int kSlots = kStay * kSteps;     // MFMAs per tile and wavefront
+static_assert(kSlots == 16, "a slot handles one C register of each kept tile");
 constexpr float kNegBig = -1.0e30f;        // "minus infinity" that survives subtraction
 constexpr float kLazyLimit = 1048576.0f;    // 2^20: a tile's 16 terms may sum to this before the reference moves
 
-// The streamed operand goes through an LDS ring filled by load-to-LDS kAhead tiles ahead, so
-// that the four wavefronts of a block share one copy, the global reads are whole 256-byte
-// rows, and the prefetch depth costs no registers.
-constexpr int kAhead = 3;
-constexpr int kStages = kAhead + 1;
+// LDS ring of the streamed operand.  While tile i's logits are reduced, the products of tile
+// i+1 run from registers, tile i+2 is read from LDS and tiles i+3 .. i+5 are on their way.
+constexpr int kStages = 4;
 constexpr int kTileBytes = 32 * kD * 2;                  // 8 KB: 32 rows
 constexpr int kBiasBytes = 4 * 256;                      // pass 2: one 256-byte slot per wavefront
 constexpr int kStageBytes = kTileBytes + kBiasBytes;
@@ -44,6 +58,15 @@ constexpr int kStageBytes = kTileBytes + kBiasBytes;
 struct Tile {
   u32x4 f[kSteps];
 };
+
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
 
 // rows [row0, row0+32) of a row-major [rows][128] bf16 matrix as an MFMA operand: lane
 // (r = lane%32, kg = lane/32) holds elements 16s + 8kg .. +8 of row row0 + r for k-step s.
@@ -59,54 +82,42 @@ __device__ __forceinline__ void load_tile(Tile& t, const u32x4* base, int row0, 
 // One wavefront's share of a 32-row tile on its way to LDS: two load-to-LDS instructions,
 // each 4 whole rows (lane i: row i/16 of the four, physical piece i%16).  The 16-byte pieces
 // of a row are XOR-swizzled with the row number so that the operand reads below spread over
-// the banks.  Rows past `last` re-read row `last`.
-__device__ __forceinline__ void stream_tile_to_lds(const u32x4* base, int row0, int last,
-                                                   unsigned stage_lds, int wave, int lane) {
+// the banks.  Rows past `last_row` (relative to the tile) re-read that row.
+__device__ __forceinline__ void stream_tile_to_lds(const void* tile, int last_row, unsigned stage_lds,
+                                                   int wave, int lane) {
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int chunk = 2 * wave + j;                      // 4 rows each
-    const int row_in_tile = 4 * chunk + (lane >> 4);
-    int row = row0 + row_in_tile;
-    row = row < last ? row : last;
-    const int piece = (lane & 15) ^ (row_in_tile & 15);
-    load_to_lds_b128(base + (size_t)row * kRowVec + piece, stage_lds + chunk * 1024);
+    const int row = 4 * chunk + (lane >> 4);
+    const int piece = (lane & 15) ^ (row & 15);
+    const unsigned off = (unsigned)(row < last_row ? row : last_row) * 256u + (unsigned)piece * 16u;
+    load_to_lds_b128(tile, off, stage_lds + chunk * 1024);
   }
 }
 
-// The tile as an MFMA operand, from LDS (same register layout as load_tile).
-__device__ __forceinline__ void read_tile_from_lds(Tile& t, const unsigned char* stage, int lane) {
+// LDS byte offsets, within a stage, of this lane's fragments of the tile (layout of load_tile)
+__device__ __forceinline__ void fragment_offsets(unsigned (&off)[kSteps], int lane) {
   const int r = lane & 31, kg = lane >> 5;
 #pragma unroll
-  for (int s = 0; s < kSteps; ++s)
-    t.f[s] = *reinterpret_cast<const u32x4*>(stage + r * 256 + (((2 * s + kg) ^ (r & 15)) << 4));
+  for (int s = 0; s < kSteps; ++s) off[s] = (unsigned)(r * 256 + (((2 * s + kg) ^ (r & 15)) << 4));
 }
 
-// The kStay products of one streamed tile with the tiles that stay, as kStay independent
-// MFMA chains issued round-robin (a single chain on one accumulator would wait for each
-// result before the next step).  The streamed tile is the A (row) operand.
-template <bool kZeroInit, int KS>
-__device__ __forceinline__ void tile_products(const Tile& stream, const Tile (&stay)[KS],
-                                              const floatx16& init, floatx16 (&c)[KS]) {
-#pragma unroll
-  for (int t = 0; t < KS; ++t) {
-    if (kZeroInit) {                                     // a literal zero is an MFMA immediate: no moves
-#pragma unroll
-      for (int e = 0; e < 16; ++e) c[t][e] = 0.f;
-    } else {
-      c[t] = init;
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < kSteps; ++s)
-#pragma unroll
-    for (int t = 0; t < KS; ++t)
-      c[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, stream.f[s]),
-                                                     __builtin_bit_cast(bf16x8, stay[t].f[s]),
-                                                     c[t], 0, 0, 0);
+// product `m` of a tile: k-step m/2, kept tile m%2, so that the two accumulator chains alternate
+__device__ __forceinline__ void product(int m, const Tile& stream, const Tile (&stay)[kStay],
+                                        const floatx16& init, floatx16 (&c)[kStay]) {
+  const int s = m >> 1, t = m & 1;
+  c[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, stream.f[s]),
+                                                 __builtin_bit_cast(bf16x8, stay[t].f[s]),
+                                                 s == 0 ? init : c[t], 0, 0, 0);
 }
 
 // row of C register e in lane half kg: 8*(e/4) + 4*kg + e%4
 __device__ __forceinline__ int c_row(int e, int kg) { return 8 * (e >> 2) + 4 * kg + (e & 3); }
+
+__device__ __forceinline__ void wait_lds() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
 
 // ---- pass 1: grid (ceil(Tq / 256), HQ), 256 threads; a wavefront owns 64 queries, the
 // block streams the keys its last query sees ----
@@ -116,47 +127,71 @@ __global__ __launch_bounds__(256, 2) void teacher_rowstat_kernel(
   extern __shared__ __align__(16) unsigned char smem[];
   // Blocks are handed out in the order of the linear block index, and a block of late
   // queries sees up to twice the keys of an early one: the index is mapped so that the
-  // longest blocks of all heads start first and the shortest fill the tail.
+  // longest blocks of all heads start first and the shortest fill the tail.  Within that, the
+  // KV head varies fastest: consecutive blocks go to the eight XCDs in turn, so with eight KV
+  // heads each L2 serves the keys of one.
   const int lin = blockIdx.y * gridDim.x + blockIdx.x;
   const int bx = gridDim.x - 1 - lin / gridDim.y;
-  const int g = lin % gridDim.y, h = g / G;
+  const int H = gridDim.y / G, h = lin % gridDim.y % H, g = h * G + lin % gridDim.y / H;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31, kg = lane >> 5;
-  const int q0 = (bx * 4 + wave) * (kStayRow * 32);
+  const int q0 = (bx * 4 + wave) * (kStay * 32);
   const int P0 = Tk - Tq;
   const u32x4* qh = q + (size_t)g * Tq * kRowVec;
-  const u32x4* kh = k + (size_t)h * Tk * kRowVec;
+  const unsigned char* kh = reinterpret_cast<const unsigned char*>(k + (size_t)h * Tk * kRowVec);
   const unsigned lds0 = lds_address(smem);
 
   // every wavefront walks all the key tiles of the block (barriers), also one whose queries
   // are all padding
-  int block_last_q = bx * 4 * (kStayRow * 32) + 4 * kStayRow * 32 - 1;
+  int block_last_q = bx * kBlockRows + kBlockRows - 1;
   block_last_q = block_last_q < Tq - 1 ? block_last_q : Tq - 1;
   const int ntiles = (P0 + block_last_q) / 32 + 1;
 
-  auto stream = [&](int tile) {                          // clamped: a tile past the end re-reads the last
+  auto stream = [&](int tile, int stage) {               // clamped: a tile past the end re-reads the last
     const int tl = tile < ntiles ? tile : ntiles - 1;
-    stream_tile_to_lds(kh, tl * 32, Tk - 1, lds0 + (unsigned)((tile % kStages) * kStageBytes), wave, lane);
+    stream_tile_to_lds(kh + (size_t)tl * kTileBytes, Tk - 1 - tl * 32, lds0 + (unsigned)(stage * kStageBytes), wave, lane);
   };
 #pragma unroll
-  for (int d = 0; d < kStages; ++d) stream(d);            // all stages: tiles 0 .. kAhead
+  for (int d = 0; d < kStages; ++d) stream(d, d);
 
-  Tile qt[kStayRow];                                        // B operands: the wavefront's queries
+  Tile qt[kStay];                                        // B operands: the wavefront's queries
 #pragma unroll
-  for (int t = 0; t < kStayRow; ++t) load_tile(qt[t], qh, q0 + 32 * t, Tq - 1, lane);
-  float m[kStayRow], l[kStayRow];
+  for (int t = 0; t < kStay; ++t) load_tile(qt[t], qh, q0 + 32 * t, Tq - 1, lane);
+  unsigned off[kSteps];
+  fragment_offsets(off, lane);
+  float m[kStay], l[kStay];
 #pragma unroll
-  for (int t = 0; t < kStayRow; ++t) { m[t] = kNegBig; l[t] = 0.f; }
+  for (int t = 0; t < kStay; ++t) { m[t] = kNegBig; l[t] = 0.f; }
   floatx16 zero;
 #pragma unroll
   for (int e = 0; e < 16; ++e) zero[e] = 0.f;
 
-  // softmax statistics of one key tile from its logits s (C[key][query])
-  auto reduce = [&](floatx16 (&s)[kStayRow], int tile) {
+  // The reference m is lazy: a tile is summed against the current one, and only if some lane's
+  // sum leaves the safe range (an element more than kLazyLimit above the reference, an overflow
+  // to infinity, the first tile) is the tile's maximum taken and the tile summed again.  That
+  // keeps the 16 maximum operations out of the common path.
+  auto tile_sum = [&](const float (&x)[16], float neg_m) {
+    float sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sum += __builtin_amdgcn_exp2f(fmaf(x[e], cscale, neg_m));
+    return sum;
+  };
+  auto move_reference = [&](const float (&x)[16], int t) {
+    float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
+    mx = fmaxf(mx, fmaxf(fmaxf(fmaxf(x[8], x[9]), fmaxf(x[10], x[11])),
+                         fmaxf(fmaxf(x[12], x[13]), fmaxf(x[14], x[15]))));
+    mx *= cscale;                                        // cscale > 0: max commutes with the scaling
+    const float mn = fmaxf(m[t], mx);
+    l[t] *= __builtin_amdgcn_exp2f(m[t] - mn);
+    m[t] = mn;
+    l[t] += tile_sum(x, -mn);
+  };
+  // softmax statistics of one key tile from its logits s (C[key][query]), any tile
+  auto reduce = [&](const floatx16 (&s)[kStay], int tile) {
     const int key0 = tile * 32;
 #pragma unroll
-    for (int t = 0; t < kStayRow; ++t) {
+    for (int t = 0; t < kStay; ++t) {
       const int qcol = q0 + 32 * t + r;                  // this lane's query
       if (key0 > P0 + q0 + 32 * t + 31) continue;        // nothing of this tile is visible (uniform)
       float x[16];
@@ -167,60 +202,91 @@ __global__ __launch_bounds__(256, 2) void teacher_rowstat_kernel(
         for (int e = 0; e < 16; ++e)
           if (key0 + c_row(e, kg) > P0 + qcol) x[e] = -INFINITY;
       }
-      // The reference m is lazy: the tile is summed against the current one, and only if
-      // some lane's sum leaves the safe range (an element more than kLazyLimit above the
-      // reference, an overflow to infinity, the first tile) is the tile's maximum taken and
-      // the tile summed again.  That keeps the 16 maximum operations out of the common path
-      // (three vector operations per logit instead of four).
-      float neg_m = -m[t];
-      float sum = 0.f;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) sum += __builtin_amdgcn_exp2f(fmaf(x[e], cscale, neg_m));
-      if (__any(!(sum <= kLazyLimit))) {                 // per-lane statistics: no cross-lane step
-        float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
-        mx = fmaxf(mx, fmaxf(fmaxf(fmaxf(x[8], x[9]), fmaxf(x[10], x[11])),
-                             fmaxf(fmaxf(x[12], x[13]), fmaxf(x[14], x[15]))));
-        mx *= cscale;                                    // cscale > 0: max commutes with the scaling
-        const float mn = fmaxf(m[t], mx);
-        l[t] *= __builtin_amdgcn_exp2f(m[t] - mn);
-        m[t] = mn;
-        neg_m = -mn;
-        sum = 0.f;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sum += __builtin_amdgcn_exp2f(fmaf(x[e], cscale, neg_m));
-      }
-      l[t] += sum;
+      const float sum = tile_sum(x, -m[t]);
+      if (__any(!(sum <= kLazyLimit))) move_reference(x, t);   // per-lane statistics: no cross-lane step
+      else l[t] += sum;
     }
   };
 
-  // Software pipeline: while the vector ALUs turn tile i's logits into statistics, the matrix
-  // cores work on tile i+1 and tiles i+2, i+3 are on their way to LDS (tile i+4 follows as
-  // soon as every wavefront is done with tile i's stage).  Each wavefront issues two
-  // load-to-LDS per tile and nothing else on the vector-memory path inside the loop, so
-  // "tile i+1 has landed" is "at most 2*(kAhead-1) operations outstanding".
-  Tile ta;
-  floatx16 sa[kStayRow], sb[kStayRow];
-  wait_vmcnt<2 * kAhead>();                              // tile 0 landed (kAhead younger tiles in flight)
+  // Each wavefront issues two load-to-LDS per tile and nothing else on the vector-memory path
+  // inside the loop.  At the top of tile i's step tiles up to i+4 have been issued, so "tile i+2
+  // has landed" is "at most 4 operations outstanding"; behind the barrier everybody's part has,
+  // and everybody has read tile i+1 (its reads were waited for), whose stage tile i+5 takes.
+  auto handover = [&](int tile, int stage) {             // stage: of tile + 1
+    wait_lds();
+    wait_vmcnt<4>();
+    block_barrier_no_drain();
+    stream(tile + 1 + kStages, stage);
+  };
+  Tile ta, tb;
+  floatx16 sa[kStay], sb[kStay];
+  wait_vmcnt<0>();
   block_barrier_no_drain();
-  read_tile_from_lds(ta, smem, lane);
-  tile_products<true, kStayRow>(ta, qt, zero, sa);                 // tile 0, C[key][query]
-  auto step = [&](floatx16 (&s_cur)[kStayRow], floatx16 (&s_next)[kStayRow], int tile) {
-    wait_vmcnt<2 * (kAhead - 1)>();                      // own part of tile+1 landed
-    block_barrier_no_drain();                            // everyone's part; everyone done with `tile`
-    stream(tile + kStages);                              // into the stage of `tile`
-    read_tile_from_lds(ta, smem + ((tile + 1) % kStages) * kStageBytes, lane);
-    tile_products<true, kStayRow>(ta, qt, zero, s_next);
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    ta.f[s] = *reinterpret_cast<const u32x4*>(smem + off[s]);
+    tb.f[s] = *reinterpret_cast<const u32x4*>(smem + kStageBytes + off[s]);
+  }
+  wait_lds();
+  block_barrier_no_drain();
+  stream(kStages, 0);
+#pragma unroll
+  for (int i = 0; i < kSlots; ++i) product(i, ta, qt, zero, sa);
+
+  // Step of tile i: `frag` holds tile i+1, `next` receives tile i+2, s_cur is tile i.
+  // The common form (kStage = i % kStages): all of tile i visible to all of the queries.
+  auto visible_step = [&](Tile& frag, Tile& next, floatx16 (&s_cur)[kStay], floatx16 (&s_next)[kStay],
+                          int tile, auto stage_tag) {
+    constexpr int kStage = decltype(stage_tag)::value, kRead = (kStage + 2) % kStages * kStageBytes;
+    handover(tile, (kStage + 1) % kStages);
+    float neg_m[kStay], sum[kStay];
+#pragma unroll
+    for (int t = 0; t < kStay; ++t) { neg_m[t] = -m[t]; sum[t] = 0.f; }
+    static_for<kSlots>([&](auto i_) {
+      constexpr int i = decltype(i_)::value;
+      product(i, frag, qt, zero, s_next);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (i < kSteps) next.f[i] = *reinterpret_cast<const u32x4*>(smem + kRead + off[i]);
+#pragma unroll
+      for (int t = 0; t < kStay; ++t) sum[t] += __builtin_amdgcn_exp2f(fmaf(s_cur[t][i], cscale, neg_m[t]));
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    if (__any(!(sum[0] <= kLazyLimit) || !(sum[1] <= kLazyLimit))) {
+      reduce(s_cur, tile);
+    } else {
+#pragma unroll
+      for (int t = 0; t < kStay; ++t) l[t] += sum[t];
+    }
+  };
+  auto any_step = [&](Tile& frag, Tile& next, floatx16 (&s_cur)[kStay], floatx16 (&s_next)[kStay], int tile) {
+    handover(tile, (tile + 1) % kStages);
+    const unsigned char* stage = smem + (tile + 2) % kStages * kStageBytes;
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) next.f[s] = *reinterpret_cast<const u32x4*>(stage + off[s]);
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) product(i, frag, qt, zero, s_next);
     reduce(s_cur, tile);
   };
-  for (int tile = 0; tile < ntiles; tile += 2) {
-    step(sa, sb, tile);
-    step(sb, sa, tile + 1);
+  // every wavefront makes the same number of steps, whichever form they take
+  const int visible = (P0 + q0 + 1) / 32;                // tiles all of whose keys its first query sees
+  int tile = 0;
+  for (; tile + kStages <= (visible < ntiles ? visible : ntiles); tile += kStages) {
+    visible_step(tb, ta, sa, sb, tile, std::integral_constant<int, 0>{});
+    visible_step(ta, tb, sb, sa, tile + 1, std::integral_constant<int, 1>{});
+    visible_step(tb, ta, sa, sb, tile + 2, std::integral_constant<int, 2>{});
+    visible_step(ta, tb, sb, sa, tile + 3, std::integral_constant<int, 3>{});
+  }
+  for (; tile < ntiles; tile += 2) {
+    any_step(tb, ta, sa, sb, tile);
+    any_step(ta, tb, sb, sa, tile + 1);
   }
   wait_vmcnt<0>();                                       // nothing may land in LDS after the block is gone
 
-  // the two lane halves hold disjoint key rows of the same query: merge, then one bias per row
+  // The two lane halves hold disjoint key rows of the same query: merge, then one bias per row.
+  // It is stored divided by the logit scale, which the column pass applies after its maximum.
+  const float inv_c = 1.0f / cscale;
 #pragma unroll
-  for (int t = 0; t < kStayRow; ++t) {
+  for (int t = 0; t < kStay; ++t) {
     const float mo = __shfl_xor(m[t], 32, 64), lo = __shfl_xor(l[t], 32, 64);
     const float M = fmaxf(m[t], mo);
     const float L = l[t] * __builtin_amdgcn_exp2f(m[t] - M) + lo * __builtin_amdgcn_exp2f(mo - M);
@@ -228,22 +294,25 @@ __global__ __launch_bounds__(256, 2) void teacher_rowstat_kernel(
     if (kg == 0 && j < tq_pad) {
       float bias = -INFINITY;                            // padded rows never win a maximum
       if (j < Tq) bias = -(M + __log2f(L) + (hnorm ? __log2f(hnorm[j]) : 0.f));
-      rowbias[(size_t)g * tq_pad + j] = bias;
+      rowbias[(size_t)g * tq_pad + j] = bias * inv_c;
     }
   }
 }
 
-// ---- pass 2: grid (ceil(T / 512), H, JS), 256 threads; a wavefront owns 128 prompt keys,
-// the block streams its share of the group's query tiles ----
-__global__ __launch_bounds__(256) void teacher_colmax_kernel(
-    const u32x4* q, const u32x4* k, const float* rowbias, int G, int Tq, int Tk, int T,
+// ---- pass 2: grid ceil(T / 256) * H * JS, 256 threads; a wavefront owns 64 prompt keys, the
+// block streams its share of the group's query tiles ----
+__global__ __launch_bounds__(256, 2) void teacher_colmax_kernel(
+    const u32x4* q, const u32x4* k, const float* rowbias, int G, int H, int JS, int Tq, int Tk, int T,
     int tq_pad, float cscale, float* __restrict__ part) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int h = blockIdx.y, js = blockIdx.z, JS = gridDim.z, H = gridDim.y;
+  // the KV head varies fastest (one per XCD with eight heads), then the keys: the blocks that
+  // run together stream the same queries through an L2
+  const int nkb = (T + kBlockRows - 1) / kBlockRows;
+  const int h = blockIdx.x % H, kb = blockIdx.x / H % nkb, js = blockIdx.x / H / nkb;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31, kg = lane >> 5;
-  const int k0 = (blockIdx.x * 4 + wave) * (kStay * 32);
+  const int k0 = (kb * 4 + wave) * (kStay * 32);
   const u32x4* kh = k + (size_t)h * Tk * kRowVec;
   const unsigned lds0 = lds_address(smem);
 
@@ -252,67 +321,80 @@ __global__ __launch_bounds__(256) void teacher_colmax_kernel(
   const int first = (int)((long long)total * js / JS), end = (int)((long long)total * (js + 1) / JS);
   const int n = end - first;                             // >= 1: JS <= total
   // A query tile and the biases of its 32 rows (each wavefront fetches its own copy of the
-  // 128 bytes, which keeps the count of vector-memory operations per wavefront uniform).
-  auto stream = [&](int i) {                             // clamped: re-reading an item cannot change a maximum
-    const int item = first + (i < n ? i : n - 1);
-    const int g = h * G + item / ntq, j0 = (item % ntq) * 32;
-    const unsigned stage = lds0 + (unsigned)((i % kStages) * kStageBytes);
-    stream_tile_to_lds(q + (size_t)g * Tq * kRowVec, j0, Tq - 1, stage, wave, lane);
-    load_to_lds_b32(rowbias + (size_t)g * tq_pad + j0 + (lane & 31), stage + kTileBytes + wave * 256);
+  // 128 bytes, which keeps the count of vector-memory operations per wavefront uniform); called
+  // for item 0, 1, 2, ...; past the end it re-reads the last one, which cannot change a maximum.
+  int g_in = h * G + first / ntq, j_in = first % ntq * 32, left = n;
+  auto stream = [&](int stage) {
+    const unsigned at = lds0 + (unsigned)(stage * kStageBytes);
+    stream_tile_to_lds(q + ((size_t)g_in * Tq + j_in) * kRowVec, Tq - 1 - j_in, at, wave, lane);
+    load_to_lds_b32(rowbias + (size_t)g_in * tq_pad + j_in, (unsigned)(lane & 31) * 4u, at + kTileBytes + wave * 256);
+    --left;                                              // selects, no branch: a step stays one block of code
+    const bool wraps = j_in + 32 == tq_pad;
+    g_in += left > 0 && wraps ? 1 : 0;
+    j_in = left > 0 ? (wraps ? 0 : j_in + 32) : j_in;
   };
 #pragma unroll
-  for (int d = 0; d < kStages; ++d) stream(d);            // all stages: tiles 0 .. kAhead
+  for (int d = 0; d < kStages; ++d) stream(d);
 
   Tile kt[kStay];                                        // B operands: the wavefront's keys
 #pragma unroll
   for (int t = 0; t < kStay; ++t) load_tile(kt[t], kh, k0 + 32 * t, T - 1, lane);
+  unsigned off[kSteps];
+  fragment_offsets(off, lane);
   float cm[kStay];
 #pragma unroll
   for (int t = 0; t < kStay; ++t) cm[t] = -INFINITY;
 
-  // The bias of a row, divided by the logit scale (which is applied after the maximum), is
-  // the initial value of the row's accumulators: C[query][key] then holds logit + bias / c and
-  // the column pass is a bare maximum.
-  const float inv_c = 1.0f / cscale;
-  auto read = [&](Tile& qt, floatx16& init, int i) {
-    const unsigned char* stage = smem + (i % kStages) * kStageBytes;
-    read_tile_from_lds(qt, stage, lane);
-    const float* rb = reinterpret_cast<const float*>(stage + kTileBytes + wave * 256) + 4 * kg;
+  // The bias of a row, divided by the logit scale, is the initial value of the row's
+  // accumulators: C[query][key] then holds logit + bias / c and the column pass is a bare maximum.
+  const unsigned bias_off = (unsigned)(kTileBytes + wave * 256 + 16 * kg);
+  auto read_bias = [&](floatx16& init, int a, int stage_bytes) {
+    const floatx4 b4 = *reinterpret_cast<const floatx4*>(smem + stage_bytes + bias_off + 32 * a);
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const floatx4 b4 = *reinterpret_cast<const floatx4*>(rb + 8 * a);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) init[4 * a + e] = b4[e] * inv_c;
-    }
-  };
-  auto reduce = [&](const floatx16 (&s)[kStay]) {
-#pragma unroll
-    for (int t = 0; t < kStay; ++t) {
-      float best = cm[t];
-#pragma unroll
-      for (int e = 0; e < 16; ++e) best = fmaxf(best, s[t][e]);
-      cm[t] = best;
-    }
+    for (int e = 0; e < 4; ++e) init[4 * a + e] = b4[e];
   };
 
   // software pipeline as in the row pass; three load-to-LDS per wavefront and item
-  Tile qa;
-  floatx16 ia, sa[kStay], sb[kStay];
-  wait_vmcnt<3 * kAhead>();
+  Tile ta, tb;
+  floatx16 init, sa[kStay], sb[kStay];
+  wait_vmcnt<0>();
   block_barrier_no_drain();
-  read(qa, ia, 0);
-  tile_products<false, kStay>(qa, kt, ia, sa);                  // item 0, C[query][key]
-  auto step = [&](floatx16 (&s_cur)[kStay], floatx16 (&s_next)[kStay], int i) {
-    wait_vmcnt<3 * (kAhead - 1)>();
+#pragma unroll
+  for (int s = 0; s < kSteps; ++s) {
+    ta.f[s] = *reinterpret_cast<const u32x4*>(smem + off[s]);
+    tb.f[s] = *reinterpret_cast<const u32x4*>(smem + kStageBytes + off[s]);
+  }
+#pragma unroll
+  for (int a = 0; a < 4; ++a) read_bias(init, a, 0);
+#pragma unroll
+  for (int i = 0; i < kSlots; ++i) product(i, ta, kt, init, sa);
+#pragma unroll
+  for (int a = 0; a < 4; ++a) read_bias(init, a, kStageBytes);
+  wait_lds();
+  block_barrier_no_drain();
+  stream(0);
+  auto step = [&](Tile& frag, Tile& next, floatx16 (&s_cur)[kStay], floatx16 (&s_next)[kStay], auto stage_tag) {
+    constexpr int kStage = decltype(stage_tag)::value, kRead = (kStage + 2) % kStages * kStageBytes;
+    wait_lds();
+    wait_vmcnt<6>();
     block_barrier_no_drain();
-    stream(i + kStages);
-    read(qa, ia, i + 1);
-    tile_products<false, kStay>(qa, kt, ia, s_next);
-    reduce(s_cur);
+    stream((kStage + 1) % kStages);
+    static_for<kSlots>([&](auto i_) {
+      constexpr int i = decltype(i_)::value;
+      product(i, frag, kt, init, s_next);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (i < kSteps) next.f[i] = *reinterpret_cast<const u32x4*>(smem + kRead + off[i]);
+      if constexpr (i >= kSteps && i < kSteps + 4) read_bias(init, i - kSteps, kRead);
+      cm[i & 1] = fmaxf(fmaxf(cm[i & 1], s_cur[i & 1][i & ~1]), s_cur[i & 1][i | 1]);
+      asm volatile("" : "+v"(cm[i & 1]));                // stays in its slot
+      __builtin_amdgcn_sched_barrier(0);
+    });
   };
-  for (int i = 0; i < n; i += 2) {
-    step(sa, sb, i);
-    step(sb, sa, i + 1);                                 // i + 1 == n: a re-read item, harmless
+  for (int i = 0; i < n; i += kStages) {                 // past n: re-read items, harmless
+    step(tb, ta, sa, sb, std::integral_constant<int, 0>{});
+    step(ta, tb, sb, sa, std::integral_constant<int, 1>{});
+    step(tb, ta, sa, sb, std::integral_constant<int, 2>{});
+    step(ta, tb, sb, sa, std::integral_constant<int, 3>{});
   }
   wait_vmcnt<0>();
 
@@ -339,7 +421,7 @@ __global__ __launch_bounds__(256) void teacher_finish_kernel(const float* __rest
 
 int teacher_splits(int H, int G, int Tq, int T) {
   const int tq_pad = (Tq + 31) / 32 * 32;
-  const long long col_blocks = (long long)((T + 4 * kStay * 32 - 1) / (4 * kStay * 32)) * H;
+  const long long col_blocks = (long long)((T + kBlockRows - 1) / kBlockRows) * H;
   long long js = col_blocks > 0 ? (512 + col_blocks - 1) / col_blocks : 1;   // ~2 blocks per CU
   const long long items = (long long)G * (tq_pad / 32);
   if (js > items) js = items;
@@ -367,12 +449,12 @@ int launch_teacher_scores(const void* q, const void* k, const float* vnorm, cons
   const float cscale = scale * 1.4426950408889634f;
   const auto* qv = static_cast<const u32x4*>(q);
   const auto* kv = static_cast<const u32x4*>(k);
-  const dim3 g1((tq_pad + 4 * kStayRow * 32 - 1) / (4 * kStayRow * 32), HQ);
+  const dim3 g1((tq_pad + kBlockRows - 1) / kBlockRows, HQ);
   constexpr size_t lds = (size_t)kStages * kStageBytes;
   teacher_rowstat_kernel<<<g1, 256, lds, stream>>>(qv, kv, hnorm, G, Tq, Tk, tq_pad, cscale, rowbias);
   if (hipGetLastError() != hipSuccess) return KVZAP_ERR_RUNTIME;
-  const dim3 g2((T + 4 * kStay * 32 - 1) / (4 * kStay * 32), H, JS);
-  teacher_colmax_kernel<<<g2, 256, lds, stream>>>(qv, kv, rowbias, G, Tq, Tk, T, tq_pad, cscale, part);
+  const unsigned g2 = (unsigned)((T + kBlockRows - 1) / kBlockRows) * H * JS;
+  teacher_colmax_kernel<<<g2, 256, lds, stream>>>(qv, kv, rowbias, G, H, JS, Tq, Tk, T, tq_pad, cscale, part);
   if (hipGetLastError() != hipSuccess) return KVZAP_ERR_RUNTIME;
   const int n = H * T;
   teacher_finish_kernel<<<(n + 255) / 256, 256, 0, stream>>>(part, vnorm, n, JS, log_s);
