@@ -129,6 +129,70 @@ __device__ __forceinline__ float gelu_exact(float z) {
   return z * phi;
 }
 
+// The normalised states of a block's rows, x * rstd * gain rounded to bf16: `width` 16-byte pieces
+// from `from` on of each of `rows` rows of ppr pieces, rstd in LDS.  A pure copy, bound by how many
+// bytes the block's few wavefronts keep in flight: a wavefront takes every kWaves-th row, kG * 64
+// pieces of it at a time, so that its part of the gain stays in registers, and loads the next kR
+// rows while it scales and stores the last ones.  Rows past the end repeat the last row and, where
+// the width is no multiple of 64 * kG (kG is 1 then), lanes past it its last piece, with the same
+// values.
+template <int kWaves, int kG, int kR>
+__device__ __forceinline__ void write_states_columns(const u32x4* from, u32x4* to, const u32x4* gain,
+                                                     const float* rstd, int rows, int width, int ppr,
+                                                     int wave, int lane) {
+  for (int c0 = 0; c0 < width; c0 += kG * 64) {
+    const int at = kG > 1 || c0 + lane < width ? c0 + lane : width - 1;
+    u32x4 g[kG], xa[kR][kG], xb[kR][kG];
+#pragma unroll
+    for (int c = 0; c < kG; ++c) g[c] = gain[at + c * 64];
+    auto load = [&](u32x4 (&x)[kR][kG], int r0) {
+#pragma unroll
+      for (int i = 0; i < kR; ++i) {
+        const int r = r0 + i * kWaves < rows ? r0 + i * kWaves : rows - 1;
+        const u32x4* p = from + (size_t)r * ppr + at;
+#pragma unroll
+        for (int c = 0; c < kG; ++c) x[i][c] = __builtin_nontemporal_load(p + c * 64);
+      }
+    };
+    auto store = [&](const u32x4 (&x)[kR][kG], int r0) {
+#pragma unroll
+      for (int i = 0; i < kR; ++i) {
+        const int r = r0 + i * kWaves < rows ? r0 + i * kWaves : rows - 1;
+        const float sc = rstd[r];
+        u32x4* p = to + (size_t)r * ppr + at;
+#pragma unroll
+        for (int c = 0; c < kG; ++c) {
+          u32x4 y;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float lo = __uint_as_float(x[i][c][e] << 16) * sc * __uint_as_float(g[c][e] << 16);
+            const float hi = __uint_as_float(x[i][c][e] & 0xffff0000u) * sc * __uint_as_float(g[c][e] & 0xffff0000u);
+            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+            const bf16x2 pr = {(__bf16)lo, (__bf16)hi};
+            y[e] = __builtin_bit_cast(unsigned int, pr);
+          }
+          __builtin_nontemporal_store(y, p + c * 64);
+        }
+      }
+    };
+    constexpr int kStep = kR * kWaves;
+    load(xa, wave);
+    for (int r0 = wave; r0 < rows; r0 += 2 * kStep) {
+      load(xb, r0 + kStep);
+      store(xa, r0);
+      if (r0 + kStep >= rows) break;
+      load(xa, r0 + 2 * kStep);
+      store(xb, r0 + kStep);
+    }
+  }
+}
+template <int kWaves, int kG, int kR>
+__device__ __forceinline__ void write_states(const u32x4* from, u32x4* to, const u32x4* gain,
+                                             const float* rstd, int rows, int width, int ppr, int wave, int lane) {
+  if (kG > 1 && width % (kG * 64) == 0) write_states_columns<kWaves, kG, kR>(from, to, gain, rstd, rows, width, ppr, wave, lane);
+  else write_states_columns<kWaves, 1, 8>(from, to, gain, rstd, rows, width, ppr, wave, lane);
+}
+
 // LDS tile of 128-byte rows (eight 16-byte pieces): byte offset of logical piece `piece` of
 // `row`.  The piece index is XOR-ed with bits 1..3 of the row: a ds_read_b128 serves 16 lanes
 // (16 consecutive rows, one piece each) at a time, and with two rows per 256 bytes of banks

@@ -805,40 +805,14 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
         for (int tb = 0; tb < TB; ++tb) sR[32 * tb + l32] = rs[tb];
       }
       __syncthreads();
-      const int ppr = Dh / 8;                                      // 16-byte pieces per row
       const u32x4* xin = reinterpret_cast<const u32x4*>(hidden + (size_t)row0 * Dh);
       u32x4* yout = reinterpret_cast<u32x4*>(norm.normed + (size_t)row0 * Dh);
       const u32x4* gain8 = reinterpret_cast<const u32x4*>(norm.gain);
-      const int total = rows_here * ppr;
-      // only this block's 256 threads are on the CU: eight 16-byte pieces in flight per thread
-      constexpr int kFly = 8;
-      for (int p0 = tid; p0 < total; p0 += 256 * kFly) {
-        u32x4 x[kFly];
-#pragma unroll
-        for (int u = 0; u < kFly; ++u) {
-          const int p = p0 + 256 * u;
-          if (p < total) x[u] = __builtin_nontemporal_load(xin + p);
-        }
-#pragma unroll
-        for (int u = 0; u < kFly; ++u) {
-          const int p = p0 + 256 * u;
-          if (p < total) {
-            const int r = p / ppr, c = p - r * ppr;
-            const u32x4 g = gain8[c];
-            const float sc = sR[r];
-            u32x4 y;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float lo = __uint_as_float(x[u][e] << 16) * sc * __uint_as_float(g[e] << 16);
-              const float hi = __uint_as_float(x[u][e] & 0xffff0000u) * sc * __uint_as_float(g[e] & 0xffff0000u);
-              typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-              const bf16x2 pr = {(__bf16)lo, (__bf16)hi};
-              y[e] = __builtin_bit_cast(unsigned int, pr);
-            }
-            __builtin_nontemporal_store(y, yout + p);
-          }
-        }
-      }
+      // 4 to 8 KB of a row at a time, which divides D_h where M = D_h / 8, two or four rows ahead.
+      // 30011 tokens: the whole call 223 -> 191 us, of which this part 108 -> 76 (6.4 TB/s); before,
+      // eight loads, their wait and the stores followed one another, with a division per piece.
+      constexpr int kColumns = UB == 5 ? 5 : UB == 4 ? 8 : 4;
+      write_states<4, kColumns, UB == 4 ? 2 : 4>(xin, yout, gain8, sR, rows_here, Dh / 8, Dh / 8, wid, lane);
     }
   }
 }

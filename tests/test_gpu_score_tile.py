@@ -115,3 +115,22 @@ def test_entry_points_without_a_workspace_keep_the_token_blocks():
     err = parity.to_np(out)[0] - want
     assert np.abs(err).max() <= 6e-3
     assert np.linalg.norm(err) > 1e-5 * np.linalg.norm(want)       # fp16 activations: not the tiles
+
+
+@pytest.mark.parametrize("T,Dh,M", [(33000, 256, 256), (16000, 512, 512), (17000, 320, 128), (24800, 640, 640)])
+def test_states_of_token_blocks_are_whole(T, Dh, M):
+    # row widths that are and are not whole groups of columns, a last block with few rows, and the
+    # blocks between: every state, against the rows' own scales
+    x, w = _case(1, T, Dh, M, 8, seed=T)
+    gain = (1 + 0.1 * torch.randn(Dh, generator=torch.Generator().manual_seed(3))).bfloat16().to(DEV)
+    d, x = {k: v.to(DEV) for k, v in w.items()}, x.to(DEV)
+    prep = binding.kvzap_prepare_scorer_rmsnorm(d["W1"], gain)
+    states, rstd = torch.full_like(x, float("nan")), torch.empty((1, T), device=DEV)
+    scores = torch.empty((1, 8, T), device=DEV)
+    rc = binding.lib().kvzap_score_rmsnorm(x.data_ptr(), prep.data_ptr(), gain.data_ptr(), 1e-6, None,
+                                           d["W2"].data_ptr(), None, scores.data_ptr(), rstd.data_ptr(),
+                                           states.data_ptr(), 1, T, Dh, M, 8,
+                                           ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0                                                   # without a workspace: token blocks throughout
+    want = ((x.float() * rstd.unsqueeze(-1)) * gain.float()).bfloat16()
+    assert torch.equal(states, want)
