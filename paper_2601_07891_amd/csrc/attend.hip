@@ -94,66 +94,85 @@ struct Source {
 
 constexpr int kRowVec = kD * 2 / 16;   // 16-byte pieces per row
 
-// Offset (in 16-byte pieces) of packed row r of the head from Source::K / Source::V.  Paged:
-// row r is row r % page_rows of page pages[r / page_rows]; a table entry outside the pool is
+// Paged prefix: the pool rows of kLookup consecutive chunks' 16-row halves, half i in lane i % 64
+// of word i / 64.  Looked up once per split, all halves at a time: looked up chunk by chunk, the
+// round trip of every entry stood ahead of the chunk's loads.  A table entry outside the pool is
 // clamped into it, so nothing outside the pool is ever read.
-template <bool kPaged>
-__device__ __forceinline__ size_t prefix_offset(const Source& s, int r) {
-  if (!kPaged) return (size_t)r * kRowVec;
-  int slot = r >> s.log_page;
-  slot = slot < s.max_pages - 1 ? slot : s.max_pages - 1;
-  int page = s.pages[slot];
-  page = page < 0 ? 0 : (page < s.num_pages ? page : s.num_pages - 1);
-  return (((size_t)page << s.log_page) + (size_t)(r & ((1 << s.log_page) - 1))) * kRowVec;
+constexpr int kLookup = 64;              // chunks, the most a split has unless its head exceeds the bound
+struct Rows {
+  int row[2];
+};
+__device__ __forceinline__ Rows look_up(const Source& s, int chunk0, int lane) {
+  Rows w;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    int r = chunk0 * kChunkRows + (i * 64 + lane) * 16;
+    r = r < s.n_p ? r : (s.n_p > 0 ? s.n_p - 1 : 0);
+    int slot = r >> s.log_page;
+    slot = slot < s.max_pages - 1 ? slot : s.max_pages - 1;
+    int page = s.pages[slot];
+    page = page < 0 ? 0 : (page < s.num_pages ? page : s.num_pages - 1);
+    w.row[i] = (page << s.log_page) + (r & ((1 << s.log_page) - 1));
+  }
+  return w;
 }
 
-// Loads chunk `vc` of the head's chunk list (prefix chunks, then ring chunks).  Rows past
-// the end of the segment are read from its last row (their weights are forced to zero).
-// A page holds a multiple of 16 rows, so each 16-row half of a chunk is contiguous.
+// Where chunk `vc` of the head's chunk list (prefix chunks, then ring chunks) is.  Its 16-row
+// halves are each contiguous because a page holds a multiple of 16 rows.  Rows past the end of the
+// segment are read from its last row (their weights are forced to zero), so a half that starts
+// past it is that row alone.
+struct Place {
+  bool ring;
+  int row0, n_seg;
+  size_t half[2];    // first row of each half, in 16-byte pieces from the store, the pool or the ring
+};
 template <bool kPaged>
-__device__ __forceinline__ void load_chunk(Chunk& c, int vc, int cp, const Source& s, int li,
-                                           int lg, int& row0, int& n_seg) {
-  const bool ring = vc >= cp;
-  const u32x4* Kb = ring ? s.Kr : s.K;
-  const u32x4* Vb = ring ? s.Vr : s.V;
-  n_seg = ring ? s.n_r : s.n_p;
-  row0 = (ring ? vc - cp : vc) * kChunkRows;
-  const int klocal = 4 * (li & 3) + (li >> 2);          // row of this lane inside a 16-row set
-  if (row0 + kChunkRows <= n_seg) {
-    size_t half[2];
-    if (kPaged && !ring) {
-      half[0] = prefix_offset<kPaged>(s, row0);
-      half[1] = prefix_offset<kPaged>(s, row0 + 16);
-    } else {
-      half[0] = (size_t)row0 * kRowVec;
-      half[1] = half[0] + 16 * kRowVec;
+__device__ __forceinline__ Place place_of(int vc, int cp, const Source& s, const Rows& rows, int chunk0) {
+  Place p;
+  p.ring = vc >= cp;
+  p.n_seg = p.ring ? s.n_r : s.n_p;
+  p.row0 = (p.ring ? vc - cp : vc) * kChunkRows;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    int r = p.row0 + 16 * t < p.n_seg ? p.row0 + 16 * t : p.n_seg - 1;
+    if (kPaged) {
+      const int i = (2 * (vc - chunk0) + t) & 63;
+      const int lo = __builtin_amdgcn_readlane(rows.row[0], i), hi = __builtin_amdgcn_readlane(rows.row[1], i);
+      const int pool = vc - chunk0 < kLookup / 2 ? lo : hi;
+      r = p.ring ? r : pool;
     }
+    p.half[t] = (size_t)r * kRowVec;
+  }
+  return p;
+}
+
+__device__ __forceinline__ void load_chunk(Chunk& c, const Place& p, const Source& s, int li, int lg) {
+  const u32x4* Kb = p.ring ? s.Kr : s.K;
+  const u32x4* Vb = p.ring ? s.Vr : s.V;
+  const int klocal = 4 * (li & 3) + (li >> 2);          // row of this lane inside a 16-row set
+  if (p.row0 + kChunkRows <= p.n_seg) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const u32x4* kp = Kb + half[t] + klocal * kRowVec + lg;
+      const u32x4* kp = Kb + p.half[t] + klocal * kRowVec + lg;
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) c.k[t][kk] = kp[kk * 4];
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      c.v[j] = Vb[half[j >> 2] + (size_t)(4 * (j & 3) + lg) * kRowVec + li];
+      c.v[j] = Vb[p.half[j >> 2] + (size_t)(4 * (j & 3) + lg) * kRowVec + li];
   } else {
-    const int last = n_seg - 1;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      int r = row0 + 16 * t + klocal;
-      r = r < last ? r : last;
-      const size_t o = (kPaged && !ring) ? prefix_offset<kPaged>(s, r) : (size_t)r * kRowVec;
-      const u32x4* kp = Kb + o + lg;
+      int lim = p.n_seg - 1 - (p.row0 + 16 * t);        // last row of the segment, within the half
+      lim = lim < 0 ? 0 : lim;
+      const u32x4* kp = Kb + p.half[t] + (klocal < lim ? klocal : lim) * kRowVec + lg;
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) c.k[t][kk] = kp[kk * 4];
-    }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      int r = row0 + 4 * j + lg;
-      r = r < last ? r : last;
-      const size_t o = (kPaged && !ring) ? prefix_offset<kPaged>(s, r) : (size_t)r * kRowVec;
-      c.v[j] = Vb[o + li];
+      for (int j = 0; j < 4; ++j) {
+        const int r = 4 * j + lg;
+        c.v[4 * t + j] = Vb[p.half[t] + (size_t)(r < lim ? r : lim) * kRowVec + li];
+      }
     }
   }
 }
@@ -222,7 +241,10 @@ __device__ __forceinline__ void consume_chunk(const Chunk& c, const u32x4 (&qb)[
   a.l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ones), p, a.l, 0, 0, 0);
 }
 
-// grid (NS, B*H), 64 threads.  part: [B*H][NS][G][128] fp32, ml: [B*H][NS][G][2] fp32.
+// grid (B*H, NS), 64 threads.  The head varies fastest and is shifted by one from split to split:
+// workgroups go to the eight XCDs in turn, so the blocks that have work (short heads: the first
+// splits only) come one after the other on all of them, and a long head's splits meet every XCD.
+// part: [B*H][NS][G][128] fp32, ml: [B*H][NS][G][2] fp32.
 // Contiguous layout: K_rows/V_rows are the row store, row_offsets the heads' first rows.
 // Paged layout: K_rows/V_rows are the page pool, row_offsets is null, block_table given.
 template <bool kPaged>
@@ -230,9 +252,11 @@ __global__ __launch_bounds__(64, 2) void attend_partial_kernel(
     const u32x4* q, const u32x4* K_rows, const u32x4* V_rows, int64_t cap_rows,
     const int64_t* row_offsets, const int32_t* block_table, int max_pages, int log_page,
     int num_pages, const int32_t* lengths, const u32x4* K_ring, const u32x4* V_ring,
-    const int32_t* seq_pos, int window, float cscale, int H, int G, int spc, float* part,
+    const int32_t* seq_pos, int window, float cscale, int H, int G, int NS, int spc, float* part,
     float* ml) {
-  const int bh = blockIdx.y, split = blockIdx.x, NS = gridDim.x;
+  const int split = blockIdx.y + gridDim.y * blockIdx.z, BH = gridDim.x;
+  if (split >= NS) return;
+  const int bh = (int)((blockIdx.x + (unsigned)split) % (unsigned)BH);
   const int b = bh / H;
   const HeadExtent e = head_extent(row_offsets, lengths, seq_pos, window, cap_rows, bh, b);
   const int cp = chunks_of(e.n_p), ct = cp + chunks_of(e.n_r);
@@ -270,22 +294,32 @@ __global__ __launch_bounds__(64, 2) void attend_partial_kernel(
   // Two chunk buffers; the steady-state loop has no branch around a load, so the
   // compiler's wait counts let the loads of one buffer fly while the other is consumed.
   Chunk ca, cb;
-  int row0a, nsega, row0b, nsegb;
-  load_chunk<kPaged>(ca, c0, cp, src, li, lg, row0a, nsega);
-  int vc = c0;
-  while (vc + 2 < c1) {
-    load_chunk<kPaged>(cb, vc + 1, cp, src, li, lg, row0b, nsegb);
-    consume_chunk(ca, qb, acc, row0a, nsega, lg, cscale);
-    load_chunk<kPaged>(ca, vc + 2, cp, src, li, lg, row0a, nsega);
-    consume_chunk(cb, qb, acc, row0b, nsegb, lg, cscale);
-    vc += 2;
-  }
-  if (vc + 1 < c1) {
-    load_chunk<kPaged>(cb, vc + 1, cp, src, li, lg, row0b, nsegb);
-    consume_chunk(ca, qb, acc, row0a, nsega, lg, cscale);
-    consume_chunk(cb, qb, acc, row0b, nsegb, lg, cscale);
-  } else {
-    consume_chunk(ca, qb, acc, row0a, nsega, lg, cscale);
+  Rows rows{};
+  for (int chunk0 = c0; chunk0 < c1; chunk0 += kLookup) {
+    const int end = kPaged && chunk0 + kLookup < c1 ? chunk0 + kLookup : c1;
+    if (kPaged) rows = look_up(src, chunk0, lane);
+    auto place = [&](int vc) { return place_of<kPaged>(vc, cp, src, rows, chunk0); };
+    Place pa = place(chunk0), pb;
+    load_chunk(ca, pa, src, li, lg);
+    int vc = chunk0;
+    while (vc + 2 < end) {
+      pb = place(vc + 1);
+      load_chunk(cb, pb, src, li, lg);
+      consume_chunk(ca, qb, acc, pa.row0, pa.n_seg, lg, cscale);
+      pa = place(vc + 2);
+      load_chunk(ca, pa, src, li, lg);
+      consume_chunk(cb, qb, acc, pb.row0, pb.n_seg, lg, cscale);
+      vc += 2;
+    }
+    if (vc + 1 < end) {
+      pb = place(vc + 1);
+      load_chunk(cb, pb, src, li, lg);
+      consume_chunk(ca, qb, acc, pa.row0, pa.n_seg, lg, cscale);
+      consume_chunk(cb, qb, acc, pb.row0, pb.n_seg, lg, cscale);
+    } else {
+      consume_chunk(ca, qb, acc, pa.row0, pa.n_seg, lg, cscale);
+    }
+    if (!kPaged) break;
   }
 
   if (li < G) {
@@ -365,14 +399,16 @@ __global__ __launch_bounds__(256) void attend_combine_kernel(
 // Chunks per split (one split = one wave).  Long splits amortise a wave's start-up (its
 // first loads are not overlapped with anything), the partial result it writes and the work
 // of the combine kernel, which folds every split of a head in one block; short ones fill
-// the chip when there are few heads.  Aim at ~2048 waves if every head were at the bound,
-// within 4..64 chunks (128..2048 rows).  Measured on 512 heads of 4k..32k rows: 16 chunks
-// 5.62, 32: 5.76, 64: 5.87, 128: 5.54 TB/s; on 8 heads of 131072 rows a target of 8192
-// waves (1025 splits per head) gives 4.4 TB/s, 2048 waves 5.2, 1024 waves 5.0.
+// the chip when there are few heads.  Aim at ~2048 waves and at most 96 splits a head if every
+// head were at the bound, within 4..64 chunks (128..2048 rows).  Measured (8 KV heads, us per
+// call at 4 / 8 / 16 / 32 / 64 chunks): 64 sequences of 4k..32k rows (bound 38k) 1040 / 953 / 895 /
+// 858 / 840; 24 of 4k..8k 139 / 130 / 129 / 129 / 121; 16 of 0.5k..2k 22 / 22 / 20 / 24 / 39;
+// 3 of 1k..8k 18 / 18 / 17 / 24 / 40; 1 of 32k 31 / 28 / 28 / 26 / 40.
 int attend_split_chunks(int BH, int max_rows, int window) {
   const long long ct = (max_rows + kChunkRows - 1) / kChunkRows +
                        ((window > 0 ? window : 0) + kChunkRows - 1) / kChunkRows;
-  long long want = ct * BH / 2048;
+  const long long fill = ct * BH / 2048, fold = ct / 96;
+  const long long want = fill > fold ? fill : fold;
   int spc = 4;
   while (spc < 64 && spc < want) spc *= 2;
   return spc;
@@ -416,14 +452,16 @@ int launch_attend_decode(const void* q, const void* K_rows, const void* V_rows,
   const auto* vv = static_cast<const u32x4*>(V_rows);
   const auto* kr = static_cast<const u32x4*>(K_ring);
   const auto* vr = static_cast<const u32x4*>(V_ring);
+  const unsigned ny = NS < 65535 ? NS : 65535;
+  const dim3 grid(BH, ny, (NS + ny - 1) / ny);
   if (paged)
-    hipLaunchKernelGGL(attend_partial_kernel<true>, dim3(NS, BH), dim3(64), 0, stream, qv, kv, vv,
+    hipLaunchKernelGGL(attend_partial_kernel<true>, grid, dim3(64), 0, stream, qv, kv, vv,
                        cap_rows, nullptr, block_table, max_pages, log_page, num_pages, lengths, kr,
-                       vr, seq_pos, window, cscale, H, G, spc, part, ml);
+                       vr, seq_pos, window, cscale, H, G, NS, spc, part, ml);
   else
-    hipLaunchKernelGGL(attend_partial_kernel<false>, dim3(NS, BH), dim3(64), 0, stream, qv, kv, vv,
+    hipLaunchKernelGGL(attend_partial_kernel<false>, grid, dim3(64), 0, stream, qv, kv, vv,
                        cap_rows, row_offsets, nullptr, 0, 0, 0, lengths, kr, vr, seq_pos, window,
-                       cscale, H, G, spc, part, ml);
+                       cscale, H, G, NS, spc, part, ml);
   if (hipGetLastError() != hipSuccess) return KVZAP_ERR_RUNTIME;
   hipLaunchKernelGGL(attend_combine_kernel, dim3(BH * G), dim3(256), 0, stream, part, ml,
                      cap_rows, paged ? nullptr : row_offsets, lengths, seq_pos, window, H, G, NS,

@@ -338,3 +338,11 @@ def test_decode_evict_paged_without_a_page_sets_the_error_flag():
     assert int(st.error_flag[0]) == 1
     assert (parity.to_np(st.lengths) == P).all()        # never beyond the pages a head owns
     assert (parity.to_np(st.pos_pool)[2:] == -1).all()  # pages 2, 3 untouched
+
+
+@pytest.mark.parametrize("rows", [2047, 2048, 2049, 2080, 4097, 6200])
+def test_attend_paged_split_longer_than_one_lookup(rows):
+    # a bound far below the lengths: the last split runs over 64 chunks and more, whose pages are
+    # looked up 64 chunks at a time (one group, one and a bit, two, four), ring chunks among them
+    _attend_case([[rows, 3], [rows + 100, rows - 40]], 16, 70, [128, 33], HQ=8, seed=rows, max_rows=16)
+    _attend_case([[rows, 700]], 64, 0, None, HQ=8, seed=rows + 1, max_rows=16)
