@@ -3,7 +3,7 @@
 Argument marshalling only: tensors are checked for device, dtype and
 contiguity, outputs and workspaces are allocated with torch when the caller
 does not pass them, raw pointers and the current HIP stream are handed to the C
-ABI.  Every step of the prune path runs in the library's kernels; there is no
+ABI; the short calls do all that in native code (csrc/host.cpp).  Every step of the prune path runs in the library's kernels; there is no
 fallback, and a missing library is an error.
 """
 from __future__ import annotations
@@ -16,6 +16,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libkvzap.so")
+HOST_PATH = os.path.join(_HERE, "_kvzap_host.so")
 
 CALL_SCORE, CALL_MASK, CALL_COMPACT, CALL_DECODE_EVICT, CALL_ATTEND_DECODE = 0, 1, 2, 3, 4
 CALL_ASSIGN_PAGES, CALL_TOPK_THRESHOLD, CALL_TEACHER_SCORES, CALL_COMPRESS = 5, 6, 7, 8
@@ -109,12 +110,44 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+_host = None
+
+
+def _native():
+    """The checks, allocations and calls of the short entry points in native code (csrc/host.cpp)."""
+    global _host
+    if _host is None:
+        lib()
+        try:
+            from . import _kvzap_host
+        except ImportError as e:
+            raise FileNotFoundError(
+                f"{HOST_PATH} cannot be loaded ({e}): build it with __graft_entry__.build() "
+                "or `python paper_2601_07891_amd/build.py`; there is no fallback path") from e
+        _host = _kvzap_host
+    return _host
+
+
+def _done(result, where: str):
+    if type(result) is int and result != 0:
+        raise KvzapError(result, where)
+    return result
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
         stream = torch.cuda.current_stream()
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream or None
     return int(stream) or None
+
+
+def _on(stream, workspace: Optional[torch.Tensor], device, *query, least: int = 0):
+    """(workspace, stream handle) of a call on a stream that the caller names: what the native code
+    would allocate is allocated here, where the allocator is told of the stream."""
+    if workspace is None:
+        workspace, _ = _workspace(max(kvzap_workspace_bytes(*query), least), device, None, stream)
+    return workspace, _stream(stream) or 0
 
 
 def _check(t: Optional[torch.Tensor], dtype, name: str, optional: bool = False):
@@ -157,32 +190,11 @@ def kvzap_score(hidden: torch.Tensor, W1: torch.Tensor, b1: Optional[torch.Tenso
                 workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """hidden bf16 [B,T,Dh]; MLP: W1 [M,Dh], b1 [M], W2 [H,M], b2 [H];
     linear: W1 [H,Dh], b1 [H], W2 = b2 = None.  Returns scores fp32 [B,H,T]."""
-    bf = torch.bfloat16
-    _check(hidden, bf, "hidden"); _check(W1, bf, "W1")
-    _check(b1, bf, "b1", True); _check(W2, bf, "W2", True); _check(b2, bf, "b2", True)
-    B, T, Dh = hidden.shape
-    if W2 is not None:
-        M, H = W1.shape[0], W2.shape[0]
-        if W1.shape != (M, Dh) or W2.shape != (H, M):
-            raise ValueError("W1 must be [M,Dh] and W2 [H,M]")
-        if (b1 is not None and b1.shape != (M,)) or (b2 is not None and b2.shape != (H,)):
-            raise ValueError("b1 must be [M] and b2 [H]")
-    else:
-        M, H = 0, W1.shape[0]
-        if W1.shape != (H, Dh) or (b1 is not None and b1.shape != (H,)):
-            raise ValueError("W1 must be [H,Dh] and b1 [H]")
-    if scores is None:
-        scores = torch.empty((B, H, T), dtype=torch.float32, device=hidden.device)
-    _check(scores, torch.float32, "scores")
-    if scores.shape != (B, H, T):
-        raise ValueError("scores must be [B,H,T]")
-    ws, ws_bytes = _workspace(kvzap_workspace_bytes(CALL_SCORE, B, T, Dh, M, H), hidden.device,
-                              workspace, stream)
-    rc = lib().kvzap_score(_ptr(hidden), _ptr(W1), _ptr(b1), _ptr(W2), _ptr(b2), _ptr(scores),
-                           B, T, Dh, M, H, _ptr(ws), ws_bytes, _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_score")
-    return scores
+    if stream is not None:
+        B, T, Dh = hidden.shape
+        M, H = (W1.shape[0], W2.shape[0]) if W2 is not None else (0, W1.shape[0])
+        workspace, stream = _on(stream, workspace, hidden.device, CALL_SCORE, B, T, Dh, M, H)
+    return _done(_native().score(hidden, W1, b1, W2, b2, scores, workspace, stream), "kvzap_score")
 
 
 def kvzap_mask(scores: torch.Tensor, tau: float, window: int,
@@ -194,27 +206,11 @@ def kvzap_mask(scores: torch.Tensor, tau: float, window: int,
                ) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
     """scores fp32 [B,H,T] -> (keep_idx int32 [B*H*T] packed, lengths int32 [B,H],
     offsets int64 [B*H+1])."""
-    _check(scores, torch.float32, "scores")
-    _check(seq_lens, torch.int32, "seq_lens", True)
-    B, H, T = scores.shape
-    dev = scores.device
-    if keep_idx is None:
-        keep_idx = torch.empty(B * H * T, dtype=torch.int32, device=dev)
-    if lengths is None:
-        lengths = torch.empty((B, H), dtype=torch.int32, device=dev)
-    if offsets is None:
-        offsets = torch.empty(B * H + 1, dtype=torch.int64, device=dev)
-    _check(keep_idx, torch.int32, "keep_idx"); _check(lengths, torch.int32, "lengths")
-    _check(offsets, torch.int64, "offsets")
-    if keep_idx.numel() < B * H * T or lengths.numel() != B * H or offsets.numel() != B * H + 1:
-        raise ValueError("output buffers have the wrong size")
-    ws, ws_bytes = _workspace(kvzap_workspace_bytes(CALL_MASK, B, T, 0, 0, H), dev, workspace, stream)
-    rc = lib().kvzap_mask(_ptr(scores), float(tau), int(window), _ptr(seq_lens), B, H, T,
-                          _ptr(keep_idx), _ptr(lengths), _ptr(offsets), _ptr(ws), ws_bytes,
-                          _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_mask")
-    return keep_idx, lengths, offsets
+    if stream is not None:
+        B, H, T = scores.shape
+        workspace, stream = _on(stream, workspace, scores.device, CALL_MASK, B, T, 0, 0, H)
+    return _done(_native().mask(scores, tau, window, seq_lens, keep_idx, lengths, offsets, workspace, stream),
+                 "kvzap_mask")
 
 
 def kvzap_mask_static(scores: torch.Tensor, tau: float, window: int,
@@ -241,28 +237,9 @@ def kvzap_compact(K: torch.Tensor, V: torch.Tensor, keep_idx: torch.Tensor,
                   cap_rows: Optional[int] = None, stream=None
                   ) -> Tuple[torch.Tensor, torch.Tensor]:
     """K, V bf16 [B,H,T,D] -> packed (K_out, V_out) bf16 [cap_rows, D]."""
-    bf = torch.bfloat16
-    _check(K, bf, "K"); _check(V, bf, "V")
-    _check(keep_idx, torch.int32, "keep_idx"); _check(lengths, torch.int32, "lengths")
-    _check(offsets, torch.int64, "offsets")
-    B, H, T, D = K.shape
-    if V.shape != K.shape:
-        raise ValueError("K and V must have the same shape")
-    if cap_rows is None:
-        cap_rows = B * H * T if K_out is None else K_out.shape[0]
-    if K_out is None:
-        K_out = torch.empty((cap_rows, D), dtype=bf, device=K.device)
-    if V_out is None:
-        V_out = torch.empty((cap_rows, D), dtype=bf, device=K.device)
-    _check(K_out, bf, "K_out"); _check(V_out, bf, "V_out")
-    if K_out.shape[0] < cap_rows or V_out.shape[0] < cap_rows or K_out.shape[1] != D:
-        raise ValueError("K_out / V_out smaller than cap_rows")
-    rc = lib().kvzap_compact(_ptr(K), _ptr(V), _ptr(keep_idx), _ptr(lengths), _ptr(offsets),
-                             _ptr(K_out), _ptr(V_out), int(cap_rows), B, H, T, D,
-                             _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_compact")
-    return K_out, V_out
+    if stream is not None:
+        stream = _stream(stream) or 0
+    return _done(_native().compact(K, V, keep_idx, lengths, offsets, K_out, V_out, cap_rows, stream), "kvzap_compact")
 
 
 class DecodeState:
@@ -296,28 +273,14 @@ def kvzap_decode_evict(hidden_new: torch.Tensor, W1: torch.Tensor, b1, W2, b2,
                        stream=None) -> None:
     """One decode step of one layer: hidden_new bf16 [B,Dh], k_new/v_new bf16 [B,H,D];
     `state` is updated in place."""
-    bf = torch.bfloat16
-    _check(hidden_new, bf, "hidden_new"); _check(W1, bf, "W1"); _check(b1, bf, "b1", True)
-    _check(W2, bf, "W2", True); _check(b2, bf, "b2", True)
-    _check(k_new, bf, "k_new"); _check(v_new, bf, "v_new")
-    B, Dh = hidden_new.shape
-    M = W1.shape[0] if W2 is not None else 0
     st = state
-    if (B, st.H, st.D) != tuple(k_new.shape) or k_new.shape != v_new.shape or B != st.B:
-        raise ValueError("k_new / v_new must be [B,H,D] matching the state")
-    ws, ws_bytes = _workspace(
-        kvzap_workspace_bytes(CALL_DECODE_EVICT, B, 1, Dh, M, st.H), hidden_new.device, workspace, stream)
-    ring = st.window > 0
-    rc = lib().kvzap_decode_evict(
-        _ptr(hidden_new), _ptr(W1), _ptr(b1), _ptr(W2), _ptr(b2), Dh, M,
-        _ptr(k_new), _ptr(v_new), _ptr(st.K_prefix), _ptr(st.V_prefix), _ptr(st.prefix_pos),
-        _ptr(st.slab_offsets), _ptr(st.slab_capacity),
-        _ptr(st.K_ring) if ring else None, _ptr(st.V_ring) if ring else None,
-        _ptr(st.score_ring) if ring else None, _ptr(st.lengths), _ptr(st.seq_pos),
-        float(tau), int(st.window), B, st.H, st.D, _ptr(st.error_flag),
-        _ptr(ws), ws_bytes, _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_decode_evict")
+    if stream is not None:
+        workspace, stream = _on(stream, workspace, hidden_new.device, CALL_DECODE_EVICT, hidden_new.shape[0], 1,
+                                hidden_new.shape[1], W1.shape[0] if W2 is not None else 0, st.H)
+    _done(_native().decode_evict(hidden_new, W1, b1, W2, b2, k_new, v_new, st.B, st.H, st.D, st.window, st.K_prefix,
+                                 st.V_prefix, st.prefix_pos, st.slab_offsets, st.slab_capacity, st.K_ring, st.V_ring,
+                                 st.score_ring, st.lengths, st.seq_pos, st.error_flag, tau, workspace, stream),
+          "kvzap_decode_evict")
 
 
 def kvzap_attend_decode(q: torch.Tensor, K_rows: torch.Tensor, V_rows: torch.Tensor,
@@ -329,44 +292,11 @@ def kvzap_attend_decode(q: torch.Tensor, K_rows: torch.Tensor, V_rows: torch.Ten
     """q bf16 [B,HQ,D]; K_rows/V_rows bf16 [total_rows,D]; row_offsets int64 [B*H];
     lengths int32 [B,H]; ring tensors bf16 [B,H,window,D] and seq_pos int32 [B] (None when
     window == 0).  Returns out bf16 [B,HQ,D]."""
-    bf = torch.bfloat16
-    _check(q, bf, "q"); _check(K_rows, bf, "K_rows"); _check(V_rows, bf, "V_rows")
-    _check(row_offsets, torch.int64, "row_offsets"); _check(lengths, torch.int32, "lengths")
-    B, HQ, D = q.shape
-    if lengths.dim() != 2 or lengths.shape[0] != B:
-        raise ValueError("lengths must be [B,H]")
-    H = lengths.shape[1]
-    if row_offsets.numel() != B * H:
-        raise ValueError("row_offsets must have B*H entries")
-    if K_rows.dim() != 2 or K_rows.shape[1] != D or K_rows.shape != V_rows.shape:
-        raise ValueError("K_rows and V_rows must both be [total_rows, D]")
-    if window > 0:
-        _check(K_ring, bf, "K_ring"); _check(V_ring, bf, "V_ring")
-        _check(seq_pos, torch.int32, "seq_pos")
-        if tuple(K_ring.shape) != (B, H, window, D) or K_ring.shape != V_ring.shape:
-            raise ValueError("K_ring and V_ring must be [B,H,window,D]")
-        if seq_pos.numel() != B:
-            raise ValueError("seq_pos must have B entries")
-    if out is None:
-        out = torch.empty((B, HQ, D), dtype=bf, device=q.device)
-    else:
-        _check(out, bf, "out")
-        if out.shape != q.shape:
-            raise ValueError("out must be [B,HQ,D]")
-    ws, ws_bytes = _workspace(
-        kvzap_workspace_bytes(CALL_ATTEND_DECODE, B, int(max_rows), HQ, int(window), H),
-        q.device, workspace, stream)
-    ring = window > 0
-    total_rows = K_rows.shape[0]
-    rc = lib().kvzap_attend_decode(
-        _ptr(q), _ptr(K_rows) if total_rows else None, _ptr(V_rows) if total_rows else None,
-        total_rows, _ptr(row_offsets), _ptr(lengths),
-        _ptr(K_ring) if ring else None, _ptr(V_ring) if ring else None,
-        _ptr(seq_pos) if ring else None, int(window), int(max_rows), float(scale), _ptr(out),
-        B, H, HQ, D, _ptr(ws), ws_bytes, _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_attend_decode")
-    return out
+    if stream is not None:
+        workspace, stream = _on(stream, workspace, q.device, CALL_ATTEND_DECODE, q.shape[0], int(max_rows), q.shape[1],
+                                int(window), lengths.shape[1])
+    return _done(_native().attend_decode(q, K_rows, V_rows, row_offsets, lengths, K_ring, V_ring, seq_pos, window,
+                                         max_rows, scale, out, workspace, stream), "kvzap_attend_decode")
 
 
 def kvzap_assign_pages(lengths: torch.Tensor, page_rows: int, free_pages: torch.Tensor,
@@ -376,28 +306,11 @@ def kvzap_assign_pages(lengths: torch.Tensor, page_rows: int, free_pages: torch.
                        workspace: Optional[torch.Tensor] = None, stream=None):
     """lengths int32 [B,H]; free_pages int32 [n_free].  Returns (block_table int32
     [B*H, max_pages], result int32 [2] = (pages taken, status)), both on the device."""
-    _check(lengths, torch.int32, "lengths"); _check(free_pages, torch.int32, "free_pages")
-    B, H = lengths.shape
-    if block_table is None:
-        block_table = torch.empty((B * H, max_pages), dtype=torch.int32, device=lengths.device)
-    else:
-        _check(block_table, torch.int32, "block_table")
-        if tuple(block_table.shape) != (B * H, max_pages):
-            raise ValueError("block_table must be [B*H, max_pages]")
-    if result is None:
-        result = torch.empty(4, dtype=torch.int32, device=lengths.device)
-    else:
-        _check(result, torch.int32, "result")
-    ws, ws_bytes = _workspace(kvzap_workspace_bytes(CALL_ASSIGN_PAGES, B, 1, 0, 0, H),
-                              lengths.device, workspace, stream)
-    n_free = free_pages.numel()
-    rc = lib().kvzap_assign_pages(_ptr(lengths), B, H, int(page_rows), int(reserve_rows),
-                                  _ptr(free_pages) if n_free else None, n_free,
-                                  _ptr(block_table), int(max_pages), _ptr(result),
-                                  _ptr(ws), ws_bytes, _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_assign_pages")
-    return block_table, result
+    if stream is not None:
+        B, H = lengths.shape
+        workspace, stream = _on(stream, workspace, lengths.device, CALL_ASSIGN_PAGES, B, 1, 0, 0, H)
+    return _done(_native().assign_pages(lengths, page_rows, free_pages, max_pages, reserve_rows, block_table, result,
+                                        workspace, stream), "kvzap_assign_pages")
 
 
 def kvzap_compact_paged(K: torch.Tensor, V: torch.Tensor, keep_idx: torch.Tensor,
@@ -405,25 +318,10 @@ def kvzap_compact_paged(K: torch.Tensor, V: torch.Tensor, keep_idx: torch.Tensor
                         block_table: torch.Tensor, page_rows: int, K_pool: torch.Tensor,
                         V_pool: torch.Tensor, stream=None) -> None:
     """K, V bf16 [B,H,T,D]; pools bf16 [num_pages, page_rows, D], written in place."""
-    bf = torch.bfloat16
-    _check(K, bf, "K"); _check(V, bf, "V"); _check(K_pool, bf, "K_pool"); _check(V_pool, bf, "V_pool")
-    _check(keep_idx, torch.int32, "keep_idx"); _check(lengths, torch.int32, "lengths")
-    _check(offsets, torch.int64, "offsets"); _check(block_table, torch.int32, "block_table")
-    B, H, T, D = K.shape
-    if V.shape != K.shape or K_pool.shape != V_pool.shape:
-        raise ValueError("K/V and the two pools must have matching shapes")
-    if K_pool.dim() != 3 or K_pool.shape[1] != page_rows or K_pool.shape[2] != D:
-        raise ValueError("pools must be [num_pages, page_rows, D]")
-    if block_table.dim() != 2 or block_table.shape[0] != B * H:
-        raise ValueError("block_table must be [B*H, max_pages]")
-    num_pages = K_pool.shape[0]
-    rc = lib().kvzap_compact_paged(_ptr(K), _ptr(V), _ptr(keep_idx), _ptr(lengths), _ptr(offsets),
-                                   _ptr(block_table), block_table.shape[1], int(page_rows),
-                                   _ptr(K_pool) if num_pages else None,
-                                   _ptr(V_pool) if num_pages else None, num_pages,
-                                   B, H, T, D, _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_compact_paged")
+    if stream is not None:
+        stream = _stream(stream) or 0
+    _done(_native().compact_paged(K, V, keep_idx, lengths, offsets, block_table, page_rows, K_pool, V_pool, stream),
+          "kvzap_compact_paged")
 
 
 def kvzap_attend_decode_paged(q: torch.Tensor, K_pool: torch.Tensor, V_pool: torch.Tensor,
@@ -434,40 +332,12 @@ def kvzap_attend_decode_paged(q: torch.Tensor, K_pool: torch.Tensor, V_pool: tor
                               workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """kvzap_attend_decode over pools bf16 [num_pages, page_rows, D] and a block table int32
     [B*H, max_pages]."""
-    bf = torch.bfloat16
-    _check(q, bf, "q"); _check(K_pool, bf, "K_pool"); _check(V_pool, bf, "V_pool")
-    _check(block_table, torch.int32, "block_table"); _check(lengths, torch.int32, "lengths")
-    B, HQ, D = q.shape
-    if lengths.dim() != 2 or lengths.shape[0] != B:
-        raise ValueError("lengths must be [B,H]")
-    H = lengths.shape[1]
-    if K_pool.dim() != 3 or K_pool.shape[1:] != (page_rows, D) or K_pool.shape != V_pool.shape:
-        raise ValueError("pools must both be [num_pages, page_rows, D]")
-    if block_table.dim() != 2 or block_table.shape[0] != B * H:
-        raise ValueError("block_table must be [B*H, max_pages]")
-    if window > 0:
-        _check(K_ring, bf, "K_ring"); _check(V_ring, bf, "V_ring")
-        _check(seq_pos, torch.int32, "seq_pos")
-        if tuple(K_ring.shape) != (B, H, window, D) or K_ring.shape != V_ring.shape:
-            raise ValueError("K_ring and V_ring must be [B,H,window,D]")
-    if out is None:
-        out = torch.empty((B, HQ, D), dtype=bf, device=q.device)
-    else:
-        _check(out, bf, "out")
-    ws, ws_bytes = _workspace(
-        kvzap_workspace_bytes(CALL_ATTEND_DECODE, B, int(max_rows), HQ, int(window), H),
-        q.device, workspace, stream)
-    ring = window > 0
-    num_pages = K_pool.shape[0]
-    rc = lib().kvzap_attend_decode_paged(
-        _ptr(q), _ptr(K_pool) if num_pages else None, _ptr(V_pool) if num_pages else None,
-        num_pages, _ptr(block_table), block_table.shape[1], int(page_rows), _ptr(lengths),
-        _ptr(K_ring) if ring else None, _ptr(V_ring) if ring else None,
-        _ptr(seq_pos) if ring else None, int(window), int(max_rows), float(scale), _ptr(out),
-        B, H, HQ, D, _ptr(ws), ws_bytes, _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_attend_decode_paged")
-    return out
+    if stream is not None:
+        workspace, stream = _on(stream, workspace, q.device, CALL_ATTEND_DECODE, q.shape[0], int(max_rows), q.shape[1],
+                                int(window), lengths.shape[1])
+    return _done(_native().attend_decode_paged(q, K_pool, V_pool, block_table, page_rows, lengths, K_ring, V_ring,
+                                               seq_pos, window, max_rows, scale, out, workspace, stream),
+                 "kvzap_attend_decode_paged")
 
 
 def kvzap_extend_pages(lengths: torch.Tensor, page_counts: torch.Tensor, page_rows: int,
@@ -524,28 +394,14 @@ def kvzap_decode_evict_paged(hidden_new: torch.Tensor, W1: torch.Tensor, b1, W2,
                              tau: float, workspace: Optional[torch.Tensor] = None,
                              stream=None) -> None:
     """One decode step of one layer on the paged cache; `state` is updated in place."""
-    bf = torch.bfloat16
-    _check(hidden_new, bf, "hidden_new"); _check(W1, bf, "W1"); _check(b1, bf, "b1", True)
-    _check(W2, bf, "W2", True); _check(b2, bf, "b2", True)
-    _check(k_new, bf, "k_new"); _check(v_new, bf, "v_new")
-    B, Dh = hidden_new.shape
-    M = W1.shape[0] if W2 is not None else 0
     st = state
-    if (B, st.H, st.D) != tuple(k_new.shape) or k_new.shape != v_new.shape or B != st.B:
-        raise ValueError("k_new / v_new must be [B,H,D] matching the state")
-    ws, ws_bytes = _workspace(
-        kvzap_workspace_bytes(CALL_DECODE_EVICT, B, 1, Dh, M, st.H), hidden_new.device, workspace, stream)
-    ring = st.window > 0
-    rc = lib().kvzap_decode_evict_paged(
-        _ptr(hidden_new), _ptr(W1), _ptr(b1), _ptr(W2), _ptr(b2), Dh, M,
-        _ptr(k_new), _ptr(v_new), _ptr(st.K_pool), _ptr(st.V_pool), _ptr(st.pos_pool),
-        st.num_pages, _ptr(st.block_table), st.max_pages, st.page_rows,
-        _ptr(st.K_ring) if ring else None, _ptr(st.V_ring) if ring else None,
-        _ptr(st.score_ring) if ring else None, _ptr(st.lengths), _ptr(st.seq_pos),
-        float(tau), int(st.window), B, st.H, st.D, _ptr(st.error_flag),
-        _ptr(ws), ws_bytes, _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_decode_evict_paged")
+    if stream is not None:
+        workspace, stream = _on(stream, workspace, hidden_new.device, CALL_DECODE_EVICT, hidden_new.shape[0], 1,
+                                hidden_new.shape[1], W1.shape[0] if W2 is not None else 0, st.H)
+    _done(_native().decode_evict_paged(hidden_new, W1, b1, W2, b2, k_new, v_new, st.B, st.H, st.D, st.window, st.K_pool,
+                                       st.V_pool, st.pos_pool, st.block_table, st.K_ring, st.V_ring, st.score_ring,
+                                       st.lengths, st.seq_pos, st.error_flag, st.num_pages, st.max_pages, st.page_rows,
+                                       tau, workspace, stream), "kvzap_decode_evict_paged")
 
 
 def kvzap_topk_threshold(scores: torch.Tensor, window: int, k: int, per_layer: bool,
@@ -554,21 +410,12 @@ def kvzap_topk_threshold(scores: torch.Tensor, window: int, k: int, per_layer: b
                          workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """scores fp32 [B,H,T] -> tau fp32 [B,H]: the k-th largest non-window score per head, or
     per sequence over its pooled heads."""
-    _check(scores, torch.float32, "scores"); _check(seq_lens, torch.int32, "seq_lens", True)
-    B, H, T = scores.shape
-    if tau_out is None:
-        tau_out = torch.empty((B, H), dtype=torch.float32, device=scores.device)
-    else:
-        _check(tau_out, torch.float32, "tau_out")
-    ws, ws_bytes = _workspace(
-        kvzap_workspace_bytes(CALL_TOPK_THRESHOLD, B, T, 0, 1 if per_layer else 0, H),
-        scores.device, workspace, stream)
-    rc = lib().kvzap_topk_threshold(_ptr(scores), int(window), _ptr(seq_lens), int(k),
-                                    1 if per_layer else 0, B, H, T, _ptr(tau_out), _ptr(ws),
-                                    ws_bytes, _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_topk_threshold")
-    return tau_out
+    if stream is not None:
+        B, H, T = scores.shape
+        workspace, stream = _on(stream, workspace, scores.device, CALL_TOPK_THRESHOLD, B, T, 0,
+                                1 if per_layer else 0, H)
+    return _done(_native().topk_threshold(scores, window, k, per_layer, seq_lens, tau_out, workspace, stream),
+                 "kvzap_topk_threshold")
 
 
 def kvzap_mask_per_head(scores: torch.Tensor, tau: torch.Tensor, window: int,
@@ -578,25 +425,11 @@ def kvzap_mask_per_head(scores: torch.Tensor, tau: torch.Tensor, window: int,
                         offsets: Optional[torch.Tensor] = None,
                         workspace: Optional[torch.Tensor] = None, stream=None):
     """kvzap_mask with tau fp32 [B,H] on the device.  Returns (keep_idx, lengths, offsets)."""
-    _check(scores, torch.float32, "scores"); _check(tau, torch.float32, "tau")
-    _check(seq_lens, torch.int32, "seq_lens", True)
-    B, H, T = scores.shape
-    if tau.numel() != B * H:
-        raise ValueError("tau must have B*H entries")
-    dev = scores.device
-    if keep_idx is None:
-        keep_idx = torch.empty(B * H * T, dtype=torch.int32, device=dev)
-    if lengths is None:
-        lengths = torch.empty((B, H), dtype=torch.int32, device=dev)
-    if offsets is None:
-        offsets = torch.empty(B * H + 1, dtype=torch.int64, device=dev)
-    ws, ws_bytes = _workspace(kvzap_workspace_bytes(CALL_MASK, B, T, 0, 0, H), dev, workspace, stream)
-    rc = lib().kvzap_mask_per_head(_ptr(scores), _ptr(tau), int(window), _ptr(seq_lens), B, H, T,
-                                   _ptr(keep_idx), _ptr(lengths), _ptr(offsets), _ptr(ws),
-                                   ws_bytes, _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_mask_per_head")
-    return keep_idx, lengths, offsets
+    if stream is not None:
+        B, H, T = scores.shape
+        workspace, stream = _on(stream, workspace, scores.device, CALL_MASK, B, T, 0, 0, H)
+    return _done(_native().mask_per_head(scores, tau, window, seq_lens, keep_idx, lengths, offsets, workspace, stream),
+                 "kvzap_mask_per_head")
 
 
 def kvzap_teacher_scores(q: torch.Tensor, k: torch.Tensor, T: int, scale: float,
@@ -641,41 +474,11 @@ def kvzap_mask_compact(scores: torch.Tensor, tau: float, window: int, K: torch.T
                        workspace: Optional[torch.Tensor] = None, stream=None):
     """kvzap_mask + kvzap_compact in one library call.  Returns (keep_idx, lengths, offsets,
     K_out, V_out) as the two separate calls would."""
-    bf = torch.bfloat16
-    _check(scores, torch.float32, "scores"); _check(K, bf, "K"); _check(V, bf, "V")
-    _check(seq_lens, torch.int32, "seq_lens", True)
-    B, H, T = scores.shape
-    if tuple(K.shape[:3]) != (B, H, T) or K.shape != V.shape:
-        raise ValueError("K and V must be [B,H,T,D]")
-    D = K.shape[3]
-    dev = scores.device
-    if keep_idx is None:
-        keep_idx = torch.empty(B * H * T, dtype=torch.int32, device=dev)
-    if lengths is None:
-        lengths = torch.empty((B, H), dtype=torch.int32, device=dev)
-    if offsets is None:
-        offsets = torch.empty(B * H + 1, dtype=torch.int64, device=dev)
-    if cap_rows is None:
-        cap_rows = B * H * T if K_out is None else K_out.shape[0]
-    if K_out is None:
-        K_out = torch.empty((cap_rows, D), dtype=bf, device=dev)
-    if V_out is None:
-        V_out = torch.empty((cap_rows, D), dtype=bf, device=dev)
-    _check(keep_idx, torch.int32, "keep_idx"); _check(lengths, torch.int32, "lengths")
-    _check(offsets, torch.int64, "offsets"); _check(K_out, bf, "K_out"); _check(V_out, bf, "V_out")
-    if keep_idx.numel() < B * H * T or lengths.numel() != B * H or offsets.numel() != B * H + 1:
-        raise ValueError("output buffers have the wrong size")
-    if K_out.shape[0] < cap_rows or V_out.shape[0] < cap_rows or K_out.shape[1] != D or V_out.shape[1] != D:
-        raise ValueError("K_out and V_out must be [>= cap_rows, D]")
-    ws, ws_bytes = _workspace(max(kvzap_workspace_bytes(CALL_MASK_COMPACT, B, T, 0, 0, H), 256), dev,
-                              workspace, stream)
-    rc = lib().kvzap_mask_compact(_ptr(scores), float(tau), int(window), _ptr(seq_lens), _ptr(K),
-                                  _ptr(V), _ptr(keep_idx), _ptr(lengths), _ptr(offsets), _ptr(K_out),
-                                  _ptr(V_out), int(cap_rows), B, H, T, D, _ptr(ws), ws_bytes,
-                                  _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_mask_compact")
-    return keep_idx, lengths, offsets, K_out, V_out
+    if stream is not None:
+        B, H, T = scores.shape
+        workspace, stream = _on(stream, workspace, scores.device, CALL_MASK_COMPACT, B, T, 0, 0, H, least=256)
+    return _done(_native().mask_compact(scores, tau, window, K, V, seq_lens, keep_idx, lengths, offsets, K_out, V_out,
+                                        cap_rows, workspace, stream), "kvzap_mask_compact")
 
 
 def kvzap_compress(hidden: torch.Tensor, W1: torch.Tensor, b1, W2, b2, K: torch.Tensor,
@@ -746,53 +549,20 @@ def kvzap_score_rmsnorm(x: torch.Tensor, W1_prepared: torch.Tensor, gain: torch.
                         stream=None):
     """The MLP surrogate on the un-normalised residual stream x bf16 [B,T,Dh].  Returns
     (scores fp32 [B,H,T], rstd fp32 [B,T], normed bf16 [B,T,Dh] or None)."""
-    bf = torch.bfloat16
-    _check(x, bf, "x"); _check(gain, bf, "gain"); _check(b1, bf, "b1", True); _check(W2, bf, "W2")
-    _check(b2, bf, "b2", True)
-    B, T, Dh = x.shape
-    H, M = W2.shape
-    if W1_prepared.dtype != torch.uint8 or W1_prepared.numel() < M * Dh * 2:
-        raise ValueError("W1_prepared must come from kvzap_prepare_scorer_rmsnorm")
-    if gain.shape != (Dh,):
-        raise ValueError("gain must be [Dh]")
-    if scores is None:
-        scores = torch.empty((B, H, T), dtype=torch.float32, device=x.device)
-    if rstd is None:
-        rstd = torch.empty((B, T), dtype=torch.float32, device=x.device)
-    if normed is None and want_normed:
-        normed = torch.empty_like(x)
-    _check(scores, torch.float32, "scores"); _check(rstd, torch.float32, "rstd")
-    _check(normed, bf, "normed", True)
-    if scores.shape != (B, H, T) or rstd.shape != (B, T) or (normed is not None and normed.shape != x.shape):
-        raise ValueError("scores must be [B,H,T], rstd [B,T], normed like x")
-    ws, ws_bytes = _workspace(kvzap_workspace_bytes(CALL_SCORE_PREPARED, B, T, Dh, M, H), x.device, None, stream)
-    rc = lib().kvzap_score_rmsnorm_ws(_ptr(x), _ptr(W1_prepared), _ptr(gain), float(eps), _ptr(b1),
-                                      _ptr(W2), _ptr(b2), _ptr(scores), _ptr(rstd), _ptr(normed),
-                                      B, T, Dh, M, H, _ptr(ws), ws_bytes, _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_score_rmsnorm_ws")
-    return scores, rstd, normed
+    workspace = None
+    if stream is not None:
+        (B, T, Dh), (H, M) = x.shape, W2.shape
+        workspace, stream = _on(stream, None, x.device, CALL_SCORE_PREPARED, B, T, Dh, M, H)
+    return _done(_native().score_rmsnorm(x, W1_prepared, gain, eps, b1, W2, b2, want_normed, scores, rstd, normed,
+                                         workspace, stream), "kvzap_score_rmsnorm_ws")
 
 
 def kvzap_score_prepared(hidden: torch.Tensor, W1_prepared: torch.Tensor, b1, W2: torch.Tensor, b2,
                          scores: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """kvzap_score with W1 replaced by kvzap_prepare_scorer's output (same scores, bit for bit)."""
-    bf = torch.bfloat16
-    _check(hidden, bf, "hidden"); _check(W1_prepared, torch.uint8, "W1_prepared")
-    _check(b1, bf, "b1", True); _check(W2, bf, "W2"); _check(b2, bf, "b2", True)
-    B, T, Dh = hidden.shape
-    H, M = W2.shape
-    if W1_prepared.numel() < M * Dh * 2:
-        raise ValueError("W1_prepared is smaller than M*Dh bf16 values")
-    if scores is None:
-        scores = torch.empty((B, H, T), dtype=torch.float32, device=hidden.device)
-    _check(scores, torch.float32, "scores")
-    if scores.shape != (B, H, T):
-        raise ValueError("scores must be [B,H,T]")
-    ws, ws_bytes = _workspace(kvzap_workspace_bytes(CALL_SCORE_PREPARED, B, T, Dh, M, H), hidden.device,
-                              None, stream)
-    rc = lib().kvzap_score_prepared_ws(_ptr(hidden), _ptr(W1_prepared), _ptr(b1), _ptr(W2), _ptr(b2),
-                                       _ptr(scores), B, T, Dh, M, H, _ptr(ws), ws_bytes, _stream(stream))
-    if rc != 0:
-        raise KvzapError(rc, "kvzap_score_prepared_ws")
-    return scores
+    workspace = None
+    if stream is not None:
+        (B, T, Dh), (H, M) = hidden.shape, W2.shape
+        workspace, stream = _on(stream, None, hidden.device, CALL_SCORE_PREPARED, B, T, Dh, M, H)
+    return _done(_native().score_prepared(hidden, W1_prepared, b1, W2, b2, scores, workspace, stream),
+                 "kvzap_score_prepared_ws")

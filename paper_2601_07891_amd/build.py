@@ -17,6 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libkvzap.so")
+HOST_PATH = os.path.join(HERE, "_kvzap_host.so")      # Python module: the wrappers' native part
 CEILINGS_PATH = os.path.join(HERE, "kvzap_ceilings")
 SOURCES = ["api.hip", "mask.hip", "compact.hip", "score_linear.hip", "score_mlp.hip", "score_tile.hip",
            "decode.hip", "attend.hip", "paged.hip", "topk.hip", "teacher.hip"]
@@ -78,9 +79,29 @@ def build(verbose: bool = True) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    _build_host()
     if verbose:
         print(f"built {LIB_PATH}")
     return LIB_PATH
+
+
+def _build_host() -> None:
+    """The host-only module, against the installed torch and the library built above."""
+    import sysconfig
+
+    import torch
+    torch_dir = os.path.dirname(torch.__file__)
+    includes = [os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
+                os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"]]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1",
+           "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), *[x for d in includes for x in ("-isystem", d)],
+           os.path.join(CSRC, "host.cpp"), "-o", HOST_PATH, "-L", HERE, "-l:" + os.path.basename(LIB_PATH),
+           "-L", os.path.join(torch_dir, "lib"),
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"host module failed:\n{r.stdout}\n{r.stderr}")
 
 
 def build_ceilings(verbose: bool = True) -> str:

@@ -1,0 +1,114 @@
+"""The native part of the Python wrappers: what it refuses, and that a call on a stream that the
+caller names computes what the call on the current stream does."""
+import pytest
+import torch
+
+from paper_2601_07891_amd import binding as kv, synth
+
+BF = torch.bfloat16
+
+
+def _calls(dev, stream=None):
+    """name -> a call of every wrapper that goes through the native code, on small inputs"""
+    B, H, T, D, Dh, M, w = 2, 4, 300, 128, 512, 128, 16
+    g = torch.Generator().manual_seed(1)
+    r = lambda *s: torch.randn(s, generator=g).to(BF).to(dev)
+    hid, W1, b1, W2, b2, Wl = r(B, T, Dh), r(M, Dh), r(M), r(H, M), r(H), r(H, Dh)
+    gain, K, V, q = r(Dh), r(B, H, T, D), r(B, H, T, D), r(B, 2 * H, D)
+    scores = torch.randn((B, H, T), generator=g).to(dev)
+    sl = torch.tensor([T, 70], dtype=torch.int32, device=dev)
+    tau = torch.zeros((B, H), device=dev)
+    gpu = dev != "cpu"
+    prep = kv.kvzap_prepare_scorer(W1) if gpu else torch.zeros(M * Dh * 2, dtype=torch.uint8)
+    prep_n = kv.kvzap_prepare_scorer_rmsnorm(W1, gain) if gpu else prep
+    i32 = dict(dtype=torch.int32, device=dev)
+    idx = torch.arange(T, **i32).repeat(B * H)
+    n = torch.full((B, H), T, **i32)
+    off = torch.arange(B * H + 1, dtype=torch.int64, device=dev) * T
+    free, table = torch.arange(400, **i32), torch.arange(B * H * 20, **i32).view(B * H, 20)
+    pools = torch.zeros((2, 160, 16, D), dtype=BF, device=dev)
+    rows = K.reshape(-1, D)
+
+    def evict():
+        st = kv.DecodeState(B, H, D, w, [40] * (B * H), dev)
+        kv.kvzap_decode_evict(hid[:, 0].contiguous(), W1, b1, W2, b2, K[:, :, 0].contiguous(), V[:, :, 0].contiguous(),
+                              st, 0.0, stream=stream)
+        return st.K_ring, st.score_ring, st.seq_pos
+
+    def evict_paged():
+        st = kv.PagedDecodeState(B, H, D, w, 16, 40, 4, dev)
+        kv.kvzap_decode_evict_paged(hid[:, 0].contiguous(), Wl, None, None, None, K[:, :, 0].contiguous(),
+                                    V[:, :, 0].contiguous(), st, 0.0, stream=stream)
+        return st.K_ring, st.score_ring, st.seq_pos
+
+    def paged_gather():
+        kv.kvzap_compact_paged(K, V, idx, n, off[:-1].contiguous(), table, 16, pools[0], pools[1], stream=stream)
+        return pools
+
+    return {
+        "score": lambda: kv.kvzap_score(hid, W1, b1, W2, b2, stream=stream),
+        "score_linear": lambda: kv.kvzap_score(hid, Wl, None, None, None, stream=stream),
+        "score_prepared": lambda: kv.kvzap_score_prepared(hid, prep, b1, W2, b2, stream=stream),
+        "score_rmsnorm": lambda: kv.kvzap_score_rmsnorm(hid, prep_n, gain, 1e-6, b1, W2, b2, want_normed=True, stream=stream),
+        "mask": lambda: kv.kvzap_mask(scores, 0.0, w, sl, keep_idx=torch.zeros(B * H * T, **i32), stream=stream),
+        "mask_per_head": lambda: kv.kvzap_mask_per_head(scores, tau, w, sl, keep_idx=torch.zeros(B * H * T, **i32), stream=stream),
+        "mask_compact": lambda: kv.kvzap_mask_compact(scores, 0.0, 0, K, V, keep_idx=torch.zeros(B * H * T, **i32), cap_rows=9,
+                                                      K_out=torch.zeros((9, D), dtype=BF, device=dev), stream=stream),
+        "compact": lambda: kv.kvzap_compact(K, V, idx, n, off, stream=stream),
+        "compact_paged": paged_gather,
+        "topk_threshold": lambda: kv.kvzap_topk_threshold(scores, w, 40, True, sl, stream=stream),
+        "assign_pages": lambda: kv.kvzap_assign_pages(n, 16, free, 30, 3, result=torch.zeros(2, **i32), stream=stream),
+        "decode_evict": evict,
+        "decode_evict_paged": evict_paged,
+        "attend_decode": lambda: kv.kvzap_attend_decode(q, rows, rows, off[:-1].contiguous(), n, None, None, None, 0, T, 0.1,
+                                                        stream=stream),
+        "attend_decode_paged": lambda: kv.kvzap_attend_decode_paged(q, pools[0], pools[1], table, 16, n, K[:, :, :w].contiguous(),
+                                                                    V[:, :, :w].contiguous(), sl, w, T, 0.1, stream=stream),
+    }
+
+
+@pytest.mark.parametrize("name", sorted(_calls("cpu")))
+def test_host_tensors_are_refused(name):
+    with pytest.raises(ValueError, match="must be a device tensor"):
+        _calls("cpu")[name]()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["stream", "handle", "null"])
+def test_a_named_stream(kind):
+    side = torch.cuda.Stream()
+    want = {k: f() for k, f in _calls("cuda:0").items()}
+    torch.cuda.synchronize()
+    calls = _calls("cuda:0", {"stream": side, "handle": side.cuda_stream, "null": 0}[kind])
+    torch.cuda.synchronize()
+    for name, f in calls.items():
+        got = f()
+        torch.cuda.synchronize()
+        many = lambda x: x if isinstance(x, tuple) else (x,)
+        for a, b in zip(many(got), many(want[name])):
+            if name == "mask_compact" and a.dtype == BF:       # (V_out is not filled beyond what is kept)
+                a, b = a[:9], b[:9]
+            assert torch.equal(a, b), name
+
+
+@pytest.mark.gpu
+def test_what_is_refused():
+    dev = "cuda:0"
+    s = torch.zeros((1, 2, 64), device=dev)
+    K = torch.zeros((1, 2, 64, 128), dtype=BF, device=dev)
+    for call, text in [
+        (lambda: kv.kvzap_mask(None, 0.0, 4), "scores is required"),
+        (lambda: kv.kvzap_mask(s.double(), 0.0, 4), "scores must be torch.float32, got torch.float64"),
+        (lambda: kv.kvzap_mask(s.transpose(1, 2), 0.0, 4), "scores must be contiguous"),
+        (lambda: kv.kvzap_mask(s[0], 0.0, 4), "3 dimensions"),
+        (lambda: kv.kvzap_mask(s, 0.0, 4, lengths=torch.zeros(3, dtype=torch.int32, device=dev)), "wrong size"),
+        (lambda: kv.kvzap_mask_per_head(s, s[0, 0], 4), "B\\*H entries"),
+        (lambda: kv.kvzap_mask_compact(s, 0.0, 4, K, K[:, :, :63].contiguous()), "must be \\[B,H,T,D\\]"),
+        (lambda: kv.kvzap_mask_compact(s, 0.0, 4, K, K, cap_rows=9, K_out=K[0, 0, :8].contiguous()), "cap_rows"),
+    ]:
+        with pytest.raises(ValueError, match=text):
+            call()
+    with pytest.raises(kv.KvzapError):
+        kv.kvzap_mask(s, float("nan"), 4)
+    with pytest.raises(TypeError):
+        kv.kvzap_mask([1.0], 0.0, 4)
