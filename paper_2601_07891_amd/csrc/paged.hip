@@ -140,7 +140,11 @@ constexpr int kThreads = 256;
 
 // Same work split as the contiguous gather: grid (tiles, B*H, {K,V}), a thread moves one
 // 16-byte piece of one kept row per pass; only the destination differs.  Rows whose page
-// slot lies beyond the table or whose table entry is not a page of the pool are skipped.
+// slot lies beyond the table or whose table entry is not a page of the pool are skipped.  The row
+// is loaded before it is known whether it goes anywhere (from row 0 where the index is no row):
+// with the load behind the test of the page, it waited for the block table as well as for the
+// index.  3 padded sequences of 20011 tokens, 113 MB: 23.6 -> 20.4 us; 131072 tokens, 135 MB: 28.2
+// -> 25.6 us (5.3 TB/s).
 template <int LPR>
 __global__ __launch_bounds__(kThreads) void compact_paged_kernel(
     const u32x4* __restrict__ K, const u32x4* __restrict__ V,
@@ -157,17 +161,15 @@ __global__ __launch_bounds__(kThreads) void compact_paged_kernel(
   const u32x4* src = (blockIdx.z ? V : K) + (size_t)bh * T * LPR;
   u32x4* dst = blockIdx.z ? V_pool : K_pool;
   const int32_t* pages = block_table + (size_t)bh * max_pages;
-  for (int j0 = blockIdx.x * kRowsPerPass; j0 < n; j0 += gridDim.x * kRowsPerPass) {
-    const int j = j0 + sub;
-    if (j < n && (j >> log_page) < max_pages) {
-      const int t = keep_idx[in0 + j];
-      const int page = pages[j >> log_page];
-      if (t >= 0 && t < T && page >= 0 && page < num_pages) {
-        const u32x4 row = __builtin_nontemporal_load(src + (size_t)t * LPR + piece);
-        const size_t out_row = ((size_t)page << log_page) + (size_t)(j & ((1 << log_page) - 1));
-        __builtin_nontemporal_store(row, dst + out_row * LPR + piece);
-      }
-    }
+  const int lim = ((int64_t)max_pages << log_page) < n ? max_pages << log_page : n;
+  for (int j0 = blockIdx.x * kRowsPerPass; j0 < lim; j0 += gridDim.x * kRowsPerPass) {
+    const int j = j0 + sub, jc = j < lim ? j : lim - 1;
+    const int t = keep_idx[in0 + jc];
+    const int page = pages[jc >> log_page];
+    const bool from = t >= 0 && t < T, to = page >= 0 && page < num_pages;
+    const u32x4 row = __builtin_nontemporal_load(src + (size_t)(from ? t : 0) * LPR + piece);
+    const size_t out_row = ((size_t)page << log_page) + (size_t)(j & ((1 << log_page) - 1));
+    if (j < lim && from && to) __builtin_nontemporal_store(row, dst + out_row * LPR + piece);
   }
 }
 
