@@ -121,7 +121,8 @@ __global__ __launch_bounds__(kThreads) void score_linear_kernel(
   }
 }
 
-// Short inputs (up to 512 groups of 16 tokens; 1024 tokens: 10 us against 18 us): with one group per wavefront the walk over
+// Short inputs (up to 512 groups of 16 tokens) that the kernel below does not take, with more than eight heads or a
+// larger D_h (1024 tokens: 10 us against 18 us): with one group per wavefront the walk over
 // D_h above is what a call costs (13 us at D_h = 4096: 128 operand loads through one CU's
 // texture path per wavefront, however many are in flight).  Here the four wavefronts of a
 // block share ONE group and take a quarter of D_h each, W comes straight from global memory
@@ -177,6 +178,87 @@ __global__ __launch_bounds__(256) void score_linear_short_kernel(
   }
 }
 
+// The shortest inputs, for up to eight heads.  Loads in the operand layout fetch 64 bytes from each
+// of 16 rows, which lie D_h * 2 bytes (8 KB) apart: they run at some 24 bytes per clock and CU, and
+// those 5 of 10 us are what a call on 16 to 1024 tokens costs, however they are split.  Here every
+// load takes 1 KB of ONE row, straight to LDS, and the operands are read from there.
+// A block is 8 tokens x all of D_h, a wavefront 512 inputs of it: 8 KB of tokens and 8 KB of W.
+// The 16 columns of an MFMA are the 8 tokens twice, with the first and the second 256 inputs, and
+// its 16 rows the 8 heads likewise: half the steps, no padded heads, and the two diagonal 8 x 8
+// blocks of C are the result.
+// Measured, us per call (here / the kernels above): D_h = 4096: 128 tokens 5.2 / 9.7, 1024: 5.0 / 10.0,
+// 2048: 5.8 / 10.2, 4096: 9.1 / 10.7, 8192: 16.6 / 18.0, 16384: 34.5 / 29.2; D_h = 5120: 1024: 5.7 /
+// 14.1, 8192: 22.1 / 28.0, 16384: 40.8 / 32.4; D_h = 2048: 1024: 3.9 / 6.0, 8192: 8.6 / 9.9.
+constexpr long long kRowMaxTokens = 8192;    // beyond, W per 8 tokens is too much to stage
+constexpr int kRowTokens = 8, kRowInputs = 512, kRowMaxWaves = 10;
+constexpr int kRowWaveBytes = 2 * kRowTokens * kRowInputs * 2;
+
+// LDS slot <-> 16-byte piece of a 1 KB row (its own inverse): the 16 lanes that are served
+// together read one piece, and the one 32 on, of 8 rows, and meet 16 different bank groups
+__device__ __forceinline__ int row_slot(int piece, int row) { return piece ^ (2 * row) ^ (piece >> 5); }
+
+__global__ __launch_bounds__(kRowMaxWaves * 64) void score_linear_rows_kernel(
+    const unsigned char* hidden, const unsigned char* W, const unsigned short* __restrict__ bias,
+    float* __restrict__ scores, long long rows, int T, int Dh, int H) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 15, kg = lane >> 4, waves = blockDim.x / 64;
+  const long long r0 = (long long)blockIdx.x * kRowTokens;
+  const int pieces = Dh / 8 - wid * 64 < 64 ? Dh / 8 - wid * 64 : 64;      // of this wavefront, >= 8
+  unsigned char* const mine = smem + wid * kRowWaveBytes;
+#pragma unroll
+  for (int i = 0; i < 2 * kRowTokens; ++i) {
+    const int row = i & 7;
+    int piece = row_slot(lane, row);
+    if (piece > pieces - 1) piece = pieces - 1;                            // past D_h: its products are dropped
+    const long long r = r0 + row < rows ? r0 + row : rows - 1;             // past the end: results dropped
+    const unsigned char* base = i < kRowTokens ? hidden + (size_t)r * Dh * 2 : W + (size_t)(row < H ? row : H - 1) * Dh * 2;
+    load_to_lds_b128(base + wid * (kRowInputs * 2), (unsigned)piece * 16u, lds_address(mine) + i * 1024);
+  }
+  wait_vmcnt<0>();
+  const u32x4 zero4 = {0u, 0u, 0u, 0u};
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < kRowInputs / 64; ++s) {
+    const int piece = (col >> 3) * 32 + s * 4 + kg, row = col & 7;
+    const unsigned char* at = mine + row * 1024 + row_slot(piece, row) * 16;
+    const u32x4 b = *reinterpret_cast<const u32x4*>(at), w = *reinterpret_cast<const u32x4*>(at + 8 * 1024);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, piece < pieces ? w : zero4),
+                                                  __builtin_bit_cast(bf16x8, piece < pieces ? b : zero4), acc, 0, 0, 0);
+  }
+  // lane (col, kg), register e: row 4*kg + e of C.  The wavefronts' sums meet in LDS.
+  *reinterpret_cast<floatx4*>(mine + lane * 16) = acc;
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const int tok = lane & 7, h = lane >> 3;
+    const int first = ((h >> 2) * 16 + tok) * 16 + (h & 3) * 4, second = first + (2 * 16 + 8) * 16;
+    float s = 0.0f;
+    for (int w = 0; w < waves; ++w) {
+      const unsigned char* from = smem + w * kRowWaveBytes;
+      s += *reinterpret_cast<const float*>(from + first) + *reinterpret_cast<const float*>(from + second);
+    }
+    const long long r = r0 + tok;
+    if (h < H && r < rows) {
+      const long long bidx = r / T;
+      scores[((size_t)bidx * H + h) * T + (r - bidx * T)] = s + (bias ? bf16_bits_to_float(bias[h]) : 0.0f);
+    }
+  }
+}
+
+int launch_linear_rows(const void* hidden, const void* W, const void* b, float* scores, long long rows,
+                       int T, int Dh, int H, hipStream_t stream) {
+  static const hipError_t attr_rc =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(score_linear_rows_kernel),
+      hipFuncAttributeMaxDynamicSharedMemorySize, kRowMaxWaves * kRowWaveBytes);
+  if (attr_rc != hipSuccess) return KVZAP_ERR_RUNTIME;
+  const int waves = (Dh + kRowInputs - 1) / kRowInputs;
+  score_linear_rows_kernel<<<dim3((unsigned)((rows + kRowTokens - 1) / kRowTokens)), waves * 64,
+                             waves * kRowWaveBytes, stream>>>(
+      static_cast<const unsigned char*>(hidden), static_cast<const unsigned char*>(W),
+      static_cast<const unsigned short*>(b), scores, rows, T, Dh, H);
+  return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
+}
+
 template <int kThreads, int kUnroll>
 int launch_linear(const void* hidden, const void* W, const void* b, float* scores, long long rows,
                   int T, int Dh, int H, long long want_blocks, hipStream_t stream) {
@@ -203,6 +285,8 @@ int launch_score_linear(const void* hidden, const void* W, const void* b, float*
                         int B, int T, int Dh, int H, hipStream_t stream) {
   const long long rows = (long long)B * T;
   const long long ngroups = (rows + 15) / 16;
+  if (H <= kRowTokens && Dh <= kRowMaxWaves * kRowInputs && rows <= kRowMaxTokens)
+    return launch_linear_rows(hidden, W, b, scores, rows, T, Dh, H, stream);
   // from 64k tokens: 16-wavefront blocks (W is staged into LDS once per block, and 16 x 8
   // loads in flight per block are what the HBM stream needs: 128k tokens 194 us against
   // 205 us with small blocks); shorter inputs: 4-wavefront blocks so that more CUs take part

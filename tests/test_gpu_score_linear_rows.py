@@ -1,0 +1,29 @@
+"""The linear surrogate on short inputs, loaded row by row: at the edges of its 8-token blocks, with
+widths that end inside a wavefront's 512 inputs, fewer heads than eight, and batches whose sequences
+end inside a block.  fp32 sums of bf16 products over D_h: within 2 * sqrt(D_h) * 2^-24 of the sum of
+the products' magnitudes (a random walk of roundings, with a factor for its tail)."""
+import pytest
+import torch
+
+from paper_2601_07891_amd import binding
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("B,T,Dh,H", [
+    (1, 1, 64, 1), (1, 7, 512, 8), (1, 8, 576, 8), (1, 9, 1088, 3), (3, 5, 4096, 8), (1, 1024, 4096, 8),
+    (2, 1023, 2048, 4), (1, 130, 5120, 8), (1, 130, 5184, 8), (1, 130, 4096, 9), (5, 77, 4992, 7),
+    (1, 8192, 256, 8), (1, 8193, 256, 8),
+])
+@pytest.mark.parametrize("bias", [False, True])
+def test_against_float64(B, T, Dh, H, bias):
+    g = torch.Generator().manual_seed(B * T + Dh)
+    x = torch.randn((B, T, Dh), generator=g).bfloat16()
+    W = (torch.randn((H, Dh), generator=g) * Dh ** -0.5).bfloat16()
+    b = torch.randn(H, generator=g).bfloat16() if bias else None
+    got = binding.kvzap_score(x.to(DEV), W.to(DEV), None if b is None else b.to(DEV), None, None).double().cpu()
+    x64, W64 = x.double(), W.double()
+    want = x64 @ W64.t() + (0 if b is None else b.double())
+    size = x64.abs() @ W64.abs().t() + 1.0
+    assert ((got.transpose(1, 2) - want).abs() <= 2 * Dh ** 0.5 * 2.0 ** -24 * size).all()
