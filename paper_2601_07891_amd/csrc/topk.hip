@@ -323,25 +323,28 @@ __global__ __launch_bounds__(kThreads) void topk_final_kernel(
 // once) and does all three passes (digits of 11, 11 and 10 bits) on LDS histograms.  Scores
 // crowd into few exponents, so the wavefronts' atomics would collide on a few words: each bin
 // has four counters side by side, chosen by the lane, which spread over four banks.
-// Measured, us per call (one launch / the four above), 8 heads: 1024 scores 7.1 / 19.8,
-// 16384: 9.1 / 21.8, 32768: 13.1 / 22.0, 65536: 21.2 / 22.8; 24 heads of 20011: 13.1 / 23.4;
-// 64 heads of 65536: 21.4 / 45.7; a layer of 8 pooled heads of 8192: 20.6 / 21.0.
+// Measured, us per call (one launch / the four above), 8 heads: 1024 scores 6.2 / 21.9,
+// 16384: 9.1 / 22.6, 32768: 12.8 / 22.7, 65536: 20.2 / 23.5; 24 heads of 20011: 10.0 / 24.1 (13.1 with
+// 32 keys a thread and a NaN test per key and pass); 64 heads of 65536: 20.9 / 45.9; a layer of 8
+// pooled heads of 8192: 19.3 / 22.3.  It is the one CU's vector work, so kPer follows the size.
 // Past 65536 the keys no longer fit the registers and the many blocks of the chain win.
 constexpr int kOneThreads = 1024;
 constexpr int kOneWaves = kOneThreads / 64;
 constexpr int kOneBins = 2048;
 constexpr int kCopies = 4;
 constexpr long long kOneMax = 64 * kOneThreads;            // scores of a group
-constexpr unsigned kNoKey = 0xffffffffu;                  // the key of a NaN: no score has it
+constexpr unsigned kNoKey = 0xffffffffu;                  // of a NaN: no score's first digit is 2047
 
 // Bin of the rank-th entry (1-based, in bin order) of s_hist, the rank inside it and the
 // total: every thread gets the same answer.  Outside [1, total] the bin is meaningless.
+template <bool kFirst>       // the first digit: its last bin holds the NaNs and does not count
 __device__ __forceinline__ void pick_one(const unsigned* s_hist, long long& rank, unsigned& bin,
                                          unsigned& total, unsigned* s_wave, unsigned* s_pick) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   __syncthreads();                                         // the histogram is complete
   const u32x4 c0 = reinterpret_cast<const u32x4*>(s_hist)[2 * tid], c1 = reinterpret_cast<const u32x4*>(s_hist)[2 * tid + 1];
-  const unsigned v0 = c0.x + c0.y + c0.z + c0.w, v1 = c1.x + c1.y + c1.z + c1.w, mine = v0 + v1;
+  const unsigned v0 = c0.x + c0.y + c0.z + c0.w;
+  const unsigned v1 = kFirst && tid == kOneThreads - 1 ? 0u : c1.x + c1.y + c1.z + c1.w, mine = v0 + v1;
   unsigned inc = mine;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -385,8 +388,9 @@ __global__ __launch_bounds__(kOneThreads) void topk_one_kernel(
   // element i of this thread is entry tid + i*kOneThreads of the pooled rows; past the end it
   // re-reads entry 0 of the group, which exists, and drops it
   unsigned key[kPer];
+  const int n = n_pop * rows;
   {
-    const int n = n_pop * rows, div = n_pop > 0 ? n_pop : 1;
+    const int div = n_pop > 0 ? n_pop : 1;
     const int dr = kOneThreads / div, dt = kOneThreads - dr * div;
     int r = tid / div, t = tid - r * div;
     float s[kPer];
@@ -413,8 +417,8 @@ __global__ __launch_bounds__(kOneThreads) void topk_one_kernel(
   clear();
 #pragma unroll
   for (int i = 0; i < kPer; ++i)
-    if (key[i] != kNoKey) atomicAdd(&s_hist[(key[i] >> 21) * kCopies + copy], 1u);
-  pick_one(s_hist, rank, bin, population, s_wave, s_pick);
+    if (tid + i * kOneThreads < n) atomicAdd(&s_hist[(key[i] >> 21) * kCopies + copy], 1u);
+  pick_one<true>(s_hist, rank, bin, population, s_wave, s_pick);
   float tau;
   if (k <= 0) {
     tau = INFINITY;
@@ -425,14 +429,14 @@ __global__ __launch_bounds__(kOneThreads) void topk_one_kernel(
     clear();                                                // (its reader is past pick_one's last barrier)
 #pragma unroll
     for (int i = 0; i < kPer; ++i)
-      if (key[i] != kNoKey && (key[i] >> 21) == prefix) atomicAdd(&s_hist[(key[i] >> 10 & 2047u) * kCopies + copy], 1u);
-    pick_one(s_hist, rank, bin, total, s_wave, s_pick);
+      if ((key[i] >> 21) == prefix) atomicAdd(&s_hist[(key[i] >> 10 & 2047u) * kCopies + copy], 1u);
+    pick_one<false>(s_hist, rank, bin, total, s_wave, s_pick);
     prefix = prefix << 11 | bin;
     clear();
 #pragma unroll
     for (int i = 0; i < kPer; ++i)
-      if (key[i] != kNoKey && (key[i] >> 10) == prefix) atomicAdd(&s_hist[(key[i] & 1023u) * kCopies + copy], 1u);
-    pick_one(s_hist, rank, bin, total, s_wave, s_pick);
+      if ((key[i] >> 10) == prefix) atomicAdd(&s_hist[(key[i] & 1023u) * kCopies + copy], 1u);
+    pick_one<false>(s_hist, rank, bin, total, s_wave, s_pick);
     tau = key_to_float(prefix << 10 | bin);
   }
   for (int h = tid; h < rows; h += kOneThreads) tau_out[(size_t)g * rows + h] = tau;
@@ -460,10 +464,11 @@ int launch_topk_threshold(const float* scores, int window, const int32_t* seq_le
                           hipStream_t stream) {
   const long long pool = (long long)T * (per_layer ? H : 1);
   if (pool <= kOneMax) {
-    if (pool <= 8 * kOneThreads) return launch_one<8>(scores, window, seq_lens, k, per_layer, B, H, T, tau_out, stream);
-    if (pool <= 16 * kOneThreads) return launch_one<16>(scores, window, seq_lens, k, per_layer, B, H, T, tau_out, stream);
-    if (pool <= 32 * kOneThreads) return launch_one<32>(scores, window, seq_lens, k, per_layer, B, H, T, tau_out, stream);
-    return launch_one<64>(scores, window, seq_lens, k, per_layer, B, H, T, tau_out, stream);
+    const int per = (int)((pool + kOneThreads - 1) / kOneThreads);
+#define KVZAP_ONE(N) if (per <= N) return launch_one<N>(scores, window, seq_lens, k, per_layer, B, H, T, tau_out, stream)
+    KVZAP_ONE(4); KVZAP_ONE(8); KVZAP_ONE(12); KVZAP_ONE(16); KVZAP_ONE(20); KVZAP_ONE(24); KVZAP_ONE(32);
+    KVZAP_ONE(40); KVZAP_ONE(48); KVZAP_ONE(64);
+#undef KVZAP_ONE
   }
   const int groups = per_layer ? B : B * H;
   const Layout l = topk_layout(H, T, per_layer);
