@@ -114,16 +114,23 @@ __device__ __forceinline__ void product(int m, const Tile& stream, const Tile (&
 // row of C register e in lane half kg: 8*(e/4) + 4*kg + e%4
 __device__ __forceinline__ int c_row(int e, int kg) { return 8 * (e >> 2) + 4 * kg + (e & 3); }
 
+// The bias of query j from its row's maximum and sum, divided by the logit scale, which the column
+// pass applies after its maximum.  Padded rows never win a maximum.
+__device__ __forceinline__ float row_bias(float M, float L, int j, int Tq, const float* hnorm, float cscale) {
+  const float inv_c = 1.0f / cscale;
+  return (j < Tq ? -(M + __log2f(L) + (hnorm ? __log2f(hnorm[j]) : 0.f)) : -INFINITY) * inv_c;
+}
+
 __device__ __forceinline__ void wait_lds() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// ---- pass 1: grid (ceil(Tq / 256), HQ), 256 threads; a wavefront owns 64 queries, the
-// block streams the keys its last query sees ----
+// ---- pass 1: grid (ceil(Tq / 256), HQ, KS), 256 threads; a wavefront owns 64 queries, the
+// block streams its share of the keys its last query sees ----
 __global__ __launch_bounds__(256, 2) void teacher_rowstat_kernel(
     const u32x4* q, const u32x4* k, const float* __restrict__ hnorm, int G, int Tq, int Tk,
-    int tq_pad, float cscale, float* __restrict__ rowbias) {
+    int tq_pad, float cscale, float* __restrict__ rowbias, float2* __restrict__ part) {
   extern __shared__ __align__(16) unsigned char smem[];
   // Blocks are handed out in the order of the linear block index, and a block of late
   // queries sees up to twice the keys of an early one: the index is mapped so that the
@@ -146,10 +153,12 @@ __global__ __launch_bounds__(256, 2) void teacher_rowstat_kernel(
   // are all padding
   int block_last_q = bx * kBlockRows + kBlockRows - 1;
   block_last_q = block_last_q < Tq - 1 ? block_last_q : Tq - 1;
-  const int ntiles = (P0 + block_last_q) / 32 + 1;
+  const int all = (P0 + block_last_q) / 32 + 1, ks = blockIdx.z, KS = gridDim.z;
+  const int tile0 = (int)((long long)all * ks / KS);     // tile i of this block is key tile tile0 + i
+  const int ntiles = (int)((long long)all * (ks + 1) / KS) - tile0;   // >= 1: KS <= all
 
   auto stream = [&](int tile, int stage) {               // clamped: a tile past the end re-reads the last
-    const int tl = tile < ntiles ? tile : ntiles - 1;
+    const int tl = tile0 + (tile < ntiles ? tile : ntiles - 1);
     stream_tile_to_lds(kh + (size_t)tl * kTileBytes, Tk - 1 - tl * 32, lds0 + (unsigned)(stage * kStageBytes), wave, lane);
   };
 #pragma unroll
@@ -189,7 +198,8 @@ __global__ __launch_bounds__(256, 2) void teacher_rowstat_kernel(
   };
   // softmax statistics of one key tile from its logits s (C[key][query]), any tile
   auto reduce = [&](const floatx16 (&s)[kStay], int tile) {
-    const int key0 = tile * 32;
+    if (tile >= ntiles) return;                          // the step that evens out an odd number
+    const int key0 = (tile0 + tile) * 32;
 #pragma unroll
     for (int t = 0; t < kStay; ++t) {
       const int qcol = q0 + 32 * t + r;                  // this lane's query
@@ -268,7 +278,7 @@ __global__ __launch_bounds__(256, 2) void teacher_rowstat_kernel(
     reduce(s_cur, tile);
   };
   // every wavefront makes the same number of steps, whichever form they take
-  const int visible = (P0 + q0 + 1) / 32;                // tiles all of whose keys its first query sees
+  const int visible = (P0 + q0 + 1) / 32 - tile0;        // tiles all of whose keys its first query sees
   int tile = 0;
   for (; tile + kStages <= (visible < ntiles ? visible : ntiles); tile += kStages) {
     visible_step(tb, ta, sa, sb, tile, std::integral_constant<int, 0>{});
@@ -283,8 +293,7 @@ __global__ __launch_bounds__(256, 2) void teacher_rowstat_kernel(
   wait_vmcnt<0>();                                       // nothing may land in LDS after the block is gone
 
   // The two lane halves hold disjoint key rows of the same query: merge, then one bias per row.
-  // It is stored divided by the logit scale, which the column pass applies after its maximum.
-  const float inv_c = 1.0f / cscale;
+  // With several shares of the keys their statistics meet in teacher_rowmerge_kernel.
 #pragma unroll
   for (int t = 0; t < kStay; ++t) {
     const float mo = __shfl_xor(m[t], 32, 64), lo = __shfl_xor(l[t], 32, 64);
@@ -292,11 +301,26 @@ __global__ __launch_bounds__(256, 2) void teacher_rowstat_kernel(
     const float L = l[t] * __builtin_amdgcn_exp2f(m[t] - M) + lo * __builtin_amdgcn_exp2f(mo - M);
     const int j = q0 + 32 * t + r;
     if (kg == 0 && j < tq_pad) {
-      float bias = -INFINITY;                            // padded rows never win a maximum
-      if (j < Tq) bias = -(M + __log2f(L) + (hnorm ? __log2f(hnorm[j]) : 0.f));
-      rowbias[(size_t)g * tq_pad + j] = bias * inv_c;
+      const size_t at = (size_t)g * tq_pad + j;
+      if (KS > 1) part[(size_t)ks * gridDim.y * tq_pad + at] = make_float2(M, L);
+      else rowbias[at] = row_bias(M, L, j, Tq, hnorm, cscale);
     }
   }
+}
+
+__global__ __launch_bounds__(256) void teacher_rowmerge_kernel(
+    const float2* __restrict__ part, const float* __restrict__ hnorm, int KS, int rows, int Tq, int tq_pad,
+    float cscale, float* __restrict__ rowbias) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= rows) return;
+  float M = kNegBig, L = 0.f;
+  for (int s = 0; s < KS; ++s) {
+    const float2 p = part[(size_t)s * rows + i];
+    const float mn = fmaxf(M, p.x);
+    L = L * __builtin_amdgcn_exp2f(M - mn) + p.y * __builtin_amdgcn_exp2f(p.x - mn);
+    M = mn;
+  }
+  rowbias[i] = row_bias(M, L, i % tq_pad, Tq, hnorm, cscale);
 }
 
 // ---- pass 2: grid ceil(T / 256) * H * JS, 256 threads; a wavefront owns 64 prompt keys, the
@@ -413,6 +437,8 @@ __global__ __launch_bounds__(256) void teacher_finish_kernel(const float* __rest
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   float best = -INFINITY;
+  // eight loads in flight: up to 64 shares one after the other took 7 us
+#pragma unroll 8
   for (int s = 0; s < JS; ++s) best = fmaxf(best, part[(size_t)s * n + i]);
   out[i] = best * 0.69314718055994531f + (vnorm ? __logf(vnorm[i]) : 0.f);
 }
@@ -429,11 +455,28 @@ int teacher_splits(int H, int G, int Tq, int T) {
   return js < 1 ? 1 : (int)js;
 }
 
+// Shares of the keys in the row pass: up to 1024 blocks (two per CU and as many to even out the early
+// and late queries' unequal work) where blocks of 256 queries are fewer, with at least 8 key tiles
+// of the prompt (T positions, no more than the earliest queries see) in each.  Measured, us per call
+// (with shares / one block per 256 queries): 32 heads: prompt and repeat 512 29 / 41, 1024: 38 / 52,
+// 2048: 92 / 101, 4096: 293 / 313; 16 heads, prompt 2048, repeat 512: 27 / 53; 8192, 2048: 137 / 193.
+int teacher_key_splits(int HQ, int Tq, int T) {
+  const long long blocks = (long long)((Tq + kBlockRows - 1) / kBlockRows) * HQ;
+  long long ks = blocks < 1024 ? 1024 / blocks : 1;
+  if (ks > T / 256) ks = T / 256;
+  return ks < 1 ? 1 : (int)ks;
+}
+
+size_t teacher_rowbias_bytes(int HQ, int Tq) { return align_up((size_t)HQ * ((Tq + 31) / 32 * 32) * sizeof(float), 256); }
+
 size_t teacher_workspace_bytes(int H, int HQ, int Tq, int T) {
-  const int tq_pad = (Tq + 31) / 32 * 32;
   const int js = teacher_splits(H, HQ / H, Tq, T);
-  return align_up((size_t)HQ * tq_pad * sizeof(float), 256) +
-         align_up((size_t)js * H * (T > 0 ? T : 1) * sizeof(float), 256);
+  // biases; then the column pass's maxima per share of the queries and, before them in the same
+  // place, the row pass's statistics per share of the keys
+  const size_t cols = align_up((size_t)js * H * (T > 0 ? T : 1) * sizeof(float), 256);
+  const int ks = teacher_key_splits(HQ, Tq, T);
+  const size_t rows = ks > 1 ? align_up((size_t)ks * HQ * ((Tq + 31) / 32 * 32) * sizeof(float2), 256) : 0;
+  return teacher_rowbias_bytes(HQ, Tq) + (cols > rows ? cols : rows);
 }
 
 int launch_teacher_scores(const void* q, const void* k, const float* vnorm, const float* hnorm,
@@ -444,14 +487,18 @@ int launch_teacher_scores(const void* q, const void* k, const float* vnorm, cons
   const int tq_pad = (Tq + 31) / 32 * 32;
   const int JS = teacher_splits(H, G, Tq, T);
   float* rowbias = static_cast<float*>(workspace);
-  float* part = reinterpret_cast<float*>(static_cast<char*>(workspace) +
-                                         align_up((size_t)HQ * tq_pad * sizeof(float), 256));
+  float* part = reinterpret_cast<float*>(static_cast<char*>(workspace) + teacher_rowbias_bytes(HQ, Tq));
+  const int KS = teacher_key_splits(HQ, Tq, T);
   const float cscale = scale * 1.4426950408889634f;
   const auto* qv = static_cast<const u32x4*>(q);
   const auto* kv = static_cast<const u32x4*>(k);
-  const dim3 g1((tq_pad + kBlockRows - 1) / kBlockRows, HQ);
+  const dim3 g1((Tq + kBlockRows - 1) / kBlockRows, HQ, KS);
   constexpr size_t lds = (size_t)kStages * kStageBytes;
-  teacher_rowstat_kernel<<<g1, 256, lds, stream>>>(qv, kv, hnorm, G, Tq, Tk, tq_pad, cscale, rowbias);
+  teacher_rowstat_kernel<<<g1, 256, lds, stream>>>(qv, kv, hnorm, G, Tq, Tk, tq_pad, cscale, rowbias,
+                                                 reinterpret_cast<float2*>(part));
+  if (KS > 1)
+    teacher_rowmerge_kernel<<<(HQ * tq_pad + 255) / 256, 256, 0, stream>>>(
+        reinterpret_cast<const float2*>(part), hnorm, KS, HQ * tq_pad, Tq, tq_pad, cscale, rowbias);
   if (hipGetLastError() != hipSuccess) return KVZAP_ERR_RUNTIME;
   const unsigned g2 = (unsigned)((T + kBlockRows - 1) / kBlockRows) * H * JS;
   teacher_colmax_kernel<<<g2, 256, lds, stream>>>(qv, kv, rowbias, G, H, JS, Tq, Tk, T, tq_pad, cscale, part);

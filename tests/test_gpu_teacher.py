@@ -122,6 +122,7 @@ def test_rejects_bad_arguments():
     (96, 0, 63), (95, 1, 64), (127, 1, 65),       # the first query sees 3 whole key tiles, 3, and 4
     (128, 31, 255), (129, 32, 257),               # blocks of 256 kept rows: one short, one more
     (1, 0, 300), (600, 40, 33),                   # every tile on the diagonal; two query tiles
+    (511, 1, 33), (512, 3, 290), (1290, 0, 257),  # one share of the keys, two, five
 ])
 def test_edges_of_tiles_and_of_whole_visible_groups(T, instr, Tq):
     _check(H=3, G=2, T=T, instr=instr, Tq=Tq, seed=T + Tq)
