@@ -1,11 +1,20 @@
 """The native part of the Python wrappers: what it refuses, and that a call on a stream that the
 caller names computes what the call on the current stream does."""
+import os
+
 import pytest
 import torch
 
 from paper_2601_07891_amd import binding as kv, synth
 
 BF = torch.bfloat16
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _built():
+    if not (os.path.exists(kv.LIB_PATH) and os.path.exists(kv.HOST_PATH)):
+        from paper_2601_07891_amd import build
+        build.build(verbose=False)
 
 
 def _calls(dev, stream=None):
