@@ -904,7 +904,12 @@ constexpr float kBlockFixed = 7.0f;                                        // us
 constexpr float kBlockThin[5] = {0.55f, 0.77f, 0.97f, 1.15f, 1.29f};       // us per 64 inputs, few blocks
 constexpr float kBlockFull[5] = {0.70f, 1.07f, 1.33f, 1.68f, 1.58f};       // ... 256 blocks
 constexpr float kTileFixed[kScoreTiles] = {10.5f, 10.0f, 10.0f, 9.5f, 9.5f};
-constexpr float kTileStep[kScoreTiles] = {0.44f, 0.25f, 0.16f, 0.10f, 0.085f};   // us per 64 inputs and round
+constexpr float kTileStep[kScoreTiles] = {0.53f, 0.25f, 0.16f, 0.10f, 0.085f};   // us per 64 inputs and round
+// ... and per 64 inputs of every round but the first: the blocks of later rounds start at different
+// times and share less through L2 (12288 tokens in three rounds of 128 x 64 tiles: 91 us; without
+// this the model said 64, and 18000 to 24576 tokens went to tiles at 114 to 130 us instead of token
+// blocks at 97 to 102)
+constexpr float kTileAgain[kScoreTiles] = {0.16f, 0.25f, 0.25f, 0.25f, 0.25f};
 
 inline float cost_blocks(long long rows, int Dh, int M) {
   const int tok = M / 128 <= 4 ? 128 : 96, i = M / 128 - 1;
@@ -919,7 +924,8 @@ inline float cost_tile(int tile, long long rows, int Dh, int M) {
   const long long blocks = score_tile_blocks(tile, rows, M);
   const long long rounds = (blocks + kChipCUs - 1) / kChipCUs;
   const float fill = rounds > 1 ? 1.0f : 0.75f + 0.25f * (float)blocks / kChipCUs;
-  return kTileFixed[tile] + (float)(rounds - 1) * 3.0f + (float)rounds * fill * (float)(Dh / kBK) * kTileStep[tile];
+  return kTileFixed[tile] +
+         (float)(Dh / kBK) * ((float)rounds * fill * kTileStep[tile] + (float)(rounds - 1) * kTileAgain[tile]);
 }
 
 inline Plan plan_tile(long long rows, int Dh, int M) {                     // one tile for all rows
