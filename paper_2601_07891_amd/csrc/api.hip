@@ -94,7 +94,7 @@ size_t kvzap_workspace_bytes(int which_call, int B, int T, int Dh, int M, int H)
       return mask_workspace(B, H, T);
     case KVZAP_CALL_ATTEND_DECODE:   // T = max_rows, Dh = HQ, M = window
       if (check_attend_shape(B, H, Dh, T, M) != KVZAP_OK) return 0;
-      return kvzap::attend_workspace_query(B, H, Dh, T, M);
+      return kvzap::attend_workspace_bytes(B, H, Dh, T, M);
     case KVZAP_CALL_TEACHER_SCORES:       // T = prompt length, Dh = HQ, M = Tq
       if (Dh <= 0 || M <= 0 || Dh % H != 0 || H > 65535) return 0;
       return kvzap::teacher_workspace_bytes(H, Dh, M, T);

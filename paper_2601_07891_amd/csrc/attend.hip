@@ -4,15 +4,20 @@
 //
 // The kernel is bound by reading K and V once (512 bytes per row against 4*G*128
 // flops), so the design is about streaming rows with as few vector-ALU instructions
-// per byte as possible; both contractions run on v_mfma_f32_16x16x32_bf16 straight
-// from the registers the global loads fill, with no LDS and no barrier:
+// per byte as possible; both contractions run on v_mfma_f32_16x16x32_bf16:
 //
-//   one wave = one split of one KV head, 32-row chunks, the next chunk's loads in
+//   one wave = an equal part of all heads' rows, 32-row chunks, the next chunk's loads in
 //   flight while the current one is consumed.
 //
-//   S^T = K q^T      A = K   lane (i = l%16, kg = l/16) loads 16 bytes of row rho(i) at
+// Every load instruction takes four whole rows of K or V (1 KB) with the non-temporal hint: that is
+// the form in which this part's memory gives 7.0 TB/s.  Without the hint, or with it and 64 bytes of a
+// 128-byte line per instruction (K in the operand layout straight from memory), a read stream gets 6.1.
+//
+//   S^T = K q^T      A = K   lane (i = l%16, kg = l/16) holds 16 bytes of row rho(i) at
 //                            byte 64*kk + 16*kg for kk = 0..3 (the k-slices an MFMA
-//                            step wants); two 16-row sets per chunk
+//                            step wants); two 16-row sets per chunk.  Loaded like V below and
+//                            turned through 8 KB of LDS of the wavefront's own (pieces XOR-swizzled
+//                            with the row: no bank conflicts either way)
 //                    B = q   lane (g = l%16, kg) holds q[g][32kk + 8kg ..+8], zero for
 //                            g >= G
 //                    C       lane (g, s = l/16), register r: row i = 4s + r of the set
@@ -79,8 +84,8 @@ __device__ __forceinline__ HeadExtent head_extent(const int64_t* row_offsets,
 __device__ __forceinline__ int chunks_of(int rows) { return (rows + kChunkRows - 1) / kChunkRows; }
 
 struct Chunk {
-  u32x4 k[2][4];   // [set][k-step]
-  u32x4 v[8];      // [row group j]
+  u32x4 k[8];      // [row group j]: piece l%16 of row 4j + l/16
+  u32x4 v[8];
 };
 
 // Where the rows of one head live.
@@ -151,30 +156,26 @@ __device__ __forceinline__ Place place_of(int vc, int cp, const Source& s, const
 __device__ __forceinline__ void load_chunk(Chunk& c, const Place& p, const Source& s, int li, int lg) {
   const u32x4* Kb = p.ring ? s.Kr : s.K;
   const u32x4* Vb = p.ring ? s.Vr : s.V;
-  const int klocal = 4 * (li & 3) + (li >> 2);          // row of this lane inside a 16-row set
   if (p.row0 + kChunkRows <= p.n_seg) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const u32x4* kp = Kb + p.half[t] + klocal * kRowVec + lg;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) c.k[t][kk] = kp[kk * 4];
+    for (int j = 0; j < 8; ++j) {
+      const size_t at = p.half[j >> 2] + (size_t)(4 * (j & 3) + lg) * kRowVec + li;
+      c.k[j] = __builtin_nontemporal_load(Kb + at);
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      c.v[j] = Vb[p.half[j >> 2] + (size_t)(4 * (j & 3) + lg) * kRowVec + li];
+    for (int j = 0; j < 8; ++j) {
+      const size_t at = p.half[j >> 2] + (size_t)(4 * (j & 3) + lg) * kRowVec + li;
+      c.v[j] = __builtin_nontemporal_load(Vb + at);
+    }
   } else {
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      int lim = p.n_seg - 1 - (p.row0 + 16 * t);        // last row of the segment, within the half
+    for (int j = 0; j < 8; ++j) {
+      int lim = p.n_seg - 1 - (p.row0 + 16 * (j >> 2));  // last row of the segment, within the half
       lim = lim < 0 ? 0 : lim;
-      const u32x4* kp = Kb + p.half[t] + (klocal < lim ? klocal : lim) * kRowVec + lg;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) c.k[t][kk] = kp[kk * 4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r = 4 * j + lg;
-        c.v[4 * t + j] = Vb[p.half[t] + (size_t)(r < lim ? r : lim) * kRowVec + li];
-      }
+      const int r = 4 * (j & 3) + lg;
+      const size_t at = p.half[j >> 2] + (size_t)(r < lim ? r : lim) * kRowVec + li;
+      c.k[j] = __builtin_nontemporal_load(Kb + at);
+      c.v[j] = __builtin_nontemporal_load(Vb + at);
     }
   }
 }
@@ -189,15 +190,27 @@ __device__ __forceinline__ float shfl_xor_f(float x, int mask) {
   return __shfl_xor(x, mask, 64);
 }
 
-__device__ __forceinline__ void consume_chunk(const Chunk& c, const u32x4 (&qb)[4], Accum& a,
-                                              int row0, int n_seg, int lg, float cscale) {
+// The wavefront's LDS operations complete in order: a fence for the compiler is all that has to stand
+// between one lane's write and another lane's read.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ void consume_chunk(const Chunk& c, const u32x4 (&qb)[4], Accum& a, u32x4* turn,
+                                              int row0, int n_seg, int li, int lg, float cscale) {
+  wave_fence();                                          // the reads of the chunk before
+#pragma unroll
+  for (int j = 0; j < 8; ++j) turn[(4 * j + lg) * kRowVec + (li ^ ((4 * j + lg) & 15))] = c.k[j];
+  wave_fence();
   floatx4 s[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     s[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int row = 4 * (li & 3) + (li >> 2);            // of this lane in the 16-row set
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
-      s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, c.k[t][kk]),
+      s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, turn[(16 * t + row) * kRowVec + ((4 * kk + lg) ^ row)]),
                                                      __builtin_bit_cast(bf16x8, qb[kk]), s[t],
                                                      0, 0, 0);
   }
@@ -243,125 +256,258 @@ __device__ __forceinline__ void consume_chunk(const Chunk& c, const u32x4 (&qb)[
   a.l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ones), p, a.l, 0, 0, 0);
 }
 
-// grid (B*H, NS), 64 threads.  The head varies fastest and is shifted by one from split to split:
-// workgroups go to the eight XCDs in turn, so the blocks that have work (short heads: the first
-// splits only) come one after the other on all of them, and a long head's splits meet every XCD.
-// part: [B*H][NS][G][128] fp32, ml: [B*H][NS][G][2] fp32.
+// ---- pass 1: grid ceil(nw / 4), 256 threads ----
+// The chunks of all heads, in (b,h) order and each head's prefix before its ring, are one list, and
+// each of the nw wavefronts takes an equal part of it: every CU of every XCD reads the same number of
+// bytes whatever the heads' lengths are, and all of them end together.  (Cutting every head into
+// splits of the same length and handing those out one per wavefront left the XCDs up to 4 % apart and
+// paid a wavefront's start for every split: 64 sequences of 4k..32k rows 776 us with splits of 2048
+// rows, 815 with 1024, 850 with 512.)
+// A block adds up the chunk counts of all heads itself, up to 64 heads a wavefront does.  The part of a head that a wavefront
+// handles (a segment) leaves its sums in slot (wavefront + head), which grows from segment to
+// segment; span[head] = the first and the last slot of the head, written by the wavefronts that
+// hold its ends.  part: [slot][G][128] fp32, ml: [slot][G][2] fp32.
 // Contiguous layout: K_rows/V_rows are the row store, row_offsets the heads' first rows.
 // Paged layout: K_rows/V_rows are the page pool, row_offsets is null, block_table given.
-template <bool kPaged>
-__global__ __launch_bounds__(64, 2) void attend_partial_kernel(
+constexpr int kMinChunks = 4;            // of a wavefront: fewer, and the combining pass takes longer
+constexpr int kMaxBatches = 1024;        // of 64 heads: B*H <= 65535
+
+// How a wavefront finds its part of the list: from all heads' lengths, for itself (up to 64 heads) or
+// with the other three of its block, or as one of spc chunks of one head.
+enum class Deal { kWave, kBlock, kHead };
+constexpr int waves_of(Deal d) { return d == Deal::kBlock ? 4 : 1; }
+
+// inclusive sum over the lanes before and at this one
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);    // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15, 31
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
+template <bool kPaged, Deal kDeal>
+__global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_partial_kernel(
     const u32x4* q, const u32x4* K_rows, const u32x4* V_rows, int64_t cap_rows,
     const int64_t* row_offsets, const int32_t* block_table, int max_pages, int log_page,
     int num_pages, const int32_t* lengths, const u32x4* K_ring, const u32x4* V_ring,
-    const int32_t* seq_pos, int window, float cscale, int H, int G, int NS, int spc, float* part,
-    float* ml) {
-  const int split = blockIdx.y + gridDim.y * blockIdx.z, BH = gridDim.x;
-  if (split >= NS) return;
-  const int bh = (int)((blockIdx.x + (unsigned)split) % (unsigned)BH);
-  const int b = bh / H;
-  const HeadExtent e = head_extent(row_offsets, lengths, seq_pos, window, cap_rows, bh, b);
-  const int cp = chunks_of(e.n_p), ct = cp + chunks_of(e.n_r);
-  const int c0 = split * spc;
-  // the last split runs to the end of the list, so a head longer than the host's bound
-  // is still covered
-  const int c1 = (split == NS - 1) ? ct : (c0 + spc < ct ? c0 + spc : ct);
-  if (c0 >= c1) return;
+    const int32_t* seq_pos, int window, float cscale, int BH, int H, int G, int nw, int spc,
+    float* part, float* ml, int2* span) {
+  constexpr int kWaves = waves_of(kDeal);
+  __shared__ u32x4 s_turn[kWaves][kChunkRows * kRowVec];
+  __shared__ int s_batch[kDeal == Deal::kBlock ? kMaxBatches : 1];
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  const int lane = threadIdx.x, li = lane & 15, lg = lane >> 4;
-  Source src;
-  src.K = K_rows + (size_t)e.off * kRowVec;
-  src.V = V_rows + (size_t)e.off * kRowVec;
-  src.Kr = K_ring + (size_t)bh * (window > 0 ? window : 0) * kRowVec;
-  src.Vr = V_ring + (size_t)bh * (window > 0 ? window : 0) * kRowVec;
-  src.pages = kPaged ? block_table + (size_t)bh * max_pages : nullptr;
-  src.log_page = log_page; src.max_pages = max_pages; src.num_pages = num_pages;
-  src.n_p = e.n_p; src.n_r = e.n_r;
-
-  // q as the B operand: lane (g = li, kg = lg), k-step kk: q[g][32kk + 8kg ..+8]
-  u32x4 qb[4];
-  {
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-    const u32x4* qp = q + ((size_t)bh * G + (li < G ? li : 0)) * kRowVec + lg;
+  HeadExtent mine;                                       // lane i: head base + i
+  int base = 0, chunks;                                  // chunks of that head
+  auto extent = [&](int bh) {                            // past the last head: nothing, and no branch around a load
+    const int c = bh < BH ? bh : BH - 1;
+    HeadExtent e = head_extent(row_offsets, lengths, seq_pos, window, cap_rows, c, c / H);
+    if (bh >= BH) e.n_p = e.n_r = 0;
+    return e;
+  };
+  auto fetch = [&]() {
+    mine = extent(base + lane);
+    chunks = chunks_of(mine.n_p) + chunks_of(mine.n_r);
+  };
+  const int w = blockIdx.x * kWaves + wv;
+  int begin = 0, left;                                   // this wavefront's part of the list
+  auto part_of = [&](int total) {
+    int per = (int)(((unsigned)total + (unsigned)nw - 1) / (unsigned)nw);
+    per = per > kMinChunks ? per : kMinChunks;
+    begin = w < nw ? w * per : total;
+    left = total - begin < per ? total - begin : per;
+  };
+  int skip;                                              // chunks ahead of `begin` from head `base` on
+  if constexpr (kDeal == Deal::kHead) {
+    const int NS = nw / BH, bh = w / NS, split = w - bh * NS;
+    base = bh;
+    fetch();
+    const int ct = __builtin_amdgcn_readfirstlane(chunks);
+    skip = split * spc;
+    left = split == NS - 1 ? ct - skip : (ct - skip < spc ? ct - skip : spc);   // the last takes what is beyond the bound
+    if (left <= 0) return;
+  } else if constexpr (kDeal == Deal::kWave) {
+    fetch();
+    part_of(__builtin_amdgcn_readlane(wave_scan(chunks), 63));
+    if (left <= 0) return;
+    skip = begin;
+  } else {
+    // the wavefronts add up 64 heads at a time, the loads of four batches in flight
+    const int batches = (BH + 63) / 64;
+    for (int i = wv; i < batches; i += 4 * kWaves) {
+      int n[4];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) qb[kk] = li < G ? qp[kk * 4] : zero;
+      for (int u = 0; u < 4; ++u) {
+        const HeadExtent e = extent((i + u * kWaves) * 64 + lane);
+        n[u] = chunks_of(e.n_p) + chunks_of(e.n_r);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int sum = wave_scan(n[u]);
+        if (lane == 63 && i + u * kWaves < batches) s_batch[i + u * kWaves] = sum;
+      }
+    }
+    __syncthreads();
+    int total = 0;
+    for (int i = 0; i < batches; i += 64)
+      total += __builtin_amdgcn_readlane(wave_scan(i + lane < batches ? s_batch[i + lane] : 0), 63);
+    part_of(total);
+    if (left <= 0) return;
+    // the batches that end at or before `begin` are passed over
+    int passed = 0;
+    skip = begin;
+    for (int i = 0; i < batches; i += 64) {
+      const int upto = wave_scan(i + lane < batches ? s_batch[i + lane] : 0);
+      const unsigned long long done = __ballot(upto <= skip);
+      if (!done) break;
+      passed = i + __popcll(done);
+      skip -= __builtin_amdgcn_readlane(upto, 63 - __builtin_clzll(done));
+      if (~done) break;
+    }
+    base = passed * 64;
+    fetch();
+  }
+  int at = 0;                                            // the wavefront's head is base + at
+  while (kDeal != Deal::kHead) {
+    const int upto = wave_scan(chunks);
+    const unsigned long long past = __ballot(upto > skip);
+    if (past) {
+      at = __builtin_ctzll(past);
+      skip -= __builtin_amdgcn_readlane(upto - chunks, at);
+      break;
+    }
+    skip -= __builtin_amdgcn_readlane(upto, 63);
+    base += 64;
+    if (base >= BH) return;                              // (never: begin < total)
+    fetch();
   }
 
-  Accum acc;
-#pragma unroll
-  for (int t = 0; t < 8; ++t) acc.o[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-  acc.l = floatx4{0.f, 0.f, 0.f, 0.f};
-  acc.m = -INFINITY;
+  u32x4* const turn = s_turn[wv];
+  int first = skip;                                      // its chunk of that head
+  for (;;) {
+    at = __builtin_amdgcn_readfirstlane(at);
+    const int bh = base + at;
+    HeadExtent e;
+    e.n_p = __builtin_amdgcn_readlane(mine.n_p, at);
+    e.n_r = __builtin_amdgcn_readlane(mine.n_r, at);
+    e.off = (int64_t)(((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(mine.off >> 32), at) << 32) |
+                      (unsigned)__builtin_amdgcn_readlane((int)mine.off, at));
+    const int cp = chunks_of(e.n_p), ct = cp + chunks_of(e.n_r);
+    const int c0 = __builtin_amdgcn_readfirstlane(first);
+    const int c1 = __builtin_amdgcn_readfirstlane(ct - c0 < left ? ct : c0 + left);
+    Source src;
+    src.K = K_rows + (size_t)e.off * kRowVec;
+    src.V = V_rows + (size_t)e.off * kRowVec;
+    src.Kr = K_ring + (size_t)bh * (window > 0 ? window : 0) * kRowVec;
+    src.Vr = V_ring + (size_t)bh * (window > 0 ? window : 0) * kRowVec;
+    src.pages = kPaged ? block_table + (size_t)bh * max_pages : nullptr;
+    src.log_page = log_page; src.max_pages = max_pages; src.num_pages = num_pages;
+    src.n_p = e.n_p; src.n_r = e.n_r;
 
-  // Two chunk buffers; the steady-state loop has no branch around a load, so the
-  // compiler's wait counts let the loads of one buffer fly while the other is consumed.
-  Chunk ca, cb;
-  Rows rows{};
-  for (int chunk0 = c0; chunk0 < c1; chunk0 += kLookup) {
-    const int end = kPaged && chunk0 + kLookup < c1 ? chunk0 + kLookup : c1;
-    if (kPaged) rows = look_up(src, chunk0, lane);
-    auto place = [&](int vc) { return place_of<kPaged>(vc, cp, src, rows, chunk0); };
-    Place pa = place(chunk0), pb;
-    load_chunk(ca, pa, src, li, lg);
-    int vc = chunk0;
-    while (vc + 2 < end) {
-      pb = place(vc + 1);
-      load_chunk(cb, pb, src, li, lg);
-      consume_chunk(ca, qb, acc, pa.row0, pa.n_seg, lg, cscale);
-      pa = place(vc + 2);
+    // q as the B operand: lane (g = li, kg = lg), k-step kk: q[g][32kk + 8kg ..+8]
+    u32x4 qb[4];
+    {
+      const u32x4 zero = {0u, 0u, 0u, 0u};
+      const u32x4* qp = q + ((size_t)bh * G + (li < G ? li : 0)) * kRowVec + lg;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) qb[kk] = li < G ? qp[kk * 4] : zero;
+    }
+
+    Accum acc;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) acc.o[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    acc.l = floatx4{0.f, 0.f, 0.f, 0.f};
+    acc.m = -INFINITY;
+
+    // Two chunk buffers; the steady-state loop has no branch around a load, so the
+    // compiler's wait counts let the loads of one buffer fly while the other is consumed.
+    Chunk ca, cb;
+    Rows rows{};
+    for (int chunk0 = c0; chunk0 < c1; chunk0 += kLookup) {
+      const int end = kPaged && chunk0 + kLookup < c1 ? chunk0 + kLookup : c1;
+      if (kPaged) rows = look_up(src, chunk0, lane);
+      auto place = [&](int vc) { return place_of<kPaged>(vc, cp, src, rows, chunk0); };
+      Place pa = place(chunk0), pb;
       load_chunk(ca, pa, src, li, lg);
-      consume_chunk(cb, qb, acc, pb.row0, pb.n_seg, lg, cscale);
-      vc += 2;
+      int vc = chunk0;
+      while (vc + 2 < end) {
+        pb = place(vc + 1);
+        load_chunk(cb, pb, src, li, lg);
+        consume_chunk(ca, qb, acc, turn, pa.row0, pa.n_seg, li, lg, cscale);
+        pa = place(vc + 2);
+        load_chunk(ca, pa, src, li, lg);
+        consume_chunk(cb, qb, acc, turn, pb.row0, pb.n_seg, li, lg, cscale);
+        vc += 2;
+      }
+      if (vc + 1 < end) {
+        pb = place(vc + 1);
+        load_chunk(cb, pb, src, li, lg);
+        consume_chunk(ca, qb, acc, turn, pa.row0, pa.n_seg, li, lg, cscale);
+        consume_chunk(cb, qb, acc, turn, pb.row0, pb.n_seg, li, lg, cscale);
+      } else {
+        consume_chunk(ca, qb, acc, turn, pa.row0, pa.n_seg, li, lg, cscale);
+      }
+      if (!kPaged) break;
     }
-    if (vc + 1 < end) {
-      pb = place(vc + 1);
-      load_chunk(cb, pb, src, li, lg);
-      consume_chunk(ca, qb, acc, pa.row0, pa.n_seg, lg, cscale);
-      consume_chunk(cb, qb, acc, pb.row0, pb.n_seg, lg, cscale);
-    } else {
-      consume_chunk(ca, qb, acc, pa.row0, pa.n_seg, lg, cscale);
-    }
-    if (!kPaged) break;
-  }
 
-  if (li < G) {
-    const size_t slot = ((size_t)bh * NS + split) * G + li;
-    float* dst = part + slot * kD + 32 * lg;
+    const int slot = kDeal == Deal::kHead ? w : w + bh;
+    if (li < G) {
+      const size_t out = (size_t)slot * G + li;
+      float* dst = part + out * kD + 32 * lg;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      floatx4 lo = {acc.o[0][r], acc.o[1][r], acc.o[2][r], acc.o[3][r]};
-      floatx4 hi = {acc.o[4][r], acc.o[5][r], acc.o[6][r], acc.o[7][r]};
-      *reinterpret_cast<floatx4*>(dst + 8 * r) = lo;
-      *reinterpret_cast<floatx4*>(dst + 8 * r + 4) = hi;
+      for (int r = 0; r < 4; ++r) {
+        floatx4 lo = {acc.o[0][r], acc.o[1][r], acc.o[2][r], acc.o[3][r]};
+        floatx4 hi = {acc.o[4][r], acc.o[5][r], acc.o[6][r], acc.o[7][r]};
+        *reinterpret_cast<floatx4*>(dst + 8 * r) = lo;
+        *reinterpret_cast<floatx4*>(dst + 8 * r + 4) = hi;
+      }
+      if (lg == 0) {
+        ml[out * 2] = acc.m;
+        ml[out * 2 + 1] = acc.l[0];
+      }
     }
-    if (lg == 0) {
-      ml[slot * 2] = acc.m;
-      ml[slot * 2 + 1] = acc.l[0];
+    if (lane == 0) {
+      if (c0 == 0) span[bh].x = slot;
+      if (c1 == ct) span[bh].y = slot;
     }
+    left -= c1 - c0;
+    if (left <= 0) return;
+    // the next head that has chunks: there is one, `left` of the list are still ahead
+    unsigned long long more = __ballot(chunks > 0) & (at < 63 ? ~0ull << (at + 1) : 0ull);
+    while (!more) {
+      base += 64;
+      if (base >= BH) return;
+      fetch();
+      more = __ballot(chunks > 0);
+    }
+    at = __builtin_ctzll(more);
+    first = 0;
   }
 }
 
-// grid B*H*G, 256 threads: thread (c = tid%32, sg = tid/32) folds the splits sg, sg+8, ...
-// of output elements 4c..4c+3 with a running reference, then the 8 groups meet in LDS.
-constexpr int kCombineGroups = 8;
-
-__global__ __launch_bounds__(256) void attend_combine_kernel(
-    const float* part, const float* ml, int64_t total_rows, const int64_t* row_offsets,
-    const int32_t* lengths, const int32_t* seq_pos, int window, int H, int G, int NS, int spc,
-    unsigned short* out) {
-  __shared__ floatx4 s_num[kCombineGroups][32];
-  __shared__ float s_m[kCombineGroups], s_den[kCombineGroups];
+// ---- pass 2: grid B*H*G, kGroups * 32 threads: thread (c = tid%32, sg = tid/32) folds the slots
+// sg, sg + kGroups, ... of output elements 4c..4c+3 with a running reference, then the groups meet
+// in LDS.
+template <int kGroups>
+__global__ __launch_bounds__(kGroups * 32) void attend_combine_kernel(
+    const float* part, const float* ml, const int2* span, int64_t total_rows, const int64_t* row_offsets,
+    const int32_t* lengths, const int32_t* seq_pos, int window, int H, int G, unsigned short* out) {
+  __shared__ floatx4 s_num[kGroups][32];
+  __shared__ float s_m[kGroups], s_den[kGroups];
   const int bh = blockIdx.x / G, g = blockIdx.x % G;
   const int c = threadIdx.x & 31, sg = threadIdx.x >> 5;
   const HeadExtent e = head_extent(row_offsets, lengths, seq_pos, window, total_rows, bh, bh / H);
-  const int ct = chunks_of(e.n_p) + chunks_of(e.n_r);
-  int ns = (ct + spc - 1) / spc;
-  ns = ns < NS ? ns : NS;
+  const int2 slots = span[bh];
+  const int ns = e.n_p + e.n_r > 0 ? slots.y - slots.x + 1 : 0;   // of an empty head nobody wrote the span
   float m = -INFINITY, den = 0.f;
   floatx4 num = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-  for (int s = sg; s < ns; s += kCombineGroups) {
-    const size_t slot = ((size_t)bh * NS + s) * G + g;
+  for (int s = sg; s < ns; s += kGroups) {
+    const size_t slot = (size_t)(slots.x + s) * G + g;
     const float ms = ml[slot * 2], ls = ml[slot * 2 + 1];
     const floatx4 a = *reinterpret_cast<const floatx4*>(part + slot * kD + 4 * c);
     const float mn = fmaxf(m, ms);
@@ -376,11 +522,11 @@ __global__ __launch_bounds__(256) void attend_combine_kernel(
   if (sg == 0) {
     float mm = s_m[0];
 #pragma unroll
-    for (int k = 1; k < kCombineGroups; ++k) mm = fmaxf(mm, s_m[k]);
+    for (int k = 1; k < kGroups; ++k) mm = fmaxf(mm, s_m[k]);
     floatx4 n = {0.f, 0.f, 0.f, 0.f};
     float dsum = 0.f;
 #pragma unroll
-    for (int k = 0; k < kCombineGroups; ++k) {
+    for (int k = 0; k < kGroups; ++k) {
       // a group that saw no split has m = -inf and zero sums; exp2(-inf - mm) = 0 unless
       // mm is -inf too (no split at all), which the ns > 0 test below covers
       const float w = (s_m[k] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(s_m[k] - mm);
@@ -396,60 +542,56 @@ __global__ __launch_bounds__(256) void attend_combine_kernel(
   }
 }
 
-}  // namespace
-
-// Chunks per split (one split = one wave).  Long splits amortise a wave's start-up (its
-// first loads are not overlapped with anything), the partial result it writes and the work
-// of the combine kernel, which folds every split of a head in one block; short ones fill
-// the chip when there are few heads.  If every head were at the bound: about 2048 waves, longer
-// splits for about 96 a head (up to 120 below 480 chunks, more where 64 chunks do not hold the
-// head) as long as that leaves a wave per CU, within 4..64 chunks (128..2048 rows).  Measured (8 KV heads, us per
-// call at 4 / 8 / 16 / 32 / 64 chunks): 64 sequences of 4k..32k rows (bound 38k) 1040 / 953 / 895 /
-// 858 / 840; 24 of 4k..8k 139 / 130 / 129 / 129 / 121; 16 of 0.5k..2k 22 / 22 / 20 / 24 / 39;
-// 3 of 1k..8k 18 / 18 / 17 / 24 / 40; 1 of 32k 31 / 28 / 28 / 26 / 40.  One KV head of 32k 12 / 13 /
-// 15 / 20 / 35, 64k 18 / 15 / 17 / 23 / 37, 128k 32 / 24 / 20 / 26 / 40; two of 128k 41 / 34 / 29 / 27 / 40.
-int attend_split_chunks(int BH, int max_rows, int window) {
-  const long long ct = (max_rows + kChunkRows - 1) / kChunkRows +
-                       ((window > 0 ? window : 0) + kChunkRows - 1) / kChunkRows;
-  const long long fill = ct * BH / 2048, fold = ct / 96;
-  int spc = 4;
-  while (spc < 64 && (spc < fill || (spc < fold && ct * BH >= 256ll * 2 * spc))) spc *= 2;
-  return spc;
+// How the first pass is dealt out: nw wavefronts (a multiple of B*H where each has spc chunks of one head).
+//
+// Equal parts of all heads' chunks in 4-wavefront blocks on 28 of an XCD's 32 CUs, or where there are
+// no more than 64 heads in one-wavefront blocks on all of them, but at least kMinChunks chunks each and
+// no more than 256 wavefronts for one head, whose sums one block combines.  Measured, us per call
+// (before, in splits of one head handed out one by one with 64-byte K loads / now): 8 KV heads, 4 query
+// heads each: 64 sequences of 4k..32k rows 837 / 699 (6.96 TB/s; with 1024 wavefronts 711, 2048 787),
+// 64 of 16000 708 / 614, 24 of 4k..8k 123 / 96, 16 of 0.5k..2k 25.3 / 22.3, 8 of 0.1k..30k 115 / 81, 3 of
+// 1k..8k 20.0 / 18.2, 1 of 128k 94 / 87, of 32k 30.2 / 29.1, of 2500 12.2 / 12.2; one KV head of 128k 23.8 /
+// 20.9, two 33.6 / 30.4.
+// Heads of a few chunks are better off with a wavefront of their own, since a part's every head begins
+// with a wait for its first rows: 512 heads of 64 rows beside the window 16.9 us in equal parts, 14.6 head
+// by head, 2048 heads 48.4 / 42.9, 8192 194 / 183; 512 of 512 rows (20 chunks) 33.8 / 33.7.
+constexpr int kShortHead = 20;           // chunks, by the caller's bound
+struct Dealt {
+  Deal deal;
+  int nw, spc;
+};
+Dealt deal_of(int BH, long long ct) {
+  if (ct <= kShortHead) {
+    int spc = kMinChunks;
+    while (spc < ct && 2048ll * spc < ct * BH) spc *= 2;
+    const int splits = (int)((ct + spc - 1) / spc);
+    return {Deal::kHead, BH * (splits > 0 ? splits : 1), spc};
+  }
+  const long long nw = (ct * BH + kMinChunks - 1) / kMinChunks, most = BH > 64 ? 896 : BH < 4 ? 256 * BH : 1024;
+  return {BH > 64 ? Deal::kBlock : Deal::kWave, (int)(nw < most ? nw : most), 0};
+}
+long long bound_chunks(int max_rows, int window) {
+  return ((long long)max_rows + kChunkRows - 1) / kChunkRows + ((long long)window + kChunkRows - 1) / kChunkRows;
 }
 
-int attend_splits(int BH, int max_rows, int window) {
-  const int ct = (max_rows + kChunkRows - 1) / kChunkRows +
-                 ((window > 0 ? window : 0) + kChunkRows - 1) / kChunkRows;
-  const int spc = attend_split_chunks(BH, max_rows, window);
-  const int ns = (ct + spc - 1) / spc;
-  return ns > 0 ? ns : 1;
-}
-
-namespace {
-size_t splits_bytes(int BH, int G, long long splits) {
-  const size_t slots = (size_t)BH * splits * G;
-  return align_up(slots * kD * sizeof(float), 256) + align_up(slots * 2 * sizeof(float), 256);
+struct Layout {
+  size_t ml, span, bytes;                // of the workspace: sums, then references and denominators, then spans
+};
+// Room for the slots of any bound up to ct chunks: a part of the list has fewer than nw + BH segments, and
+// splits of spc >= ct * BH / 2048 chunks are no more than BH + 2048.
+Layout layout_of(int BH, int G, long long ct) {
+  const long long parts = (ct * BH + kMinChunks - 1) / kMinChunks;
+  const size_t slots = (size_t)((parts < 2048 ? parts : 2048) + BH) * G;
+  Layout l;
+  l.ml = align_up(slots * kD * sizeof(float), 256);
+  l.span = l.ml + align_up(slots * 2 * sizeof(float), 256);
+  l.bytes = l.span + align_up((size_t)BH * sizeof(int2), 256);
+  return l;
 }
 }  // namespace
 
 size_t attend_workspace_bytes(int B, int H, int HQ, int max_rows, int window) {
-  return splits_bytes(B * H, HQ / H, attend_splits(B * H, max_rows, window));
-}
-
-// A longer bound can mean fewer splits (they double in length): what the largest of the bounds up
-// to this one takes, so that a workspace queried for the longest serves them all.  ct of the
-// longest list that attend_split_chunks cuts into splits of spc chunks or fewer.
-size_t attend_workspace_query(int B, int H, int HQ, int max_rows, int window) {
-  const long long BH = (long long)B * H;
-  const long long ct = ((long long)max_rows + kChunkRows - 1) / kChunkRows + ((long long)window + kChunkRows - 1) / kChunkRows;
-  long long most = 1;
-  for (int spc = 4; spc <= 64; spc *= 2) {
-    const long long filled = (2048ll * (spc + 1) - 1) / BH;
-    const long long folded = std::max(96ll * (spc + 1) - 1, (512ll * spc - 1) / BH);
-    const long long longest = spc < 64 ? std::min(ct, std::min(filled, folded)) : ct;
-    most = std::max(most, (longest + spc - 1) / spc);
-  }
-  return splits_bytes(B * H, HQ / H, most);
+  return layout_of(B * H, HQ / H, bound_chunks(max_rows, window)).bytes;
 }
 
 int launch_attend_decode(const void* q, const void* K_rows, const void* V_rows,
@@ -460,12 +602,13 @@ int launch_attend_decode(const void* q, const void* K_rows, const void* V_rows,
                          void* out, int B, int H, int HQ, void* workspace,
                          hipStream_t stream) {
   const int G = HQ / H, BH = B * H;
-  const int NS = attend_splits(BH, max_rows, window);
-  const int spc = attend_split_chunks(BH, max_rows, window);
-  const size_t slots = (size_t)BH * NS * G;
-  float* part = static_cast<float*>(workspace);
-  float* ml = reinterpret_cast<float*>(static_cast<char*>(workspace) +
-                                       align_up(slots * kD * sizeof(float), 256));
+  const long long ct = bound_chunks(max_rows, window);
+  const Dealt dealt = deal_of(BH, ct);
+  const Layout lay = layout_of(BH, G, ct);
+  char* const ws = static_cast<char*>(workspace);
+  float* part = reinterpret_cast<float*>(ws);
+  float* ml = reinterpret_cast<float*>(ws + lay.ml);
+  int2* span = reinterpret_cast<int2*>(ws + lay.span);
   const float cscale = scale * 1.4426950408889634f;
   const bool paged = block_table != nullptr;
   int log_page = 0;
@@ -477,20 +620,26 @@ int launch_attend_decode(const void* q, const void* K_rows, const void* V_rows,
   const auto* vv = static_cast<const u32x4*>(V_rows);
   const auto* kr = static_cast<const u32x4*>(K_ring);
   const auto* vr = static_cast<const u32x4*>(V_ring);
-  const unsigned ny = NS < 65535 ? NS : 65535;
-  const dim3 grid(BH, ny, (NS + ny - 1) / ny);
-  if (paged)
-    hipLaunchKernelGGL(attend_partial_kernel<true>, grid, dim3(64), 0, stream, qv, kv, vv,
-                       cap_rows, nullptr, block_table, max_pages, log_page, num_pages, lengths, kr,
-                       vr, seq_pos, window, cscale, H, G, NS, spc, part, ml);
-  else
-    hipLaunchKernelGGL(attend_partial_kernel<false>, grid, dim3(64), 0, stream, qv, kv, vv,
-                       cap_rows, row_offsets, nullptr, 0, 0, 0, lengths, kr, vr, seq_pos, window,
-                       cscale, H, G, NS, spc, part, ml);
+  auto launch = [&](auto kernel) {
+    const int waves = waves_of(dealt.deal);
+    kernel<<<(dealt.nw + waves - 1) / waves, waves * 64, 0, stream>>>(
+        qv, kv, vv, cap_rows, paged ? nullptr : row_offsets, block_table, max_pages, log_page, num_pages,
+        lengths, kr, vr, seq_pos, window, cscale, BH, H, G, dealt.nw, dealt.spc, part, ml, span);
+  };
+  switch (dealt.deal) {
+    case Deal::kHead: launch(paged ? attend_partial_kernel<true, Deal::kHead> : attend_partial_kernel<false, Deal::kHead>); break;
+    case Deal::kWave: launch(paged ? attend_partial_kernel<true, Deal::kWave> : attend_partial_kernel<false, Deal::kWave>); break;
+    case Deal::kBlock: launch(paged ? attend_partial_kernel<true, Deal::kBlock> : attend_partial_kernel<false, Deal::kBlock>); break;
+  }
   if (hipGetLastError() != hipSuccess) return KVZAP_ERR_RUNTIME;
-  hipLaunchKernelGGL(attend_combine_kernel, dim3(BH * G), dim3(256), 0, stream, part, ml,
-                     cap_rows, paged ? nullptr : row_offsets, lengths, seq_pos, window, H, G, NS,
-                     spc, static_cast<unsigned short*>(out));
+  const int64_t* offsets = paged ? nullptr : row_offsets;
+  auto* bits = static_cast<unsigned short*>(out);
+  if (dealt.nw / BH > 128)                               // one KV head's hundreds of slots: 24 us with 8 groups
+    attend_combine_kernel<32><<<BH * G, 1024, 0, stream>>>(part, ml, span, cap_rows, offsets, lengths,
+                                                           seq_pos, window, H, G, bits);
+  else
+    attend_combine_kernel<8><<<BH * G, 256, 0, stream>>>(part, ml, span, cap_rows, offsets, lengths,
+                                                         seq_pos, window, H, G, bits);
   if (hipGetLastError() != hipSuccess) return KVZAP_ERR_RUNTIME;
   return KVZAP_OK;
 }

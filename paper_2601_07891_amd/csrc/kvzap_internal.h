@@ -323,6 +323,5 @@ int launch_compact_paged(const void* K, const void* V, const int32_t* keep_idx,
                          void* V_pool, int num_pages, int BH, int T, int D, hipStream_t stream);
 // what a call takes, and what is asked for: enough for every smaller bound as well
 size_t attend_workspace_bytes(int B, int H, int HQ, int max_rows, int window);
-size_t attend_workspace_query(int B, int H, int HQ, int max_rows, int window);
 
 }  // namespace kvzap

@@ -226,3 +226,21 @@ def test_rejects_bad_arguments():
     assert call(ws_bytes=16) == -6    # workspace too small
     assert call(ring=False) == -1     # window > 0 without ring pointers
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("B,H,top,window,max_rows", [
+    (16, 4, 900, 128, None),      # 64 heads: every wavefront finds its part for itself
+    (13, 5, 900, 40, None),       # 65: with its block
+    (65, 4, 150, 0, 5000),        # 260 heads, parts of many short ones under a long bound
+    (130, 4, 60, 33, None),       # a wavefront per split of one head
+    (3, 2, 3000, 0, 10),          # ... the last of which goes past the bound
+    (1, 1, 40000, 128, None),     # one head's hundreds of parts are combined by 32 groups
+])
+def test_rows_are_dealt_out_whole(B, H, top, window, max_rows):
+    # every third head is empty, so that parts begin, end and pass over heads everywhere
+    rng = np.random.default_rng(B * 1000 + H)
+    lengths = rng.integers(0, top + 1, size=(B, H))
+    lengths[rng.random((B, H)) < 0.33] = 0
+    lengths[-1, -1] = top
+    seq_pos = rng.integers(0, 200, size=B).tolist() if window else None
+    _run_case(lengths, window, seq_pos, HQ=2 * H, seed=B + H, max_rows=max_rows)
