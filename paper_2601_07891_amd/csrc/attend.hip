@@ -190,13 +190,6 @@ __device__ __forceinline__ float shfl_xor_f(float x, int mask) {
   return __shfl_xor(x, mask, 64);
 }
 
-// The wavefront's LDS operations complete in order: a fence for the compiler is all that has to stand
-// between one lane's write and another lane's read.
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 __device__ __forceinline__ void consume_chunk(const Chunk& c, const u32x4 (&qb)[4], Accum& a, u32x4* turn,
                                               int row0, int n_seg, int li, int lg, float cscale) {
   wave_fence();                                          // the reads of the chunk before

@@ -86,6 +86,13 @@ __device__ __forceinline__ void load_to_lds_b128_stream(const void* base, unsign
                : "memory");
 }
 
+// The wavefront's LDS operations complete in order: a fence for the compiler is all that has to stand
+// between one lane's write and another lane's read.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ unsigned lds_address(const void* p) {
   return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }

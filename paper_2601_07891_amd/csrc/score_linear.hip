@@ -8,14 +8,11 @@
 // v_mfma_f32_16x16x32_bf16 with tokens on the N side and heads (padded to 16) on
 // the M side:
 //   A (16 x 32)  = W rows (heads) from LDS, staged once per block
-//   B (32 x 16)  = 16 tokens x 32 inputs, loaded straight from global memory in
-//                  the instruction's operand layout (lane = token + 16*k-group,
-//                  16 bytes per lane), no LDS round trip for the streamed data.
-//                  Ordinary (cached) loads on purpose: a 128-byte line is
-//                  consumed by two consecutive load instructions of the same
-//                  wavefront, and with the non-temporal hint the second one
-//                  fetched the line again (5.1 instead of 6.0 TB/s measured;
-//                  a pure read stream reaches 6.0-6.4 TB/s on this part)
+//   B (32 x 16)  = 16 tokens x 32 inputs in the instruction's operand layout (lane = token +
+//                  16*k-group, 16 bytes per lane): long inputs in whole lines through LDS
+//                  (score_linear_stream_kernel), others straight from global memory.  That way a
+//                  128-byte line is consumed by two consecutive load instructions, and with the
+//                  non-temporal hint the second one fetches it again (5.1 instead of 6.0 TB/s)
 //   C (16 x 16)  = fp32 accumulators, heads 0..15 x 16 tokens
 // Each wavefront owns groups of 16 consecutive tokens and walks the whole D_h.
 #include "kvzap_internal.h"
@@ -119,6 +116,178 @@ __global__ __launch_bounds__(kThreads) void score_linear_kernel(
       }
     }
   }
+}
+
+// Long inputs: the same contraction with the tokens as a stream of whole lines.  A load instruction
+// takes 256 bytes of each of four rows with the non-temporal hint, the form in which this part's
+// memory gives 7.0 TB/s (6.0 with the 64 bytes of a row that the operand layout asks for, hint or not),
+// and the wavefront turns them into that layout through 4 KB of LDS of its own, pieces XOR-swizzled with
+// the row.  One block per CU; a wavefront's groups of 16 tokens are one stream of stages of 256 inputs,
+// the next stage loading while the current one is multiplied.
+//   Scores wait in LDS until the wavefront is through (or its share of the LDS is full): stored group
+// by group, their 0.3 % of the bytes, 64 at a time, took 7 % of the time.
+//   Blocks start at different inputs of a row, those of one XCD (every eighth) and neighbours alike: where
+// rows are 2^n bytes long, blocks that walk D_h in step read from the same few memory channels (32768 x
+// 4096: in step 48 us, with the block index alone as the shift 63, with this one 44).
+constexpr int kStreamWaves = 8, kStreamBlocks = 256;
+constexpr int kTurnBytes = 16 * 256;
+
+__global__ __launch_bounds__(kStreamWaves * 64, 2) void score_linear_stream_kernel(
+    const unsigned char* __restrict__ hidden, const unsigned short* __restrict__ W,
+    const unsigned short* __restrict__ bias, float* __restrict__ scores, long long rows, int T, int Dh, int H,
+    int held) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  u32x4* sW = reinterpret_cast<u32x4*>(smem);            // [H][Dh/8 + 4], as above
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int threads = blockDim.x, waves = threads / 64;
+  const int pieces_per_row = Dh / 8, lds_stride = pieces_per_row + 4;
+  unsigned char* const own = smem + (size_t)H * lds_stride * 16 + (size_t)wid * (kTurnBytes + held * H * 64);
+  u32x4* const turn = reinterpret_cast<u32x4*>(own);
+  float* const done = reinterpret_cast<float*>(own + kTurnBytes);          // [H][held * 16]
+  const int col = lane & 15, kg = lane >> 4;
+  const long long ngroups = (rows + 15) / 16;
+  // the block's groups go round its wavefronts: next to each other in memory at any time
+  const long long g0 = ngroups * blockIdx.x / gridDim.x + wid, g1 = ngroups * (blockIdx.x + 1) / gridDim.x;
+  const int steps = Dh / 32, per_group = (steps + 7) / 8;
+  const int n = g0 < g1 ? (int)((g1 - g0 + waves - 1) / waves) * per_group : 0;
+  const int k_first = (int)((3 * (blockIdx.x / 8) + blockIdx.x % 8) % (unsigned)per_group);
+
+  long long g_in = g0;
+  int k_in = k_first, left_in = per_group;
+  unsigned row_off[4];
+  auto enter_group = [&]() {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = 4 * i + kg;                        // past the end: clamped, result discarded
+      row_off[i] = (unsigned)(rows - g_in * 16 > row ? row : (int)(rows - g_in * 16) - 1) * (unsigned)Dh * 2u;
+    }
+  };
+  auto load = [&](u32x4 (&v)[8]) {
+    const unsigned char* base = hidden + (size_t)g_in * 16 * Dh * 2;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      unsigned at = (unsigned)(k_in * 512 + (u >> 2) * 256 + col * 16);
+      at = at < (unsigned)Dh * 2u - 16u ? at : (unsigned)Dh * 2u - 16u;    // past D_h: not multiplied
+      v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (row_off[u & 3] + at)));
+    }
+    if (++k_in == per_group) k_in = 0;
+    if (--left_in == 0) {
+      left_in = per_group;
+      g_in += waves;
+      if (g_in < g1) enter_group();
+    }
+  };
+  u32x4 va[8], vb[8];
+  if (n > 0) {
+    enter_group();
+    load(va);
+  }
+
+  const int total_pieces = H * pieces_per_row;
+  for (int base = 0; base < total_pieces; base += threads * 8) {
+    u32x4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = base + u * threads + (int)threadIdx.x;
+      v[u] = reinterpret_cast<const u32x4*>(W)[i < total_pieces ? i : total_pieces - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = base + u * threads + (int)threadIdx.x;
+      if (i < total_pieces) {
+        const int h = i / pieces_per_row, p = i - h * pieces_per_row;
+        sW[h * lds_stride + p] = v[u];
+      }
+    }
+  }
+  __syncthreads();
+  if (n == 0) return;
+
+  const bool head_ok = col < H;
+  const u32x4* const sWrow = sW + (size_t)(col % H) * lds_stride + kg;
+  const u32x4 zero4 = {0u, 0u, 0u, 0u};
+  // Eight sums, one for each of a stage's products, folded into one every eight stages: a product does
+  // not wait for the one before it, and the chains of additions are short (one chain through D_h = 4096:
+  // 3e-7 of the exact scores, like this 8e-8).
+  floatx4 acc[2][4], folded = {0.f, 0.f, 0.f, 0.f}, bias4;
+  auto clear = [&]() {
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) acc[half][kk] = floatx4{0.f, 0.f, 0.f, 0.f};
+  };
+  clear();
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    bias4[e] = bias ? bf16_bits_to_float(bias[4 * kg + e < H ? 4 * kg + e : H - 1]) : 0.0f;
+  long long g_at = g0;                                   // first group whose scores are held
+  int k_at = k_first, left_at = per_group, have = 0;
+  auto flush = [&]() {
+    wave_fence();
+    for (int i = lane; i < have * 16; i += 64) {
+      const long long r = (g_at + (i >> 4) * waves) * 16 + (i & 15);
+      if (r < rows) {
+        const long long bidx = r / T;
+        float* to = scores + (size_t)bidx * H * T + (r - bidx * T);
+        for (int h = 0; h < H; ++h) to[(size_t)h * T] = done[h * held * 16 + i];
+      }
+    }
+    wave_fence();
+    g_at += (long long)have * waves;
+    have = 0;
+  };
+  auto consume = [&](const u32x4 (&v)[8]) {
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      wave_fence();                                      // the reads of the half before
+#pragma unroll
+      for (int i = 0; i < 4; ++i) turn[(4 * i + kg) * 16 + (col ^ (4 * i + kg))] = v[half * 4 + i];
+      wave_fence();
+      u32x4 a[4], b[4];
+      const int s0 = k_at * 8 + half * 4;                // MFMA step of D_h
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        b[kk] = turn[col * 16 + ((4 * kk + kg) ^ col)];
+        const u32x4 w = sWrow[(size_t)(s0 + kk < steps ? s0 + kk : steps - 1) * 4];
+        a[kk] = head_ok ? w : zero4;
+      }
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        if (s0 + kk < steps)                             // uniform
+          acc[half][kk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(bf16x8, a[kk]), __builtin_bit_cast(bf16x8, b[kk]), acc[half][kk], 0, 0, 0);
+    }
+    if (++k_at == per_group) k_at = 0;
+    --left_at;
+    if ((left_at & 7) == 0) {
+      folded += ((acc[0][0] + acc[0][1]) + (acc[0][2] + acc[0][3])) + ((acc[1][0] + acc[1][1]) + (acc[1][2] + acc[1][3]));
+      clear();
+    }
+    if (left_at == 0) {                                  // C: token `col` of the group, heads 4*kg + e
+      left_at = per_group;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * kg + e < H) done[((4 * kg + e) * held + have) * 16 + col] = folded[e] + bias4[e];
+      folded = floatx4{0.f, 0.f, 0.f, 0.f};
+      if (++have == held) flush();
+    }
+  };
+  int i = 0;
+  while (i + 2 < n) {
+    load(vb);
+    consume(va);
+    load(va);
+    consume(vb);
+    i += 2;
+  }
+  if (i + 1 < n) {
+    load(vb);
+    consume(va);
+    consume(vb);
+  } else {
+    consume(va);
+  }
+  flush();
 }
 
 // Short inputs (up to 512 groups of 16 tokens) that the kernel below does not take, with more than eight heads or a
@@ -282,18 +451,59 @@ int launch_linear(const void* hidden, const void* W, const void* b, float* score
   return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
 }
 
+// Wavefronts of a block, as many as W leaves room for, and the groups whose scores each can hold (0: no room)
+struct Stream {
+  int waves, held;
+};
+Stream stream_of(int Dh, int H) {
+  const long long room = 160 * 1024 - (long long)H * ((long long)Dh * 2 + 64);
+  for (int waves = kStreamWaves; waves >= 4; waves -= 2) {
+    const long long held = (room / waves - kTurnBytes) / (H * 64);
+    if (held > 0) return {waves, (int)(held < 16 ? held : 16)};
+  }
+  return {0, 0};
+}
+
+int launch_linear_stream(const void* hidden, const void* W, const void* b, float* scores, long long rows,
+                         int T, int Dh, int H, Stream st, hipStream_t stream) {
+  // once per process, which drives one GPU (thread-safe: a function-local static)
+  static const hipError_t attr_rc =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(score_linear_stream_kernel),
+      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (attr_rc != hipSuccess) return KVZAP_ERR_RUNTIME;
+  const size_t lds = (size_t)H * ((size_t)Dh * 2 + 64) + (size_t)st.waves * (kTurnBytes + st.held * H * 64);
+  score_linear_stream_kernel<<<kStreamBlocks, st.waves * 64, lds, stream>>>(
+      static_cast<const unsigned char*>(hidden), static_cast<const unsigned short*>(W),
+      static_cast<const unsigned short*>(b), scores, rows, T, Dh, H, st.held);
+  return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
+}
+
 }  // namespace
+
+// The kernel over whole lines from 30 MB on: below, staging W in every block costs more than the
+// streaming gains.  us per call (it / the kernels it takes the place of), H = 8 unless named: 262144 x 5120 402
+// (6.7 TB/s) / 450, 131072 x 4096 160 / 195, 65536 x 4096 87 / 103, x 2048 46 / 57, 32768 x 4096 44 / 55, 20000 x
+// 5120 37 / 55, 16384 x 4096 24 / 30, 10000 x 2048 11.0 / 12.2; 40000 x 8192 109 / 143;
+// 14 heads 8192 x 4096 15.5 / 20.3; one head 262144 x 4096 317 / 375, 20000 x 1024 10.6 / 12.0; not taken:
+// 12000 x 1024 8.5 / 8.3, 12000 x 512 6.5 / 5.6, two heads 6500 x 2048 9.2 / 8.8.
+// Against the row kernel it wins once that one's blocks, which fill a CU's LDS, come in a third round:
+// 4096 x 4096 13.1 / 10.5, 4500: 13.7 / 13.7, 8192: 14.5 / 19.0, 5000 x 3072 11.6 / 12.6, 8192 x 5120 17.9 / 22.0.
+constexpr long long kStreamBytes = 30000000;
 
 int launch_score_linear(const void* hidden, const void* W, const void* b, float* scores,
                         int B, int T, int Dh, int H, hipStream_t stream) {
   const long long rows = (long long)B * T;
   const long long ngroups = (rows + 15) / 16;
-  if (H <= kRowTokens && Dh <= kRowMaxWaves * kRowInputs && rows <= (H <= 2 ? kRowMaxTokensFewHeads : kRowMaxTokens))
-    return launch_linear_rows(hidden, W, b, scores, rows, T, Dh, H, stream);
-  // from 64k tokens: 16-wavefront blocks (W is staged into LDS once per block, and 16 x 8
-  // loads in flight per block are what the HBM stream needs: 128k tokens 194 us against
-  // 205 us with small blocks); shorter inputs: 4-wavefront blocks so that more CUs take part
-  // (32k tokens: 60 us against 69 us)
+  const Stream st = stream_of(Dh, H);
+  const bool long_enough = st.held > 0 && ngroups > 256 && rows * Dh * 2 >= kStreamBytes;
+  if (H <= kRowTokens && Dh <= kRowMaxWaves * kRowInputs && rows <= (H <= 2 ? kRowMaxTokensFewHeads : kRowMaxTokens)) {
+    const int per_cu = kRowMaxWaves / ((Dh + kRowInputs - 1) / kRowInputs);          // blocks that the LDS holds
+    if (!long_enough || rows <= 18ll * per_cu * kStreamBlocks)                       // 2.25 rounds of 8 tokens
+      return launch_linear_rows(hidden, W, b, scores, rows, T, Dh, H, stream);
+  }
+  if (long_enough) return launch_linear_stream(hidden, W, b, scores, rows, T, Dh, H, st, stream);
+  // where W leaves that kernel no room or the input is short; from 64k tokens 16-wavefront blocks (W is
+  // staged into LDS once per block), shorter inputs 4-wavefront blocks so that more CUs take part
   if (ngroups >= 4096) return launch_linear<1024, 8>(hidden, W, b, scores, rows, T, Dh, H, 1024, stream);
   if (ngroups > 512 || Dh % 128 != 0)       // 16k tokens: 26 us with the kernel above, 32 us here
     return launch_linear<256, 8>(hidden, W, b, scores, rows, T, Dh, H, 1024, stream);

@@ -1,4 +1,4 @@
-"""The linear surrogate on short inputs, loaded row by row: at the edges of its 8-token blocks, with
+"""The linear surrogate on short inputs, loaded row by row, and on long ones, streamed: at the edges of its 8-token blocks, with
 widths that end inside a wavefront's 512 inputs, fewer heads than eight, and batches whose sequences
 end inside a block.  fp32 sums of bf16 products over D_h: within 2 * sqrt(D_h) * 2^-24 of the sum of
 the products' magnitudes (a random walk of roundings, with a factor for its tail)."""
@@ -27,3 +27,26 @@ def test_against_float64(B, T, Dh, H, bias):
     want = x64 @ W64.t() + (0 if b is None else b.double())
     size = x64.abs() @ W64.abs().t() + 1.0
     assert ((got.transpose(1, 2) - want).abs() <= 2 * Dh ** 0.5 * 2.0 ** -24 * size).all()
+
+
+@pytest.mark.parametrize("B,T,Dh,H", [
+    (1, 4609, 4096, 8),           # the first input of a third round of row blocks
+    (1, 3663, 4096, 9), (1, 4112, 4096, 9), (1, 5001, 4096, 16),       # more heads than the row kernel's
+    (3, 2731, 4160, 8), (1, 9999, 2112, 3),                            # D_h ends inside a stage
+    (1, 6145, 8192, 8), (1, 4400, 8960, 8),                            # W leaves room for 6 and 4 wavefronts
+    (2, 40001, 448, 1), (7, 33500, 64, 5),                             # one and a half stages a row; less than one
+    (1, 32768, 512, 8),
+])
+@pytest.mark.parametrize("bias", [False, True])
+def test_long_inputs_against_float64(B, T, Dh, H, bias):
+    g = torch.Generator(device=DEV).manual_seed(B * T + Dh)
+    x = torch.randn((B, T, Dh), generator=g, device=DEV).bfloat16()
+    W = (torch.randn((H, Dh), generator=g, device=DEV) * Dh ** -0.5).bfloat16()
+    b = torch.randn(H, generator=g, device=DEV).bfloat16() if bias else None
+    got = binding.kvzap_score(x, W, b, None, None).double()
+    W64 = W.double()
+    for i in range(B):
+        x64 = x[i].double()
+        want = x64 @ W64.t() + (0 if b is None else b.double())
+        size = x64.abs() @ W64.abs().t() + 1.0
+        assert ((got[i].t() - want).abs() <= 2 * Dh ** 0.5 * 2.0 ** -24 * size).all()
