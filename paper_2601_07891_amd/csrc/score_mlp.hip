@@ -338,13 +338,14 @@ __device__ __forceinline__ void wait_lds_fragment(bf16x8& frag) {
 
 // UB 32-unit blocks per wavefront, TB 32-token blocks per block; kSplit: the block covers one
 // K-slice (blockIdx.y) and writes its part of the first projection to `partial`
-template <int UB, int TB, bool kNorm, bool kSplit = false>
+template <int UB, int TB, bool kNorm, bool kSplit = false, bool kStates = false>
 __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
     const unsigned short* hidden, const unsigned char* W1f,   // not __restrict__: their loads must stay ordered w.r.t. the waits
     const unsigned short* __restrict__ b1, const unsigned short* __restrict__ W2,
     const unsigned short* __restrict__ b2, float* __restrict__ scores,
     long long rows, int T, int Dh, int H, int nk, float* __restrict__ partial, NormArgs norm) {
   static_assert(!(kSplit && kNorm), "the normalising form is not cut over K");
+  static_assert(kNorm || !kStates, "the normalised states belong to the normalising form");
   constexpr int U = 128 * UB;
   constexpr int TOK = 32 * TB;               // tokens per block
   constexpr int STAGE = TOK * 128;           // bytes per LDS stage (TOK rows of one K tile)
@@ -402,9 +403,13 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
   const unsigned lds0 = lds_address(smem);
   auto dma = [&](int j, int tile) {
     // streamed (non-temporal): every hidden byte is read once, while the W1 fragments that all
-    // blocks share have to stay in the same L2; measured 2 % on the launch
-    load_to_lds_b128_stream(hb + (size_t)tile * (kBK * 2), h_off[j],
-                            lds0 + (unsigned)((tile % kNS) * STAGE + (j * 4 + wid) * 1024));
+    // blocks share have to stay in the same L2; measured 2 % on the launch.  Where the states are
+    // written the block reads its rows again, and finds what was loaded without the hint in the
+    // memory-side cache: 30011 x 4096 192 -> 178 us, 131072 x 4096 782 -> 728, 65536 x 5120 610 -> 564,
+    // 60000 x 2048 164 -> 145.
+    const unsigned to = lds0 + (unsigned)((tile % kNS) * STAGE + (j * 4 + wid) * 1024);
+    if constexpr (kStates) load_to_lds_b128(hb + (size_t)tile * (kBK * 2), h_off[j], to);
+    else load_to_lds_b128_stream(hb + (size_t)tile * (kBK * 2), h_off[j], to);
   };
   // A fragments of this wavefront: unit blocks rb = wid*UB + ub; fragment (ub, kk) of K tile t
   // is the KB at  abase + t*kATile + (ub*4 + kk)*1024, 16 bytes per lane.  They are loaded
@@ -826,25 +831,21 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
       scores[((size_t)bidx * H + head) * T + t] = s;
     }
   }
-  if constexpr (kNorm) {
-    if (norm.normed) {
-      // the normalised states for the layer's own projections: the row scale is known only
-      // now, so the block goes over its rows a second time (x * rstd * gain, rounded to bf16)
-      float* sR = reinterpret_cast<float*>(sW2 + 16 * U * 2);     // [TOK]
-      if (wid == 0 && kg == 0) {
+  if constexpr (kStates) {
+    // the normalised states for the layer's own projections: the row scale is known only
+    // now, so the block goes over its rows a second time (x * rstd * gain, rounded to bf16)
+    float* sR = reinterpret_cast<float*>(sW2 + 16 * U * 2);     // [TOK]
+    if (wid == 0 && kg == 0) {
 #pragma unroll
-        for (int tb = 0; tb < TB; ++tb) sR[32 * tb + l32] = rs[tb];
-      }
-      __syncthreads();
-      const u32x4* xin = reinterpret_cast<const u32x4*>(hidden + (size_t)row0 * Dh);
-      u32x4* yout = reinterpret_cast<u32x4*>(norm.normed + (size_t)row0 * Dh);
-      const u32x4* gain8 = reinterpret_cast<const u32x4*>(norm.gain);
-      // 4 to 8 KB of a row at a time, which divides D_h where M = D_h / 8, two or four rows ahead.
-      // 30011 tokens: the whole call 223 -> 191 us, of which this part 108 -> 76 (6.4 TB/s); before,
-      // eight loads, their wait and the stores followed one another, with a division per piece.
-      constexpr int kColumns = UB == 5 ? 5 : UB == 4 ? 8 : 4;
-      write_states<4, kColumns, UB == 4 ? 2 : 4>(xin, yout, gain8, sR, rows_here, Dh / 8, wid, lane);
+      for (int tb = 0; tb < TB; ++tb) sR[32 * tb + l32] = rs[tb];
     }
+    __syncthreads();
+    const u32x4* xin = reinterpret_cast<const u32x4*>(hidden + (size_t)row0 * Dh);
+    u32x4* yout = reinterpret_cast<u32x4*>(norm.normed + (size_t)row0 * Dh);
+    const u32x4* gain8 = reinterpret_cast<const u32x4*>(norm.gain);
+    // 4 or 5 KB of a row at a time, which divides D_h where M = D_h / 8, four rows ahead
+    // (131072 x 4096: 8 KB and two rows 753 us, this 728; 16384 x 4096 125 and 127)
+    write_states<4, UB == 5 ? 5 : 4, 4>(xin, yout, gain8, sR, rows_here, Dh / 8, wid, lane);
   }
 }
 
@@ -934,14 +935,14 @@ int launch_frag(const void* hidden, const void* W1f, const void* b1, const void*
   // + W2 as [16][M] fp16, then (normalising form) the row scales, b1 and the sums of squares as fp32
   constexpr size_t lds = ring + (size_t)16 * (128 * UB) * 2 + TOK * sizeof(float) +
                          (128 * UB) * sizeof(float) + TOK * sizeof(float) + 16 * sizeof(float);   // + b2
-  auto launch = [&](auto split) {
-    constexpr bool kSplit = decltype(split)::value;
+  auto launch = [&](auto split, auto states) {
+    constexpr bool kSplit = decltype(split)::value, kStates = decltype(states)::value;
     // once per process, which drives one GPU (thread-safe: a function-local static)
     static const hipError_t attr_rc =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(score_mlp_frag_kernel<UB, TB, kNorm, kSplit>),
+        hipFuncSetAttribute(reinterpret_cast<const void*>(score_mlp_frag_kernel<UB, TB, kNorm, kSplit, kStates>),
         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (attr_rc != hipSuccess) return KVZAP_ERR_RUNTIME;
-    score_mlp_frag_kernel<UB, TB, kNorm, kSplit><<<dim3((unsigned)((rows + TOK - 1) / TOK), ks), 256, lds, stream>>>(
+    score_mlp_frag_kernel<UB, TB, kNorm, kSplit, kStates><<<dim3((unsigned)((rows + TOK - 1) / TOK), ks), 256, lds, stream>>>(
         static_cast<const unsigned short*>(hidden), static_cast<const unsigned char*>(W1f),
         static_cast<const unsigned short*>(b1), static_cast<const unsigned short*>(W2),
         static_cast<const unsigned short*>(b2), scores, rows, T, Dh, H, Dh / kBK / ks, partial, norm);
@@ -949,12 +950,15 @@ int launch_frag(const void* hidden, const void* W1f, const void* b1, const void*
   };
   if constexpr (!kNorm) {
     if (ks > 1) {
-      const int rc = launch(std::true_type{});
+      const int rc = launch(std::true_type{}, std::false_type{});
       if (rc != KVZAP_OK) return rc;
       return launch_finish(partial, b1, W2, b2, scores, rows, T, 128 * UB, H, ks, stream);
     }
   }
-  return launch(std::false_type{});
+  if constexpr (kNorm) {
+    if (norm.normed) return launch(std::false_type{}, std::true_type{});
+  }
+  return launch(std::false_type{}, std::false_type{});
 }
 
 template <bool kNorm>
