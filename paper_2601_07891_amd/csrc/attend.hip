@@ -270,17 +270,6 @@ constexpr int kMaxBatches = 1024;        // of 64 heads: B*H <= 65535
 enum class Deal { kWave, kBlock, kHead };
 constexpr int waves_of(Deal d) { return d == Deal::kBlock ? 4 : 1; }
 
-// inclusive sum over the lanes before and at this one
-__device__ __forceinline__ int wave_scan(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);    // row_shr:1, 2, 4, 8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15, 31
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
-  return v;
-}
-
 template <bool kPaged, Deal kDeal>
 __global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_partial_kernel(
     const u32x4* q, const u32x4* K_rows, const u32x4* V_rows, int64_t cap_rows,

@@ -96,13 +96,9 @@ __global__ __launch_bounds__(kThreads) void mask_count_kernel(
   const float* row = scores + (size_t)bh * T;
   const bool vec_ok = (T % 4) == 0;
   const int t0 = chunk * kMaskChunk + threadIdx.x * kPerThread;
-  const int c = __popc(keep_bits4(row, t0, T, Tb, window, tau, vec_ok));
-  // block sum: wave reduce then LDS
-  int v = c;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  const int v = wave_scan(__popc(keep_bits4(row, t0, T, Tb, window, tau, vec_ok)));
   __shared__ int wave_sum[kThreads / 64];
-  if ((threadIdx.x & 63) == 0) wave_sum[threadIdx.x >> 6] = v;
+  if ((threadIdx.x & 63) == 63) wave_sum[threadIdx.x >> 6] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
     int tot = 0;
@@ -156,19 +152,9 @@ __global__ __launch_bounds__(kScanThreads) void mask_scan_kernel(
 
 constexpr int kFusedMaxChunks = 8192;
 
-// block-wide sum of a 64-bit value (all threads get the result)
-__device__ __forceinline__ long long block_sum_i64(long long v, long long* lds_scratch) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) lds_scratch[threadIdx.x >> 6] = v;
-  __syncthreads();
-  long long s = 0;
-#pragma unroll
-  for (int w = 0; w < kThreads / 64; ++w) s += lds_scratch[w];
-  return s;
-}
-
+// The kernel is a chain of memory round trips: the scores and the counts are loaded side by side, the
+// counts four to a load (one by one, the last of 1024 chunks made four dependent trips), and both of a
+// head's sums meet at one barrier.  Mask and gather of 8 x 131072 scores 52.9 -> 51.5 us.
 template <bool kFused>
 __global__ __launch_bounds__(kThreads) void mask_emit_kernel(
     const float* __restrict__ scores, float tau_all, const float* __restrict__ tau_head, int window,
@@ -176,50 +162,55 @@ __global__ __launch_bounds__(kThreads) void mask_emit_kernel(
     const int64_t* __restrict__ chunk_prefix, const int32_t* __restrict__ chunk_counts,
     int32_t* __restrict__ keep_idx, int32_t* __restrict__ lengths,
     int64_t* __restrict__ offsets) {
+  constexpr int kWaves = kThreads / 64;
   const int chunk = blockIdx.x, bh = blockIdx.y;
-  long long my_prefix;
-  if (kFused) {
-    __shared__ long long scratch[kThreads / 64];
-    const int BH = gridDim.y;
-    const int mine = bh * nchunks + chunk;               // chunks are ordered (b,h)-major
-    long long before = 0;
-    for (int i = threadIdx.x; i < mine; i += kThreads) before += chunk_counts[i];
-    my_prefix = block_sum_i64(before, scratch);
-    if (chunk == 0) {                                    // this head's length and start
-      long long own = 0;
-      for (int i = threadIdx.x; i < nchunks; i += kThreads) own += chunk_counts[mine + i];
-      const long long head_total = block_sum_i64(own, scratch);
-      if (threadIdx.x == 0) {
-        offsets[bh] = my_prefix;
-        lengths[bh] = (int32_t)head_total;
-        if (bh == BH - 1) offsets[BH] = my_prefix + head_total;
-      }
-    }
-  } else {
-    my_prefix = chunk_prefix[(size_t)bh * nchunks + chunk];
-  }
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const float tau = tau_head ? tau_head[bh] : tau_all;
   const int Tb = seq_len_of(seq_lens, bh / H, T);
   const float* row = scores + (size_t)bh * T;
   const bool vec_ok = (T % 4) == 0;
   const int t0 = chunk * kMaskChunk + threadIdx.x * kPerThread;
-  const unsigned bits = keep_bits4(row, t0, T, Tb, window, tau, vec_ok);
-  const int c = __popc(bits);
-  // exclusive scan of c over the block: within the wave by shuffles, across waves via LDS
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  int incl = c;
+  int before = 0, own = 0;                                 // kept ahead of this chunk; in this head
+  if (kFused) {
+    // chunks are ordered (b,h)-major; the first chunk of a head adds up the head's as well.  The array
+    // is padded to 256 bytes, so that four counts at a time stay inside it.
+    const int mine = bh * nchunks + chunk, end = chunk == 0 ? mine + nchunks : mine;
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll 2
+    for (int i = threadIdx.x * 4; i < end; i += kThreads * 4) {
+      const i32x4 n = *reinterpret_cast<const i32x4*>(chunk_counts + i);
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int up = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += up;
+      for (int e = 0; e < 4; ++e) {
+        before += i + e < mine ? n[e] : 0;
+        own += i + e >= mine && i + e < end ? n[e] : 0;
+      }
+    }
   }
-  __shared__ int wave_tot[kThreads / 64];
-  if (lane == 63) wave_tot[wid] = incl;
+  const unsigned bits = keep_bits4(row, t0, T, Tb, window, tau, vec_ok);
+  const int c = __popc(bits), incl = wave_scan(c);
+  __shared__ int s_before[kWaves], s_own[kWaves], s_kept[kWaves];
+  before = kFused ? wave_scan(before) : 0;
+  own = kFused && chunk == 0 ? wave_scan(own) : 0;         // (uniform)
+  if (lane == 63) {
+    s_kept[wid] = incl;
+    s_before[wid] = before;
+    s_own[wid] = own;
+  }
   __syncthreads();
-  int before = 0;
+  int64_t prefix = kFused ? 0 : chunk_prefix[(size_t)bh * nchunks + chunk];
+  int ahead = 0, head_total = 0;
 #pragma unroll
-  for (int w = 0; w < kThreads / 64; ++w) before += (w < wid) ? wave_tot[w] : 0;
-  int64_t pos = my_prefix + before + incl - c;
+  for (int w = 0; w < kWaves; ++w) {
+    prefix += s_before[w];
+    head_total += s_own[w];
+    ahead += w < wid ? s_kept[w] : 0;
+  }
+  if (kFused && chunk == 0 && threadIdx.x == 0) {          // this head's length and start
+    offsets[bh] = prefix;
+    lengths[bh] = head_total;
+    if (bh == (int)gridDim.y - 1) offsets[bh + 1] = prefix + head_total;
+  }
+  int64_t pos = prefix + ahead + incl - c;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     if (bits & (1u << e)) keep_idx[pos++] = t0 + e;
@@ -321,13 +312,10 @@ __global__ __launch_bounds__(kDirectThreads) void mask_direct_kernel(
       if (sg + kDirectWaves < nseg) count(sb, qb);
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    before += __shfl_down(before, off, 64);
-    in_row += __shfl_down(in_row, off, 64);
-  }
+  before = wave_scan(before);
+  in_row = wave_scan(in_row);
   const unsigned long long kept = __ballot(own);
-  if (lane == 0) { s_before[wv] = before; s_own[wv] = in_row; }
+  if (lane == 63) { s_before[wv] = before; s_own[wv] = in_row; }
   if (tid == 0) s_first = __popcll(kept);
   __syncthreads();
   int start = 0, mine = 0;

@@ -190,3 +190,13 @@ def test_repeatable_and_buffers_reused():
     for a, b in zip(*outs):
         assert torch.equal(a.view(torch.uint8) if a.dtype == torch.bfloat16 else a,
                            b.view(torch.uint8) if b.dtype == torch.bfloat16 else b)
+
+
+@pytest.mark.parametrize("B,H,T,w,tau", [(5, 5, 42001, 128, 0.4), (1, 3, 349999, 0, 0.1), (3, 7, 10241, 3, 0.0)])
+def test_counts_that_end_inside_a_load(B, H, T, w, tau):
+    # the chunks ahead of one are summed four to a load: heads that start and end inside a load, and
+    # more than 1024 chunks, whose last ones take a second round
+    scores = synth.make_scores(B, H, T, seed=T)
+    K, V = _kv(B, H, T, 8, T)
+    idx, n, off, Ko, Vo = _run(scores, tau, w, K, V)
+    parity.assert_prune_matches(idx, n, off, Ko, Vo, K, V, scores.double().numpy(), tau, w)
