@@ -42,6 +42,7 @@
 //
 // A second small kernel combines the splits of each head and writes bf16.
 #include <algorithm>
+#include <type_traits>
 
 #include "kvzap_internal.h"
 
@@ -64,9 +65,13 @@ struct HeadExtent {
 __device__ __forceinline__ HeadExtent head_extent(const int64_t* row_offsets,
                                                   const int32_t* lengths,
                                                   const int32_t* seq_pos, int window,
-                                                  int64_t cap_rows, int bh, int b) {
+                                                  int64_t cap_rows, int bh, int b, const void* stand_in) {
+  // one trip to memory: what is absent is read from `stand_in` (8 bytes) and discarded, since a load
+  // behind a branch waits for the ones before it
+  const int64_t off = *(row_offsets ? row_offsets + bh : static_cast<const int64_t*>(stand_in));
+  const int32_t pos = *(window > 0 ? seq_pos + b : static_cast<const int32_t*>(stand_in));
   HeadExtent e;
-  e.off = row_offsets ? row_offsets[bh] : 0;
+  e.off = row_offsets ? off : 0;
   int64_t n = lengths[bh];
   if (e.off < 0 || e.off > cap_rows) { e.off = 0; n = 0; }
   if (n < 0) n = 0;
@@ -74,7 +79,7 @@ __device__ __forceinline__ HeadExtent head_extent(const int64_t* row_offsets,
   e.n_p = (int)n;
   int r = 0;
   if (window > 0) {
-    r = seq_pos[b];
+    r = pos;
     r = r < 0 ? 0 : (r > window ? window : r);
   }
   e.n_r = r;
@@ -153,6 +158,13 @@ __device__ __forceinline__ Place place_of(int vc, int cp, const Source& s, const
   return p;
 }
 
+template <bool kStream>
+__device__ __forceinline__ u32x4 load_piece(const u32x4* p) {
+  if constexpr (kStream) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
+template <bool kStream>
 __device__ __forceinline__ void load_chunk(Chunk& c, const Place& p, const Source& s, int li, int lg) {
   const u32x4* Kb = p.ring ? s.Kr : s.K;
   const u32x4* Vb = p.ring ? s.Vr : s.V;
@@ -160,12 +172,12 @@ __device__ __forceinline__ void load_chunk(Chunk& c, const Place& p, const Sourc
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const size_t at = p.half[j >> 2] + (size_t)(4 * (j & 3) + lg) * kRowVec + li;
-      c.k[j] = __builtin_nontemporal_load(Kb + at);
+      c.k[j] = load_piece<kStream>(Kb + at);
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const size_t at = p.half[j >> 2] + (size_t)(4 * (j & 3) + lg) * kRowVec + li;
-      c.v[j] = __builtin_nontemporal_load(Vb + at);
+      c.v[j] = load_piece<kStream>(Vb + at);
     }
   } else {
 #pragma unroll
@@ -174,8 +186,8 @@ __device__ __forceinline__ void load_chunk(Chunk& c, const Place& p, const Sourc
       lim = lim < 0 ? 0 : lim;
       const int r = 4 * (j & 3) + lg;
       const size_t at = p.half[j >> 2] + (size_t)(r < lim ? r : lim) * kRowVec + li;
-      c.k[j] = __builtin_nontemporal_load(Kb + at);
-      c.v[j] = __builtin_nontemporal_load(Vb + at);
+      c.k[j] = load_piece<kStream>(Kb + at);
+      c.v[j] = load_piece<kStream>(Vb + at);
     }
   }
 }
@@ -263,6 +275,10 @@ __device__ __forceinline__ void consume_chunk(const Chunk& c, const u32x4 (&qb)[
 // Contiguous layout: K_rows/V_rows are the row store, row_offsets the heads' first rows.
 // Paged layout: K_rows/V_rows are the page pool, row_offsets is null, block_table given.
 constexpr int kMinChunks = 4;            // of a wavefront: fewer, and the combining pass takes longer
+// Up to this many chunks (64 MB) in all are read without the streaming hint, which keeps them out of the
+// memory-side cache that a step may find them in: three states of 3 sequences of 1k..8k rows in turn
+// 27.8 us a step with it, 26.6 without; past that the hint wins: 1 of 32k 38.8 / 42.6, 40 of 0.3k..2.4k 59.6 / 66.4.
+constexpr int kStreamChunks = 4096;
 constexpr int kMaxBatches = 1024;        // of 64 heads: B*H <= 65535
 
 // How a wavefront finds its part of the list: from all heads' lengths, for itself (up to 64 heads) or
@@ -287,7 +303,7 @@ __global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_partial_kernel
   int base = 0, chunks;                                  // chunks of that head
   auto extent = [&](int bh) {                            // past the last head: nothing, and no branch around a load
     const int c = bh < BH ? bh : BH - 1;
-    HeadExtent e = head_extent(row_offsets, lengths, seq_pos, window, cap_rows, c, c / H);
+    HeadExtent e = head_extent(row_offsets, lengths, seq_pos, window, cap_rows, c, c / H, q);
     if (bh >= BH) e.n_p = e.n_r = 0;
     return e;
   };
@@ -297,7 +313,9 @@ __global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_partial_kernel
   };
   const int w = blockIdx.x * kWaves + wv;
   int begin = 0, left;                                   // this wavefront's part of the list
+  bool stream = (long long)nw * spc > kStreamChunks;
   auto part_of = [&](int total) {
+    stream = total > kStreamChunks;
     int per = (int)(((unsigned)total + (unsigned)nw - 1) / (unsigned)nw);
     per = per > kMinChunks ? per : kMinChunks;
     begin = w < nw ? w * per : total;
@@ -305,10 +323,13 @@ __global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_partial_kernel
   };
   int skip;                                              // chunks ahead of `begin` from head `base` on
   if constexpr (kDeal == Deal::kHead) {
-    const int NS = nw / BH, bh = w / NS, split = w - bh * NS;
-    base = bh;
-    fetch();
-    const int ct = __builtin_amdgcn_readfirstlane(chunks);
+    // the heads' first splits start first, shifted by one from split to split: a short head's blocks that
+    // have nothing come last, and a long head's meet every XCD
+    const int NS = nw / BH, split = w / BH;
+    base = (w + split) % BH;
+    mine = extent(base);
+    chunks = chunks_of(mine.n_p) + chunks_of(mine.n_r);
+    const int ct = chunks;
     skip = split * spc;
     left = split == NS - 1 ? ct - skip : (ct - skip < spc ? ct - skip : spc);   // the last takes what is beyond the bound
     if (left <= 0) return;
@@ -409,34 +430,39 @@ __global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_partial_kernel
     // compiler's wait counts let the loads of one buffer fly while the other is consumed.
     Chunk ca, cb;
     Rows rows{};
-    for (int chunk0 = c0; chunk0 < c1; chunk0 += kLookup) {
-      const int end = kPaged && chunk0 + kLookup < c1 ? chunk0 + kLookup : c1;
-      if (kPaged) rows = look_up(src, chunk0, lane);
-      auto place = [&](int vc) { return place_of<kPaged>(vc, cp, src, rows, chunk0); };
-      Place pa = place(chunk0), pb;
-      load_chunk(ca, pa, src, li, lg);
-      int vc = chunk0;
-      while (vc + 2 < end) {
-        pb = place(vc + 1);
-        load_chunk(cb, pb, src, li, lg);
-        consume_chunk(ca, qb, acc, turn, pa.row0, pa.n_seg, li, lg, cscale);
-        pa = place(vc + 2);
-        load_chunk(ca, pa, src, li, lg);
-        consume_chunk(cb, qb, acc, turn, pb.row0, pb.n_seg, li, lg, cscale);
-        vc += 2;
+    auto rows_of = [&](auto stream_tag) {
+      constexpr bool kStream = decltype(stream_tag)::value;
+      for (int chunk0 = c0; chunk0 < c1; chunk0 += kLookup) {
+        const int end = kPaged && chunk0 + kLookup < c1 ? chunk0 + kLookup : c1;
+        if (kPaged) rows = look_up(src, chunk0, lane);
+        auto place = [&](int vc) { return place_of<kPaged>(vc, cp, src, rows, chunk0); };
+        Place pa = place(chunk0), pb;
+        load_chunk<kStream>(ca, pa, src, li, lg);
+        int vc = chunk0;
+        while (vc + 2 < end) {
+          pb = place(vc + 1);
+          load_chunk<kStream>(cb, pb, src, li, lg);
+          consume_chunk(ca, qb, acc, turn, pa.row0, pa.n_seg, li, lg, cscale);
+          pa = place(vc + 2);
+          load_chunk<kStream>(ca, pa, src, li, lg);
+          consume_chunk(cb, qb, acc, turn, pb.row0, pb.n_seg, li, lg, cscale);
+          vc += 2;
+        }
+        if (vc + 1 < end) {
+          pb = place(vc + 1);
+          load_chunk<kStream>(cb, pb, src, li, lg);
+          consume_chunk(ca, qb, acc, turn, pa.row0, pa.n_seg, li, lg, cscale);
+          consume_chunk(cb, qb, acc, turn, pb.row0, pb.n_seg, li, lg, cscale);
+        } else {
+          consume_chunk(ca, qb, acc, turn, pa.row0, pa.n_seg, li, lg, cscale);
+        }
+        if (!kPaged) break;
       }
-      if (vc + 1 < end) {
-        pb = place(vc + 1);
-        load_chunk(cb, pb, src, li, lg);
-        consume_chunk(ca, qb, acc, turn, pa.row0, pa.n_seg, li, lg, cscale);
-        consume_chunk(cb, qb, acc, turn, pb.row0, pb.n_seg, li, lg, cscale);
-      } else {
-        consume_chunk(ca, qb, acc, turn, pa.row0, pa.n_seg, li, lg, cscale);
-      }
-      if (!kPaged) break;
-    }
+    };
+    if (kDeal == Deal::kBlock || stream) rows_of(std::true_type{});
+    else rows_of(std::false_type{});
 
-    const int slot = kDeal == Deal::kHead ? w : w + bh;
+    const int slot = kDeal == Deal::kHead ? bh * (nw / BH) + w / BH : w + bh;
     if (li < G) {
       const size_t out = (size_t)slot * G + li;
       float* dst = part + out * kD + 32 * lg;
@@ -482,7 +508,7 @@ __global__ __launch_bounds__(kGroups * 32) void attend_combine_kernel(
   __shared__ float s_m[kGroups], s_den[kGroups];
   const int bh = blockIdx.x / G, g = blockIdx.x % G;
   const int c = threadIdx.x & 31, sg = threadIdx.x >> 5;
-  const HeadExtent e = head_extent(row_offsets, lengths, seq_pos, window, total_rows, bh, bh / H);
+  const HeadExtent e = head_extent(row_offsets, lengths, seq_pos, window, total_rows, bh, bh / H, part);
   const int2 slots = span[bh];
   const int ns = e.n_p + e.n_r > 0 ? slots.y - slots.x + 1 : 0;   // of an empty head nobody wrote the span
   float m = -INFINITY, den = 0.f;
@@ -536,14 +562,18 @@ __global__ __launch_bounds__(kGroups * 32) void attend_combine_kernel(
 // 20.9, two 33.6 / 30.4.
 // Heads of a few chunks are better off with a wavefront of their own, since a part's every head begins
 // with a wait for its first rows: 512 heads of 64 rows beside the window 16.9 us in equal parts, 14.6 head
-// by head, 2048 heads 48.4 / 42.9, 8192 194 / 183; 512 of 512 rows (20 chunks) 33.8 / 33.7.
+// by head, 2048 heads 48.4 / 42.9, 8192 194 / 183; 512 of 512 rows (20 chunks) 33.8 / 33.7.  So is a
+// list of up to kFewWaves splits at the smallest, all of which are resident at once and start without the sum over
+// the heads: 1 of 0.7k..3k rows 7.4 / 6.7 for this pass, 2 of 2000 in pages 8.6 / 8.1; with 4096
+// splits 3 of 1k..8k 14.4 / 15.2.
 constexpr int kShortHead = 20;           // chunks, by the caller's bound
+constexpr long long kFewWaves = 2048;    // eight on each CU
 struct Dealt {
   Deal deal;
   int nw, spc;
 };
 Dealt deal_of(int BH, long long ct) {
-  if (ct <= kShortHead) {
+  if (ct <= kShortHead || (ct * BH <= kFewWaves * kMinChunks && ct <= 256 * kMinChunks)) {
     int spc = kMinChunks;
     while (spc < ct && 2048ll * spc < ct * BH) spc *= 2;
     const int splits = (int)((ct + spc - 1) / spc);
@@ -619,6 +649,9 @@ int launch_attend_decode(const void* q, const void* K_rows, const void* V_rows,
   if (dealt.nw / BH > 128)                               // one KV head's hundreds of slots: 24 us with 8 groups
     attend_combine_kernel<32><<<BH * G, 1024, 0, stream>>>(part, ml, span, cap_rows, offsets, lengths,
                                                            seq_pos, window, H, G, bits);
+  else if (dealt.nw / BH > 16)                           // 1 sequence of 32k rows 39.3 -> 38.7 us a step
+    attend_combine_kernel<16><<<BH * G, 512, 0, stream>>>(part, ml, span, cap_rows, offsets, lengths,
+                                                          seq_pos, window, H, G, bits);
   else
     attend_combine_kernel<8><<<BH * G, 256, 0, stream>>>(part, ml, span, cap_rows, offsets, lengths,
                                                          seq_pos, window, H, G, bits);

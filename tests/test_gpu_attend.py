@@ -235,6 +235,10 @@ def test_rejects_bad_arguments():
     (130, 4, 60, 33, None),       # a wavefront per split of one head
     (3, 2, 3000, 0, 10),          # ... the last of which goes past the bound
     (1, 1, 40000, 128, None),     # one head's hundreds of parts are combined by 32 groups
+    (16, 4, 900, 128, 5000),      # a long bound: equal parts of the list, 64 heads
+    (13, 5, 900, 40, 5000),       # ... and 65
+    (8, 8, 9000, 128, None),      # more than 4096 chunks: streamed, a wavefront's own part
+    (260, 8, 150, 33, None),      # ... and two splits of a head
 ])
 def test_rows_are_dealt_out_whole(B, H, top, window, max_rows):
     # every third head is empty, so that parts begin, end and pass over heads everywhere
