@@ -41,9 +41,11 @@
 // common chunk needs no cross-lane traffic at all.
 //
 // A second small kernel combines the splits of each head and writes bf16.
-#include <algorithm>
+#include <limits.h>
+
 #include <type_traits>
 
+#include "attend_deal.h"
 #include "kvzap_internal.h"
 
 namespace kvzap {
@@ -274,7 +276,7 @@ __device__ __forceinline__ void consume_chunk(const Chunk& c, const u32x4 (&qb)[
 // hold its ends.  part: [slot][G][128] fp32, ml: [slot][G][2] fp32.
 // Contiguous layout: K_rows/V_rows are the row store, row_offsets the heads' first rows.
 // Paged layout: K_rows/V_rows are the page pool, row_offsets is null, block_table given.
-constexpr int kMinChunks = 4;            // of a wavefront: fewer, and the combining pass takes longer
+using deal::Deal;
 // Up to this many chunks (64 MB) in all are read without the streaming hint, which keeps them out of the
 // memory-side cache that a step may find them in: three states of 3 sequences of 1k..8k rows in turn
 // 27.8 us a step with it, 26.6 without; past that the hint wins: 1 of 32k 38.8 / 42.6, 40 of 0.3k..2.4k 59.6 / 66.4.
@@ -283,7 +285,6 @@ constexpr int kMaxBatches = 1024;        // of 64 heads: B*H <= 65535
 
 // How a wavefront finds its part of the list: from all heads' lengths, for itself (up to 64 heads) or
 // with the other three of its block, or as one of spc chunks of one head.
-enum class Deal { kWave, kBlock, kHead };
 constexpr int waves_of(Deal d) { return d == Deal::kBlock ? 4 : 1; }
 
 template <bool kPaged, Deal kDeal>
@@ -316,10 +317,9 @@ __global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_partial_kernel
   bool stream = (long long)nw * spc > kStreamChunks;
   auto part_of = [&](int total) {
     stream = total > kStreamChunks;
-    int per = (int)(((unsigned)total + (unsigned)nw - 1) / (unsigned)nw);
-    per = per > kMinChunks ? per : kMinChunks;
-    begin = w < nw ? w * per : total;
-    left = total - begin < per ? total - begin : per;
+    const deal::Part part = deal::part_of(total, nw, w);
+    begin = part.begin;
+    left = part.n;
   };
   int skip;                                              // chunks ahead of `begin` from head `base` on
   if constexpr (kDeal == Deal::kHead) {
@@ -550,38 +550,6 @@ __global__ __launch_bounds__(kGroups * 32) void attend_combine_kernel(
   }
 }
 
-// How the first pass is dealt out: nw wavefronts (a multiple of B*H where each has spc chunks of one head).
-//
-// Equal parts of all heads' chunks in 4-wavefront blocks on 28 of an XCD's 32 CUs, or where there are
-// no more than 64 heads in one-wavefront blocks on all of them, but at least kMinChunks chunks each and
-// no more than 256 wavefronts for one head, whose sums one block combines.  Measured, us per call
-// (before, in splits of one head handed out one by one with 64-byte K loads / now): 8 KV heads, 4 query
-// heads each: 64 sequences of 4k..32k rows 837 / 699 (6.96 TB/s; with 1024 wavefronts 711, 2048 787),
-// 64 of 16000 708 / 614, 24 of 4k..8k 123 / 96, 16 of 0.5k..2k 25.3 / 22.3, 8 of 0.1k..30k 115 / 81, 3 of
-// 1k..8k 20.0 / 18.2, 1 of 128k 94 / 87, of 32k 30.2 / 29.1, of 2500 12.2 / 12.2; one KV head of 128k 23.8 /
-// 20.9, two 33.6 / 30.4.
-// Heads of a few chunks are better off with a wavefront of their own, since a part's every head begins
-// with a wait for its first rows: 512 heads of 64 rows beside the window 16.9 us in equal parts, 14.6 head
-// by head, 2048 heads 48.4 / 42.9, 8192 194 / 183; 512 of 512 rows (20 chunks) 33.8 / 33.7.  So is a
-// list of up to kFewWaves splits at the smallest, all of which are resident at once and start without the sum over
-// the heads: 1 of 0.7k..3k rows 7.4 / 6.7 for this pass, 2 of 2000 in pages 8.6 / 8.1; with 4096
-// splits 3 of 1k..8k 14.4 / 15.2.
-constexpr int kShortHead = 20;           // chunks, by the caller's bound
-constexpr long long kFewWaves = 2048;    // eight on each CU
-struct Dealt {
-  Deal deal;
-  int nw, spc;
-};
-Dealt deal_of(int BH, long long ct) {
-  if (ct <= kShortHead || (ct * BH <= kFewWaves * kMinChunks && ct <= 256 * kMinChunks)) {
-    int spc = kMinChunks;
-    while (spc < ct && 2048ll * spc < ct * BH) spc *= 2;
-    const int splits = (int)((ct + spc - 1) / spc);
-    return {Deal::kHead, BH * (splits > 0 ? splits : 1), spc};
-  }
-  const long long nw = (ct * BH + kMinChunks - 1) / kMinChunks, most = BH > 64 ? 896 : BH < 4 ? 256 * BH : 1024;
-  return {BH > 64 ? Deal::kBlock : Deal::kWave, (int)(nw < most ? nw : most), 0};
-}
 long long bound_chunks(int max_rows, int window) {
   return ((long long)max_rows + kChunkRows - 1) / kChunkRows + ((long long)window + kChunkRows - 1) / kChunkRows;
 }
@@ -589,11 +557,8 @@ long long bound_chunks(int max_rows, int window) {
 struct Layout {
   size_t ml, span, bytes;                // of the workspace: sums, then references and denominators, then spans
 };
-// Room for the slots of any bound up to ct chunks: a part of the list has fewer than nw + BH segments, and
-// splits of spc >= ct * BH / 2048 chunks are no more than BH + 2048.
 Layout layout_of(int BH, int G, long long ct) {
-  const long long parts = (ct * BH + kMinChunks - 1) / kMinChunks;
-  const size_t slots = (size_t)((parts < 2048 ? parts : 2048) + BH) * G;
+  const size_t slots = (size_t)deal::slots_of(BH, ct) * G;
   Layout l;
   l.ml = align_up(slots * kD * sizeof(float), 256);
   l.span = l.ml + align_up(slots * 2 * sizeof(float), 256);
@@ -615,7 +580,6 @@ int launch_attend_decode(const void* q, const void* K_rows, const void* V_rows,
                          hipStream_t stream) {
   const int G = HQ / H, BH = B * H;
   const long long ct = bound_chunks(max_rows, window);
-  const Dealt dealt = deal_of(BH, ct);
   const Layout lay = layout_of(BH, G, ct);
   char* const ws = static_cast<char*>(workspace);
   float* part = reinterpret_cast<float*>(ws);
@@ -627,6 +591,8 @@ int launch_attend_decode(const void* q, const void* K_rows, const void* V_rows,
   while ((1 << log_page) < page_rows) ++log_page;
   // rows a head can address: the whole store, or what its block-table row covers
   const int64_t cap_rows = paged ? (num_pages > 0 ? (int64_t)max_pages * page_rows : 0) : total_rows;
+  const int most_rows = (int)(cap_rows < INT_MAX ? cap_rows : INT_MAX);   // of a head: lengths are 32-bit
+  const deal::Dealt dealt = deal::deal_of(BH, ct, BH * bound_chunks(most_rows, window));
   const auto* qv = static_cast<const u32x4*>(q);
   const auto* kv = static_cast<const u32x4*>(K_rows);
   const auto* vv = static_cast<const u32x4*>(V_rows);
