@@ -6,18 +6,19 @@
 // flops), so the design is about streaming rows with as few vector-ALU instructions
 // per byte as possible; both contractions run on v_mfma_f32_16x16x32_bf16:
 //
-//   one wave = an equal part of all heads' rows, 32-row chunks, the next chunk's loads in
-//   flight while the current one is consumed.
+//   one wave = an equal part of all heads' rows, or a split of one head's (attend_deal.h), in
+//   32-row chunks, the next chunk's loads in flight while the current one is consumed.
 //
-// Every load instruction takes four whole rows of K or V (1 KB) with the non-temporal hint: that is
-// the form in which this part's memory gives 7.0 TB/s.  Without the hint, or with it and 64 bytes of a
+// Streamed: every load instruction takes four whole rows of K or V (1 KB) with the non-temporal hint, the
+// form in which this part's memory gives 7.0 TB/s.  Without the hint, or with it and 64 bytes of a
 // 128-byte line per instruction (K in the operand layout straight from memory), a read stream gets 6.1.
+// The smallest steps, which a cache serves and whose time is a wavefront's from start to end, do without.
 //
 //   S^T = K q^T      A = K   lane (i = l%16, kg = l/16) holds 16 bytes of row rho(i) at
 //                            byte 64*kk + 16*kg for kk = 0..3 (the k-slices an MFMA
-//                            step wants); two 16-row sets per chunk.  Loaded like V below and
-//                            turned through 8 KB of LDS of the wavefront's own (pieces XOR-swizzled
-//                            with the row: no bank conflicts either way)
+//                            step wants); two 16-row sets per chunk.  Streamed, it is loaded like V
+//                            below and turned through 8 KB of LDS of the wavefront's own (pieces
+//                            XOR-swizzled with the row: no bank conflicts either way)
 //                    B = q   lane (g = l%16, kg) holds q[g][32kk + 8kg ..+8], zero for
 //                            g >= G
 //                    C       lane (g, s = l/16), register r: row i = 4s + r of the set
@@ -43,13 +44,13 @@
 // A second small kernel combines the splits of each head and writes bf16.
 #include <limits.h>
 
-#include <type_traits>
-
 #include "attend_deal.h"
 #include "kvzap_internal.h"
 
 namespace kvzap {
 namespace {
+
+using deal::Deal;
 
 constexpr int kD = 128;                 // head dimension (elements)
 constexpr int kChunkRows = 32;
@@ -91,8 +92,8 @@ __device__ __forceinline__ HeadExtent head_extent(const int64_t* row_offsets,
 __device__ __forceinline__ int chunks_of(int rows) { return (rows + kChunkRows - 1) / kChunkRows; }
 
 struct Chunk {
-  u32x4 k[8];      // [row group j]: piece l%16 of row 4j + l/16
-  u32x4 v[8];
+  u32x4 k[8];      // operand layout: [4*t + kk] of set t; streamed: [row group j], as v
+  u32x4 v[8];      // [row group j]: piece l%16 of row 4j + l/16
 };
 
 // Where the rows of one head live.
@@ -109,10 +110,11 @@ struct Source {
 constexpr int kRowVec = kD * 2 / 16;   // 16-byte pieces per row
 
 // Paged prefix: the pool rows of kLookup consecutive chunks' 16-row halves, half i in lane i % 64
-// of word i / 64.  Looked up once per split, all halves at a time: looked up chunk by chunk, the
-// round trip of every entry stood ahead of the chunk's loads.  A table entry outside the pool is
-// clamped into it, so nothing outside the pool is ever read.
-constexpr int kLookup = 64;              // chunks, the most a split has unless its head exceeds the bound
+// of word i / 64.  Looked up all halves at a time: looked up chunk by chunk, the round trip of every
+// entry stood ahead of the chunk's loads.  A table entry outside the pool is clamped into it, so nothing
+// outside the pool is ever read.  A part of more than kLookup chunks (64 sequences of 4k..32k rows: 330)
+// empties its two buffers for each lookup, which costs such a call 3.5 % over the contiguous layout (701 / 726 us).
+constexpr int kLookup = 64;              // chunks
 struct Rows {
   int row[2];
 };
@@ -160,36 +162,56 @@ __device__ __forceinline__ Place place_of(int vc, int cp, const Source& s, const
   return p;
 }
 
-template <bool kStream>
-__device__ __forceinline__ u32x4 load_piece(const u32x4* p) {
-  if constexpr (kStream) return __builtin_nontemporal_load(p);
-  else return *p;
-}
-
+// kStream: every load takes four whole rows with the non-temporal hint, K as well (to be turned in LDS).
+// Otherwise plain loads, K's in the operand layout: [4*t + kk] of the chunk's set t.
 template <bool kStream>
 __device__ __forceinline__ void load_chunk(Chunk& c, const Place& p, const Source& s, int li, int lg) {
   const u32x4* Kb = p.ring ? s.Kr : s.K;
   const u32x4* Vb = p.ring ? s.Vr : s.V;
-  if (p.row0 + kChunkRows <= p.n_seg) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const size_t at = p.half[j >> 2] + (size_t)(4 * (j & 3) + lg) * kRowVec + li;
-      c.k[j] = load_piece<kStream>(Kb + at);
+  const bool whole = p.row0 + kChunkRows <= p.n_seg;
+  auto at = [&](int t, int r) {                            // piece 0 of row r of half t
+    if (!whole) {
+      int lim = p.n_seg - 1 - (p.row0 + 16 * t);           // last row of the segment, within the half
+      lim = lim < 0 ? 0 : lim;
+      r = r < lim ? r : lim;
     }
+    return p.half[t] + (size_t)r * kRowVec;
+  };
+  if constexpr (kStream) {
+    if (whole) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const size_t at = p.half[j >> 2] + (size_t)(4 * (j & 3) + lg) * kRowVec + li;
-      c.v[j] = load_piece<kStream>(Vb + at);
+      for (int j = 0; j < 8; ++j)
+        c.k[j] = __builtin_nontemporal_load(Kb + p.half[j >> 2] + (size_t)(4 * (j & 3) + lg) * kRowVec + li);
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        c.v[j] = __builtin_nontemporal_load(Vb + p.half[j >> 2] + (size_t)(4 * (j & 3) + lg) * kRowVec + li);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const size_t row = at(j >> 2, 4 * (j & 3) + lg) + li;
+        c.k[j] = __builtin_nontemporal_load(Kb + row);
+        c.v[j] = __builtin_nontemporal_load(Vb + row);
+      }
     }
   } else {
+    const int klocal = 4 * (li & 3) + (li >> 2);           // row of this lane inside a 16-row set
+    if (whole) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      int lim = p.n_seg - 1 - (p.row0 + 16 * (j >> 2));  // last row of the segment, within the half
-      lim = lim < 0 ? 0 : lim;
-      const int r = 4 * (j & 3) + lg;
-      const size_t at = p.half[j >> 2] + (size_t)(r < lim ? r : lim) * kRowVec + li;
-      c.k[j] = load_piece<kStream>(Kb + at);
-      c.v[j] = load_piece<kStream>(Vb + at);
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) c.k[4 * t + kk] = Kb[p.half[t] + klocal * kRowVec + lg + kk * 4];
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        c.v[j] = Vb[p.half[j >> 2] + (size_t)(4 * (j & 3) + lg) * kRowVec + li];
+    } else {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const size_t row = at(t, klocal) + lg;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) c.k[4 * t + kk] = Kb[row + kk * 4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c.v[4 * t + j] = Vb[at(t, 4 * j + lg) + li];
+      }
     }
   }
 }
@@ -204,22 +226,30 @@ __device__ __forceinline__ float shfl_xor_f(float x, int mask) {
   return __shfl_xor(x, mask, 64);
 }
 
+// turn: 8 KB of LDS of the wavefront's own, where the chunk was streamed
+template <bool kStream>
 __device__ __forceinline__ void consume_chunk(const Chunk& c, const u32x4 (&qb)[4], Accum& a, u32x4* turn,
                                               int row0, int n_seg, int li, int lg, float cscale) {
-  wave_fence();                                          // the reads of the chunk before
+  if constexpr (kStream) {
+    wave_fence();                                        // the reads of the chunk before
 #pragma unroll
-  for (int j = 0; j < 8; ++j) turn[(4 * j + lg) * kRowVec + (li ^ ((4 * j + lg) & 15))] = c.k[j];
-  wave_fence();
+    for (int j = 0; j < 8; ++j) turn[(4 * j + lg) * kRowVec + (li ^ ((4 * j + lg) & 15))] = c.k[j];
+    wave_fence();
+  }
   floatx4 s[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     s[t] = floatx4{0.f, 0.f, 0.f, 0.f};
     const int row = 4 * (li & 3) + (li >> 2);            // of this lane in the 16-row set
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-      s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, turn[(16 * t + row) * kRowVec + ((4 * kk + lg) ^ row)]),
+    for (int kk = 0; kk < 4; ++kk) {
+      u32x4 k;
+      if constexpr (kStream) k = turn[(16 * t + row) * kRowVec + ((4 * kk + lg) ^ row)];
+      else k = c.k[4 * t + kk];
+      s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k),
                                                      __builtin_bit_cast(bf16x8, qb[kk]), s[t],
                                                      0, 0, 0);
+    }
   }
   float x[8];
 #pragma unroll
@@ -263,48 +293,151 @@ __device__ __forceinline__ void consume_chunk(const Chunk& c, const u32x4 (&qb)[
   a.l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ones), p, a.l, 0, 0, 0);
 }
 
-// ---- pass 1: grid ceil(nw / 4), 256 threads ----
+// What the first pass's kernels are given.  Contiguous layout: K_rows/V_rows are the row store,
+// row_offsets the heads' first rows.  Paged layout: K_rows/V_rows are the page pool, row_offsets is
+// null, block_table given.  part: [slot][G][128] fp32, ml: [slot][G][2] fp32.
+struct Args {
+  const u32x4* q; const u32x4* K_rows; const u32x4* V_rows;
+  int64_t cap_rows;
+  const int64_t* row_offsets; const int32_t* block_table;
+  int max_pages, log_page, num_pages;
+  const int32_t* lengths; const u32x4* K_ring; const u32x4* V_ring; const int32_t* seq_pos;
+  int window;
+  float cscale;
+  int BH, H, G;
+  float* part; float* ml;
+};
+
+// Chunks [c0, c1) of head bh, whose sums go to `slot`.
+template <bool kPaged, bool kStream>
+__device__ __forceinline__ void attend_segment(const Args& a, const HeadExtent& e, int bh, int cp, int c0, int c1,
+                                               int slot, u32x4* turn, int lane) {
+  const int li = lane & 15, lg = lane >> 4;
+  Source src;
+  src.K = a.K_rows + (size_t)e.off * kRowVec;
+  src.V = a.V_rows + (size_t)e.off * kRowVec;
+  src.Kr = a.K_ring + (size_t)bh * (a.window > 0 ? a.window : 0) * kRowVec;
+  src.Vr = a.V_ring + (size_t)bh * (a.window > 0 ? a.window : 0) * kRowVec;
+  src.pages = kPaged ? a.block_table + (size_t)bh * a.max_pages : nullptr;
+  src.log_page = a.log_page; src.max_pages = a.max_pages; src.num_pages = a.num_pages;
+  src.n_p = e.n_p; src.n_r = e.n_r;
+
+  // q as the B operand: lane (g = li, kg = lg), k-step kk: q[g][32kk + 8kg ..+8]
+  u32x4 qb[4];
+  {
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    const u32x4* qp = a.q + ((size_t)bh * a.G + (li < a.G ? li : 0)) * kRowVec + lg;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) qb[kk] = li < a.G ? qp[kk * 4] : zero;
+  }
+
+  Accum acc;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) acc.o[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  acc.l = floatx4{0.f, 0.f, 0.f, 0.f};
+  acc.m = -INFINITY;
+
+  // Two chunk buffers; the steady-state loop has no branch around a load, so the
+  // compiler's wait counts let the loads of one buffer fly while the other is consumed.
+  Chunk ca, cb;
+  Rows rows{};
+  for (int chunk0 = c0; chunk0 < c1; chunk0 += kLookup) {
+    const int end = kPaged && chunk0 + kLookup < c1 ? chunk0 + kLookup : c1;
+    if (kPaged) rows = look_up(src, chunk0, lane);
+    auto place = [&](int vc) { return place_of<kPaged>(vc, cp, src, rows, chunk0); };
+    auto load = [&](Chunk& c, const Place& p) { load_chunk<kStream>(c, p, src, li, lg); };
+    auto consume = [&](const Chunk& c, const Place& p) {
+      consume_chunk<kStream>(c, qb, acc, turn, p.row0, p.n_seg, li, lg, a.cscale);
+    };
+    Place pa = place(chunk0), pb;
+    load(ca, pa);
+    int vc = chunk0;
+    while (vc + 2 < end) {
+      pb = place(vc + 1);
+      load(cb, pb);
+      consume(ca, pa);
+      pa = place(vc + 2);
+      load(ca, pa);
+      consume(cb, pb);
+      vc += 2;
+    }
+    if (vc + 1 < end) {
+      pb = place(vc + 1);
+      load(cb, pb);
+      consume(ca, pa);
+      consume(cb, pb);
+    } else {
+      consume(ca, pa);
+    }
+    if (!kPaged) break;
+  }
+
+  if (li < a.G) {
+    const size_t out = (size_t)slot * a.G + li;
+    float* dst = a.part + out * kD + 32 * lg;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      floatx4 lo = {acc.o[0][r], acc.o[1][r], acc.o[2][r], acc.o[3][r]};
+      floatx4 hi = {acc.o[4][r], acc.o[5][r], acc.o[6][r], acc.o[7][r]};
+      *reinterpret_cast<floatx4*>(dst + 8 * r) = lo;
+      *reinterpret_cast<floatx4*>(dst + 8 * r + 4) = hi;
+    }
+    if (lg == 0) {
+      a.ml[out * 2] = acc.m;
+      a.ml[out * 2 + 1] = acc.l[0];
+    }
+  }
+}
+
+// ---- pass 1, head by head: grid (B*H, splits), 64 threads, one split of spc chunks each ----
+// The head varies fastest and is shifted by one from split to split: workgroups go to the eight XCDs in
+// turn, so the blocks that have work (short heads: the first splits only) come one after the other on all
+// of them, and a long head's splits meet every XCD.  Slot head * NS + split.
+// Streamed, with K turned in LDS, it is 1 us longer from start to end than without (more to fetch of the
+// program, and K's way through LDS), which the smallest steps do not make up for.
+template <bool kPaged, bool kStream>
+__global__ __launch_bounds__(64, 2) void attend_split_kernel(Args a, int NS, int spc) {
+  __shared__ u32x4 s_turn[kStream ? kChunkRows * kRowVec : 1];
+  const int split = blockIdx.y + gridDim.y * blockIdx.z;
+  if (split >= NS) return;
+  const int bh = (int)((blockIdx.x + (unsigned)split) % (unsigned)a.BH);
+  const HeadExtent e = head_extent(a.row_offsets, a.lengths, a.seq_pos, a.window, a.cap_rows, bh, bh / a.H, a.q);
+  const int cp = chunks_of(e.n_p), ct = cp + chunks_of(e.n_r);
+  const int c0 = split * spc;
+  // the last split runs to the end of the list, so a head longer than the host's bound
+  // is still covered
+  const int c1 = split == NS - 1 ? ct : (ct - c0 < spc ? ct : c0 + spc);
+  if (c0 >= c1) return;
+  attend_segment<kPaged, kStream>(a, e, bh, cp, c0, c1, bh * NS + split, s_turn, threadIdx.x);
+}
+
+// ---- pass 1, as one list: grid ceil(nw / waves), streamed ----
 // The chunks of all heads, in (b,h) order and each head's prefix before its ring, are one list, and
 // each of the nw wavefronts takes an equal part of it: every CU of every XCD reads the same number of
 // bytes whatever the heads' lengths are, and all of them end together.  (Cutting every head into
 // splits of the same length and handing those out one per wavefront left the XCDs up to 4 % apart and
 // paid a wavefront's start for every split: 64 sequences of 4k..32k rows 776 us with splits of 2048
 // rows, 815 with 1024, 850 with 512.)
-// A block adds up the chunk counts of all heads itself, up to 64 heads a wavefront does.  The part of a head that a wavefront
-// handles (a segment) leaves its sums in slot (wavefront + head), which grows from segment to
-// segment; span[head] = the first and the last slot of the head, written by the wavefronts that
-// hold its ends.  part: [slot][G][128] fp32, ml: [slot][G][2] fp32.
-// Contiguous layout: K_rows/V_rows are the row store, row_offsets the heads' first rows.
-// Paged layout: K_rows/V_rows are the page pool, row_offsets is null, block_table given.
-using deal::Deal;
-// Up to this many chunks (64 MB) in all are read without the streaming hint, which keeps them out of the
-// memory-side cache that a step may find them in: three states of 3 sequences of 1k..8k rows in turn
-// 27.8 us a step with it, 26.6 without; past that the hint wins: 1 of 32k 38.8 / 42.6, 40 of 0.3k..2.4k 59.6 / 66.4.
-constexpr int kStreamChunks = 4096;
+// A block adds up the chunk counts of all heads itself, up to 64 heads a wavefront does.  The part of a
+// head that a wavefront handles (a segment) leaves its sums in slot (wavefront + head), which grows from
+// segment to segment; span[head] = the first and the last slot of the head, written by the wavefronts
+// that hold its ends.
 constexpr int kMaxBatches = 1024;        // of 64 heads: B*H <= 65535
-
-// How a wavefront finds its part of the list: from all heads' lengths, for itself (up to 64 heads) or
-// with the other three of its block, or as one of spc chunks of one head.
 constexpr int waves_of(Deal d) { return d == Deal::kBlock ? 4 : 1; }
 
 template <bool kPaged, Deal kDeal>
-__global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_partial_kernel(
-    const u32x4* q, const u32x4* K_rows, const u32x4* V_rows, int64_t cap_rows,
-    const int64_t* row_offsets, const int32_t* block_table, int max_pages, int log_page,
-    int num_pages, const int32_t* lengths, const u32x4* K_ring, const u32x4* V_ring,
-    const int32_t* seq_pos, int window, float cscale, int BH, int H, int G, int nw, int spc,
-    float* part, float* ml, int2* span) {
+__global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_list_kernel(Args a, int nw, int2* span) {
   constexpr int kWaves = waves_of(kDeal);
   __shared__ u32x4 s_turn[kWaves][kChunkRows * kRowVec];
   __shared__ int s_batch[kDeal == Deal::kBlock ? kMaxBatches : 1];
-  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, BH = a.BH;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   HeadExtent mine;                                       // lane i: head base + i
   int base = 0, chunks;                                  // chunks of that head
   auto extent = [&](int bh) {                            // past the last head: nothing, and no branch around a load
     const int c = bh < BH ? bh : BH - 1;
-    HeadExtent e = head_extent(row_offsets, lengths, seq_pos, window, cap_rows, c, c / H, q);
+    HeadExtent e = head_extent(a.row_offsets, a.lengths, a.seq_pos, a.window, a.cap_rows, c, c / a.H, a.q);
     if (bh >= BH) e.n_p = e.n_r = 0;
     return e;
   };
@@ -312,28 +445,17 @@ __global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_partial_kernel
     mine = extent(base + lane);
     chunks = chunks_of(mine.n_p) + chunks_of(mine.n_r);
   };
-  const int w = blockIdx.x * kWaves + wv;
-  int begin = 0, left;                                   // this wavefront's part of the list
-  bool stream = (long long)nw * spc > kStreamChunks;
+  // this wavefront's part of the list; where a third and more have none, those that have are spread over the blocks
+  // (16 sequences of 64 rows under a bound of 6208 14.7 -> 12.7 us a call)
+  int w = 0, begin = 0, left = 0;
   auto part_of = [&](int total) {
-    stream = total > kStreamChunks;
+    w = 3ll * total < 2ll * nw * deal::kMinChunks ? wv * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * kWaves + wv;
     const deal::Part part = deal::part_of(total, nw, w);
     begin = part.begin;
     left = part.n;
   };
   int skip;                                              // chunks ahead of `begin` from head `base` on
-  if constexpr (kDeal == Deal::kHead) {
-    // the heads' first splits start first, shifted by one from split to split: a short head's blocks that
-    // have nothing come last, and a long head's meet every XCD
-    const int NS = nw / BH, split = w / BH;
-    base = (w + split) % BH;
-    mine = extent(base);
-    chunks = chunks_of(mine.n_p) + chunks_of(mine.n_r);
-    const int ct = chunks;
-    skip = split * spc;
-    left = split == NS - 1 ? ct - skip : (ct - skip < spc ? ct - skip : spc);   // the last takes what is beyond the bound
-    if (left <= 0) return;
-  } else if constexpr (kDeal == Deal::kWave) {
+  if constexpr (kDeal == Deal::kWave) {
     fetch();
     part_of(__builtin_amdgcn_readlane(wave_scan(chunks), 63));
     if (left <= 0) return;
@@ -375,7 +497,7 @@ __global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_partial_kernel
     fetch();
   }
   int at = 0;                                            // the wavefront's head is base + at
-  while (kDeal != Deal::kHead) {
+  for (;;) {
     const int upto = wave_scan(chunks);
     const unsigned long long past = __ballot(upto > skip);
     if (past) {
@@ -402,82 +524,8 @@ __global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_partial_kernel
     const int cp = chunks_of(e.n_p), ct = cp + chunks_of(e.n_r);
     const int c0 = __builtin_amdgcn_readfirstlane(first);
     const int c1 = __builtin_amdgcn_readfirstlane(ct - c0 < left ? ct : c0 + left);
-    Source src;
-    src.K = K_rows + (size_t)e.off * kRowVec;
-    src.V = V_rows + (size_t)e.off * kRowVec;
-    src.Kr = K_ring + (size_t)bh * (window > 0 ? window : 0) * kRowVec;
-    src.Vr = V_ring + (size_t)bh * (window > 0 ? window : 0) * kRowVec;
-    src.pages = kPaged ? block_table + (size_t)bh * max_pages : nullptr;
-    src.log_page = log_page; src.max_pages = max_pages; src.num_pages = num_pages;
-    src.n_p = e.n_p; src.n_r = e.n_r;
-
-    // q as the B operand: lane (g = li, kg = lg), k-step kk: q[g][32kk + 8kg ..+8]
-    u32x4 qb[4];
-    {
-      const u32x4 zero = {0u, 0u, 0u, 0u};
-      const u32x4* qp = q + ((size_t)bh * G + (li < G ? li : 0)) * kRowVec + lg;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) qb[kk] = li < G ? qp[kk * 4] : zero;
-    }
-
-    Accum acc;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) acc.o[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    acc.l = floatx4{0.f, 0.f, 0.f, 0.f};
-    acc.m = -INFINITY;
-
-    // Two chunk buffers; the steady-state loop has no branch around a load, so the
-    // compiler's wait counts let the loads of one buffer fly while the other is consumed.
-    Chunk ca, cb;
-    Rows rows{};
-    auto rows_of = [&](auto stream_tag) {
-      constexpr bool kStream = decltype(stream_tag)::value;
-      for (int chunk0 = c0; chunk0 < c1; chunk0 += kLookup) {
-        const int end = kPaged && chunk0 + kLookup < c1 ? chunk0 + kLookup : c1;
-        if (kPaged) rows = look_up(src, chunk0, lane);
-        auto place = [&](int vc) { return place_of<kPaged>(vc, cp, src, rows, chunk0); };
-        Place pa = place(chunk0), pb;
-        load_chunk<kStream>(ca, pa, src, li, lg);
-        int vc = chunk0;
-        while (vc + 2 < end) {
-          pb = place(vc + 1);
-          load_chunk<kStream>(cb, pb, src, li, lg);
-          consume_chunk(ca, qb, acc, turn, pa.row0, pa.n_seg, li, lg, cscale);
-          pa = place(vc + 2);
-          load_chunk<kStream>(ca, pa, src, li, lg);
-          consume_chunk(cb, qb, acc, turn, pb.row0, pb.n_seg, li, lg, cscale);
-          vc += 2;
-        }
-        if (vc + 1 < end) {
-          pb = place(vc + 1);
-          load_chunk<kStream>(cb, pb, src, li, lg);
-          consume_chunk(ca, qb, acc, turn, pa.row0, pa.n_seg, li, lg, cscale);
-          consume_chunk(cb, qb, acc, turn, pb.row0, pb.n_seg, li, lg, cscale);
-        } else {
-          consume_chunk(ca, qb, acc, turn, pa.row0, pa.n_seg, li, lg, cscale);
-        }
-        if (!kPaged) break;
-      }
-    };
-    if (kDeal == Deal::kBlock || stream) rows_of(std::true_type{});
-    else rows_of(std::false_type{});
-
-    const int slot = kDeal == Deal::kHead ? bh * (nw / BH) + w / BH : w + bh;
-    if (li < G) {
-      const size_t out = (size_t)slot * G + li;
-      float* dst = part + out * kD + 32 * lg;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        floatx4 lo = {acc.o[0][r], acc.o[1][r], acc.o[2][r], acc.o[3][r]};
-        floatx4 hi = {acc.o[4][r], acc.o[5][r], acc.o[6][r], acc.o[7][r]};
-        *reinterpret_cast<floatx4*>(dst + 8 * r) = lo;
-        *reinterpret_cast<floatx4*>(dst + 8 * r + 4) = hi;
-      }
-      if (lg == 0) {
-        ml[out * 2] = acc.m;
-        ml[out * 2 + 1] = acc.l[0];
-      }
-    }
+    const int slot = w + bh;
+    attend_segment<kPaged, true>(a, e, bh, cp, c0, c1, slot, turn, lane);
     if (lane == 0) {
       if (c0 == 0) span[bh].x = slot;
       if (c1 == ct) span[bh].y = slot;
@@ -499,18 +547,27 @@ __global__ __launch_bounds__(waves_of(kDeal) * 64, 2) void attend_partial_kernel
 
 // ---- pass 2: grid B*H*G, kGroups * 32 threads: thread (c = tid%32, sg = tid/32) folds the slots
 // sg, sg + kGroups, ... of output elements 4c..4c+3 with a running reference, then the groups meet
-// in LDS.
+// in LDS.  span: of a list; null where a head has NS slots, one for each spc chunks.
 template <int kGroups>
 __global__ __launch_bounds__(kGroups * 32) void attend_combine_kernel(
-    const float* part, const float* ml, const int2* span, int64_t total_rows, const int64_t* row_offsets,
-    const int32_t* lengths, const int32_t* seq_pos, int window, int H, int G, unsigned short* out) {
+    const float* part, const float* ml, const int2* span, int NS, int spc, int64_t total_rows,
+    const int64_t* row_offsets, const int32_t* lengths, const int32_t* seq_pos, int window, int H, int G,
+    unsigned short* out) {
   __shared__ floatx4 s_num[kGroups][32];
   __shared__ float s_m[kGroups], s_den[kGroups];
   const int bh = blockIdx.x / G, g = blockIdx.x % G;
   const int c = threadIdx.x & 31, sg = threadIdx.x >> 5;
+  int2 slots = *(span ? span + bh : reinterpret_cast<const int2*>(part));
   const HeadExtent e = head_extent(row_offsets, lengths, seq_pos, window, total_rows, bh, bh / H, part);
-  const int2 slots = span[bh];
-  const int ns = e.n_p + e.n_r > 0 ? slots.y - slots.x + 1 : 0;   // of an empty head nobody wrote the span
+  const int ct = chunks_of(e.n_p) + chunks_of(e.n_r);
+  int ns;
+  if (span) {
+    ns = ct > 0 ? slots.y - slots.x + 1 : 0;             // of an empty head nobody wrote the span
+  } else {
+    slots.x = bh * NS;
+    ns = (ct + spc - 1) / spc;
+    ns = ns < NS ? ns : NS;
+  }
   float m = -INFINITY, den = 0.f;
   floatx4 num = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
@@ -592,35 +649,38 @@ int launch_attend_decode(const void* q, const void* K_rows, const void* V_rows,
   // rows a head can address: the whole store, or what its block-table row covers
   const int64_t cap_rows = paged ? (num_pages > 0 ? (int64_t)max_pages * page_rows : 0) : total_rows;
   const int most_rows = (int)(cap_rows < INT_MAX ? cap_rows : INT_MAX);   // of a head: lengths are 32-bit
-  const deal::Dealt dealt = deal::deal_of(BH, ct, BH * bound_chunks(most_rows, window));
-  const auto* qv = static_cast<const u32x4*>(q);
-  const auto* kv = static_cast<const u32x4*>(K_rows);
-  const auto* vv = static_cast<const u32x4*>(V_rows);
-  const auto* kr = static_cast<const u32x4*>(K_ring);
-  const auto* vr = static_cast<const u32x4*>(V_ring);
-  auto launch = [&](auto kernel) {
-    const int waves = waves_of(dealt.deal);
-    kernel<<<(dealt.nw + waves - 1) / waves, waves * 64, 0, stream>>>(
-        qv, kv, vv, cap_rows, paged ? nullptr : row_offsets, block_table, max_pages, log_page, num_pages,
-        lengths, kr, vr, seq_pos, window, cscale, BH, H, G, dealt.nw, dealt.spc, part, ml, span);
-  };
-  switch (dealt.deal) {
-    case Deal::kHead: launch(paged ? attend_partial_kernel<true, Deal::kHead> : attend_partial_kernel<false, Deal::kHead>); break;
-    case Deal::kWave: launch(paged ? attend_partial_kernel<true, Deal::kWave> : attend_partial_kernel<false, Deal::kWave>); break;
-    case Deal::kBlock: launch(paged ? attend_partial_kernel<true, Deal::kBlock> : attend_partial_kernel<false, Deal::kBlock>); break;
+  const deal::Dealt dealt = deal::deal_of(BH, G, ct, BH * bound_chunks(most_rows, window));
+  const Args args{static_cast<const u32x4*>(q), static_cast<const u32x4*>(K_rows), static_cast<const u32x4*>(V_rows), cap_rows,
+                  paged ? nullptr : row_offsets, block_table, max_pages, log_page, num_pages, lengths,
+                  static_cast<const u32x4*>(K_ring), static_cast<const u32x4*>(V_ring), seq_pos, window, cscale,
+                  BH, H, G, part, ml};
+  const int NS = dealt.nw / BH;
+  if (dealt.deal == Deal::kHead) {
+    const unsigned ny = NS < 65535 ? NS : 65535;
+    const dim3 grid(BH, ny, (NS + ny - 1) / ny);
+    auto launch = [&](auto kernel) { kernel<<<grid, 64, 0, stream>>>(args, NS, dealt.spc); };
+    if (dealt.stream) launch(paged ? attend_split_kernel<true, true> : attend_split_kernel<false, true>);
+    else launch(paged ? attend_split_kernel<true, false> : attend_split_kernel<false, false>);
+    span = nullptr;
+  } else {
+    const int waves = waves_of(dealt.deal), blocks = (dealt.nw + waves - 1) / waves;
+    auto launch = [&](auto kernel) { kernel<<<blocks, waves * 64, 0, stream>>>(args, dealt.nw, span); };
+    if (dealt.deal == Deal::kWave) launch(paged ? attend_list_kernel<true, Deal::kWave> : attend_list_kernel<false, Deal::kWave>);
+    else launch(paged ? attend_list_kernel<true, Deal::kBlock> : attend_list_kernel<false, Deal::kBlock>);
   }
   if (hipGetLastError() != hipSuccess) return KVZAP_ERR_RUNTIME;
   const int64_t* offsets = paged ? nullptr : row_offsets;
   auto* bits = static_cast<unsigned short*>(out);
-  if (dealt.nw / BH > 128)                               // one KV head's hundreds of slots: 24 us with 8 groups
-    attend_combine_kernel<32><<<BH * G, 1024, 0, stream>>>(part, ml, span, cap_rows, offsets, lengths,
-                                                           seq_pos, window, H, G, bits);
-  else if (dealt.nw / BH > 16)                           // 1 sequence of 32k rows 39.3 -> 38.7 us a step
-    attend_combine_kernel<16><<<BH * G, 512, 0, stream>>>(part, ml, span, cap_rows, offsets, lengths,
-                                                          seq_pos, window, H, G, bits);
-  else
-    attend_combine_kernel<8><<<BH * G, 256, 0, stream>>>(part, ml, span, cap_rows, offsets, lengths,
-                                                         seq_pos, window, H, G, bits);
+  auto combine = [&](auto kernel, int groups) {
+    kernel<<<BH * G, groups * 32, 0, stream>>>(part, ml, span, NS, dealt.spc, cap_rows, offsets, lengths, seq_pos, window,
+                                               H, G, bits);
+  };
+  // By the slots that a head can have.  In a list one head may have them all (8 sequences, one head of 60000 rows and 63 of
+  // 200: 20.8 us with 8 groups, 17.6 with 16), but past 64 heads the wider blocks cost the usual call more than they
+  // give that one (40 sequences of 0.3k..2.4k rows 45.0 / 46.3); one KV head's hundreds took 24 us with 8.
+  if (NS > 128) combine(attend_combine_kernel<32>, 32);
+  else if (NS > 64 || dealt.deal == Deal::kWave) combine(attend_combine_kernel<16>, 16);
+  else combine(attend_combine_kernel<8>, 8);
   if (hipGetLastError() != hipSuccess) return KVZAP_ERR_RUNTIME;
   return KVZAP_OK;
 }

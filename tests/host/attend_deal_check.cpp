@@ -3,8 +3,10 @@
 // as the kernel sums them), and no form writes more slots than the workspace has for its bound or a longer one.
 //
 // usage: attend_deal_check [--plant]   (--plant takes the store's size for granted: must fail)
+//        attend_deal_check BH G max_rows window store_rows   (prints the form of one call)
 #include <climits>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 
 #include "attend_deal.h"
@@ -14,6 +16,14 @@ using namespace kvzap::deal;
 static long long chunks(long long rows) { return (rows + 31) / 32; }
 
 int main(int argc, char** argv) {
+  if (argc == 6) {
+    const int BH = std::atoi(argv[1]);
+    const long long ring = chunks(std::atoll(argv[4]));
+    const Dealt d = deal_of(BH, std::atoi(argv[2]), chunks(std::atoll(argv[3])) + ring, BH * (chunks(std::atoll(argv[5])) + ring));
+    if (d.deal == Deal::kHead) std::printf("%s %d\n", d.stream ? "streamed" : "plain", d.nw / BH);
+    else std::printf("%s %d\n", d.deal == Deal::kWave ? "list" : "block", d.nw);
+    return 0;
+  }
   const bool plant = argc > 1 && !std::strcmp(argv[1], "--plant");
   const int heads[] = {1, 2, 3, 4, 8, 24, 63, 64, 65, 72, 512, 513, 2080, 4097, 65535};
   const long long bounds[] = {0, 1, 31, 640, 641, 3000, 6272, 14336, 32768, 39000, 131072, 2000000, INT_MAX};
@@ -27,8 +37,9 @@ int main(int argc, char** argv) {
     for (int window : windows)
       for (long long bound : bounds)
         for (long long store : stores) {
+          const int G = 1 + checked % 16;
           const long long ct = chunks(bound) + chunks(window), most = BH * (chunks(store) + chunks(window));
-          const Dealt d = deal_of(BH, ct, plant ? 0 : most);
+          const Dealt d = deal_of(BH, G, ct, plant ? 0 : most);
           ++checked;
           if (d.nw < 1) fail("no wavefront", BH, ct, most);
           if (d.deal == Deal::kHead) {

@@ -1,31 +1,16 @@
 """How decode attention deals its rows out (paper_2601_07891_amd/csrc/attend_deal.h):
 tests/host/attend_deal_check.cpp, compiled here with g++ from the header that the kernels use.  CPU only."""
-import os
-import shutil
 import subprocess
 
-import pytest
-
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SRC = os.path.join(ROOT, "tests", "host", "attend_deal_check.cpp")
-INC = os.path.join(ROOT, "paper_2601_07891_amd", "csrc")
+from tests.deal import checker
 
 
-@pytest.fixture(scope="module")
-def checker(tmp_path_factory):
-    if shutil.which("g++") is None:
-        pytest.skip("no host compiler")
-    exe = str(tmp_path_factory.mktemp("deal") / "attend_deal_check")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-fwrapv", "-I", INC, SRC, "-o", exe], check=True)
-    return exe
-
-
-def test_parts_stay_inside_the_list_whatever_the_lengths_say(checker):
-    r = subprocess.run([checker], capture_output=True, text=True)
+def test_parts_stay_inside_the_list_whatever_the_lengths_say():
+    r = subprocess.run([checker()], capture_output=True, text=True)
     assert r.returncode == 0 and " 0 faults" in r.stdout, r.stdout
 
 
-def test_a_list_longer_than_its_sum_can_hold_is_caught(checker):
+def test_a_list_longer_than_its_sum_can_hold_is_caught():
     # the planted mistake: lists are made however much the store could hold
-    r = subprocess.run([checker, "--plant"], capture_output=True, text=True)
+    r = subprocess.run([checker(), "--plant"], capture_output=True, text=True)
     assert r.returncode == 1 and "part outside the list" in r.stdout

@@ -13,7 +13,7 @@ import torch
 
 from oracle import kvzap_oracle as O
 from paper_2601_07891_amd import binding, synth
-from tests import parity
+from tests import deal, parity
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -228,20 +228,27 @@ def test_rejects_bad_arguments():
     torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("B,H,top,window,max_rows", [
-    (16, 4, 900, 128, None),      # 64 heads: every wavefront finds its part for itself
-    (13, 5, 900, 40, None),       # 65: with its block
-    (65, 4, 150, 0, 5000),        # 260 heads, parts of many short ones under a long bound
-    (130, 4, 60, 33, None),       # a wavefront per split of one head
-    (3, 2, 3000, 0, 10),          # ... the last of which goes past the bound
-    (1, 1, 40000, 128, None),     # one head's hundreds of parts are combined by 32 groups
-    (16, 4, 900, 128, 5000),      # a long bound: equal parts of the list, 64 heads
-    (13, 5, 900, 40, 5000),       # ... and 65
-    (8, 8, 9000, 128, None),      # more than 4096 chunks: streamed, a wavefront's own part
-    (260, 8, 150, 33, None),      # ... and two splits of a head
+@pytest.mark.parametrize("B,H,top,window,max_rows,form", [
+    (16, 4, 900, 128, None, "plain 9"),
+    (13, 5, 900, 40, None, "plain 8"),
+    (65, 4, 150, 0, 5000, "block 896"),       # parts of many short heads under a long bound
+    (130, 4, 60, 33, None, "plain 1"),
+    (3, 2, 3000, 0, 10, "plain 1"),           # the only split goes far past the bound
+    (2, 2, 3000, 16, 500, "plain 5"),         # ... the last of several
+    (1, 1, 40000, 128, None, "plain 314"),    # one head's hundreds of parts are combined by 32 groups
+    (16, 4, 900, 128, 5000, "streamed 21"),
+    (13, 5, 900, 40, 5000, "streamed 20"),
+    (8, 8, 3000, 0, 1500, "streamed 12"),     # the last split goes past the bound
+    (260, 8, 150, 33, None, "streamed 1"),
+    (8, 8, 9000, 128, None, "list 1024"),     # every wavefront finds its part for itself, inside heads
+    (8, 8, 9000, 0, 7800, "list 1024"),       # heads longer than the bound
+    (9, 8, 3000, 70, 12000, "block 896"),     # with its block: parts that begin and end inside heads
+    (140, 8, 60, 0, 700, "block 896"),        # 18 batches of 64 heads: a second round of the sum over them
+    (530, 8, 40, 0, 700, "block 896"),        # 67: a second round of their scan
 ])
-def test_rows_are_dealt_out_whole(B, H, top, window, max_rows):
+def test_rows_are_dealt_out_whole(B, H, top, window, max_rows, form):
     # every third head is empty, so that parts begin, end and pass over heads everywhere
+    assert deal.form(B * H, 2, max_rows or top, window, B * H * top) == form
     rng = np.random.default_rng(B * 1000 + H)
     lengths = rng.integers(0, top + 1, size=(B, H))
     lengths[rng.random((B, H)) < 0.33] = 0

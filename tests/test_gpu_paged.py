@@ -7,7 +7,7 @@ import torch
 
 from oracle import kvzap_oracle as O
 from paper_2601_07891_amd import binding, synth
-from tests import parity
+from tests import deal, parity
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -346,3 +346,84 @@ def test_attend_paged_split_longer_than_one_lookup(rows):
     # looked up 64 chunks at a time (one group, one and a bit, two, four), ring chunks among them
     _attend_case([[rows, 3], [rows + 100, rows - 40]], 16, 70, [128, 33], HQ=8, seed=rows, max_rows=16)
     _attend_case([[rows, 700]], 64, 0, None, HQ=8, seed=rows + 1, max_rows=16)
+
+
+@pytest.mark.parametrize("B,H,top,window,max_rows,form", [
+    (3, 8, 1500, 40, 3000, "plain 24"),
+    (16, 4, 900, 128, 5000, "streamed 21"),
+    (8, 8, 3000, 0, 1500, "streamed 12"),     # the last split goes past the bound
+    (8, 8, 900, 40, 9000, "list 1024"),       # parts that begin inside a head's pages and end in the next
+    (9, 8, 900, 70, 12000, "block 896"),
+])
+def test_attend_paged_in_every_form(B, H, top, window, max_rows, form):
+    assert deal.form(B * H, 2, max_rows, window, top + 32) == form
+    rng = np.random.default_rng(B * 100 + H)
+    lengths = rng.integers(0, top + 1, size=(B, H))
+    lengths[rng.random((B, H)) < 0.33] = 0
+    lengths[-1, -1] = top
+    seq_pos = rng.integers(0, 200, size=B).tolist() if window else None
+    _attend_case(lengths, 16, window, seq_pos, HQ=2 * H, seed=B + H, max_rows=max_rows)
+
+
+@pytest.mark.parametrize("B,H,P,rows,window,form", [
+    (1, 1, 16, 530000, 0, "list 256"),        # parts of 65 chunks: a second lookup each
+    (9, 8, 16, 30000, 70, "block 896"),       # parts of 76, most of which cross a head's border
+    (8, 8, 1 << 20, 1500, 0, "streamed 36"),  # tables that could address 2^31 chunks in all: no list
+])
+def test_attend_paged_over_shared_pages(B, H, P, rows, window, form):
+    """Heads whose tables name a few pages again and again (as prompts that share a prefix do).  A row that
+    occurs n times counts n times, so the reference needs the distinct rows only.  A few rows that most of
+    the weight falls on occur once each, where a part or a lookup begins or ends: one lost, or taken twice,
+    is seen."""
+    D, HQ, plain, spikes = 128, 2 * H, 125, 13
+    max_pages = 1024 if P > 16 else (rows + P - 1) // P
+    max_rows = 9000 if P > 16 else rows
+    assert deal.form(B * H, 2, max_rows, window, max_pages * P) == form
+    rng = np.random.default_rng(rows)
+    num_pages = 1 if P > 16 else plain + spikes
+    q, Kf, Vf, Kg, Vg = synth.make_attend_inputs(B, H, HQ, D, num_pages * P, window, 5, DEV)
+    q[:] = q[0, 0].clone()                    # one query, so that a spike is one for every head
+    lengths = rng.integers(rows - 300, rows + 1, size=(B, H)).astype(np.int32)
+    table = np.full((B * H, max_pages), -1, np.int32)
+    if P > 16:
+        table[:, 0] = 0
+    else:
+        Kf[plain * P:] = 0
+        at = torch.arange(plain, num_pages, device=DEV) * P
+        # (the log of) the number of plain rows, so that the spikes together outweigh them
+        unit = q[0, 0].float() / q[0, 0].float().norm() ** 2
+        Kf[at] = ((np.log(rows / spikes) + 1.0) * D ** 0.5 * unit).bfloat16()
+        chunks = (lengths.reshape(-1) + 31) // 32 + (window + 31) // 32
+        per = -(-int(chunks.sum()) // int(form.split()[1]))
+        assert per > 64                       # more than one lookup
+        for i in range(B * H):
+            n = (int(lengths.reshape(-1)[i]) + P - 1) // P
+            table[i, :n] = rng.integers(0, plain, n)
+            first = int(chunks[:i].sum())
+            begins = [0] + [c - first for c in range(0, first + n // 2, per) if c > first]
+            edges = sorted({2 * c + d for b in begins for c in (b - 1, b, b + 63, b + 64) for d in (0, 1) if 0 <= 2 * c + d < n - 1})
+            table[i, rng.choice(edges, size=spikes, replace=False)] = np.arange(plain, num_pages)
+    out = binding.kvzap_attend_decode_paged(
+        q, Kf.view(num_pages, P, D), Vf.view(num_pages, P, D), _i32(table), P, _i32(lengths),
+        Kg if window else None, Vg if window else None, _i32([200] * B) if window else None, window, max_rows, D ** -0.5)
+    got = out.double().cpu().numpy()
+    used = rows if P > 16 else num_pages * P
+    K, V, qs = synth.f64(Kf[:used]), synth.f64(Vf[:used]), synth.f64(q)
+    for i in range(B * H):
+        b, h = divmod(i, H)
+        n = int(lengths[b, h])
+        count = np.zeros(used)
+        if P > 16:
+            count[:n] = 1
+        else:
+            pool_rows = (table[i, :(n + P - 1) // P, None].astype(np.int64) * P + np.arange(P)).reshape(-1)[:n]
+            np.add.at(count, pool_rows, 1)
+        Ki = np.concatenate([K, synth.f64(Kg[b, h])]) if window else K
+        Vi = np.concatenate([V, synth.f64(Vg[b, h])]) if window else V
+        count = np.concatenate([count, np.ones(window)])
+        s = qs[b, 2 * h:2 * h + 2] @ Ki.T * D ** -0.5
+        w = count * np.exp(s - s[:, count > 0].max(axis=1, keepdims=True))
+        want = (w / w.sum(axis=1, keepdims=True)) @ Vi
+        err = np.abs(got[b, 2 * h:2 * h + 2] - want)
+        assert err.max() <= 2.0 ** -7 * max(1.0, np.abs(Vi).max()), (b, h)
+        assert np.sqrt((err ** 2).mean()) <= 2e-3 * np.sqrt((want ** 2).mean()) + 1e-3, (b, h)
