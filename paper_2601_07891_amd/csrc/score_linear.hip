@@ -16,9 +16,12 @@
 //   C (16 x 16)  = fp32 accumulators, heads 0..15 x 16 tokens
 // Each wavefront owns groups of 16 consecutive tokens and walks the whole D_h.
 #include "kvzap_internal.h"
+#include "score_linear_rule.h"
 
 namespace kvzap {
 namespace {
+
+using namespace linear;
 
 // kThreads: wavefronts of a block share one copy of W in LDS; kUnroll: independent 16-byte
 // loads in flight per lane
@@ -129,9 +132,6 @@ __global__ __launch_bounds__(kThreads) void score_linear_kernel(
 //   Blocks start at different inputs of a row, those of one XCD (every eighth) and neighbours alike: where
 // rows are 2^n bytes long, blocks that walk D_h in step read from the same few memory channels (32768 x
 // 4096: in step 48 us, with the block index alone as the shift 63, with this one 44).
-constexpr int kStreamWaves = 8, kStreamBlocks = 256;
-constexpr int kTurnBytes = 16 * 256;
-
 __global__ __launch_bounds__(kStreamWaves * 64, 2) void score_linear_stream_kernel(
     const unsigned char* __restrict__ hidden, const unsigned short* __restrict__ W,
     const unsigned short* __restrict__ bias, float* __restrict__ scores, long long rows, int T, int Dh, int H,
@@ -361,8 +361,6 @@ __global__ __launch_bounds__(256) void score_linear_short_kernel(
 // W takes its eight rows whatever H is, and the kernels above read fewer: one head at D_h = 4096 12.4 /
 // 13.0 on 6144 tokens, 16.2 / 13.6 on 7000, 17.3 / 14.7 on 8192; two 12.4 / 14.8, 16.2 / 15.2, 17.4 /
 // 15.9; three 16.3 / 16.8 on 7000.
-constexpr long long kRowMaxTokens = 8192, kRowMaxTokensFewHeads = 6144;    // beyond, W per 8 tokens is too much to stage
-constexpr int kRowTokens = 8, kRowInputs = 512, kRowMaxWaves = 10;
 constexpr int kRowWaveBytes = 2 * kRowTokens * kRowInputs * 2;
 
 // LDS slot <-> 16-byte piece of a 1 KB row (its own inverse): the 16 lanes that are served
@@ -451,21 +449,9 @@ int launch_linear(const void* hidden, const void* W, const void* b, float* score
   return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
 }
 
-// Wavefronts of a block, as many as W leaves room for, and the groups whose scores each can hold (0: no room)
-struct Stream {
-  int waves, held;
-};
-Stream stream_of(int Dh, int H) {
-  const long long room = 160 * 1024 - (long long)H * ((long long)Dh * 2 + 64);
-  for (int waves = kStreamWaves; waves >= 4; waves -= 2) {
-    const long long held = (room / waves - kTurnBytes) / (H * 64);
-    if (held > 0) return {waves, (int)(held < 16 ? held : 16)};
-  }
-  return {0, 0};
-}
-
 int launch_linear_stream(const void* hidden, const void* W, const void* b, float* scores, long long rows,
-                         int T, int Dh, int H, Stream st, hipStream_t stream) {
+                         int T, int Dh, int H, hipStream_t stream) {
+  const Stream st = stream_of(Dh, H);
   // once per process, which drives one GPU (thread-safe: a function-local static)
   static const hipError_t attr_rc =
       hipFuncSetAttribute(reinterpret_cast<const void*>(score_linear_stream_kernel),
@@ -480,34 +466,17 @@ int launch_linear_stream(const void* hidden, const void* W, const void* b, float
 
 }  // namespace
 
-// The kernel over whole lines from 30 MB on: below, staging W in every block costs more than the
-// streaming gains.  us per call (it / the kernels it takes the place of), H = 8 unless named: 262144 x 5120 402
-// (6.7 TB/s) / 450, 131072 x 4096 160 / 195, 65536 x 4096 87 / 103, x 2048 46 / 57, 32768 x 4096 44 / 55, 20000 x
-// 5120 37 / 55, 16384 x 4096 24 / 30, 10000 x 2048 11.0 / 12.2; 40000 x 8192 109 / 143;
-// 14 heads 8192 x 4096 15.5 / 20.3; one head 262144 x 4096 317 / 375, 20000 x 1024 10.6 / 12.0; not taken:
-// 12000 x 1024 8.5 / 8.3, 12000 x 512 6.5 / 5.6, two heads 6500 x 2048 9.2 / 8.8.
-// Against the row kernel it wins once that one's blocks, which fill a CU's LDS, come in a third round:
-// 4096 x 4096 13.1 / 10.5, 4500: 13.7 / 13.7, 8192: 14.5 / 19.0, 5000 x 3072 11.6 / 12.6, 8192 x 5120 17.9 / 22.0.
-constexpr long long kStreamBytes = 30000000;
-
 int launch_score_linear(const void* hidden, const void* W, const void* b, float* scores,
                         int B, int T, int Dh, int H, hipStream_t stream) {
   const long long rows = (long long)B * T;
-  const long long ngroups = (rows + 15) / 16;
-  const Stream st = stream_of(Dh, H);
-  const bool long_enough = st.held > 0 && ngroups > 256 && rows * Dh * 2 >= kStreamBytes;
-  if (H <= kRowTokens && Dh <= kRowMaxWaves * kRowInputs && rows <= (H <= 2 ? kRowMaxTokensFewHeads : kRowMaxTokens)) {
-    const int per_cu = kRowMaxWaves / ((Dh + kRowInputs - 1) / kRowInputs);          // blocks that the LDS holds
-    if (!long_enough || rows <= 18ll * per_cu * kStreamBlocks)                       // 2.25 rounds of 8 tokens
-      return launch_linear_rows(hidden, W, b, scores, rows, T, Dh, H, stream);
+  switch (form_of(rows, Dh, H)) {
+    case Form::kRows: return launch_linear_rows(hidden, W, b, scores, rows, T, Dh, H, stream);
+    case Form::kStream: return launch_linear_stream(hidden, W, b, scores, rows, T, Dh, H, stream);
+    case Form::kWide: return launch_linear<1024, 8>(hidden, W, b, scores, rows, T, Dh, H, 1024, stream);
+    case Form::kNarrow: return launch_linear<256, 8>(hidden, W, b, scores, rows, T, Dh, H, 1024, stream);
+    case Form::kShort: break;
   }
-  if (long_enough) return launch_linear_stream(hidden, W, b, scores, rows, T, Dh, H, st, stream);
-  // where W leaves that kernel no room or the input is short; from 64k tokens 16-wavefront blocks (W is
-  // staged into LDS once per block), shorter inputs 4-wavefront blocks so that more CUs take part
-  if (ngroups >= 4096) return launch_linear<1024, 8>(hidden, W, b, scores, rows, T, Dh, H, 1024, stream);
-  if (ngroups > 512 || Dh % 128 != 0)       // 16k tokens: 26 us with the kernel above, 32 us here
-    return launch_linear<256, 8>(hidden, W, b, scores, rows, T, Dh, H, 1024, stream);
-  score_linear_short_kernel<<<dim3((unsigned)ngroups), 256, 0, stream>>>(
+  score_linear_short_kernel<<<dim3((unsigned)((rows + 15) / 16)), 256, 0, stream>>>(
       static_cast<const unsigned short*>(hidden), static_cast<const unsigned short*>(W),
       static_cast<const unsigned short*>(b), scores, rows, T, Dh, H);
   return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;

@@ -6,11 +6,11 @@ from tests.deal import checker
 
 
 def test_parts_stay_inside_the_list_whatever_the_lengths_say():
-    r = subprocess.run([checker()], capture_output=True, text=True)
+    r = subprocess.run([checker("attend_deal_check")], capture_output=True, text=True)
     assert r.returncode == 0 and " 0 faults" in r.stdout, r.stdout
 
 
 def test_a_list_longer_than_its_sum_can_hold_is_caught():
     # the planted mistake: lists are made however much the store could hold
-    r = subprocess.run([checker(), "--plant"], capture_output=True, text=True)
+    r = subprocess.run([checker("attend_deal_check"), "--plant"], capture_output=True, text=True)
     assert r.returncode == 1 and "part outside the list" in r.stdout

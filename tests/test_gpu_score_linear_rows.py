@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from paper_2601_07891_amd import binding
+from tests import deal
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -29,16 +30,19 @@ def test_against_float64(B, T, Dh, H, bias):
     assert ((got.transpose(1, 2) - want).abs() <= 2 * Dh ** 0.5 * 2.0 ** -24 * size).all()
 
 
-@pytest.mark.parametrize("B,T,Dh,H", [
-    (1, 4609, 4096, 8),           # the first input of a third round of row blocks
-    (1, 3663, 4096, 9), (1, 4112, 4096, 9), (1, 5001, 4096, 16),       # more heads than the row kernel's
-    (3, 2731, 4160, 8), (1, 9999, 2112, 3),                            # D_h ends inside a stage
-    (1, 6145, 8192, 8), (1, 4400, 8960, 8),                            # W leaves room for 6 and 4 wavefronts
-    (2, 40001, 448, 1), (7, 33500, 64, 5),                             # one and a half stages a row; less than one
-    (1, 32768, 512, 8),
+@pytest.mark.parametrize("B,T,Dh,H,form", [
+    (1, 4609, 4096, 8, "rows"),                                        # a third round of row blocks
+    (1, 6145, 4096, 8, "stream"),                                      # the first input of a fourth
+    (1, 3663, 4096, 9, "short"), (1, 4112, 4096, 9, "stream"), (1, 5001, 4096, 16, "stream"),   # more heads than the row kernel's
+    (3, 2731, 4160, 8, "stream"), (1, 9999, 2112, 3, "stream"),        # D_h ends inside a stage
+    (1, 6145, 8192, 8, "stream"), (1, 4400, 8960, 8, "stream"),        # W leaves room for 6 and 4 wavefronts
+    (2, 40001, 448, 1, "stream"), (7, 37500, 64, 5, "stream"),         # one and a half stages a row; less than one
+    (7, 33500, 64, 5, "stream"), (7, 33400, 64, 5, "wide"), (1, 31249, 512, 8, "narrow"), (1, 31250, 512, 8, "stream"),
+    (1, 12701, 2048, 8, "narrow"), (1, 16385, 2048, 8, "stream"),      # the ends of the narrow blocks' last stretch
 ])
 @pytest.mark.parametrize("bias", [False, True])
-def test_long_inputs_against_float64(B, T, Dh, H, bias):
+def test_long_inputs_against_float64(B, T, Dh, H, form, bias):
+    assert deal.linear_form(B * T, Dh, H) == form
     g = torch.Generator(device=DEV).manual_seed(B * T + Dh)
     x = torch.randn((B, T, Dh), generator=g, device=DEV).bfloat16()
     W = (torch.randn((H, Dh), generator=g, device=DEV) * Dh ** -0.5).bfloat16()
