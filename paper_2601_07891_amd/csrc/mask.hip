@@ -170,7 +170,9 @@ __global__ __launch_bounds__(kThreads) void mask_emit_kernel(
   const float* row = scores + (size_t)bh * T;
   const bool vec_ok = (T % 4) == 0;
   const int t0 = chunk * kMaskChunk + threadIdx.x * kPerThread;
-  int before = 0, own = 0;                                 // kept ahead of this chunk; in this head
+  int64_t prefix = 0;                                      // kept ahead of this chunk
+  int before = 0, own = 0;                                 // this thread's part of it; of the head's
+  if (!kFused) prefix = chunk_prefix[(size_t)bh * nchunks + chunk];
   if (kFused) {
     // chunks are ordered (b,h)-major; the first chunk of a head adds up the head's as well.  The array
     // is padded to 256 bytes, so that four counts at a time stay inside it.
@@ -193,16 +195,19 @@ __global__ __launch_bounds__(kThreads) void mask_emit_kernel(
   own = kFused && chunk == 0 ? wave_scan(own) : 0;         // (uniform)
   if (lane == 63) {
     s_kept[wid] = incl;
-    s_before[wid] = before;
-    s_own[wid] = own;
+    if (kFused) {
+      s_before[wid] = before;
+      s_own[wid] = own;
+    }
   }
   __syncthreads();
-  int64_t prefix = kFused ? 0 : chunk_prefix[(size_t)bh * nchunks + chunk];
   int ahead = 0, head_total = 0;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) {
-    prefix += s_before[w];
-    head_total += s_own[w];
+    if (kFused) {
+      prefix += s_before[w];
+      head_total += s_own[w];
+    }
     ahead += w < wid ? s_kept[w] : 0;
   }
   if (kFused && chunk == 0 && threadIdx.x == 0) {          // this head's length and start
