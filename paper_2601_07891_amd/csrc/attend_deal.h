@@ -10,28 +10,31 @@ namespace deal {
 
 constexpr int kMinChunks = 4;            // of a wavefront: fewer, and the combining pass takes longer
 
-// Measured below: us per call of both passes, 8 KV heads and 4 query heads each unless named; rows cold in memory /
-// three caches in turn, which the 256 MB memory-side cache may hold.
+// As one list: equal parts of all heads' chunks in 4-wavefront blocks on 28 of an XCD's 32 CUs, or where there
+// are no more than 64 heads in one-wavefront blocks on all of them, but at least kMinChunks chunks each. us a
+// call of both passes, rows cold in memory, 8 KV heads and 4 query heads each unless named (as streamed
+// splits, as plain ones): 64 sequences of 4k..32k rows 702 (766, 843), 6.96 TB/s (with 1024 wavefronts 711,
+// 2048 787); 24 of 4k..8k 97.6 (102.8, 117), 40 of 0.3k..2.4k 45.0 (56.2, 66.6), 8 of 0.1k..30k 80.7 (103,
+// 117), 3 of 8k..32k 45.0 (51.0, 59.2), 8 of 2k..8k 33.1 (36.7, 42.4), 16 of 2k..8k 58.2 (63.0, 74.6).
 //
-// As one list: equal parts of all heads' chunks in 4-wavefront blocks on 28 of an XCD's 32 CUs, or where
-// there are no more than 64 heads in one-wavefront blocks on all of them, but at least kMinChunks chunks
-// each.  64 sequences of 4k..32k rows 702 (6.96 TB/s; in streamed splits 766, in plain ones 843; with 1024
-// wavefronts 711, 2048 787), 24 of 4k..8k 97.6 (102.8, 117), 40 of 0.3k..2.4k 45.0 (56.2, 66.6), 8 of 0.1k..30k 80.7
-// (103, 117), 3 of 8k..32k 45.0 (51.0, 59.2).
-// Head by head, streamed, where the list is short by the caller's bound: its parts wait for the sum over the heads,
-// and most bounds are loose.  3 of 1k..8k 18.0 / 16.7 (as a list 18.7 / 17.6), 1 of 32k 28.6 / 28.3 (29.3 / 28.9), 8 of
-// 1500 under a bound of 6500 15.2 / 14.1 (17.3 / 16.1), 32 of 500 under 2500 20.1 / 19.2 (22.1 / 21.2), 64 of 128 under 1012
-// 17.8 / 16.6 (21.4 / 20.0).  Ragged heads under a tight bound are the better as a list from there on and a little before: 8 of
-// 2k..8k 33.1 (36.7), 16 of 2k..8k 58.2 (63.0), 24 of 0.5k..2k 29.9 / 29.5 (31.3 / 31.0).  Past 64 heads the line is further
-// up, since the sum then goes through LDS and a barrier; and from 8 query heads for a KV head on, since the list's parts are
-// shorter and the sums of each are as large (16 query heads, 8 of 2k..4k 23.8 / 23.4, as a list 28.4 / 28.1).
-// So are heads of a few chunks at any number, since a part's every head begins with a wait for its first
-// rows: 512 heads of 64 rows under a bound of 512 15.4 / 14.3 (19.3 / 18.0).
-// The smallest lists take plain loads in the operand layout: 1 sequence of 100..500 rows 8.4 / 7.0 (streamed 8.9 /
-// 8.2), of 0.7k..3k 10.4 / 8.2 (10.0 / 9.0), of 4000 11.5 / 9.9 (11.0 / 9.9); past the line 4 of 0.3k..2.4k 13.1 / 11.4 (12.2 / 10.9).
-constexpr int kShortHead = 20;           // chunks, by the caller's bound
-constexpr long long kPlainChunks = 2560;                              // of all heads, by the bound: 42 MB
-constexpr long long split_chunks(int BH, int G) { return BH > 64 || G >= 8 ? 24576 : 15360; }   // 403 and 252 MB
+// Head by head, which starts without a sum over the heads, where the list is short by the caller's bound.
+// Plain loads in the operand layout while the rows may be found in the memory-side cache, out of which the
+// hint keeps them (a bound of many chunks is seldom full). A decoding step (evict and attend) of three caches
+// in turn, us (streamed splits, list): 1 of 0.1k..0.5k rows 17.4 (17.9, 19.5), 4 of 0.3k..2.4k 20.6 (21.1,
+// 22.1), 6 of 1500 22.0 (22.8, 24.2), 3 of 1k..8k 26.2 (27.0, 27.3), in pages 26.6 (27.5, 28.7). With every
+// row cold the streamed splits are the better from some 8 MB on: a call for 3 of 1k..8k 19.8 (18.0, 18.7).
+//
+// Streamed splits where the list may be more than that cache holds: a step for 9 of 1500 under a bound of 7644
+// in pages 26.2 (list 29.5; plain 25.2), 1 of 32k in pages 38.6 (39.6; 41.7), 16 of 1500 38.4 (39.5; 42.4), 24
+// of 1500 49.2 (47.2; 54.9), 64 of 500 48.0 (47.8; 53.9). The line to the list is further up past 64 heads,
+// whose sum goes through LDS and a barrier, and from 8 query heads for a KV head on, since the list's parts
+// are shorter and the sums of each are as large (16 query heads, 8 of 2k..4k 23.8 a call, as a list 28.4).
+//
+// Heads of a few chunks go head by head at any number, since a part's every head begins with a wait for its
+// first rows: 512 heads of 64 rows under a bound of 512 15.4 a call, as a list 19.3.
+constexpr int kShortHead = 20;                                          // chunks, by the caller's bound
+constexpr long long plain_chunks(long long ct) { return ct > 128 && ct <= 1024 ? 11264 : 4096; }   // 185 and 67 MB
+constexpr long long split_chunks(int BH, int G) { return G >= 8 ? 24576 : BH > 64 ? 18432 : 15360; }   // 403, 302, 252 MB
 // The list's length is summed on the device in 32 bits, from lengths that only the store's size bounds
 // (whatever the caller's array or its bound say, and heads may share pages): where that could come near
 // 2^31 chunks no list is made.
@@ -54,7 +57,7 @@ constexpr Dealt deal_of(int BH, int G, long long ct, long long most) {
     int spc = kMinChunks;
     while (spc < ct && (spc < fill || (spc < 64 && spc < fold && all >= 512ll * spc))) spc *= 2;
     const int splits = (int)((ct + spc - 1) / spc);
-    return {Deal::kHead, BH * (splits > 0 ? splits : 1), spc, all > kPlainChunks};
+    return {Deal::kHead, BH * (splits > 0 ? splits : 1), spc, all > plain_chunks(ct)};
   }
   const long long nw = (all + kMinChunks - 1) / kMinChunks, most_waves = BH > 64 ? 896 : BH < 4 ? 256 * BH : 1024;
   return {BH > 64 ? Deal::kBlock : Deal::kWave, (int)(nw < most_waves ? nw : most_waves), 0, true};

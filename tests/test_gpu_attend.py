@@ -236,9 +236,9 @@ def test_rejects_bad_arguments():
     (3, 2, 3000, 0, 10, "plain 1"),           # the only split goes far past the bound
     (2, 2, 3000, 16, 500, "plain 5"),         # ... the last of several
     (1, 1, 40000, 128, None, "plain 314"),    # one head's hundreds of parts are combined by 32 groups
-    (16, 4, 900, 128, 5000, "streamed 21"),
-    (13, 5, 900, 40, 5000, "streamed 20"),
-    (8, 8, 3000, 0, 1500, "streamed 12"),     # the last split goes past the bound
+    (16, 4, 900, 128, 6000, "streamed 24"),
+    (13, 5, 900, 40, 6000, "streamed 24"),
+    (12, 8, 3000, 0, 1500, "streamed 12"),    # the last split goes past the bound
     (260, 8, 150, 33, None, "streamed 1"),
     (8, 8, 9000, 128, None, "list 1024"),     # every wavefront finds its part for itself, inside heads
     (8, 8, 9000, 0, 7800, "list 1024"),       # heads longer than the bound

@@ -350,8 +350,8 @@ def test_attend_paged_split_longer_than_one_lookup(rows):
 
 @pytest.mark.parametrize("B,H,top,window,max_rows,form", [
     (3, 8, 1500, 40, 3000, "plain 24"),
-    (16, 4, 900, 128, 5000, "streamed 21"),
-    (8, 8, 3000, 0, 1500, "streamed 12"),     # the last split goes past the bound
+    (16, 4, 900, 128, 6000, "streamed 24"),
+    (12, 8, 3000, 0, 1500, "streamed 12"),    # the last split goes past the bound
     (8, 8, 900, 40, 9000, "list 1024"),       # parts that begin inside a head's pages and end in the next
     (9, 8, 900, 70, 12000, "block 896"),
 ])
