@@ -126,8 +126,11 @@ size_t kvzap_workspace_bytes(int which_call, int B, int T, int Dh, int M, int H)
  * 384 tokens, and wherever D_h can be cut into slices of at least 256 inputs for up to 112 token
  * blocks (14336 tokens, 10752 at M = 640), every token has that fp32 form.  Both are far inside
  * the 1e-2 score tolerance.
- * The sum order is fixed for a given shape, so results are run-to-run deterministic; the same
- * token scored in calls of different B*T may differ in the fourth digit.  B*T == 0 is a no-op.
+ * The sum order is fixed for a given shape and position, so results are run-to-run deterministic;
+ * the same token scored in calls of different B*T may differ in the fourth digit, and equal tokens
+ * at different positions of one call too: with the MLP where one of them is among the last (see
+ * above), with the linear surrogate on long inputs by the rounding of an fp32 sum (1e-7 of it),
+ * whose order shifts from one stretch of tokens to the next.  B*T == 0 is a no-op.
  */
 int kvzap_score(const void* hidden, const void* W1, const void* b1,
                 const void* W2, const void* b2, float* scores,
@@ -414,7 +417,9 @@ int kvzap_decode_evict(const void* hidden_new, const void* W1, const void* b1,
  * product rounded to bf16 and the denominator sums those rounded weights, so the
  * output is a convex combination of the V rows up to fp32 rounding, then rounded to
  * bf16.  Fixed combination order (run-to-run deterministic); the result does not
- * depend on the order of the rows beyond rounding.
+ * depend on the order of the rows beyond rounding.  Rows are shared out in equal parts where
+ * B * H * max_rows is large: a sequence's output then changes within that rounding with the
+ * lengths of the others in the call, not only with B * H, HQ and max_rows.
  */
 int kvzap_attend_decode(const void* q, const void* K_rows, const void* V_rows,
                         int64_t total_rows, const int64_t* row_offsets,
