@@ -36,8 +36,32 @@ MEASURED_HBM_TRAFFIC = {
     ("c3_qwen8b_128k_mlp", "score_mlp_frag_kernel"): 1213.9e6 + 4.2e6,
     ("c3_qwen8b_128k_mlp", "compact_kernel"): 146.5e6 + 143.3e6,
     # profiles/c5_attend_hbm_traffic.txt (default rows-per-head range, 32 query heads)
-    ("c5_qwen8b_decode+attend", "attend_partial_kernel"): 4926.1e6 + 10.4e6,
+    ("c5_qwen8b_decode+attend", "attend_list_kernel"): 4920.5e6 + 3.0e6,
 }
+
+
+def linear_kernel(rows: int, Dh: int, H: int) -> str:
+    """The kernel that the library gives a linear surrogate's input to (csrc/score_linear_rule.h)."""
+    room = 160 * 1024 - H * (Dh * 2 + 64)
+    fits = any(room // waves - 4096 >= H * 64 for waves in (8, 6, 4))
+    nbytes = rows * Dh * 2
+    stream = (fits and rows > 4096 and nbytes >= (30e6 if rows > 65536 or Dh >= 2560 else 32e6) and
+              not ((10000 if H <= 2 else 12700) < rows <= 16384 and nbytes <= 90e6) and
+              not (H <= 2 and Dh <= 512 and rows <= 65536))
+    if H <= 8 and Dh <= 5120 and rows <= (6144 if H <= 2 else 8192) and (
+            not stream or rows <= 6144 * (10 // -(-Dh // 512))):
+        return "score_linear_rows_kernel"
+    if stream:
+        return "score_linear_stream_kernel"
+    return "score_linear_short_kernel" if rows <= 8192 and Dh % 128 == 0 else "score_linear_kernel"
+
+
+def attend_kernel(heads: int, group: int, max_rows: int, window: int) -> str:
+    """The first of the two kernels that the library runs for a decode-attention call over an ordinary store
+    (csrc/attend_deal.h)."""
+    ct = -(-max_rows // 32) + -(-window // 32)
+    most = 24576 if group >= 8 else 18432 if heads > 64 else 15360
+    return "attend_split_kernel" if ct <= 20 or ct * heads <= most else "attend_list_kernel"
 
 
 def _host_numerics() -> dict:
@@ -289,9 +313,9 @@ def bench_attend(wl, args) -> dict:
         "ms_per_call": ms_call,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": achieved / PEAK_HBM_GBS,
-                     "traffic": (MEASURED_HBM_TRAFFIC.get((wl.name + "+attend", "attend_partial_kernel"))
+                     "traffic": (MEASURED_HBM_TRAFFIC.get((wl.name + "+attend", "attend_list_kernel"))
                                  if (lo, hi, HQ, B, P) == (4096, 32768, 32, 64, 0) else None),
-                     "kernel": "attend_partial_kernel (+ attend_combine_kernel in the same interval)",
+                     "kernel": attend_kernel(B * H, HQ // H, hi, w) + " (+ attend_combine_kernel in the same interval)",
                      "bytes_per_launch": bytes_call},
         "cpu_baseline": {"value": sample_rows / (c1 - c0), "unit": "cache rows/s",
                          "gpu_value_same_unit": rows / (ms_call * 1e-3),
@@ -658,8 +682,7 @@ def bench_prefill(wl, args, L, oracle: bool, extras: bool) -> dict:
                     "achieved": score_flops / (score_ms * 1e-3) / 1e12, "peak": PEAK_BF16_TFLOPS,
                     "unit": "TFLOP/s", "traffic": None}
     else:
-        by_rows = H <= 8 and Dh <= 5120 and B * T <= (6144 if H <= 2 else 8192)      # launch_score_linear's rule
-        roofline = {"kernel": "score_linear_rows_kernel" if by_rows else "score_linear_kernel", "bound": "hbm",
+        roofline = {"kernel": linear_kernel(B * T, Dh, H), "bound": "hbm",
                     "achieved": (B * T * (2 * Dh + 4 * H)) / (score_ms * 1e-3) / 1e9,
                     "peak": PEAK_HBM_GBS, "unit": "GB/s", "traffic": None}
     roofline["frac"] = roofline["achieved"] / roofline["peak"]

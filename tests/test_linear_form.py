@@ -18,3 +18,22 @@ from tests import deal
 ])
 def test_inputs_go_to_the_faster_kernel(rows, Dh, H, form):
     assert deal.linear_form(rows, Dh, H) == form
+
+
+def test_the_benchmark_names_the_kernels_that_run():
+    import random
+
+    import bench
+    rng = random.Random(3)
+    names = {"rows": "score_linear_rows_kernel", "stream": "score_linear_stream_kernel",
+             "short": "score_linear_short_kernel"}
+    for _ in range(150):
+        Dh, H = 64 * rng.randint(1, 120), rng.choice([1, 2, 3, 4, 8, 8, 12, 16])
+        rows = int(2 ** rng.uniform(0, 19))
+        if H * (Dh * 2 + 64) <= 160 * 1024:
+            form = deal.linear_form(rows, Dh, H)
+            assert bench.linear_kernel(rows, Dh, H) == names.get(form, "score_linear_kernel"), (rows, Dh, H, form)
+        heads, group, bound, window = rng.randint(1, 600), rng.randint(1, 16), int(2 ** rng.uniform(0, 17)), rng.choice([0, 40, 128])
+        kind = deal.form(heads, group, bound, window, bound).split()[0]
+        assert bench.attend_kernel(heads, group, bound, window) == ("attend_list_kernel" if kind in ("list", "block")
+                                                                     else "attend_split_kernel"), (heads, group, bound, window)
