@@ -13,7 +13,7 @@ INC = os.path.join(ROOT, "paper_2601_07891_amd", "csrc")
 
 
 @functools.lru_cache(None)
-def checker(name):
+def program(name):
     if shutil.which("g++") is None:
         pytest.skip("no host compiler")
     exe = os.path.join(tempfile.mkdtemp(prefix="deal"), name)
@@ -23,7 +23,7 @@ def checker(name):
 
 
 def _ask(name, *args):
-    return subprocess.run([checker(name), *(str(int(x)) for x in args)], check=True, capture_output=True,
+    return subprocess.run([program(name), *(str(int(x)) for x in args)], check=True, capture_output=True,
                           text=True).stdout.strip()
 
 
