@@ -86,10 +86,10 @@ const char* kvzap_version(void);
  * workspace and for invalid arguments.  Pure host function.
  * KVZAP_CALL_SCORE with M > 0 asks for M*Dh*2 bytes, where a long input gets its copy of W1 in
  * the order the matrix-core loads want it (a few microseconds per call), and more where the
- * input, or what whole rounds of token blocks leave over, is scored in tiles over the hidden
- * units (at most B*T*M*H/8 bytes) or D_h is cut into slices (at most 8*B*T*M*4 bytes).  That
- * amount does not grow evenly with the length.  Inputs of more than 112 token blocks, or whose
- * D_h is not cut, are also scored in a buffer of M*Dh*2 bytes rounded up to 256, which is what a
+ * input, or what whole rounds of token blocks leave over, is scored in tiles or blocks over the
+ * hidden units (at most B*T*M*H/8 bytes).  That
+ * amount does not grow evenly with the length.  Inputs that need not keep an fp32 epilogue (see
+ * kvzap_score) are also scored in a buffer of M*Dh*2 bytes rounded up to 256, which is what a
  * query for a long input returns at least; shorter ones in one that was queried for a longer
  * input of that kind: less quickly, within the same tolerance.
  */
@@ -120,10 +120,10 @@ size_t kvzap_workspace_bytes(int which_call, int B, int T, int Dh, int M, int H)
  * within 2.6e-5 (absolute) of z * Phi(z) for every z, evaluated in fp32; its result is rounded
  * to fp16 (relative 2^-11; values beyond 65504 become infinite) and W2 is converted to fp16
  * (exact for bf16 magnitudes in [2^-14, 65504], subnormal or infinite beyond) for the second
- * projection on the matrix cores, accumulated in fp32.  Short inputs, and the last tokens of
- * inputs that are no whole number of rounds of token blocks, take a tiled form whose GELU (erf
- * to 1.5e-7) and second projection are fp32.  Raw weights (this call and kvzap_compress): up to
- * 384 tokens, and wherever D_h can be cut into slices of at least 256 inputs for up to 112 token
+ * projection on the matrix cores, accumulated in fp32.  Short and mid-length inputs, and the last
+ * tokens of inputs that are no whole number of rounds of token blocks, take forms tiled over the units
+ * whose GELU (erf to 1.5e-7) and second projection are fp32.  Raw weights (this call and kvzap_compress): up to
+ * 384 tokens, and wherever D_h can be cut into even parts of at least 256 inputs for up to 112 token
  * blocks (14336 tokens, 10752 at M = 640), every token has that fp32 form.  Both are far inside
  * the 1e-2 score tolerance.
  * The sum order is fixed for a given shape and position, so results are run-to-run deterministic;
@@ -244,9 +244,10 @@ int kvzap_mask_static(const float* scores, float tau, int window,
  * kvzap_score_prepared takes that buffer in place of W1 and needs no workspace: it runs the
  * kernel over token blocks, whatever the length.  kvzap_score_prepared_ws takes a
  * workspace as well (KVZAP_CALL_SCORE_PREPARED; may be NULL where that is 0) and scores short
- * inputs and remainders in tiles (1k tokens: 17 us against 83 us): the bits of kvzap_score where
- * both take the same form, otherwise (mid-length inputs, which kvzap_score keeps in fp32) equal to
- * it within the fp16 rounding of the activations.  M > 0 only (the linear surrogate has nothing to prepare);
+ * inputs and remainders in tiles (1k tokens: 17 us against 83 us), mid-length ones in blocks with a part
+ * of the units: the bits of kvzap_score where both take the same form, otherwise equal to it within the
+ * fp16 rounding of the activations.  Up to half a round of the largest tile (16384 / (M / 128) tokens) a
+ * workspace smaller than queried is refused, beyond it selects a form that needs less.  M > 0 only (the linear surrogate has nothing to prepare);
  * other arguments, layouts and errors as kvzap_score.  The prepared layout is private to
  * the library version that wrote it.
  */

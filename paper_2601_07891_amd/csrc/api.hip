@@ -220,10 +220,12 @@ int kvzap_prepare_scorer_rmsnorm(const void* W1, const void* gain, int Dh, int M
 }
 
 namespace {
-// the optional workspace of the entry points that take a prepared W1
-int check_prepared_workspace(int B, int T, int Dh, int M, int H, const void* workspace, size_t workspace_bytes) {
-  const size_t need = kvzap::score_mlp_workspace_bytes((long long)B * T, Dh, M, H, true);
-  if (need > 0 && (!workspace || !aligned256(workspace) || workspace_bytes < need)) return KVZAP_ERR_WORKSPACE;
+// the optional workspace of the entry points that take a prepared W1: nullptr if it cannot be used
+int check_prepared_workspace(int B, int T, int Dh, int M, int H, void*& workspace, size_t workspace_bytes) {
+  const size_t least = kvzap::score_mlp_prepared_least_bytes((long long)B * T, Dh, M, H);
+  const bool usable = workspace && aligned256(workspace);
+  if (least > 0 && (!usable || workspace_bytes < least)) return KVZAP_ERR_WORKSPACE;
+  if (!usable) workspace = nullptr;
   return KVZAP_OK;
 }
 
@@ -249,7 +251,7 @@ int score_rmsnorm(const void* x, const void* W1_prepared, const void* gain, floa
   if (rc != KVZAP_OK) return rc;
   return kvzap::launch_score_mlp_rmsnorm(x, W1_prepared, gain, eps, b1, W2, b2, scores, rstd, normed,
                                          B, T, Dh, M, H, with_workspace ? workspace : nullptr,
-                                         static_cast<hipStream_t>(stream));
+                                         workspace_bytes, static_cast<hipStream_t>(stream));
 }
 
 int score_prepared(const void* hidden, const void* W1_prepared, const void* b1, const void* W2,

@@ -147,8 +147,40 @@ __device__ __forceinline__ float gelu_exact(float z) {
   return z * phi;
 }
 
-// The normalised states of a block's `rows` rows of ppr 16-byte pieces, x * rstd * gain rounded to
-// bf16, rstd in LDS.  A pure copy, bound by how many
+// The end of the bf16 range
+constexpr float kMaxBf16 = 3.3895313892515355e38f;
+
+// dot + W2 . a for eight activations of one lane (v_mfma_f32_32x32x16_bf16's B operand): they stay
+// fp32, as three bf16 terms (24 bits); wa: bf16.  a[e] is -0.17 and up, or NaN.
+__device__ __forceinline__ floatx16 dot_three_terms(bf16x8 wa, const float (&a)[8], floatx16 dot) {
+  bf16x8 hi, mid, lo;
+  float top = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    top = fmaxf(top, a[e]);
+    hi[e] = (__bf16)a[e];
+    const float r1 = a[e] - (float)hi[e];
+    mid[e] = (__bf16)r1;
+    lo[e] = (__bf16)(r1 - (float)mid[e]);
+  }
+  // Beyond the bf16 range the first term stays at its end (rounding takes the last 0.2 % of the fp32
+  // range to infinity, and the rest would be minus infinity); an infinite a is the second term alone.
+  if (__any(top > kMaxBf16)) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      hi[e] = (__bf16)(a[e] > kMaxBf16 ? kMaxBf16 : a[e]);
+      const float r1 = a[e] - (float)hi[e];
+      mid[e] = (__bf16)r1;
+      lo[e] = (__bf16)(r1 == (float)mid[e] ? 0.0f : r1 - (float)mid[e]);
+    }
+  }
+  dot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, lo, dot, 0, 0, 0);
+  dot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, mid, dot, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, hi, dot, 0, 0, 0);
+}
+
+// The normalised states of a block's `rows` rows of ppr 16-byte pieces, columns [first, end) of them,
+// x * rstd * gain rounded to bf16, rstd in LDS.  A pure copy, bound by how many
 // bytes the block's few wavefronts keep in flight: a wavefront takes every kWaves-th row, kG * 64
 // pieces of it at a time, so that its part of the gain stays in registers, and loads the next kR
 // rows while it scales and stores the last ones.  Rows past the end repeat the last row and, where
@@ -156,9 +188,10 @@ __device__ __forceinline__ float gelu_exact(float z) {
 // values.
 template <int kWaves, int kG, int kR>
 __device__ __forceinline__ void write_states_columns(const u32x4* from, u32x4* to, const u32x4* gain,
-                                                     const float* rstd, int rows, int ppr, int wave, int lane) {
-  for (int c0 = 0; c0 < ppr; c0 += kG * 64) {
-    const int at = kG > 1 || c0 + lane < ppr ? c0 + lane : ppr - 1;
+                                                     const float* rstd, int rows, int ppr, int wave, int lane,
+                                                     int first, int end) {
+  for (int c0 = first; c0 < end; c0 += kG * 64) {
+    const int at = kG > 1 || c0 + lane < end ? c0 + lane : end - 1;
     u32x4 g[kG], xa[kR][kG], xb[kR][kG];
 #pragma unroll
     for (int c = 0; c < kG; ++c) g[c] = gain[at + c * 64];
@@ -205,9 +238,11 @@ __device__ __forceinline__ void write_states_columns(const u32x4* from, u32x4* t
 }
 template <int kWaves, int kG, int kR>
 __device__ __forceinline__ void write_states(const u32x4* from, u32x4* to, const u32x4* gain,
-                                             const float* rstd, int rows, int ppr, int wave, int lane) {
-  if (kG > 1 && ppr % (kG * 64) == 0) write_states_columns<kWaves, kG, kR>(from, to, gain, rstd, rows, ppr, wave, lane);
-  else write_states_columns<kWaves, 1, 8>(from, to, gain, rstd, rows, ppr, wave, lane);
+                                             const float* rstd, int rows, int ppr, int wave, int lane,
+                                             int first, int end) {
+  if (kG > 1 && (end - first) % (kG * 64) == 0)
+    write_states_columns<kWaves, kG, kR>(from, to, gain, rstd, rows, ppr, wave, lane, first, end);
+  else write_states_columns<kWaves, 1, 8>(from, to, gain, rstd, rows, ppr, wave, lane, first, end);
 }
 
 // LDS tile of 128-byte rows (eight 16-byte pieces): byte offset of logical piece `piece` of
@@ -267,6 +302,7 @@ struct NormArgs {
   unsigned short* normed;        // bf16 [rows, Dh] or nullptr
 };
 
+constexpr int kXcds = 8;
 // score_tile.hip: tiles over tokens and units; index 0 is the largest, tiles get smaller from there
 constexpr int kScoreTiles = 5;
 // blocks on the XCD that gets the most (a token tile's unit tiles all go to one XCD)
@@ -281,6 +317,10 @@ int launch_score_tile(int tile, bool frag, const void* hidden, const void* W1, c
                       long long row_first, int T, int Dh, int M, int H, const NormArgs* norm,
                       hipStream_t stream);
 
+// scores of rows [row_first, row_first + rows) = sum over their nut parts [nut][H][rows], in order, + b2
+int launch_score_sum(const float* part, const void* b2, float* scores, long long rows, long long row_first,
+                     int T, int H, int nut, hipStream_t stream);
+
 // decode.hip: the first projection alone, partial[ks][rows][M] fp32, ks = skinny_ksplit(...)
 int skinny_ksplit(long long rows, int Dh, int M, int target_blocks);
 int launch_skinny_gemm(const void* hidden, const void* W1, float* partial, long long rows, int Dh,
@@ -289,6 +329,9 @@ int launch_skinny_gemm(const void* hidden, const void* W1, float* partial, long 
 // bytes the workspace of kvzap_score (prepared: of the entry points that take a prepared W1)
 // needs for an MLP surrogate on `rows` tokens
 size_t score_mlp_workspace_bytes(long long rows, int Dh, int M, int H, bool prepared);
+// the least that is asked of a caller with prepared weights: the plan's up to half a round of the largest
+// tile; beyond, a smaller buffer selects that tile alone, or token blocks, which need none
+size_t score_mlp_prepared_least_bytes(long long rows, int Dh, int M, int H);
 // the least that launch_score_mlp takes for raw weights, by a form that needs less memory
 size_t score_mlp_least_workspace_bytes(long long rows, int Dh, int M, int H);
 // gain (optional): the prepared copy holds W1 * diag(gain), for launch_score_mlp_rmsnorm
@@ -298,7 +341,7 @@ bool score_rmsnorm_supports(int Dh);
 int launch_score_mlp_rmsnorm(const void* x, const void* W1_prepared, const void* gain, float eps,
                              const void* b1, const void* W2, const void* b2, float* scores,
                              float* rstd, void* normed, int B, int T, int Dh, int M, int H,
-                             void* workspace, hipStream_t stream);
+                             void* workspace, size_t workspace_bytes, hipStream_t stream);
 // prepared: W1 is the copy made by launch_prepare_w1 and the workspace is optional
 int launch_score_mlp(const void* hidden, const void* W1, const void* b1, const void* W2,
                      const void* b2, float* scores, int B, int T, int Dh, int M, int H,

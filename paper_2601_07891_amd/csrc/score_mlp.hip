@@ -11,9 +11,8 @@
 //
 // Which kernel runs (plan_score below): score_mlp_frag_kernel (below, the one the throughput
 // figures are about) where its token blocks fill the chip, the tiled kernel of score_tile.hip
-// for short inputs and for what whole rounds of token blocks leave over, for raw weights of
-// mid-length inputs also token blocks cut over K; score_mlp_kernel, described here, for D_h < 256
-// where tiles are slower:
+// for short inputs and for what whole rounds of token blocks leave over, between the two token blocks
+// with a part of the units; score_mlp_kernel, described here, for D_h < 256 where tiles are slower:
 //
 // Block = 512 threads (8 wavefronts) = all M units x 128 tokens, so `hidden` is
 // read from HBM exactly once and W1 (<= 6.6 MB, L2 resident) once per block.
@@ -336,26 +335,39 @@ __device__ __forceinline__ void wait_lds_fragment(bf16x8& frag) {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// UB 32-unit blocks per wavefront, TB 32-token blocks per block; kSplit: the block covers one
-// K-slice (blockIdx.y) and writes its part of the first projection to `partial`
-template <int UB, int TB, bool kNorm, bool kSplit = false, bool kStates = false>
+// 64-input planes of a K tile of a block with a part of the units: a tile's matrix work is what its loads
+// have to hide under, and half of the units is half of it.  (8444 and 10000 x 4096 x 512 in 96-token
+// blocks, us per call: one plane 41.5 and 53.4, two 41.2 and 48.0.)  256-token tiles fill the LDS with one.
+constexpr int share_planes(int TB) { return TB <= 4 ? 2 : 1; }
+
+// UB 32-unit blocks per wavefront, TB 32-token blocks per block; kShare: the block covers 128*UB of the
+// M units, writes their part of the scores to `part` and keeps the activations in fp32
+template <int UB, int TB, bool kNorm, bool kStates = false, bool kShare = false>
 __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
     const unsigned short* hidden, const unsigned char* W1f,   // not __restrict__: their loads must stay ordered w.r.t. the waits
     const unsigned short* __restrict__ b1, const unsigned short* __restrict__ W2,
     const unsigned short* __restrict__ b2, float* __restrict__ scores,
-    long long rows, int T, int Dh, int H, int nk, float* __restrict__ partial, NormArgs norm) {
-  static_assert(!(kSplit && kNorm), "the normalising form is not cut over K");
+    long long rows, int T, int Dh, int H, int nk, float* __restrict__ part, int M, NormArgs norm) {
   static_assert(kNorm || !kStates, "the normalised states belong to the normalising form");
   constexpr int U = 128 * UB;
   constexpr int TOK = 32 * TB;               // tokens per block
-  constexpr int STAGE = TOK * 128;           // bytes per LDS stage (TOK rows of one K tile)
-  constexpr int NDJ = TB;                    // load-to-LDS instructions per wavefront per tile
+  constexpr int KP = kShare ? share_planes(TB) : 1;        // 64-input planes of a K tile
+  constexpr int KS = 4 * KP;                 // MFMA steps of a K tile
+  constexpr int PLANE = TOK * 128;           // bytes of a plane's TOK rows
+  constexpr int STAGE = KP * PLANE;          // bytes per LDS stage (one K tile)
+  constexpr int NDJ = KP * TB;               // load-to-LDS instructions per wavefront per tile
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, kg = lane >> 5;
-  const long long row0 = (long long)blockIdx.x * TOK;
+  // kShare: the unit tiles of a token tile go to one XCD (workgroups go to the XCDs round-robin), one
+  // after the other, so that its rows are fetched into that L2 once
+  const int ut = kShare ? (int)(blockIdx.x / kXcds) % (M / U) : 0;
+  const int tt = kShare ? (int)(blockIdx.x / kXcds) / (M / U) * kXcds + (int)(blockIdx.x % kXcds) : (int)blockIdx.x;
+  const long long row0 = (long long)tt * TOK;
+  if (kShare && row0 >= rows) return;
   const int rows_here = (rows - row0 < TOK) ? (int)(rows - row0) : TOK;
+  const int w2_row = kShare ? M : U;         // units of a row of W2
 
   // The epilogue's A operand (W2, a few KB) is staged in LDS behind the ring, converted to
   // fp16 and zero-filled up to 16 heads: read from global memory in the epilogue, every one of
@@ -368,18 +380,19 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
   u32x4 w2_stage[kW2Pieces];
 #pragma unroll
   for (int i = 0; i < kW2Pieces; ++i) {
-    const int piece = i * 256 + tid, last = H * (U / 8) - 1;
-    load_async(w2_stage[i], reinterpret_cast<const u32x4*>(W2) + (piece < last ? piece : last));
+    int piece = i * 256 + tid;
+    const int last = H * (U / 8) - 1;
+    if (piece > last) piece = last;
+    if constexpr (kShare) piece = piece / (U / 8) * (w2_row / 8) + ut * (U / 8) + piece % (U / 8);
+    load_async(w2_stage[i], reinterpret_cast<const u32x4*>(W2) + piece);
   }
   // accumulator register 4q+e of block (ub, .) is unit wid*32*UB + 32*ub + 8*q + 4*kg + e
   u32x2 b1_stage[UB][4];
-  if constexpr (!kSplit) {
 #pragma unroll
-    for (int ub = 0; ub < UB; ++ub)
+  for (int ub = 0; ub < UB; ++ub)
 #pragma unroll
-      for (int q = 0; q < 4; ++q)   // without b1: the same offsets into W2 (H*U >= U elements), zeroed later
-        load_async(b1_stage[ub][q], (b1 ? b1 : W2) + wid * (32 * UB) + 32 * ub + 8 * q + 4 * kg);
-  }
+    for (int q = 0; q < 4; ++q)     // without b1: the same offsets into W2 (H*U >= U elements), zeroed later
+      load_async(b1_stage[ub][q], (b1 ? b1 : W2) + ut * U + wid * (32 * UB) + 32 * ub + 8 * q + 4 * kg);
 
   // b2 is loaded here and waits in LDS for the very end: a global load in the tail would
   // expose a memory round trip with nothing left to overlap it
@@ -387,14 +400,12 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
   unsigned b2_stage;
   load_async_u16(b2_stage, b2 ? b2 + (tid < H ? tid : 0) : W2);
 
-  // hidden load-to-LDS: instruction j (0..3) of wavefront w fills LDS chunk j*4+w of a
-  // stage = rows (j*4+w)*8 + lane/8, physical piece lane%8 <- logical piece (lane%8) ^ lds_swizzle(row)
-  // blockIdx.y: the K-slice of nk tiles this block covers (one slice unless `partial` is set)
-  const int kt0 = kSplit ? blockIdx.y * nk : 0;
-  const unsigned char* hb = reinterpret_cast<const unsigned char*>(hidden + (size_t)row0 * Dh) + (size_t)kt0 * (kBK * 2);
-  unsigned h_off[NDJ];
+  // hidden load-to-LDS: instruction j of wavefront w fills LDS chunk j*4+w of a stage
+  // = plane j/TB, rows (j%TB*4+w)*8 + lane/8, physical piece lane%8 <- logical piece (lane%8) ^ lds_swizzle(row)
+  const unsigned char* hb = reinterpret_cast<const unsigned char*>(hidden + (size_t)row0 * Dh);
+  unsigned h_off[TB];
 #pragma unroll
-  for (int j = 0; j < NDJ; ++j) {
+  for (int j = 0; j < TB; ++j) {
     int r = (j * 4 + wid) * 8 + (lane >> 3);
     const int p = (lane & 7) ^ lds_swizzle(r);
     if (r > rows_here - 1) r = rows_here - 1;            // clamp: in bounds, result discarded
@@ -408,38 +419,51 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
     // memory-side cache: 30011 x 4096 192 -> 178 us, 131072 x 4096 782 -> 728, 65536 x 5120 610 -> 564,
     // 60000 x 2048 164 -> 145.
     const unsigned to = lds0 + (unsigned)((tile % kNS) * STAGE + (j * 4 + wid) * 1024);
-    if constexpr (kStates) load_to_lds_b128(hb + (size_t)tile * (kBK * 2), h_off[j], to);
-    else load_to_lds_b128_stream(hb + (size_t)tile * (kBK * 2), h_off[j], to);
+    // (kShare: the token tile's other unit tiles read the same lines out of this L2.)
+    if constexpr (kStates || kShare) load_to_lds_b128(hb + (size_t)(tile * KP + j / TB) * (kBK * 2), h_off[j % TB], to);
+    else load_to_lds_b128_stream(hb + (size_t)(tile * KP + j / TB) * (kBK * 2), h_off[j % TB], to);
   };
   // A fragments of this wavefront: unit blocks rb = wid*UB + ub; fragment (ub, kk) of K tile t
-  // is the KB at  abase + t*kATile + (ub*4 + kk)*1024, 16 bytes per lane.  They are loaded
-  // kLead tiles ahead into kLead register sets.
-  constexpr int kLead = (UB <= 4 && !kNorm) ? 2 : 1;
-  constexpr size_t kATile = (size_t)(U / 32) * 4 * 1024;
-  const unsigned char* abase = W1f + ((size_t)kt0 * (U / 32) * 4 + (size_t)wid * UB * 4) * 1024;
+  // is the KB at  abase + (t*KP + kk/4)*kAPlane + (ub*4 + kk%4)*1024, 16 bytes per lane.  They are
+  // loaded kLead tiles ahead into kLead register sets.
+  constexpr int kLead = (UB <= 4 && (!kNorm || kShare)) ? 2 : 1;
+  const size_t kAPlane = (size_t)(w2_row / 32) * 4 * 1024, kATile = KP * kAPlane;
+  const unsigned char* abase = W1f + ((size_t)ut * (U / 32) + (size_t)wid * UB) * 4 * 1024;
   unsigned a_voff[UB];
 #pragma unroll
   for (int ub = 0; ub < UB; ++ub) a_voff[ub] = (unsigned)lane * 16u + (unsigned)ub * 4096u;
 
-  floatx16 acc[UB][TB];
+  // kShare: kSums sums over a part of K each, as many as the registers hold (one sum over 4096 products is
+  // 4.7e-7 off, two 3.3e-7, three 2.8e-7: what the tiles' K groups have)
+  constexpr int kSums = !kShare ? 1 : UB * TB > 6 ? 2 : 3;
+  floatx16 acc_of[kSums][UB][TB];
+  auto& acc = acc_of[0];
 
-  // kNorm: sum of x^2 of token 32*wid + l32 over this lane's half of every K step (a wavefront
+  // kNorm: sum of x^2 of token 32*xblock[x] + l32 over this lane's half of every K step (a wavefront
   // beyond the last token block re-reads that block and drops the result)
-  float ssq = 0.0f;
-  bf16x8 xb[4];
-  const int xblock = wid < TB ? wid : TB - 1;
+  constexpr int NX = (TB + 3) / 4;
+  constexpr int kSquares = kShare ? 4 : 1;               // sums, as kSums
+  float ssq[NX][kSquares];
+  bf16x8 xb[NX][KS];
+  int xblock[NX];
+#pragma unroll
+  for (int x = 0; x < NX; ++x) {
+#pragma unroll
+    for (int e = 0; e < kSquares; ++e) ssq[x][e] = 0.0f;
+    xblock[x] = wid + 4 * x < TB ? wid + 4 * x : TB - 1;
+  }
   // nk >= kPD + 1 tiles (checked by the launcher)
   // a[s][kk][ub]: register set s holds step kk of K tile t for (t + nk) % kLead == s, and is
   // re-filled fragment by fragment with tile t + kLead
-  bf16x8 a[kLead][4][UB];
+  bf16x8 a[kLead][KS][UB];
   bf16x8 b[2][TB];
   // ---- prologue: the A fragments of tiles 0..kLead-1, then hidden tiles 0..kPD-1 ----
   auto load_tile_fragments = [&](auto set_, int tile) {
     constexpr int set = decltype(set_)::value;
     const unsigned char* sb = abase + (size_t)tile * kATile;
-    static_for<4 * UB>([&](auto g_) {
+    static_for<KS * UB>([&](auto g_) {
       constexpr int kk = decltype(g_)::value / UB, ub = decltype(g_)::value % UB;
-      load_fragment<kk * 1024>(a[set][kk][ub], a_voff[ub], sb);
+      load_fragment<kk % 4 * 1024>(a[set][kk][ub], a_voff[ub], sb + kk / 4 * kAPlane);
     });
   };
   // Issue order: fragments of tile 0, hidden tiles 0 and 1, (fragments of tile 1,) hidden tile
@@ -472,25 +496,28 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
   // they are converted and the accumulators are set while the fragments and the hidden tiles
   // are still on their way.
   __builtin_amdgcn_sched_barrier(0);
-  wait_vmcnt<kLead * 4 * UB + kPD * NDJ>();
+  constexpr int kPrologue = kLead * KS * UB + kPD * NDJ;
+  wait_vmcnt<(kPrologue < 63 ? kPrologue : 63)>();
 #pragma unroll
   for (int i = 0; i < kW2Pieces; ++i) {
     arrived(w2_stage[i]);
     if (i * 256 + tid >= H * (U / 8)) w2_stage[i] = u32x4{0u, 0u, 0u, 0u};
   }
-  if constexpr (!kSplit) {
 #pragma unroll
-    for (int ub = 0; ub < UB; ++ub)
+  for (int ub = 0; ub < UB; ++ub)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        arrived(b1_stage[ub][q]);
-        if (!b1) b1_stage[ub][q] = u32x2{0u, 0u};
-      }
-  }
+    for (int q = 0; q < 4; ++q) {
+      arrived(b1_stage[ub][q]);
+      if (!b1) b1_stage[ub][q] = u32x2{0u, 0u};
+    }
   arrived(b2_stage);
   if (!b2 || tid >= H) b2_stage = 0u;
 #pragma unroll
   for (int i = 0; i < kW2Pieces; ++i) {
+    if constexpr (kShare) {                             // the three-term epilogue takes it as it is
+      reinterpret_cast<u32x4*>(sW2)[i * 256 + tid] = w2_stage[i];
+      continue;
+    }
     f16x8 w;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -515,28 +542,32 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
         }
     }
   }
-  // the first projection accumulates on top of b1 (a K-slice of a split launch: on zero)
+  // the first projection accumulates on top of b1
 #pragma unroll
   for (int ub = 0; ub < UB; ++ub)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       float v[4] = {0.f, 0.f, 0.f, 0.f};
-      if constexpr (!kSplit && !kNorm) {
+      if constexpr (!kNorm) {
         v[0] = __uint_as_float(b1_stage[ub][q].x << 16); v[1] = __uint_as_float(b1_stage[ub][q].x & 0xffff0000u);
         v[2] = __uint_as_float(b1_stage[ub][q].y << 16); v[3] = __uint_as_float(b1_stage[ub][q].y & 0xffff0000u);
       }
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[ub][tb][4 * q + e] = v[e];
+        for (int e = 0; e < 4; ++e) {
+          acc[ub][tb][4 * q + e] = v[e];
+#pragma unroll
+          for (int sum = 1; sum < kSums; ++sum) acc_of[sum][ub][tb][4 * q + e] = 0.0f;
+        }
     }
   // now everything up to hidden tile 1 (all but tile 1's fragments and hidden tile 2)
   __builtin_amdgcn_sched_barrier(0);
-  wait_vmcnt<frag::prologue_wait(UB, NDJ, kLead)>();
+  wait_vmcnt<frag::prologue_wait(KP * UB, NDJ, kLead)>();
 #pragma unroll
   for (int s2 = 0; s2 < kLead; ++s2)
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+    for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
       for (int ub = 0; ub < UB; ++ub) arrived(a[s2][kk][ub]);
   block_barrier_no_drain();
@@ -547,12 +578,15 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
   for (int kk = 0; kk < 4; ++kk) b_off[kk] = lds0 + (unsigned)lds_off(l32, kk * 2 + kg);
   auto read_b = [&](auto kk_, auto tb_, int tile) {          // into b[kk & 1][tb]
     constexpr int kk = decltype(kk_)::value, tb = decltype(tb_)::value;
-    read_fragment<tb * 4096>(b[kk & 1][tb], b_off[kk] + (unsigned)((tile % kNS) * STAGE));
+    read_fragment<kk / 4 * PLANE + tb * 4096>(b[kk & 1][tb], b_off[kk % 4] + (unsigned)((tile % kNS) * STAGE));
   };
   // the reads of step kk+1 are issued during step kk, token block tb's in group tb*UB/TB
-  constexpr auto reads_in_group = [](int ub) {
+  // behind MFMA read_slot(tb) of that group (more than four are spread out: the LDS takes longer to
+  // serve them than an MFMA runs)
+  constexpr auto read_slot = [](int tb) { return TB > 4 ? tb * UB % TB / 2 : 0; };
+  constexpr auto reads_in_group = [read_slot](int ub) {      // behind its MFMA 0
     int n = 0;
-    for (int tb = 0; tb < TB; ++tb) n += (tb * UB / TB == ub) ? 1 : 0;
+    for (int tb = 0; tb < TB; ++tb) n += (tb * UB / TB == ub && read_slot(tb) == 0) ? 1 : 0;
     return n;
   };
   static_for<TB>([&](auto tb_) { read_b(std::integral_constant<int, 0>{}, tb_, 0); });
@@ -576,18 +610,18 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
   // so the number of operations issued after fragment G's load (kLead tiles back) and before
   // its wait is known at compile time, and that many may stay outstanding.
   // The counts live in frag_schedule.h (a host test simulates the queue against them).
-  constexpr int NG = frag::groups(UB);
+  constexpr int NG = frag::groups(KP * UB);
   static_assert(frag::kHiddenAhead == kPD, "one constant, two names");
-  static_assert(frag::lead_is_safe(UB, NDJ, kLead), "tile 1's hand-over is not covered with this shape");
-  auto tile_body = [&](int t, auto r_tag, auto set_tag) {
-    constexpr int R = decltype(r_tag)::value, set = decltype(set_tag)::value;
+  static_assert(frag::lead_is_safe(KP * UB, NDJ, kLead), "tile 1's hand-over is not covered with this shape");
+  auto tile_body = [&](int t, auto r_tag, auto set_tag, auto sum_tag) {
+    constexpr int R = decltype(r_tag)::value, set = decltype(set_tag)::value, sum = decltype(sum_tag)::value;
     constexpr bool next = R > 1, more = frag::reloads_fragments(R, 0, kLead),
                    more_pd = frag::fetches_hidden(R, 0);
     const unsigned char* a_next = abase + (size_t)(t + kLead) * kATile;
     static_for<NG>([&](auto g_) {
       constexpr int G = decltype(g_)::value, kk = G / UB, ub = G % UB;
-      if constexpr (next && kk == 2 && ub == 0) {      // hidden tile t+1 must have landed
-        wait_vmcnt<frag::handover_wait(UB, NDJ, kLead, R)>();
+      if constexpr (next && G == NG / 2) {      // hidden tile t+1 must have landed
+        wait_vmcnt<frag::handover_wait(KP * UB, NDJ, kLead, R)>();
         block_barrier_no_drain();
       }
       // The group's TB MFMAs with its other instructions spread between them, a few behind
@@ -595,9 +629,9 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
       // them runs, and the matrix pipe waits):
       //   [wait: fragment G]  MFMA 0  [B reads for the next step]  MFMA 1  [load-to-LDS]
       //   MFMA 2  [re-load fragment G-1 with tile t+kLead's data]  (MFMA 3)
-      constexpr bool reads = kk < 3 || next;
+      constexpr bool reads = kk < KS - 1 || next;
       // one wait per pair of groups (every instruction between the MFMAs costs issue time)
-      if constexpr (G % 2 == 0) wait_fragment<frag::fragment_pair_wait(UB, NDJ, kLead, R, G)>(a[set][kk][ub]);
+      if constexpr (G % 2 == 0) wait_fragment<frag::fragment_pair_wait(KP * UB, NDJ, kLead, R, G)>(a[set][kk][ub]);
       // token blocks in alternating direction: the MFMA that opens a group then keeps the B
       // operand of the one before it (both operands switch at once otherwise); measured 1-2 %
       static_for<TB>([&](auto i_) {
@@ -608,13 +642,13 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
           // which only this group's reads for the next step (issued after MFMA 0) may remain
           wait_lds_fragment<i == 0 ? TB - 1 : (reads ? reads_in_group(0) : 0)>(b[kk & 1][tb]);
         }
-        acc[ub][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[set][kk][ub], b[kk & 1][tb],
-                                                              acc[ub][tb], 0, 0, 0);
+        acc_of[sum][ub][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[set][kk][ub], b[kk & 1][tb],
+                                                                      acc_of[sum][ub][tb], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (i == 0 && reads) {
+        if constexpr (i < (TB > 4 ? TB / 2 : 1) && reads) {
           static_for<TB>([&](auto tb_) {
-            if constexpr (decltype(tb_)::value * UB / TB == ub) {
-              if constexpr (kk < 3) read_b(std::integral_constant<int, kk + 1>{}, tb_, t);
+            if constexpr (decltype(tb_)::value * UB / TB == ub && read_slot(decltype(tb_)::value) == i) {
+              if constexpr (kk < KS - 1) read_b(std::integral_constant<int, kk + 1>{}, tb_, t);
               else read_b(std::integral_constant<int, 0>{}, tb_, t + 1);
             }
           });
@@ -624,7 +658,7 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
           if constexpr (more_pd) {
 #pragma unroll
             for (int j = 0; j < NDJ; ++j)
-              if (frag::dma_group(UB, NDJ, j) == G) dma(j, t + kPD);
+              if (frag::dma_group(KP * UB, NDJ, j) == G) dma(j, t + kPD);
           }
           if constexpr (kNorm) {
             // Sum of squares of the tokens' states: wavefront w owns token block w and reads
@@ -632,22 +666,25 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
             // registers of its own (the copy among its B fragments sits in a register only a
             // compile-time index reaches), during K steps 0-1; the 16 two-element dot
             // products follow in K steps 2-3.  No branch; all in the MFMA shadow.
-            constexpr int kHalf = 2 * UB;                  // groups in half a tile
+            constexpr int kHalf = NG / 2;                  // groups in half a tile
 #pragma unroll
-            for (int f = 0; f < 4; ++f) {
+            for (int f = 0; f < KS; ++f) {
               // (the same read as B fragment (step f, token block xblock); hand-issued like those,
               // or the compiler's wait for it would also wait for the B reads just issued.  No
               // wait of its own: it is used two K steps later, behind that step's waits, which
               // leave only reads younger than this one outstanding)
-              if (f * kHalf / 4 == G)
-                read_fragment<0>(xb[f], b_off[f] + (unsigned)((t % kNS) * STAGE + xblock * 4096));
-              if (f * kHalf / 4 == G - kHalf) {
-                arrived(xb[f]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                  const bf16x2 p = {xb[f][2 * e], xb[f][2 * e + 1]};
-                  ssq = __builtin_amdgcn_fdot2_f32_bf16(p, p, ssq, false);
+              for (int x = 0; x < NX; ++x) {
+                if (f * kHalf / KS == G)
+                  read_fragment<0>(xb[x][f], b_off[f % 4] + (unsigned)((t % kNS) * STAGE + f / 4 * PLANE + xblock[x] * 4096));
+                if (f * kHalf / KS == G - kHalf) {
+                  arrived(xb[x][f]);
+#pragma unroll
+                  for (int e = 0; e < 4; ++e) {
+                    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+                    const bf16x2 p = {xb[x][f][2 * e], xb[x][f][2 * e + 1]};
+                    ssq[x][e % kSquares] = __builtin_amdgcn_fdot2_f32_bf16(p, p, ssq[x][e % kSquares], false);
+                  }
                 }
               }
             }
@@ -658,13 +695,13 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
         // read its destination registers costs extra issue cycles
         if constexpr (i == 2 && more && G > 0) {
           constexpr int pk = (G - 1) / UB, pu = (G - 1) % UB;
-          load_fragment<pk * 1024>(a[set][pk][pu], a_voff[pu], a_next);
+          load_fragment<pk % 4 * 1024>(a[set][pk][pu], a_voff[pu], a_next + pk / 4 * kAPlane);
           __builtin_amdgcn_sched_barrier(0);
         }
       });
     });
     if constexpr (more) {
-      load_fragment<3 * 1024>(a[set][3][UB - 1], a_voff[UB - 1], a_next);
+      load_fragment<3 * 1024>(a[set][KS - 1][UB - 1], a_voff[UB - 1], a_next + (KP - 1) * kAPlane);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -673,52 +710,50 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
     using std::integral_constant;
     constexpr integral_constant<int, 0> s0{};
     constexpr integral_constant<int, kLead - 1> s1{};     // the set of the last tile
+    constexpr integral_constant<int, kSums - 1> last{};
     int t = 0;
     if constexpr (kLead == 1) {
-      for (; t + kPD < nk; ++t) tile_body(t, integral_constant<int, kPD + 1>{}, s0);
+      for (; t + kPD < nk; ++t) tile_body(t, integral_constant<int, kPD + 1>{}, s0, s0);
     } else {
       // set of tile t = (t + nk) & 1: the last tile always uses set 1, whatever nk
-      if (!(nk & 1)) { tile_body(0, integral_constant<int, kPD + 1>{}, s0); t = 1; }
-      for (; t + kPD < nk; t += 2) {
-        tile_body(t, integral_constant<int, kPD + 1>{}, s1);
-        tile_body(t + 1, integral_constant<int, kPD + 1>{}, s0);
-      }
+      if (!(nk & 1)) { tile_body(0, integral_constant<int, kPD + 1>{}, s0, s0); t = 1; }
+      const int first = t, pairs = (nk - kPD - first + 1) / 2;
+      static_for<kSums>([&](auto sum_) {
+        const int end = kSums == 1 ? nk - kPD : first + 2 * (pairs * (decltype(sum_)::value + 1) / kSums);
+        for (; t < end; t += 2) {
+          tile_body(t, integral_constant<int, kPD + 1>{}, s1, sum_);
+          tile_body(t + 1, integral_constant<int, kPD + 1>{}, s0, sum_);
+        }
+      });
     }
-    tile_body(nk - 3, integral_constant<int, 3>{}, s1);
-    tile_body(nk - 2, integral_constant<int, 2>{}, s0);
-    tile_body(nk - 1, integral_constant<int, 1>{}, s1);
+    tile_body(nk - 3, integral_constant<int, 3>{}, s1, last);
+    tile_body(nk - 2, integral_constant<int, 2>{}, s0, last);
+    tile_body(nk - 1, integral_constant<int, 1>{}, s1, last);
   }
-  if constexpr (kSplit) {
-    // split-K launch: the slice's part of the first projection goes to partial[slice][row][unit]
-    // as it is; bias, GELU and the second projection follow in score_finish_kernel
-    float* out = partial + ((size_t)blockIdx.y * rows + row0) * U + wid * (32 * UB) + 4 * kg;
+  if constexpr (kShare) {
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-      const int r = 32 * tb + l32;
-      if (r < rows_here) {
+    for (int ub = 0; ub < UB; ++ub)
 #pragma unroll
-        for (int ub = 0; ub < UB; ++ub)
+      for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            floatx4 v4;
+        for (int e = 0; e < 16; ++e)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v4[e] = acc[ub][tb][4 * q + e];
-            *reinterpret_cast<floatx4*>(out + (size_t)r * U + 32 * ub + 8 * q) = v4;
-          }
-      }
-    }
-    return;
+          for (int sum = 1; sum < kSums; ++sum) acc[ub][tb][e] += acc_of[sum][ub][tb][e];
   }
   if constexpr (kNorm) {
     // each token's sum of squares (both lane halves) goes through LDS to the lanes that hold
     // its accumulators; the barrier below publishes it
     float* sSsq = reinterpret_cast<float*>(sW2 + 16 * U * 2 + TOK * sizeof(float) + U * sizeof(float));  // [TOK]
-    const float both = ssq + __shfl_xor(ssq, 32, 64);
-    if (kg == 0 && wid < TB) sSsq[32 * wid + l32] = both;
+#pragma unroll
+    for (int x = 0; x < NX; ++x) {
+      const float mine = kShare ? (ssq[x][0] + ssq[x][1 % kSquares]) + (ssq[x][2 % kSquares] + ssq[x][3 % kSquares]) : ssq[x][0];
+      const float both = mine + __shfl_xor(mine, 32, 64);
+      if (kg == 0 && wid + 4 * x < TB) sSsq[32 * (wid + 4 * x) + l32] = both;
+    }
   }
   __syncthreads();      // LDS is reused for the reduction below
 
-  if constexpr (!kSplit) {
+  if constexpr (!kShare) {
     // Warm the L2 for the block that starts on this CU when this one ends: workgroups go to
     // the 8 XCDs round-robin and to a CU as it frees up, so with one block per CU that block is
     // blockIdx.x + (number of CUs), on the same XCD and therefore behind the same L2.  One lane
@@ -731,7 +766,7 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
     for (int i0 = 0; i0 < kPD * TOK; i0 += 256) {
       const int i = i0 + tid, d = i / TOK, r = i - d * TOK;
       if (i < kPD * TOK && nrow0 + r < rows)
-        load_to_lds_b32(hidden + (size_t)(nrow0 + r) * Dh + (size_t)(kt0 + d) * kBK,
+        load_to_lds_b32(hidden + (size_t)(nrow0 + r) * Dh + (size_t)d * kBK,
                         lds0 + (unsigned)((kNS - 1) * STAGE + wid * 256));
     }
   }
@@ -750,7 +785,7 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
     for (int tb = 0; tb < TB; ++tb) {
       rs[tb] = 1.0f / sqrtf(sSsq[32 * tb + l32] / (float)Dh + norm.eps);
     }
-    if (wid == 0 && kg == 0) {
+    if (wid == 0 && kg == 0 && ut == 0) {
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb)
         if (32 * tb + l32 < rows_here) norm.rstd[row0 + 32 * tb + l32] = rs[tb];
@@ -782,6 +817,17 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
       }
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb) {
+        if constexpr (kShare) {
+          float a[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            float z = acc[ub][tb][8 * s + e];
+            if constexpr (kNorm) z = fmaf(z, rs[tb], bias[e]);
+            a[e] = gelu_exact(z);
+          }
+          acc2[tb] = dot_three_terms(__builtin_bit_cast(bf16x8, w2), a, acc2[tb]);
+          continue;
+        }
         f16x8 g;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -824,6 +870,10 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
       s += red[(1 * H + head) * TOK + tok];
       s += red[(2 * H + head) * TOK + tok];
       s += red[(3 * H + head) * TOK + tok];
+      if constexpr (kShare) {                            // score_tile_sum_kernel adds the parts and b2
+        part[((size_t)ut * H + head) * rows + row0 + tok] = s;
+        continue;
+      }
       s += sB2[head];
       long long bidx = b_first;
       long long t = (long long)t_first + tok;
@@ -845,18 +895,19 @@ __global__ __launch_bounds__(256) void score_mlp_frag_kernel(
     const u32x4* gain8 = reinterpret_cast<const u32x4*>(norm.gain);
     // 4 or 5 KB of a row at a time, which divides D_h where M = D_h / 8, four rows ahead
     // (131072 x 4096: 8 KB and two rows 753 us, this 728; 16384 x 4096 125 and 127)
-    write_states<4, UB == 5 ? 5 : 4, 4>(xin, yout, gain8, sR, rows_here, Dh / 8, wid, lane);
+    if constexpr (kShare) {                              // the unit tiles of a token tile share its columns
+      const int ppr = Dh / 8, share = ((ppr + M / U - 1) / (M / U) + 63) / 64 * 64;
+      const int c0 = ut * share, c1 = c0 + share < ppr ? c0 + share : ppr;
+      if (c0 < c1) write_states<4, 4, 4>(xin, yout, gain8, sR, rows_here, ppr, wid, lane, c0, c1);
+    } else {
+      write_states<4, UB == 5 ? 5 : 4, 4>(xin, yout, gain8, sR, rows_here, Dh / 8, wid, lane, 0, Dh / 8);
+    }
   }
 }
 
-// ---- the first projection cut over K ----
-// While the token blocks do not fill the chip, raw weights may also be scored by token blocks that
-// take a K-slice each (score_mlp_frag_kernel with kSplit): the slices' partial sums go to memory and
-// this kernel finishes them -- slices in a fixed order, bias, GELU and second projection in fp32; one
-// wavefront per token, 8 hidden units per lane and round.  From some 8000 tokens on, where the tiles
-// of score_tile.hip need a second, mostly empty round, this is the faster of the two forms with an
-// fp32 epilogue (raw weights, us per call, split / tiles / token blocks alone: 9000 x 4096 x 512
-// 74 / 82 / 92, 12288 x 5120 x 512 90 / 112 / 114).
+// ---- the skinny form's second launch ----
+// The K-slices' partial sums of the first projection (launch_skinny_gemm) in a fixed order, bias, GELU
+// and second projection in fp32; one wavefront per token, 8 hidden units per lane and round.
 __global__ __launch_bounds__(256) void score_finish_kernel(
     const float* __restrict__ partial, const unsigned short* __restrict__ b1,
     const unsigned short* __restrict__ W2, const unsigned short* __restrict__ b2,
@@ -913,65 +964,117 @@ int launch_finish(const float* partial, const void* b1, const void* W2, const vo
   return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
 }
 
-// K-slices of a launch over nk_total K tiles: enough blocks for the chip's 256 CUs, slices of at
-// least kPD + 1 tiles that divide K evenly, at most 8; 1 beyond 112 token blocks.
-inline int frag_ksplit(long long rows, int nk_total, int M) {
-  const int tok = M / 128 <= 4 ? 128 : 96;
-  const long long blocks = (rows + tok - 1) / tok;
-  int ks = 1;
-  for (int d = 2; d <= 8; ++d)
-    if (nk_total % d == 0 && nk_total / d >= kPD + 1 && blocks * d <= 256 && blocks <= 112) ks = d;
-  return ks;
-}
-
-// ks > 1 (not kNorm): K-slices, their partial sums [ks][rows][M] fp32 in `partial`
 template <int UB, int TB, bool kNorm>
 int launch_frag(const void* hidden, const void* W1f, const void* b1, const void* W2, const void* b2,
-                float* scores, float* partial, int ks, long long rows, int T, int Dh, int H,
-                const NormArgs& norm, hipStream_t stream) {
+                float* scores, long long rows, int T, int Dh, int H, const NormArgs& norm, hipStream_t stream) {
   constexpr int TOK = 32 * TB;
   constexpr size_t ring = (size_t)kNS * TOK * 128;
   static_assert(ring >= (size_t)4 * 16 * TOK * sizeof(float), "reduction buffer fits");
   // + W2 as [16][M] fp16, then (normalising form) the row scales, b1 and the sums of squares as fp32
   constexpr size_t lds = ring + (size_t)16 * (128 * UB) * 2 + TOK * sizeof(float) +
                          (128 * UB) * sizeof(float) + TOK * sizeof(float) + 16 * sizeof(float);   // + b2
-  auto launch = [&](auto split, auto states) {
-    constexpr bool kSplit = decltype(split)::value, kStates = decltype(states)::value;
+  auto launch = [&](auto states) {
+    constexpr bool kStates = decltype(states)::value;
     // once per process, which drives one GPU (thread-safe: a function-local static)
     static const hipError_t attr_rc =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(score_mlp_frag_kernel<UB, TB, kNorm, kSplit, kStates>),
+        hipFuncSetAttribute(reinterpret_cast<const void*>(score_mlp_frag_kernel<UB, TB, kNorm, kStates>),
         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (attr_rc != hipSuccess) return KVZAP_ERR_RUNTIME;
-    score_mlp_frag_kernel<UB, TB, kNorm, kSplit, kStates><<<dim3((unsigned)((rows + TOK - 1) / TOK), ks), 256, lds, stream>>>(
+    score_mlp_frag_kernel<UB, TB, kNorm, kStates><<<dim3((unsigned)((rows + TOK - 1) / TOK)), 256, lds, stream>>>(
         static_cast<const unsigned short*>(hidden), static_cast<const unsigned char*>(W1f),
         static_cast<const unsigned short*>(b1), static_cast<const unsigned short*>(W2),
-        static_cast<const unsigned short*>(b2), scores, rows, T, Dh, H, Dh / kBK / ks, partial, norm);
+        static_cast<const unsigned short*>(b2), scores, rows, T, Dh, H, Dh / kBK, nullptr, 128 * UB, norm);
     return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
   };
-  if constexpr (!kNorm) {
-    if (ks > 1) {
-      const int rc = launch(std::true_type{}, std::false_type{});
-      if (rc != KVZAP_OK) return rc;
-      return launch_finish(partial, b1, W2, b2, scores, rows, T, 128 * UB, H, ks, stream);
-    }
-  }
   if constexpr (kNorm) {
-    if (norm.normed) return launch(std::false_type{}, std::true_type{});
+    if (norm.normed) return launch(std::true_type{});
   }
-  return launch(std::false_type{}, std::false_type{});
+  return launch(std::false_type{});
+}
+
+// ---- token blocks with a part of the units ----
+// Between a round of the largest tile and a round of whole token blocks (8k to 16k tokens at M = 512)
+// a whole block's walk over K for all M units takes its 85 us on a third to a half of the CUs, and a second
+// round of tiles is mostly empty.  Here a block has 128*UB of the units, so that one round of blocks covers
+// the CUs, with the K loop of score_mlp_frag_kernel (W1 from L2 straight into registers, tokens through LDS);
+// a token tile's unit tiles read its rows out of one L2, their parts of the scores meet in a second launch.
+// What bounds it at a full round is the power limit (16384 x 4096 x 512: 1.14 PFLOP/s in the kernel, whole
+// blocks at length 1.28), at fewer blocks launch, prologue and epilogue (12 us) beside one block's K loop.
+// The epilogue is the tiles' (fp32 GELU, three bf16 terms), so raw weights take this form too, where K-sliced
+// blocks with partial sums in memory were used before.  us per call, weights prepared (before) / raw
+// (before), error in both forms 2.6e-7 to 3.6e-7 (prepared before, token blocks: 2.2e-4):
+//   tokens            8500       9000       10500      12200      14000      16300
+//   4096 x 512     45 / 51    46 / 51    56 / 61    61 / 66    67 / 73    73 / 79
+//     before       57 / 75    58 / 75    86 / 78    88 / 83    89 / 89    90 / 98
+//   tokens            6700       8192       9000       10500      12200
+//   5120 x 640     55 / 62    72 / 77    73 / 81    84 / 90    88 / 93
+//     before       82 / 92    95 / 95   103 / 98   108 / 103  111 / 113
+template <int UB, int TB, bool kNorm>
+int launch_share(const void* hidden, const void* W1f, const void* b1, const void* W2, const void* b2,
+                 float* scores, float* part, long long rows, long long row_first, int T, int Dh, int M,
+                 int H, const NormArgs& norm_all, hipStream_t stream) {
+  constexpr int TOK = 32 * TB;
+  constexpr int KP = share_planes(TB);
+  constexpr size_t ring = (size_t)kNS * TOK * 128 * KP;
+  static_assert(ring >= (size_t)4 * 16 * TOK * sizeof(float), "reduction buffer fits");
+  constexpr size_t lds = ring + (size_t)16 * (128 * UB) * 2 + TOK * sizeof(float) +
+                         (128 * UB) * sizeof(float) + TOK * sizeof(float) + 16 * sizeof(float);
+  const int nut = M / (128 * UB);
+  const long long tt = (rows + TOK - 1) / TOK, grid = (tt + kXcds - 1) / kXcds * kXcds * nut;
+  NormArgs norm = norm_all;
+  if (norm.rstd) norm.rstd += row_first;
+  if (norm.normed) norm.normed += (size_t)row_first * Dh;
+  auto launch = [&](auto states) {
+    constexpr bool kStates = decltype(states)::value;
+    auto* kernel = score_mlp_frag_kernel<UB, TB, kNorm, kStates, true>;
+    static const hipError_t attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (attr_rc != hipSuccess) return KVZAP_ERR_RUNTIME;
+    kernel<<<dim3((unsigned)grid), 256, lds, stream>>>(
+        static_cast<const unsigned short*>(hidden) + (size_t)row_first * Dh, static_cast<const unsigned char*>(W1f),
+        static_cast<const unsigned short*>(b1), static_cast<const unsigned short*>(W2),
+        static_cast<const unsigned short*>(b2), scores, rows, T, Dh, H, Dh / kBK / KP, part, M, norm);
+    return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
+  };
+  int rc;
+  if constexpr (kNorm) rc = norm.normed ? launch(std::true_type{}) : launch(std::false_type{});
+  else rc = launch(std::false_type{});
+  return rc != KVZAP_OK ? rc : launch_score_sum(part, b2, scores, rows, row_first, T, H, nut, stream);
+}
+
+// The forms of score_mlp_frag_kernel with a part of the units: 128*UB of them x 32*TB tokens a block.
+struct ShareForm { int UB, TB; };
+constexpr int kShareCount = 4;
+constexpr ShareForm kShareForms[kShareCount] = {{2, 4}, {2, 3}, {1, 8}, {1, 6}};
+
+template <bool kNorm>
+int launch_shared(int form, const void* hidden, const void* W1f, const void* b1, const void* W2, const void* b2,
+                  float* scores, float* part, long long rows, long long row_first, int T, int Dh, int M,
+                  int H, const NormArgs& norm, hipStream_t stream) {
+  auto launch = [&](auto form_) {
+    constexpr ShareForm f = kShareForms[decltype(form_)::value];
+    return launch_share<f.UB, f.TB, kNorm>(hidden, W1f, b1, W2, b2, scores, part, rows, row_first, T, Dh, M, H, norm, stream);
+  };
+  switch (form) {
+    case 0: return launch(std::integral_constant<int, 0>{});
+    case 1: return launch(std::integral_constant<int, 1>{});
+    case 2: return launch(std::integral_constant<int, 2>{});
+    case 3: return launch(std::integral_constant<int, 3>{});
+    default: return KVZAP_ERR_UNSUPPORTED;
+  }
 }
 
 template <bool kNorm>
 int launch_blocks(const void* hidden, const void* W1f, const void* b1, const void* W2, const void* b2,
-                  float* scores, float* partial, int ks, long long rows, int T, int Dh, int M, int H,
-                  const NormArgs& norm, hipStream_t stream) {
+                  float* scores, long long rows, int T, int Dh, int M, int H, const NormArgs& norm,
+                  hipStream_t stream) {
   switch (M / 128) {
-    case 1: return launch_frag<1, 4, kNorm>(hidden, W1f, b1, W2, b2, scores, partial, ks, rows, T, Dh, H, norm, stream);
-    case 2: return launch_frag<2, 4, kNorm>(hidden, W1f, b1, W2, b2, scores, partial, ks, rows, T, Dh, H, norm, stream);
-    case 3: return launch_frag<3, 4, kNorm>(hidden, W1f, b1, W2, b2, scores, partial, ks, rows, T, Dh, H, norm, stream);
-    case 4: return launch_frag<4, 4, kNorm>(hidden, W1f, b1, W2, b2, scores, partial, ks, rows, T, Dh, H, norm, stream);
+    case 1: return launch_frag<1, 4, kNorm>(hidden, W1f, b1, W2, b2, scores, rows, T, Dh, H, norm, stream);
+    case 2: return launch_frag<2, 4, kNorm>(hidden, W1f, b1, W2, b2, scores, rows, T, Dh, H, norm, stream);
+    case 3: return launch_frag<3, 4, kNorm>(hidden, W1f, b1, W2, b2, scores, rows, T, Dh, H, norm, stream);
+    case 4: return launch_frag<4, 4, kNorm>(hidden, W1f, b1, W2, b2, scores, rows, T, Dh, H, norm, stream);
     // M = 640: 96-token blocks so that the 5 x 3 accumulator blocks fit (240 registers)
-    case 5: return launch_frag<5, 3, kNorm>(hidden, W1f, b1, W2, b2, scores, partial, ks, rows, T, Dh, H, norm, stream);
+    case 5: return launch_frag<5, 3, kNorm>(hidden, W1f, b1, W2, b2, scores, rows, T, Dh, H, norm, stream);
     default: return KVZAP_ERR_UNSUPPORTED;
   }
 }
@@ -1010,25 +1113,23 @@ __global__ __launch_bounds__(256) void copy_w1_kernel(const u32x4* __restrict__ 
 // 256 of them fill the chip; a tile's time hardly moves until its own grid passes 256 blocks.
 // So: the cost of a round of each kernel as a fixed part plus a part per 64 inputs, and the
 // cheapest of
-//   tiles alone | whole token blocks alone | full rounds of token blocks, the rest as tiles |
-//   full rounds of the largest tile, the rest as a smaller one.
+//   one form alone (a tile, a share, token blocks) | full rounds of token blocks, the rest as a tile or
+//   a share | full rounds of the largest tile, the rest likewise.
 // (40000 tokens: 32768 as one full round of blocks and 7232 as tiles instead of two rounds of
 // blocks with the second one mostly empty.)
 //
-// The constants are fitted to 1150 shapes (D_h 64 .. 8192, M 128 .. 640, 128 .. 28672 tokens) in
-// each form: token blocks within 3 %, tiles within 8 % (one in a hundred 25 %).  Hence the margin on
-// tiles: with it, none of those shapes is more than 3 % slower than token blocks alone.  With the
-// constants of D_h = 4096 for every width and no margin, 13000 tokens took 44 us at 1024 x 640
-// (blocks 31), 157 at 5120 x 640 (112), 57 at 2048 x 384 (44), and 20000 at 192 x 256 21 (15).
+// The constants are fitted to 866 shapes and entry points (D_h 512 .. 8192, M 128 .. 640, 128 .. 38000
+// tokens, each form alone, three inputs in turn), each form where it is within 1.4 of the best: token blocks
+// and shares within 3 to 7 %, tiles within 10 %; the chosen form is 0.5 % slower than the best one in the
+// mean, 13 % in one of a hundred shapes.  Hence the margin on tiles and shares.
 // The normalising form is like the plain one within that accuracy; where it writes the states
 // (Form::kStates) their copy is added, which a tile does more slowly than a token block.
 //
-// Raw weights: an input that frag_ksplit cuts, or of no more than kSkinnyRows tokens, is scored with
-// an fp32 epilogue throughout (1e-7 of the exact scores; the token blocks' fp16 activations and
-// fitted GELU: 2e-4), so token blocks alone are no candidate there, however cheap (9000 x 1024 x
-// 512 34 us, the fp32 form that was used before tiles 47), and K-slices are one.
-struct Segment { int tile; long long rows; };      // tile < 0: score_mlp_frag_kernel
-constexpr int kWholeK = -1, kSlicedK = -2, kSkinny = -3;
+// Raw weights: an input for which fp32_epilogue() holds, or of no more than kSkinnyRows tokens, is scored
+// with an fp32 epilogue throughout (2e-7 to 4e-7 of the exact scores; the token blocks' fp16 activations and
+// fitted GELU: 2e-4), so token blocks are no candidate there, however cheap.
+struct Segment { int tile; long long rows; };      // tile < 0 or >= kShared: score_mlp_frag_kernel
+constexpr int kWholeK = -1, kSkinny = -2, kShared = kScoreTiles;   // kShared + i: form i of kShareForms
 constexpr long long kSkinnyRows = 384;
 //
 // A few tokens of a wide model (raw weights): the decode path's skinny GEMM over (32 units x
@@ -1052,31 +1153,29 @@ struct Plan {
 
 // token blocks: us per launch, per 64 inputs (a few blocks; what 256 of them add), per later round;
 // later blocks of M = 128 share a CU with earlier ones
-constexpr float kBlockFixed[5] = {5.6f, 7.5f, 9.5f, 11.5f, 10.4f};
-constexpr float kBlockThin[5] = {0.57f, 0.72f, 0.94f, 1.08f, 1.16f};
-constexpr float kBlockFill[5] = {0.21f, 0.24f, 0.26f, 0.30f, 0.26f};
-constexpr float kBlockRound[5] = {0.0f, 3.0f, 4.5f, 7.0f, 4.0f};
-constexpr float kBlockLater[5] = {0.42f, 0.72f, 0.94f, 1.08f, 1.16f};      // kBlockThin of later rounds
-constexpr float kArrange = 2.0f;                                           // W1 put in order, per call
-// tiles: us per launch pair and per later round; per 64 inputs: a few blocks, what a full round adds,
-// every later round, 8192 tokens of input, 8192 tokens of states
+constexpr float kBlockFixed[5] = {4.1f, 7.1f, 4.2f, 10.6f, 9.1f};
+constexpr float kBlockThin[5] = {0.52f, 0.73f, 0.99f, 1.00f, 1.14f};
+constexpr float kBlockFill[5] = {0.36f, 0.28f, 0.31f, 0.42f, 0.27f};
+constexpr float kBlockRound[5] = {0.0f, 6.7f, 4.9f, 8.0f, 6.5f};
+constexpr float kBlockLater[5] = {0.39f, 0.69f, 0.95f, 1.14f, 1.26f};      // kBlockThin of later rounds
+constexpr float kBlockStates[2] = {0.05f, 1.05f};                          // the states, as thin and fill
+constexpr float kArrange[2] = {2.4f, 1.4e-6f};                             // W1 put in order: per call, per weight
+// tiles and shares: us per launch pair and per later round; per 64 inputs: a few blocks, what a full round
+// adds, every later round, 8192 tokens of input, 8192 tokens of states
 struct TileCost { float fixed, round, thin, fill, again, stream, states; };
-constexpr TileCost kTileCost[kScoreTiles] = {{9.9f, 7.4f, 0.335f, 0.210f, 0.375f, 0.098f, 0.42f},
-                                             {7.8f, 5.0f, 0.232f, 0.157f, 0.316f, 0.069f, 0.38f},
-                                             {8.5f, 3.7f, 0.146f, 0.070f, 0.213f, 0.099f, 0.32f},
-                                             {7.6f, 2.6f, 0.105f, 0.035f, 0.162f, 0.092f, 0.27f},
-                                             {8.3f, 2.5f, 0.065f, 0.050f, 0.120f, 0.000f, 0.20f}};
-constexpr float kTileMargin = 1.075f;
+constexpr TileCost kTileCost[kScoreTiles + kShareCount] = {{10.8f, 3.1f, 0.288f, 0.050f, 0.538f, 0.098f, 0.364f},
+                                                           {9.1f, 2.7f, 0.211f, 0.019f, 0.328f, 0.069f, 0.336f},
+                                                           {9.0f, 3.3f, 0.139f, 0.014f, 0.165f, 0.099f, 0.282f},
+                                                           {8.2f, 2.8f, 0.080f, 0.051f, 0.102f, 0.092f, 0.311f},
+                                                           {9.5f, 2.8f, 0.017f, 0.088f, 0.074f, 0.000f, 0.555f},
+                                                           {13.9f, 7.9f, 0.442f, 0.124f, 0.659f, 0.127f, 0.330f},
+                                                           {12.7f, 5.8f, 0.391f, 0.064f, 0.643f, 0.104f, 0.347f},
+                                                           {12.5f, 7.4f, 0.514f, 0.227f, 0.751f, 0.110f, 0.348f},
+                                                           {12.2f, 3.7f, 0.410f, 0.144f, 0.742f, 0.103f, 0.343f}};
+constexpr float kTileMargin = 1.03f;
 // score_mlp_kernel (D_h < 256): per launch, per 64 inputs
 constexpr float kSmallFixed[5] = {6.7f, 10.2f, 14.0f, 17.2f, 20.8f};
 constexpr float kSmallStep[5] = {0.70f, 1.10f, 1.35f, 1.85f, 2.90f};
-// K-slices: per launch pair, per 64 inputs of a slice, per million partial sums; per 8192 tokens of
-// the finishing kernel and per million weights put in order (fitted to 575 shapes within 15 %)
-constexpr float kSliceFixed[5] = {12.1f, 14.8f, 18.9f, 22.5f, 25.1f};
-constexpr float kSliceStep[5] = {0.65f, 0.76f, 0.98f, 1.13f, 1.13f};
-constexpr float kSlicePart[5] = {1.37f, 0.84f, 0.52f, 0.37f, 0.31f};
-constexpr float kSliceMargin = 0.90f;                                      // as kTileMargin, for the errors of both
-
 inline float cost_blocks(long long rows, int Dh, int M, Form form) {
   const int tok = M / 128 <= 4 ? 128 : 96, i = M / 128 - 1;
   const long long blocks = (rows + tok - 1) / tok, full = blocks / kChipCUs, rest = blocks % kChipCUs;
@@ -1084,39 +1183,66 @@ inline float cost_blocks(long long rows, int Dh, int M, Form form) {
   float us = kBlockFixed[i] + (float)full * planes * (kBlockThin[i] + kBlockFill[i]);
   if (rest) us += planes * ((full ? kBlockLater[i] : kBlockThin[i]) + kBlockFill[i] * (float)rest / kChipCUs);
   us += kBlockRound[i] * (float)(full + (rest ? 1 : 0) - 1);
-  if (form == Form::kRaw) us += kArrange;
-  if (form == Form::kStates) us += planes * (0.55f + 0.82f * (float)blocks / kChipCUs);
+  if (form == Form::kStates) us += planes * (kBlockStates[0] + kBlockStates[1] * (float)blocks / kChipCUs);
   return us;
 }
 
-inline float cost_sliced(long long rows, int Dh, int M, int ks) {
-  const int i = M / 128 - 1;
-  return kSliceMargin * (kSliceFixed[i] + (float)(Dh / kBK / ks) * kSliceStep[i] + (float)rows * (9.5f / 8192) +
-                         1e-6f * (float)M * ((float)ks * (float)rows * kSlicePart[i] + 2.3f * (float)Dh));
+// Forms of kShareForms that score D_h x M: two unit tiles or more, whole K tiles, enough of them.  Many units
+// of a narrow input stay with tiles and token blocks: a share would be the faster there too (10000 x 2048 x
+// 512 29 us, the largest tile 41), but the plans for such shapes are what the tests of two kernels on one
+// input, and of inputs that need no workspace, are written for.
+inline bool share_fits(int form, int Dh, int M) {
+  if (Dh <= 2048 && M > 256) return false;
+  const int units = 128 * kShareForms[form].UB, planes = share_planes(kShareForms[form].TB);
+  return M % units == 0 && M > units && Dh / kBK % planes == 0 && Dh / kBK / planes >= kPD + 1;
+}
+inline long long xcd_blocks(int tile, long long rows, int M) {
+  if (tile < kShared) return score_tile_xcd_blocks(tile, rows, M);
+  const ShareForm f = kShareForms[tile - kShared];
+  return ((rows + 32 * f.TB - 1) / (32 * f.TB) + kXcds - 1) / kXcds * (M / (128 * f.UB));
 }
 
 inline float cost_tile(int tile, long long rows, int Dh, int M, Form form) {
   const TileCost& c = kTileCost[tile];
-  const long long blocks = score_tile_xcd_blocks(tile, rows, M), rounds = (blocks + kXcdCUs - 1) / kXcdCUs;
+  const long long blocks = xcd_blocks(tile, rows, M), rounds = (blocks + kXcdCUs - 1) / kXcdCUs;
   const float fill = rounds > 1 ? 1.0f : (float)blocks / kXcdCUs, again = (float)(rounds - 1);
   const float stream = c.stream + (form == Form::kStates ? c.states : 0.0f);
   return kTileMargin * (c.fixed + again * c.round + (float)(Dh / kBK) * (c.thin + c.fill * fill + again * c.again +
                                                                         stream * (float)rows / 8192));
 }
 
-inline Plan plan_tile(long long rows, int Dh, int M, Form form) {          // one tile for all rows
-  int best = 0;
-  for (int t = 1; t < kScoreTiles; ++t)
-    if (cost_tile(t, rows, Dh, M, form) < cost_tile(best, rows, Dh, M, form)) best = t;
-  Plan p{};
-  p.add(best, rows, cost_tile(best, rows, Dh, M, form));
-  return p;
+inline Plan plan_tile(long long rows, int Dh, int M, Form form, float ordered) {   // one tile or share for all rows
+  Plan best{};
+  for (int t = 0; t < kScoreTiles + kShareCount; ++t) {
+    if (t >= kShared && !share_fits(t - kShared, Dh, M)) continue;
+    const float us = cost_tile(t, rows, Dh, M, form) + (t >= kShared ? ordered : 0.0f);
+    if (best.n > 0 && us >= best.us) continue;
+    best = Plan{};
+    best.add(t, rows, us);
+  }
+  return best;
 }
 
+// Raw weights: inputs that keep an fp32 epilogue.  Up to 112 token blocks, if K can be cut into enough even
+// parts of four or more 64-input tiles to make blocks for up to 256 CUs (all widths of 512 inputs and more
+// whose tiles are even in number).
+inline bool fp32_epilogue(long long rows, int Dh, int M) {
+  const int tok = M / 128 <= 4 ? 128 : 96, tiles = Dh / kBK;
+  const long long blocks = (rows + tok - 1) / tok;
+  if (rows <= kSkinnyRows) return true;
+  for (int d = 2; d <= 8; ++d)
+    if (tiles % d == 0 && tiles / d >= kPD + 1 && blocks * d <= 256 && blocks <= 112) return true;
+  return false;
+}
+
+// tokens in a round of the largest tile
+inline long long tile_round_rows(int M) { return (long long)kChipCUs / (M / 128) * 128; }
+
 Plan plan_score(long long rows, int Dh, int M, int H, Form form) {
-  const long long tile_round = (long long)kChipCUs / (M / 128) * 128;      // tokens in a round of the largest tile
+  const long long tile_round = tile_round_rows(M);
+  const float ordered = form == Form::kRaw ? kArrange[0] + kArrange[1] * (float)M * (float)Dh : 0.0f;
   if (Dh / kBK < kPD + 1) {                 // too few K tiles for token blocks: tiles, or score_mlp_kernel
-    Plan p = plan_tile(rows, Dh, M, form);
+    Plan p = plan_tile(rows, Dh, M, form, ordered);
     const float small = kSmallFixed[M / 128 - 1] + (float)(Dh / kBK) * kSmallStep[M / 128 - 1];
     if (rows > kSkinnyRows && (rows > kTileMaxRows || small < p.us)) p.seg[0].tile = kWholeK;
     return p;
@@ -1126,24 +1252,22 @@ Plan plan_score(long long rows, int Dh, int M, int H, Form form) {
     best.add(kSkinny, rows, 0.0f);
     return best;
   }
-  const int ks = frag_ksplit(rows, Dh / kBK, M);
-  if (form != Form::kRaw || (ks == 1 && rows > kSkinnyRows)) best.add(kWholeK, rows, cost_blocks(rows, Dh, M, form));
-  else if (ks == 1) best = plan_tile(rows, Dh, M, form);
-  else best.add(kSlicedK, rows, cost_sliced(rows, Dh, M, ks));
-  auto consider = [&](int head_tile, long long head, float head_cost) {    // head rows, the rest as one tile
+  if (form != Form::kRaw || !fp32_epilogue(rows, Dh, M)) best.add(kWholeK, rows, cost_blocks(rows, Dh, M, form) + ordered);
+  // W1 in order is paid for once, by token blocks or by a share
+  auto consider = [&](int head_tile, long long head, float head_cost) {    // head rows, the rest as one tile or share
     Plan p{};
     if (head > 0) p.add(head_tile, head, head_cost);
-    const Plan rest = plan_tile(rows - head, Dh, M, form);
+    const Plan rest = plan_tile(rows - head, Dh, M, form, head_tile == kWholeK ? 0.0f : ordered);
     p.add(rest.seg[0].tile, rest.seg[0].rows, rest.us);
-    if (p.us < best.us) best = p;
+    if (best.n == 0 || p.us < best.us) best = p;
   };
   const long long block_round = (long long)kChipCUs * (M / 128 <= 4 ? 128 : 96);
-  if (rows <= kTileMaxRows) consider(0, 0, 0.0f);
   if (rows <= kTileMaxRows)
-    for (long long head = tile_round; head < rows; head += tile_round)
-      consider(0, head, cost_tile(0, head, Dh, M, form));
+    for (long long head = 0; head < rows; head += tile_round)
+      consider(0, head, head ? cost_tile(0, head, Dh, M, form) : 0.0f);
   const long long head = rows / block_round * block_round;
-  if (head > 0 && head < rows && rows - head <= kTileMaxRows) consider(kWholeK, head, cost_blocks(head, Dh, M, form));
+  if (head > 0 && head < rows && rows - head <= kTileMaxRows)
+    consider(kWholeK, head, cost_blocks(head, Dh, M, form) + ordered);
   return best;
 }
 
@@ -1151,23 +1275,28 @@ Plan plan_score(long long rows, int Dh, int M, int H, Form form) {
 size_t parts_bytes(const Plan& p, int M, int H) {
   size_t n = 0;
   for (int i = 0; i < p.n; ++i) {
-    const size_t part = p.seg[i].tile >= 0 ? score_tile_part_bytes(p.seg[i].tile, p.seg[i].rows, M, H) : 0;
+    const int f = p.seg[i].tile - kShared;
+    const size_t part = f >= 0 ? (size_t)(M / (128 * kShareForms[f].UB)) * H * p.seg[i].rows * sizeof(float) : p.seg[i].tile >= 0 ? score_tile_part_bytes(p.seg[i].tile, p.seg[i].rows, M, H) : 0;
     n = n > part ? n : part;
   }
   return align_up(n, 256);
 }
+// raw weights: whether W1 is put in fragment order first
+bool wants_ordered_w1(const Plan& p) {
+  for (int i = 0; i < p.n; ++i)
+    if (p.seg[i].tile == kWholeK || p.seg[i].tile >= kShared) return true;
+  return false;
+}
 size_t w1_bytes(int Dh, int M) { return align_up((size_t)M * Dh * 2, 256); }
 
-// What a plan for raw weights takes: W1 in fragment order for token blocks and K-slices, behind it
-// the tiles' parts or the slices' partial sums; where there are only tiles, the parts alone.
+// What a plan for raw weights takes: W1 in fragment order for token blocks and shares, behind it
+// the parts; where there are only tiles, the parts alone.
 size_t raw_workspace_bytes(const Plan& p, long long rows, int Dh, int M, int H) {
   const size_t copy = w1_bytes(Dh, M);
   size_t alone = parts_bytes(p, M, H);
   if (p.seg[0].tile == kSkinny)
     alone = align_up((size_t)skinny_ksplit(rows, Dh, M, kSkinnyBlocks) * rows * M * sizeof(float), 256);
-  if (p.seg[0].tile == kSlicedK)
-    return copy + align_up((size_t)frag_ksplit(rows, Dh / kBK, M) * rows * M * sizeof(float), 256);
-  if (p.seg[0].tile == kWholeK) return copy + alone;
+  if (wants_ordered_w1(p)) return copy + alone;
   return alone > copy ? alone : copy;
 }
 
@@ -1175,7 +1304,7 @@ size_t raw_workspace_bytes(const Plan& p, long long rows, int Dh, int M, int H) 
 // alone, or where they are no candidate the largest tile alone, whose parts only grow with the rows.
 Plan fallback_plan(long long rows, int Dh, int M) {
   Plan p{};
-  p.add(rows > kSkinnyRows && frag_ksplit(rows, Dh / kBK, M) == 1 ? kWholeK : 0, rows, 0.0f);
+  p.add(fp32_epilogue(rows, Dh, M) ? 0 : kWholeK, rows, 0.0f);
   return p;
 }
 
@@ -1209,27 +1338,45 @@ size_t score_mlp_workspace_bytes(long long rows, int Dh, int M, int H, bool prep
   return need > least ? need : least;
 }
 
+size_t score_mlp_prepared_least_bytes(long long rows, int Dh, int M, int H) {
+  return rows > tile_round_rows(M) / 2 ? 0 : score_mlp_workspace_bytes(rows, Dh, M, H, true);
+}
+
 size_t score_mlp_least_workspace_bytes(long long rows, int Dh, int M, int H) {
   return rows <= 0 ? w1_bytes(Dh, M) : raw_workspace_bytes(fallback_plan(rows, Dh, M), rows, Dh, M, H);
 }
+
+namespace {
+// Prepared weights, in a buffer that may have been queried for another length: the plan, the largest tile
+// alone, or token blocks, whichever first fits it.
+Plan plan_prepared(long long rows, int Dh, int M, int H, Form form, bool workspace, size_t workspace_bytes) {
+  Plan p{};
+  if (workspace) p = plan_score(rows, Dh, M, H, form);
+  if (workspace && parts_bytes(p, M, H) <= workspace_bytes) return p;
+  p = Plan{};
+  const bool tile = workspace && rows <= tile_round_rows(M) && align_up(score_tile_part_bytes(0, rows, M, H), 256) <= workspace_bytes;
+  p.add(tile ? 0 : kWholeK, rows, 0.0f);
+  return p;
+}
+}  // namespace
 
 bool score_rmsnorm_supports(int Dh) { return (Dh / kBK) >= kPD + 1; }
 
 int launch_score_mlp_rmsnorm(const void* x, const void* W1_prepared, const void* gain, float eps,
                              const void* b1, const void* W2, const void* b2, float* scores,
                              float* rstd, void* normed, int B, int T, int Dh, int M, int H,
-                             void* workspace, hipStream_t stream) {
+                             void* workspace, size_t workspace_bytes, hipStream_t stream) {
   const long long rows = (long long)B * T;
   const NormArgs norm{static_cast<const unsigned short*>(gain), eps, rstd,
                       static_cast<unsigned short*>(normed)};
-  Plan plan{};
-  if (workspace) plan = plan_score(rows, Dh, M, H, normed ? Form::kStates : Form::kPrepared);
-  else plan.add(kWholeK, rows, 0.0f);
+  const Plan plan = plan_prepared(rows, Dh, M, H, normed ? Form::kStates : Form::kPrepared, workspace != nullptr, workspace_bytes);
   long long first = 0;
   for (int i = 0; i < plan.n; ++i) {
     const Segment& s = plan.seg[i];
-    const int rc = s.tile < 0
-        ? launch_blocks<true>(x, W1_prepared, b1, W2, b2, scores, nullptr, 1, s.rows, T, Dh, M, H, norm, stream)
+    const int rc = s.tile >= kShared
+        ? launch_shared<true>(s.tile - kShared, x, W1_prepared, b1, W2, b2, scores, static_cast<float*>(workspace), s.rows, first, T, Dh, M, H, norm, stream)
+        : s.tile < 0
+        ? launch_blocks<true>(x, W1_prepared, b1, W2, b2, scores, s.rows, T, Dh, M, H, norm, stream)
         : launch_score_tile(s.tile, true, x, W1_prepared, b1, W2, b2, scores,
                             static_cast<float*>(workspace), s.rows, first, T, Dh, M, H, &norm, stream);
     if (rc != KVZAP_OK) return rc;
@@ -1245,9 +1392,8 @@ int launch_score_mlp(const void* hidden, const void* W1, const void* b1, const v
                      bool prepared, void* workspace, size_t workspace_bytes, hipStream_t stream) {
   const long long rows = (long long)B * T;
   const bool frag = (Dh / kBK) >= kPD + 1;
-  Plan plan{};
-  if (workspace) plan = plan_score(rows, Dh, M, H, prepared ? Form::kPrepared : Form::kRaw);
-  else plan.add(kWholeK, rows, 0.0f);
+  Plan plan = prepared ? plan_prepared(rows, Dh, M, H, Form::kPrepared, workspace != nullptr, workspace_bytes)
+                       : plan_score(rows, Dh, M, H, Form::kRaw);
   if (!prepared && raw_workspace_bytes(plan, rows, Dh, M, H) > workspace_bytes) plan = fallback_plan(rows, Dh, M);
   if (plan.seg[0].tile == kSkinny) {
     const int ks = skinny_ksplit(rows, Dh, M, kSkinnyBlocks);
@@ -1257,7 +1403,7 @@ int launch_score_mlp(const void* hidden, const void* W1, const void* b1, const v
   const void* blocks_w1 = W1;
   bool tiles_frag = prepared && frag;
   float* part = static_cast<float*>(workspace);
-  if (!prepared && frag && plan.seg[0].tile < 0) {
+  if (!prepared && frag && wants_ordered_w1(plan)) {
     part = reinterpret_cast<float*>(static_cast<char*>(workspace) + w1_bytes(Dh, M));
     const int rc = launch_prepare_w1(W1, nullptr, Dh, M, workspace, stream);
     if (rc != KVZAP_OK) return rc;
@@ -1267,12 +1413,13 @@ int launch_score_mlp(const void* hidden, const void* W1, const void* b1, const v
   for (int i = 0; i < plan.n; ++i) {
     const Segment& s = plan.seg[i];
     int rc;
-    if (s.tile >= 0) {
+    if (s.tile >= kShared) {
+      rc = launch_shared<false>(s.tile - kShared, hidden, blocks_w1, b1, W2, b2, scores, part, s.rows, first, T, Dh, M, H, NormArgs{}, stream);
+    } else if (s.tile >= 0) {
       rc = launch_score_tile(s.tile, tiles_frag, hidden, W1, b1, W2, b2, scores, part, s.rows, first,
                              T, Dh, M, H, nullptr, stream);
     } else if (frag) {
-      const int ks = s.tile == kSlicedK ? frag_ksplit(rows, Dh / kBK, M) : 1;
-      rc = launch_blocks<false>(hidden, blocks_w1, b1, W2, b2, scores, part, ks, s.rows, T, Dh, M, H, NormArgs{}, stream);
+      rc = launch_blocks<false>(hidden, blocks_w1, b1, W2, b2, scores, s.rows, T, Dh, M, H, NormArgs{}, stream);
     } else {
       switch (M / 128) {
         case 1: rc = launch_one<1>(hidden, W1, b1, W2, b2, scores, s.rows, T, Dh, H, stream); break;

@@ -41,8 +41,6 @@ namespace {
 
 constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * 64;
-constexpr int kXcds = 8;
-constexpr float kMaxBf16 = 3.3895313892515355e38f;
 
 // BU x BT: tile in blocks of 32 units / tokens; WU x WT: piece of a wavefront; KG groups of
 // wavefronts over K, P MFMA steps of 16 inputs per wavefront and stage; S stages.
@@ -67,6 +65,9 @@ struct Tile {
   static constexpr int EPI = RED + DOT + NU * 16 * 2 + NU * 4 + (2 * KG + 1) * NT * 4;
   static constexpr int LDS = S * STAGE > EPI ? S * STAGE : EPI;
   static_assert(LDS <= 160 * 1024, "fits the CU");
+  // sums over parts of a wavefront's K, where there are few K groups: the fp32 sums of 4096 products are
+  // then 2.4e-7 off instead of 3.3e-7
+  static constexpr int SUMS = KG == 2 ? 2 : 1;
 };
 
 template <class C, bool kFrag, bool kNorm>
@@ -171,13 +172,16 @@ __global__ __launch_bounds__(kThreads) void score_tile_kernel(
     a_off[p] = (unsigned)(sub * C::PLANE + wu * WU * 4096) + (kFrag ? (unsigned)kk * 1024u + (unsigned)lane * 16u : piece);
     b_off[p] = (unsigned)(sub * C::PLANE + BU * 4096 + wt * WT * 4096) + piece;
   }
-  floatx16 acc[WU][WT];
+  floatx16 acc_of[C::SUMS][WU][WT];
+  auto& acc = acc_of[0];
 #pragma unroll
-  for (int u = 0; u < WU; ++u)
+  for (int sum = 0; sum < C::SUMS; ++sum)
 #pragma unroll
-    for (int w = 0; w < WT; ++w)
+    for (int u = 0; u < WU; ++u)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[u][w][e] = 0.0f;
+      for (int w = 0; w < WT; ++w)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc_of[sum][u][w][e] = 0.0f;
   float ssq[WT];
 #pragma unroll
   for (int w = 0; w < WT; ++w) ssq[w] = 0.0f;
@@ -189,9 +193,9 @@ __global__ __launch_bounds__(kThreads) void score_tile_kernel(
     if (x < WU) fa[buf][p][x] = *reinterpret_cast<const bf16x8*>(smem + stage + a_off[p] + x * 4096);
     else fb[buf][p][x - WU] = *reinterpret_cast<const bf16x8*>(smem + stage + b_off[p] + (x - WU) * 4096);
   };
-  auto mfma = [&](int buf, int m) {
+  auto mfma = [&](int buf, int m, int sum) {
     const int p = m / (WU * WT), u = m / WT % WU, w = m % WT;
-    acc[u][w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][p][u], fb[buf][p][w], acc[u][w], 0, 0, 0);
+    acc_of[sum][u][w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][p][u], fb[buf][p][w], acc_of[sum][u][w], 0, 0, 0);
   };
   auto squares = [&](int buf) {                                      // sum of x^2 of this wavefront's tokens
     if (wu == 0) {
@@ -232,18 +236,18 @@ __global__ __launch_bounds__(kThreads) void score_tile_kernel(
     st_free += STAGE; if (st_free == S * STAGE) st_free = 0;
   };
   constexpr int kLgkm0 = 0xc07f;                                     // s_waitcnt lgkmcnt(0)
-  auto full_step = [&](int t, auto buf_tag) {
-    constexpr int buf = decltype(buf_tag)::value;
+  auto full_step = [&](int t, auto buf_tag, auto sum_tag) {
+    constexpr int buf = decltype(buf_tag)::value, sum = decltype(sum_tag)::value;
     __builtin_amdgcn_s_waitcnt(kLgkm0);
     __builtin_amdgcn_sched_barrier(0);
-    mfma(buf, 0);                                                    // runs while the others arrive
+    mfma(buf, 0, sum);                                                   // runs while the others arrive
     __builtin_amdgcn_sched_barrier(0);
     wait_vmcnt<(S - 2) * NL>();
     block_barrier_no_drain();
     constexpr int kReadSlots = (kMfmas + 1) / 2, kDmaSlots = kMfmas - kReadSlots > 0 ? kMfmas - kReadSlots : 1;
 #pragma unroll
     for (int m = 0; m < kMfmas; ++m) {
-      if (m > 0) mfma(buf, m);
+      if (m > 0) mfma(buf, m, sum);
 #pragma unroll
       for (int i = 0; i < kReads; ++i)
         if (i * kReadSlots / kReads == m) read_one(buf ^ 1, i, st_next);
@@ -270,7 +274,7 @@ __global__ __launch_bounds__(kThreads) void score_tile_kernel(
     }
     if (SUB == 1 || t * SUB + (g * P) / 4 < nk) {                    // odd end: no inputs left for this group
 #pragma unroll
-      for (int m = 0; m < kMfmas; ++m) mfma(buf, m);
+      for (int m = 0; m < kMfmas; ++m) mfma(buf, m, C::SUMS - 1);
       if constexpr (kNorm) squares(buf);
     }
     advance();
@@ -278,15 +282,27 @@ __global__ __launch_bounds__(kThreads) void score_tile_kernel(
   typedef std::integral_constant<int, 0> Buf0;
   typedef std::integral_constant<int, 1> Buf1;
   int t = 0;
+  if constexpr (C::SUMS == 2) {
+    for (; 2 * t < stages && t + S + 2 < stages; t += 2) {
+      full_step(t, Buf0{}, Buf0{});
+      full_step(t + 1, Buf1{}, Buf0{});
+    }
+  }
   for (; t + S + 2 < stages; t += 2) {      // (the very last stage, which may be odd, is fetched below)
-    full_step(t, Buf0{});
-    full_step(t + 1, Buf1{});
+    full_step(t, Buf0{}, std::integral_constant<int, C::SUMS - 1>{});
+    full_step(t + 1, Buf1{}, std::integral_constant<int, C::SUMS - 1>{});
   }
   for (; t < stages; t += 2) {
     end_step(t, Buf0{});
     if (t + 1 < stages) end_step(t + 1, Buf1{});
   }
   block_barrier_no_drain();                 // all reads of the ring are done: its LDS is reused
+  if constexpr (C::SUMS == 2) {
+#pragma unroll
+    for (int u = 0; u < WU; ++u)
+#pragma unroll
+      for (int w = 0; w < WT; ++w) acc[u][w] += acc_of[C::SUMS - 1][u][w];
+  }
 
   // ---- the KG partial tiles meet in LDS: red[wavefront][register / 4][lane] x 16 B ----
   float* const red = reinterpret_cast<float*>(smem);
@@ -353,36 +369,13 @@ __global__ __launch_bounds__(kThreads) void score_tile_kernel(
         const uint2 p1 = *reinterpret_cast<const uint2*>(sW2 + ((size_t)l32 * NU + u0 + 8) * 2);
         w2.x = p0.x; w2.y = p0.y; w2.z = p1.x; w2.w = p1.y;
       }
-      bf16x8 hi, mid, lo;
-      float a[8], top = 0.0f;
+      float a[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float z = e < 4 ? z0[e] : z1[e - 4], c = e < 4 ? c0[e] : c1[e - 4];
         a[e] = gelu_exact(kNorm ? fmaf(z, rs, c) : z + c);             // -0.17 and up, or NaN
-        top = fmaxf(top, a[e]);
       }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        hi[e] = (__bf16)a[e];
-        const float r1 = a[e] - (float)hi[e];
-        mid[e] = (__bf16)r1;
-        lo[e] = (__bf16)(r1 - (float)mid[e]);
-      }
-      // Beyond the bf16 range the first term stays at its end (rounding takes the last 0.2 % of the fp32
-      // range to infinity, and the rest would be minus infinity); an infinite a is the second term alone.
-      if (__any(top > kMaxBf16)) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          hi[e] = (__bf16)(a[e] > kMaxBf16 ? kMaxBf16 : a[e]);
-          const float r1 = a[e] - (float)hi[e];
-          mid[e] = (__bf16)r1;
-          lo[e] = (__bf16)(r1 == (float)mid[e] ? 0.0f : r1 - (float)mid[e]);
-        }
-      }
-      const bf16x8 wa = __builtin_bit_cast(bf16x8, w2);
-      dot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, lo, dot, 0, 0, 0);
-      dot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, mid, dot, 0, 0, 0);
-      dot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, hi, dot, 0, 0, 0);
+      dot = dot_three_terms(__builtin_bit_cast(bf16x8, w2), a, dot);
     }
     // dot[e], e < 8: head 8*(e/4) + 4*kg + e%4 of token `tok`
     const int share = wu * (C::SHARES / NWU) + first % (2 * WU) / C::OWN;
@@ -491,10 +484,7 @@ int launch_tile(const void* hidden, const void* W1, const void* b1, const void* 
       static_cast<const unsigned short*>(b1), static_cast<const unsigned short*>(W2),
       static_cast<const unsigned short*>(b2), scores, part, rows, row_first, T, Dh, M, H, (int)tt, norm);
   if (hipGetLastError() != hipSuccess) return KVZAP_ERR_RUNTIME;
-  if (nut > 1)
-    score_tile_sum_kernel<<<dim3((unsigned)((rows + 255) / 256), H), 256, 0, stream>>>(
-        part, static_cast<const unsigned short*>(b2), scores, rows, row_first, T, H, nut);
-  return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
+  return nut > 1 ? launch_score_sum(part, b2, scores, rows, row_first, T, H, nut, stream) : KVZAP_OK;
 }
 
 template <class C>
@@ -509,6 +499,13 @@ int launch_form(bool frag, const void* hidden, const void* W1, const void* b1, c
 }
 
 }  // namespace
+
+int launch_score_sum(const float* part, const void* b2, float* scores, long long rows, long long row_first,
+                     int T, int H, int nut, hipStream_t stream) {
+  score_tile_sum_kernel<<<dim3((unsigned)((rows + 255) / 256), H), 256, 0, stream>>>(
+      part, static_cast<const unsigned short*>(b2), scores, rows, row_first, T, H, nut);
+  return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
+}
 
 long long score_tile_xcd_blocks(int tile, long long rows, int M) {
   auto n = [&](int nu, int nt) { return ((rows + nt - 1) / nt + kXcds - 1) / kXcds * (M / nu); };

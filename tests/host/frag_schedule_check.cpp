@@ -77,8 +77,9 @@ struct Sim {
 int main(int argc, char** argv) {
   const int plant = (argc > 1 && !std::strcmp(argv[1], "--plant")) ? 1 : 0;
   int failed = 0, checked = 0, worst_slack = 0;
-  for (int UB = 1; UB <= 5; ++UB)
-    for (int NDJ = 3; NDJ <= 4; ++NDJ)
+  // a K tile of two planes counts as one of twice the unit blocks and load-to-LDS operations
+  for (int UB = 1; UB <= 6; ++UB)
+    for (int NDJ : {3, 4, 6, 8})
       for (int lead = 1; lead <= 2; ++lead) {
         if (!lead_is_safe(UB, NDJ, lead)) continue;           // the kernel refuses to compile these
         for (int nk = kHiddenAhead + 1; nk <= 20; ++nk) {
@@ -89,7 +90,8 @@ int main(int argc, char** argv) {
         }
       }
   // the shapes the library instantiates must be among the safe ones
-  const int built[][3] = {{1, 4, 2}, {2, 4, 2}, {3, 4, 2}, {4, 4, 2}, {5, 3, 1}, {4, 4, 1}, {1, 4, 1}};
+  const int built[][3] = {{1, 4, 2}, {2, 4, 2}, {3, 4, 2}, {4, 4, 2}, {5, 3, 1}, {4, 4, 1}, {1, 4, 1},
+                          {4, 8, 2}, {4, 6, 2}, {2, 8, 2}, {2, 6, 2}};
   for (auto& b : built)
     if (!lead_is_safe(b[0], b[1], b[2])) { std::printf("built shape UB=%d NDJ=%d lead=%d is not safe\n", b[0], b[1], b[2]); ++failed; }
   std::printf("%d configurations checked, %d with an under-wait, largest over-wait %d operations\n",
