@@ -446,26 +446,48 @@ __global__ __launch_bounds__(256) void teacher_finish_kernel(const float* __rest
 
 }  // namespace
 
-int teacher_splits(int H, int G, int Tq, int T) {
-  const int tq_pad = (Tq + 31) / 32 * 32;
-  const long long col_blocks = (long long)((T + kBlockRows - 1) / kBlockRows) * H;
-  long long js = col_blocks > 0 ? (512 + col_blocks - 1) / col_blocks : 1;   // ~2 blocks per CU
-  const long long items = (long long)G * (tq_pad / 32);
-  if (js > items) js = items;
-  if (js > 256) js = 256;
-  return js < 1 ? 1 : (int)js;
+// How many shares.  A wavefront alone on its SIMD keeps the matrix pipe almost as busy as two (5 % less: 8192
+// keys and queries 1128 us in one share of 256 blocks, 1109 in two), so what counts is how many blocks the fullest of the 256 CUs gets, and a few blocks
+// more than a multiple of 256 cost a CU's whole share again: 17 blocks of keys for 8 heads in 4 shares, 544
+// blocks, 105 us, in 3 shares 99.  Both rules take the number with the least
+//   (blocks of the fullest CU) * (tiles of a block) * us a tile + us a pair of blocks that follow each other
+//   + what a share costs the kernel that merges them,
+// fitted to 11 prompts with 1 to 32 shares.  us per call (before: some 512 and 1024 blocks, however they fell):
+// 32 heads, prompt and repeat 512 27 (30), 1024 38 (40), 2195 113 (126), prompt 4274, repeat 1068 98 (105);
+// 16 heads, 1204 39 (44), 3255 115 (129), 5646 310 (332), prompt 2414, repeat 603 34 (40).
+constexpr int kCUs = 256;
+inline float share_us(long long blocks, float tiles, float tile_us) {      // `blocks` blocks of `tiles` tiles
+  const long long n = (blocks + kCUs - 1) / kCUs;
+  return (float)n * tiles * tile_us * (n == 1 ? 1.05f : 1.0f) + 2.6f * (float)((n + 1) / 2);
 }
 
-// Shares of the keys in the row pass: up to 1024 blocks (two per CU and as many to even out the early
-// and late queries' unequal work) where blocks of 256 queries are fewer, with at least 8 key tiles
-// of the prompt (T positions, no more than the earliest queries see) in each.  Measured, us per call
-// (with shares / one block per 256 queries): 32 heads: prompt and repeat 512 29 / 41, 1024: 38 / 52,
-// 2048: 92 / 101, 4096: 293 / 313; 16 heads, prompt 2048, repeat 512: 27 / 53; 8192, 2048: 137 / 193.
+int teacher_splits(int H, int G, int Tq, int T) {
+  const long long blocks = (long long)((T + kBlockRows - 1) / kBlockRows) * H;
+  const long long items = (long long)G * ((Tq + 31) / 32);
+  int best = 1;
+  float least = share_us(blocks, (float)items, 0.24f);
+  for (int js = 2; js <= 64 && js <= items; ++js) {
+    const float us = share_us(blocks * js, (float)items / js, 0.24f) + 0.15f * js;
+    if (us < 0.99f * least) { least = us; best = js; }
+  }
+  return best;
+}
+
+// The same for the keys in the row pass, whose blocks differ (a late query sees up to twice the keys of
+// an early one; the longest go first): with one or two blocks a CU all of that difference shows, with more
+// half of it.  At least 4 key tiles of the prompt (T positions, no more than the earliest queries see) in a
+// share, and the launch that merges them.
 int teacher_key_splits(int HQ, int Tq, int T) {
   const long long blocks = (long long)((Tq + kBlockRows - 1) / kBlockRows) * HQ;
-  long long ks = blocks < 1024 ? 1024 / blocks : 1;
-  if (ks > T / 256) ks = T / 256;
-  return ks < 1 ? 1 : (int)ks;
+  const float mean = (float)(T + Tq / 2) / 32, late = (float)(Tq / 2) / 32, tile_us = 0.33f;
+  int best = 1;
+  float least = share_us(blocks, mean, tile_us) + late * tile_us * (blocks > 2 * kCUs ? 0.5f : 1.0f);
+  for (int ks = 2; ks <= 64 && ks <= T / 128; ++ks) {
+    const float us = share_us(blocks * ks, mean / ks, tile_us) +
+                     late / ks * tile_us * (blocks * ks > 2 * kCUs ? 0.5f : 1.0f) + 4.0f + 0.15f * ks;
+    if (us < 0.99f * least) { least = us; best = ks; }
+  }
+  return best;
 }
 
 size_t teacher_rowbias_bytes(int HQ, int Tq) { return align_up((size_t)HQ * ((Tq + 31) / 32 * 32) * sizeof(float), 256); }

@@ -145,3 +145,20 @@ def test_a_workspace_of_the_longest_prompt_serves_the_others(H, HQ, longest, T):
 def test_edges_of_tiles_and_of_whole_visible_groups(T, instr, Tq):
     _check(H=3, G=2, T=T, instr=instr, Tq=Tq, seed=T + Tq)
     _check(H=1, G=1, T=T, instr=instr, Tq=Tq, seed=T + Tq + 1, gain=8.0)   # the reference moves often
+
+
+# As many shares as the rules give: four key tiles in a share, fewer queries than one tile, one item a share;
+# and the fewest, in the least workspace that is accepted
+@pytest.mark.parametrize("H,G,T,Tq", [(8, 2, 511, 30), (8, 2, 512, 33), (8, 4, 1300, 64), (4, 1, 1025, 257), (8, 2, 640, 640)])
+def test_shares_at_the_ends_of_their_range(H, G, T, Tq):
+    q, k, vn, hn = _inputs(H, G, T, 16, Tq, seed=T)
+    ref = O.teacher_log_scores(synth.f64(q), synth.f64(k), D ** -0.5, T, vn.double().numpy(), hn.double().numpy())
+    least = (H * G * ((Tq + 31) // 32 * 32) * 4 + 255) // 256 * 256 + (H * T * 4 + 255) // 256 * 256
+    full = binding.kvzap_workspace_bytes(binding.CALL_TEACHER_SCORES, 1, T, H * G, Tq, H)
+    assert full >= least
+    for n in (full, least):
+        ws = torch.full((n + 4096,), 0xff, dtype=torch.uint8, device=DEV)
+        got = binding.kvzap_teacher_scores(q.to(DEV), k.to(DEV), T, D ** -0.5, vn.to(DEV), hn.to(DEV), workspace=ws[:n])
+        err = np.abs(got.double().cpu().numpy() - ref)
+        assert (err <= 2e-3 + 1e-4 * np.abs(ref)).all(), err.max()
+        assert (ws[n:] == 0xff).all()
