@@ -237,16 +237,30 @@ struct GatherArgs {
   int64_t cap_rows;
 };
 
-template <int kLpr>          // 16-byte pieces of a K/V row; 0: no gather
+// kLpr: 16-byte pieces of a K/V row; 0: no gather.  kEager: all rows of the chunk are loaded before it is
+// known which are kept
+template <int kLpr, bool kEager>
 __global__ __launch_bounds__(kDirectThreads) void mask_direct_kernel(
     const float* __restrict__ scores, float tau_all, const float* __restrict__ tau_head, int window,
     const int32_t* __restrict__ seq_lens, int H, int T, int32_t* __restrict__ keep_idx,
     int32_t* __restrict__ lengths, int64_t* __restrict__ offsets, GatherArgs rows) {
   __shared__ int s_before[kDirectWaves], s_own[kDirectWaves], s_first;
-  __shared__ int s_keep[kDirectChunk];
+  __shared__ int s_keep[kDirectChunk];                     // kept tokens; kEager: the tokens' ranks, -1: dropped
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int bh = blockIdx.y, t_begin = blockIdx.x * kDirectChunk;
   auto tau_of = [&](int row) { return tau_head ? tau_head[row] : tau_all; };
+  constexpr int kRows = kLpr > 0 ? kDirectThreads / kLpr : 1;   // rows of one tensor per pass
+  constexpr int kPasses = kEager ? kDirectChunk / kRows : 1;
+  u32x4 k_row[kPasses], v_row[kPasses];
+  if constexpr (kEager) {
+#pragma unroll
+    for (int u = 0; u < kPasses; ++u) {
+      const int t = t_begin + tid / kLpr + u * kRows;
+      const size_t from = ((size_t)bh * T + (t < T ? t : T - 1)) * kLpr + tid % kLpr;
+      k_row[u] = __builtin_nontemporal_load(rows.K + from);
+      v_row[u] = __builtin_nontemporal_load(rows.V + from);
+    }
+  }
   // this chunk's flags: one lane of the first two wavefronts per token
   bool own = false;
   const int t_mine = t_begin + tid;
@@ -327,9 +341,10 @@ __global__ __launch_bounds__(kDirectThreads) void mask_direct_kernel(
 #pragma unroll
   for (int w = 0; w < kDirectWaves; ++w) { start += s_before[w]; mine += s_own[w]; }
   const int first = s_first, out0 = start + mine;          // of this head; of this chunk
+  const int rank = (wv ? first : 0) + __popcll(kept & ((1ull << lane) - 1));
+  if (kEager && tid < kDirectChunk) s_keep[tid] = own ? rank : -1;
   if (own) {
-    const int rank = (wv ? first : 0) + __popcll(kept & ((1ull << lane) - 1));
-    s_keep[rank] = t_mine;
+    if (!kEager) s_keep[rank] = t_mine;
     keep_idx[out0 + rank] = t_mine;
   }
   const int count = __syncthreads_count(own);
@@ -340,8 +355,17 @@ __global__ __launch_bounds__(kDirectThreads) void mask_direct_kernel(
       if (bh == (int)gridDim.y - 1) offsets[bh + 1] = out0 + count;
     }
   }
-  if constexpr (kLpr > 0) {
-    constexpr int kRows = kDirectThreads / kLpr;           // rows of one tensor per pass
+  if constexpr (kEager) {
+#pragma unroll
+    for (int u = 0; u < kPasses; ++u) {
+      const int r = s_keep[tid / kLpr + u * kRows];
+      if (r >= 0 && out0 + r < rows.cap_rows) {
+        const size_t to = (size_t)(out0 + r) * kLpr + tid % kLpr;
+        __builtin_nontemporal_store(k_row[u], rows.K_out + to);
+        __builtin_nontemporal_store(v_row[u], rows.V_out + to);
+      }
+    }
+  } else if constexpr (kLpr > 0) {
     const int piece = tid % kLpr;
     const size_t base = (size_t)bh * T * kLpr + piece;
 #pragma unroll 4
@@ -366,16 +390,23 @@ __global__ __launch_bounds__(kDirectThreads) void mask_direct_kernel(
 // direct wins up to 40 segments there too.
 constexpr long long kDirectSegments = 32, kDirectSegmentsGather = 40;
 
+// With a block for every CU at most, the gather is another trip to memory behind the ranks, and reading all
+// rows while the scores are tested takes it away, also where few are kept.  The rows' registers leave
+// room for one block on a CU, so with more blocks than CUs it loses.  us per call (rows of kept tokens alone /
+// all rows, 8 heads, half kept): 2048 x 128 7.6 / 6.8, 4096 x 128 (256 blocks) 9.1 / 8.4, 5000 x 128 (320)
+// 11.2 / 13.7, 1024 x 256 9.0 / 7.3, 4096 x 256 13.0 / 11.3; a tenth kept: 4096 x 128 8.2 / 8.2, x 256 11.0 / 11.1.
+constexpr long long kEagerBlocks = 256;
+
 bool direct_fits(int B, int H, int T, long long limit) {
   return (long long)B * H * ((T + kSegment - 1) / kSegment) <= limit;
 }
 
-template <int kLpr>
+template <int kLpr, bool kEager = false>
 int launch_direct(const float* scores, float tau, const float* tau_head, int window,
                   const int32_t* seq_lens, int B, int H, int T, int32_t* keep_idx, int32_t* lengths,
                   int64_t* offsets, const GatherArgs& rows, hipStream_t stream) {
   const dim3 grid((T + kDirectChunk - 1) / kDirectChunk, B * H);
-  mask_direct_kernel<kLpr><<<grid, kDirectThreads, 0, stream>>>(scores, tau, tau_head, window, seq_lens, H, T,
+  mask_direct_kernel<kLpr, kEager><<<grid, kDirectThreads, 0, stream>>>(scores, tau, tau_head, window, seq_lens, H, T,
                                                                 keep_idx, lengths, offsets, rows);
   return hipGetLastError() == hipSuccess ? KVZAP_OK : KVZAP_ERR_RUNTIME;
 }
@@ -389,6 +420,14 @@ int launch_mask_compact(const float* scores, float tau, int window, const int32_
   if (direct_fits(B, H, T, kDirectSegmentsGather)) {
     const GatherArgs rows{static_cast<const u32x4*>(K), static_cast<const u32x4*>(V),
                           static_cast<u32x4*>(K_out), static_cast<u32x4*>(V_out), cap_rows};
+    if ((long long)B * H * ((T + kDirectChunk - 1) / kDirectChunk) <= kEagerBlocks) {
+      switch (D / 8) {
+        case 8: return launch_direct<8, true>(scores, tau, nullptr, window, seq_lens, B, H, T, keep_idx, lengths, offsets, rows, stream);
+        case 16: return launch_direct<16, true>(scores, tau, nullptr, window, seq_lens, B, H, T, keep_idx, lengths, offsets, rows, stream);
+        case 32: return launch_direct<32, true>(scores, tau, nullptr, window, seq_lens, B, H, T, keep_idx, lengths, offsets, rows, stream);
+        default: break;
+      }
+    }
     switch (D / 8) {
       case 8: return launch_direct<8>(scores, tau, nullptr, window, seq_lens, B, H, T, keep_idx, lengths, offsets, rows, stream);
       case 16: return launch_direct<16>(scores, tau, nullptr, window, seq_lens, B, H, T, keep_idx, lengths, offsets, rows, stream);

@@ -90,3 +90,31 @@ def test_assign_pages(heads, max_pages):
     np.testing.assert_array_equal(parity.to_np(table), want)
     table, res = binding.kvzap_assign_pages(dev[0], 16, dev[1][:max(used - 1, 0)].clone(), max_pages)
     assert used == 0 or (res[:2].tolist() == [0, 1] and (parity.to_np(table) == -1).all())
+
+
+# Every row of a chunk is loaded before its rank is known while the blocks are no more than the CUs: lengths
+# around whole chunks, the last grid with that form and the first without, each row width, nothing and all
+# kept, a capacity that ends inside a chunk
+@pytest.mark.parametrize("B,H,T,D", [(1, 1, 1, 64), (1, 8, 127, 128), (2, 4, 129, 256), (3, 8, 701, 128), (1, 8, 4096, 64),
+                                     (1, 8, 4097, 128), (1, 2, 16384, 256)])
+@pytest.mark.parametrize("keep", [0.0, 0.4, 1.0])
+def test_rows_loaded_ahead_of_their_ranks(B, H, T, D, keep):
+    g = torch.Generator(device="cuda").manual_seed(T + D)
+    scores = torch.rand((B, H, T), generator=g, device="cuda")
+    K = torch.randn((B, H, T, D), generator=g, device="cuda").bfloat16()
+    V = torch.randn((B, H, T, D), generator=g, device="cuda").bfloat16()
+    seq = torch.tensor([T - 3 * b if T > 6 else T for b in range(B)], dtype=torch.int32, device="cuda")
+    window, tau = (0 if keep == 0.0 else 5), 1.0 - keep if keep else 2.0
+    t = torch.arange(T, device="cuda")
+    n = seq.view(B, 1, 1)
+    flags = (t < n) & ((t >= n - window) | (scores >= tau))
+    total = int(flags.sum())
+    for cap in {B * H * T, total // 2}:
+        K_out = torch.full((B * H * T, D), -7.0, device="cuda").bfloat16()
+        V_out = K_out.clone()
+        idx, lengths, offsets, _, _ = binding.kvzap_mask_compact(scores, tau, window, K, V, seq, K_out=K_out, V_out=V_out, cap_rows=cap)
+        assert torch.equal(lengths.view(B, H), flags.sum(-1).to(torch.int32)) and int(offsets[-1]) == total
+        assert torch.equal(idx[:total], flags.nonzero()[:, 2].to(torch.int32))
+        m = min(cap, total)
+        assert torch.equal(K_out[:m], K[flags][:m]) and torch.equal(V_out[:m], V[flags][:m])
+        assert (K_out[m:] == -7).all() and (V_out[m:] == -7).all()
