@@ -306,10 +306,10 @@ __global__ __launch_bounds__(kThreads) void score_tile_kernel(
 
   // ---- the KG partial tiles meet in LDS: red[wavefront][register / 4][lane] x 16 B ----
   float* const red = reinterpret_cast<float*>(smem);
+  auto put = [&](auto w_) {
+    constexpr int w = decltype(w_)::value;
 #pragma unroll
-  for (int u = 0; u < WU; ++u)
-#pragma unroll
-    for (int w = 0; w < WT; ++w)
+    for (int u = 0; u < WU; ++u)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         floatx4 v;
@@ -317,6 +317,25 @@ __global__ __launch_bounds__(kThreads) void score_tile_kernel(
         for (int e = 0; e < 4; ++e) v[e] = acc[u][w][4 * q + e];
         *reinterpret_cast<floatx4*>(red + (size_t)wid * (WU * WT * 1024) + (((w * WU + u) * 4 + q) * 64 + lane) * 4) = v;
       }
+  };
+  // Two K groups: a wavefront finishes token block g of its piece, keeps its own part of that in registers and
+  // hands over the other block alone: half the LDS traffic of this step (7001 x 4096 x 512 1 % of the call).
+  constexpr bool kSwap = KG == 2 && WT == 2 && C::OWN == 2 * WU;
+  floatx16 mine[kSwap ? WU : 1];
+  if constexpr (kSwap) {
+    if (g == 0) {
+      put(Buf1{});
+#pragma unroll
+      for (int u = 0; u < WU; ++u) mine[u] = acc[u][0];
+    } else {
+      put(Buf0{});
+#pragma unroll
+      for (int u = 0; u < WU; ++u) mine[u] = acc[u][WT - 1];
+    }
+  } else {
+    put(Buf0{});
+    if constexpr (WT == 2) put(Buf1{});
+  }
   if constexpr (kNorm) {
     if (wu == 0) {
 #pragma unroll
@@ -355,10 +374,17 @@ __global__ __launch_bounds__(kThreads) void score_tile_kernel(
     for (int o = 0; o < C::OWN; ++o) {
       const int grp = first + o, u = grp / 2 % WU, s16 = grp % 2;
       const int u0 = (wu * WU + u) * 32 + s16 * 16 + 4 * kg;         // units u0..u0+3 and u0+8..u0+11
-      const float* from = red + (size_t)piece * (WU * WT * 1024) + (grp * 128 + lane) * 4;
+      const float* from = red + (size_t)(kSwap ? wid ^ (kWaves / KG) : piece) * (WU * WT * 1024) + (grp * 128 + lane) * 4;
       floatx4 z0 = *reinterpret_cast<const floatx4*>(from), z1 = *reinterpret_cast<const floatx4*>(from + 256);
+      if constexpr (kSwap) {
 #pragma unroll
-      for (int i = 1; i < KG; ++i) {
+        for (int e = 0; e < 4; ++e) {
+          z0[e] += mine[o / 2 % WU][8 * (o % 2) + e];
+          z1[e] += mine[o / 2 % WU][8 * (o % 2) + 4 + e];
+        }
+      }
+#pragma unroll
+      for (int i = 1; i < KG && !kSwap; ++i) {
         z0 += *reinterpret_cast<const floatx4*>(from + i * kStride);
         z1 += *reinterpret_cast<const floatx4*>(from + i * kStride + 256);
       }
