@@ -474,19 +474,25 @@ int teacher_splits(int H, int G, int Tq, int T) {
 }
 
 // The same for the keys in the row pass, whose blocks differ (a late query sees up to twice the keys of
-// an early one; the longest go first): with one or two blocks a CU all of that difference shows, with more
-// half of it.  At least 4 key tiles of the prompt (T positions, no more than the earliest queries see) in a
-// share, and the launch that merges them.
+// an early one; the longest go first): up to two blocks a CU all of that difference shows, beyond that the
+// short ones fill the CUs evenly and whole multiples of 256 no longer matter.  At least 4 key tiles of the
+// prompt (T positions, no more than the earliest queries see) in a share, and the launch that merges them.
+// us per call, 1 / 2 / 3 / 4 / 6 shares: 32 heads, 8192 1102 / 1111 / 1117 / 1120 / 1136, 3000 190 / 180 / 181 /
+// 182 / 186, prompt 4274, repeat 1068 121 / 114 / 102 / 107 / 105; 16 heads, 4512 232 / 203 / 202 / 205 / 209.
 int teacher_key_splits(int HQ, int Tq, int T) {
-  const long long blocks = (long long)((Tq + kBlockRows - 1) / kBlockRows) * HQ;
+  const long long per_share = (long long)((Tq + kBlockRows - 1) / kBlockRows) * HQ;
   const float mean = (float)(T + Tq / 2) / 32, late = (float)(Tq / 2) / 32, tile_us = 0.33f;
+  auto us_of = [&](int ks) {
+    const long long blocks = per_share * ks;
+    const float merge = ks > 1 ? 4.0f + 0.15f * ks : 0.0f;
+    if (blocks <= 2 * kCUs) return share_us(blocks, mean / ks, tile_us) + late / ks * tile_us + merge;
+    const float n = (float)blocks / kCUs;
+    return (n + 0.15f) * mean / ks * tile_us + 2.6f * (float)((blocks + 2 * kCUs - 1) / (2 * kCUs)) + merge;
+  };
   int best = 1;
-  float least = share_us(blocks, mean, tile_us) + late * tile_us * (blocks > 2 * kCUs ? 0.5f : 1.0f);
-  for (int ks = 2; ks <= 64 && ks <= T / 128; ++ks) {
-    const float us = share_us(blocks * ks, mean / ks, tile_us) +
-                     late / ks * tile_us * (blocks * ks > 2 * kCUs ? 0.5f : 1.0f) + 4.0f + 0.15f * ks;
-    if (us < 0.99f * least) { least = us; best = ks; }
-  }
+  float least = us_of(1);
+  for (int ks = 2; ks <= 64 && ks <= T / 128; ++ks)
+    if (us_of(ks) < 0.995f * least) { least = us_of(ks); best = ks; }
   return best;
 }
 
