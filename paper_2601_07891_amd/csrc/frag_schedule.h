@@ -11,6 +11,9 @@
 //                 MFMA  [load A fragment G-1 of tile t+lead]  (MFMA)         (tile t+lead exists)
 //   end of tile:  [load A fragment NG-1 of tile t+lead]
 //
+// (A K tile of two 64-input planes counts as one of twice the unit blocks: UB here is then twice the
+// kernel's, and NDJ likewise.)
+//
 // A tile's *kind* R = min(tiles left including this one, 4) says which of those later tiles
 // exist, for this tile and (R + d) for the tile d steps earlier.  The prologue issues the
 // fragments of tiles 0..lead-1 and hidden tiles 0..2 and waits for all of them but (with
