@@ -1123,7 +1123,8 @@ __global__ __launch_bounds__(256) void copy_w1_kernel(const u32x4* __restrict__ 
 // and shares within 3 to 7 %, tiles within 10 %; the chosen form is 0.5 % slower than the best one in the
 // mean, 13 % in one of a hundred shapes.  Hence the margin on tiles and shares.
 // The normalising form is like the plain one within that accuracy; where it writes the states
-// (Form::kStates) their copy is added, which a tile does more slowly than a token block.
+// (Form::kStates) their copy is added: in short inputs what one block takes for its part (1 us in the
+// smallest tile, 13 in the largest), in long ones what the memory takes for all.
 //
 // Raw weights: an input for which fp32_epilogue() holds, or of no more than kSkinnyRows tokens, is scored
 // with an fp32 epilogue throughout (2e-7 to 4e-7 of the exact scores; the token blocks' fp16 activations and
@@ -1161,17 +1162,19 @@ constexpr float kBlockLater[5] = {0.39f, 0.69f, 0.95f, 1.14f, 1.26f};      // kB
 constexpr float kBlockStates[2] = {0.05f, 1.05f};                          // the states, as thin and fill
 constexpr float kArrange[2] = {2.4f, 1.4e-6f};                             // W1 put in order: per call, per weight
 // tiles and shares: us per launch pair and per later round; per 64 inputs: a few blocks, what a full round
-// adds, every later round, 8192 tokens of input, 8192 tokens of states
+// adds, every later round, 8192 tokens of input; the copy of one block's states, us, under which a call's
+// states (kStatesStream for 8192 tokens of 64 inputs) do not show
 struct TileCost { float fixed, round, thin, fill, again, stream, states; };
-constexpr TileCost kTileCost[kScoreTiles + kShareCount] = {{10.8f, 3.1f, 0.288f, 0.050f, 0.538f, 0.098f, 0.364f},
-                                                           {9.1f, 2.7f, 0.211f, 0.019f, 0.328f, 0.069f, 0.336f},
-                                                           {9.0f, 3.3f, 0.139f, 0.014f, 0.165f, 0.099f, 0.282f},
-                                                           {8.2f, 2.8f, 0.080f, 0.051f, 0.102f, 0.092f, 0.311f},
-                                                           {9.5f, 2.8f, 0.017f, 0.088f, 0.074f, 0.000f, 0.555f},
-                                                           {13.9f, 7.9f, 0.442f, 0.124f, 0.659f, 0.127f, 0.330f},
-                                                           {12.7f, 5.8f, 0.391f, 0.064f, 0.643f, 0.104f, 0.347f},
-                                                           {12.5f, 7.4f, 0.514f, 0.227f, 0.751f, 0.110f, 0.348f},
-                                                           {12.2f, 3.7f, 0.410f, 0.144f, 0.742f, 0.103f, 0.343f}};
+constexpr TileCost kTileCost[kScoreTiles + kShareCount] = {{10.8f, 3.1f, 0.288f, 0.050f, 0.538f, 0.098f, 13.0f},
+                                                           {9.1f, 2.7f, 0.211f, 0.019f, 0.328f, 0.069f, 7.0f},
+                                                           {9.0f, 3.3f, 0.139f, 0.014f, 0.165f, 0.099f, 3.6f},
+                                                           {8.2f, 2.8f, 0.080f, 0.051f, 0.102f, 0.092f, 2.3f},
+                                                           {9.5f, 2.8f, 0.017f, 0.088f, 0.074f, 0.000f, 1.0f},
+                                                           {13.9f, 7.9f, 0.442f, 0.124f, 0.659f, 0.127f, 0.0f},
+                                                           {12.7f, 5.8f, 0.391f, 0.064f, 0.643f, 0.104f, 0.0f},
+                                                           {12.5f, 7.4f, 0.514f, 0.227f, 0.751f, 0.110f, 0.0f},
+                                                           {12.2f, 3.7f, 0.410f, 0.144f, 0.742f, 0.103f, 0.0f}};
+constexpr float kStatesStream = 0.32f;
 constexpr float kTileMargin = 1.03f;
 // score_mlp_kernel (D_h < 256): per launch, per 64 inputs
 constexpr float kSmallFixed[5] = {6.7f, 10.2f, 14.0f, 17.2f, 20.8f};
@@ -1206,9 +1209,10 @@ inline float cost_tile(int tile, long long rows, int Dh, int M, Form form) {
   const TileCost& c = kTileCost[tile];
   const long long blocks = xcd_blocks(tile, rows, M), rounds = (blocks + kXcdCUs - 1) / kXcdCUs;
   const float fill = rounds > 1 ? 1.0f : (float)blocks / kXcdCUs, again = (float)(rounds - 1);
-  const float stream = c.stream + (form == Form::kStates ? c.states : 0.0f);
-  return kTileMargin * (c.fixed + again * c.round + (float)(Dh / kBK) * (c.thin + c.fill * fill + again * c.again +
-                                                                        stream * (float)rows / 8192));
+  const float planes = (float)(Dh / kBK), inputs = (float)rows / 8192;
+  float states = form == Form::kStates ? kStatesStream * planes * inputs : 0.0f;
+  if (form == Form::kStates && states < c.states) states = c.states;
+  return kTileMargin * (c.fixed + again * c.round + planes * (c.thin + c.fill * fill + again * c.again + c.stream * inputs) + states);
 }
 
 inline Plan plan_tile(long long rows, int Dh, int M, Form form, float ordered) {   // one tile or share for all rows
